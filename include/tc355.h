@@ -95,7 +95,7 @@ int64_t tc355_get_option(tc_option key);
 /*
  * Which kernel family the calling thread's most recent entry-point call chose,
  * as a static string "op:family" (for example "tbmm:lds", "tbmm:i8",
- * "mlp:rows", "gconv:i8", "gconv:i8_taps", "gconv:band", "sconv:i8", "sconv:tile",
+ * "mlp:rows", "gconv:i8", "gconv:i8_taps", "gconv:band", "gconv:wave" (any shape), "sconv:i8", "sconv:tile",
  * "lut:sum"; ""
  * before the first call).  A debugging and testing aid: tests pick the tolerance of the
  * arithmetic that actually ran instead of re-deriving the dispatch.

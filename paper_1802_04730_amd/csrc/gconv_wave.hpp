@@ -4,8 +4,8 @@
 // row-major F x (C*KH*KW) matrix (the A operand), the B operand is gathered
 // from the input on the fly.  One wavefront owns 16 output channels x 16*TP
 // consecutive output pixels of one (n,g) and feeds the fp64 MFMA directly from
-// global memory.  Any extents; the tuned path for C%4==0, F%16==0 lives in
-// gconv_lds.hpp.
+// global memory.  Any extents; what gconv_mix.hpp does not take: reductions of
+// a step or two, tiny outputs, extents beyond its 32-bit offsets.
 #pragma once
 #include "tc355_device.hpp"
 

@@ -1,0 +1,71 @@
+"""GPU parity of the shape-generic grouped convolution (16- and 4-filter MFMA tiles over one LDS band) against the
+float64 oracle: one fp32 rounding of the exact result (2.5e-7 on the metric, as for every fp64 kernel)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1802_04730_amd import inputs
+from paper_1802_04730_amd.metric import parity_error
+
+pytestmark = pytest.mark.gpu
+
+TIGHT = 2.5e-7
+GUARD = 64
+
+# (N, G, C, F, H, W, KH, KW)
+SHAPES = [
+    (2, 2, 5, 3, 9, 11, 3, 3),        # one quad, the last filter missing; 45 taps: the last step has one
+    (1, 3, 6, 8, 13, 17, 3, 2),       # two quads; 36 taps in W1's order
+    (3, 2, 8, 12, 20, 19, 3, 3),      # three quads; channels in fours
+    (2, 2, 12, 16, 33, 45, 3, 3),     # one tile of 16 (84 pixel tiles: shares of 3 and 4)
+    (2, 3, 12, 20, 33, 45, 3, 3),     # a tile and a quad
+    (1, 2, 9, 22, 31, 30, 3, 3),      # a tile and two quads, two filters missing
+    (1, 2, 7, 27, 14, 14, 5, 5),      # a tile and three quads
+    (2, 1, 13, 32, 21, 23, 3, 3),     # two tiles
+    (2, 2, 40, 40, 12, 14, 3, 3),     # two blocks of 20 filters
+    (1, 2, 70, 33, 11, 12, 5, 5),     # 1750 taps: chunks of channels; two blocks, the second short
+    (1, 1, 37, 21, 40, 64, 5, 5),     # chunks whose last one is no multiple of four channels
+    (11, 3, 6, 10, 7, 7, 3, 3),       # several images per job, the last job with fewer
+    (5, 2, 3, 5, 4, 5, 3, 3),         # 6 pixels per image
+    (3, 40, 4, 4, 14, 14, 3, 3),      # many groups: runs that cross group boundaries
+    (9, 25, 11, 18, 16, 21, 1, 1),    # 1 x 1 filters
+    (2, 5, 4, 7, 1, 64, 1, 5),        # a single row
+    (2, 3, 10, 6, 64, 3, 3, 3),       # one output column
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("with_bias", [True, False])
+def test_gconv_generic(shape, with_bias, oracle_threads):
+    from paper_1802_04730_amd import tc355 as tc
+    N, G, C, F, H, W, KH, KW = shape
+    I, W1, bias = inputs.make_gconv(*shape, seed=C + F)
+    ref = oracle.group_conv(I, W1, bias if with_bias else None)
+    buf = torch.full((ref.size + 2 * GUARD,), 777.0, device="cuda")
+    O = buf[GUARD:GUARD + ref.size].view(ref.shape)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    tc.tc_group_conv(dev(I), dev(W1), dev(bias) if with_bias else None, O)
+    torch.cuda.synchronize()
+    assert tc.last_path() == "gconv:wave"
+    err = parity_error(O.cpu().numpy().astype(np.float64), ref)
+    print("gconv generic %s: parity error %.3e" % (shape, err), flush=True)
+    assert err <= TIGHT
+    assert bool((buf[:GUARD] == 777.0).all()) and bool((buf[GUARD + ref.size:] == 777.0).all())
+
+
+def test_gconv_generic_keeps_infinities_out_of_the_padding(oracle_threads):
+    """Unused k slots of a last step (27 taps: one) multiply nothing: an Inf gives Inf where the definition does and leaves
+    every output that does not read it finite."""
+    from paper_1802_04730_amd import tc355 as tc
+    I, W1, bias = inputs.make_gconv(2, 2, 3, 6, 12, 13, 3, 3, seed=5)
+    W1 = np.abs(W1) + 0.01
+    I[1, 0, 2, 11, 12] = np.inf
+    I[0, 1, 0, 0, 0] = np.inf
+    ref = oracle.group_conv(I, W1, bias)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    O = torch.full(ref.shape, float("nan"), device="cuda")
+    tc.tc_group_conv(dev(I), dev(W1), dev(bias), O)
+    got = O.cpu().numpy()
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.isposinf(ref).sum() == 12
+    assert not np.isnan(got).any()
