@@ -27,6 +27,7 @@
 #include "gemm_tile.hpp"
 #include "gemm_wave.hpp"
 #include "kron_lds.hpp"
+#include "kron_tile.hpp"
 #include "kron_wave.hpp"
 #include "lut_sum.hpp"
 #include "mlp_fused.hpp"
@@ -391,6 +392,107 @@ size_t mlp_sync_bytes() { return round256((MLP_SYNC_WORDS + (size_t)(MLP_MAX_LAY
 // fp64 copy of one layer's output; whole 16-row tiles (the small-batch kernel keeps it in a tiled layout)
 size_t mlp_act_bytes(int64_t batch, int64_t width) {
   return round256((size_t)ceil_div(batch, 16) * 16 * (size_t)width * sizeof(double));
+}
+
+// ---- Kronecker layer of any extents with its operands in LDS ----
+template <typename TS, int TJ>
+tc_status launch_kron_tile(const KronTileArgs& a, dim3 grid, int64_t lds, hipStream_t s) {
+  static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
+  if (!lds_ok.load(std::memory_order_acquire)) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kron_tile_kernel<TS, TJ>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+      return TC_ERR_LAUNCH;
+    lds_ok.store(1, std::memory_order_release);
+  }
+  kron_tile_kernel<TS, TJ><<<grid, dim3(KT_THREADS), (size_t)lds, s>>>(a);
+  return launch_status();
+}
+
+template <typename TS>
+tc_status launch_kron_tile_tj(int tj, const KronTileArgs& a, dim3 grid, int64_t lds, hipStream_t s) {
+  switch (tj) {
+    case 1: return launch_kron_tile<TS, 1>(a, grid, lds, s);
+    case 2: return launch_kron_tile<TS, 2>(a, grid, lds, s);
+    case 3: return launch_kron_tile<TS, 3>(a, grid, lds, s);
+    case 4: return launch_kron_tile<TS, 4>(a, grid, lds, s);
+    case 5: return launch_kron_tile<TS, 5>(a, grid, lds, s);
+    case 6: return launch_kron_tile<TS, 6>(a, grid, lds, s);
+    case 7: return launch_kron_tile<TS, 7>(a, grid, lds, s);
+    default: return launch_kron_tile<TS, 8>(a, grid, lds, s);
+  }
+}
+
+struct KronTilePlan {
+  int64_t nb, lsp, itb, iblocks, jblocks, tj, k4, ls, ls1, ls2, xs, lds, groups, occ;
+  bool wide;
+  double cost;
+};
+
+// A plan from its free choices, and an estimate of the launch in clocks; false where it does not fit LDS.
+bool plan_kron_tile(int64_t B, int64_t I, int64_t K, int64_t J, int64_t L, int64_t iblocks, int64_t nb, int64_t lsp, bool wide, int cus, KronTilePlan* p) {
+  const int64_t size = wide ? 8 : 4, ltiles = ceil_div(L, 16);
+  p->nb = nb; p->lsp = lsp; p->wide = wide;
+  p->itb = ceil_div(ceil_div(I, 16), iblocks);
+  p->iblocks = ceil_div(ceil_div(I, 16), p->itb);
+  p->jblocks = ceil_div(ceil_div(J, 16), 8);
+  p->tj = ceil_div(ceil_div(J, 16), p->jblocks);
+  if (p->iblocks * p->jblocks > 65535 || p->itb > 8) return false;
+  p->k4 = ceil_div(K, 4) * 4;
+  // bank spread of the operand reads: see kron_tile.hpp
+  auto up = [](int64_t n, int64_t rem, int64_t mod) { return n + ((rem - n) % mod + mod) % mod; };
+  p->ls = up(L, 4, 8);
+  p->ls1 = up(p->k4, 4, 8);
+  p->ls2 = wide ? up(ceil_div(L, 4) * 4, 2, 4) : up(ceil_div(L, 4) * 4, 4, 8);
+  if (prod_reaches({nb, p->k4, p->ls}, 1 << 16)) return false;
+  const int64_t x = nb * p->k4 * p->ls + 16;  // (the last row is read up to 15 elements past its end)
+  const int64_t sums = nb * p->itb * (lsp - 1) * p->tj * 4 * WAVE * 8 / size;
+  p->xs = ceil_div(std::max(x, sums), 16) * 16;
+  p->lds = (p->xs + 16 * p->tj * p->ls2 + std::min<int64_t>(16 * p->itb, I) * p->ls1 + 16) * size;  // (operands are read up to 7 elements ahead)
+  if (p->lds > 160 * 1024) return false;
+  p->groups = ceil_div(B, nb);
+  p->occ = std::max<int64_t>(1, std::min<int64_t>(p->tj <= 4 ? 2 : 1, 160 * 1024 / (p->lds + 512)));
+  // What a launch costs in clocks, as far as the choices change it: MFMAs (74 clocks each with what surrounds them, 79 where
+  // operands are widened at the read), staging, the exchange of partial sums.  A wavefront's chain is two tiles' time
+  // while the other half of the workgroup shares its SIMD; `occ` workgroups cover part of each other's staging.  The
+  // constants are fitted to the measured times of 45 shapes at every choice of (iblocks, nb, lsp, wide): the plan taken
+  // is on average 0.3 % from the best one, 2.4 % at worst.
+  const int64_t blocks = p->iblocks * p->jblocks, jobs = nb * p->itb * lsp, per_cu = ceil_div(p->groups * blocks, cus);
+  const double tile = (double)ceil_div(ltiles, lsp) * (p->k4 / 4 + 4 * p->tj) * (wide ? 74.0 : 79.0) + 355;
+  const double stage = 2500 + (double)nb * K * L / KT_THREADS * 130 + (lsp > 1 ? 107.0 * lsp * p->tj : 0.0);
+  const int64_t share = std::min(p->occ, per_cu), rest = jobs % KT_WAVES;
+  const double chain = (jobs / KT_WAVES * 2 + (rest > 4 ? 2 : rest > 0 ? 1 : 0)) * tile + stage;
+  p->cost = (double)(std::min<int64_t>(16 * p->itb, I) * K + 16 * p->tj * L) / KT_THREADS * 145 +
+            (double)ceil_div(per_cu, share) * std::max(chain, share * (std::max(jobs / 4.0, 1.0) * tile + 0.72 * stage));
+  return true;
+}
+
+// Returns false where no block of 16 rows, of columns and one batch element fit LDS.
+bool try_kron_tile(const float* W1, const float* W2, const float* X, float* Y, int64_t B, int64_t I, int64_t K, int64_t J, int64_t L,
+                   hipStream_t s, tc_status* st) {
+  const int cus = device_cus();
+  if (cus <= 0 || K < 2 || L < 2 || K > 40000 || L > 40000) return false;
+  KronTilePlan best{}, pl{};
+  bool any = false;
+  // More blocks of rows than needed only while there are fewer than two workgroups per compute unit, more batch elements
+  // per stage only while there is a workgroup for half of them: at most 32 plans are looked at.
+  const int64_t tiles_i = ceil_div(I, 16), least = ceil_div(tiles_i, 8), jblocks = ceil_div(ceil_div(J, 16), 8);
+  for (int64_t iblocks = least; iblocks <= tiles_i && iblocks < least + 8 && (iblocks == least || B * (iblocks - 1) * jblocks < 2 * cus); iblocks++)
+    for (int64_t nb = 1; nb <= 8 && (nb == 1 || (nb <= B && ceil_div(B, nb) * iblocks * jblocks >= cus / 2)); nb++)
+      for (int64_t lsp = 1; lsp <= 8 && (lsp == 1 || (nb * ceil_div(tiles_i, iblocks) * lsp <= KT_WAVES && lsp <= ceil_div(L, 16))); lsp *= 2)
+        for (int wide = 1; wide >= 0; wide--)
+          if (plan_kron_tile(B, I, K, J, L, iblocks, nb, lsp, wide, cus, &pl) && (!any || pl.cost < best.cost)) { best = pl; any = true; }
+  if (!any) return false;
+  KronTileArgs a{};
+  a.W1 = W1; a.W2 = W2; a.X = X; a.Y = Y;
+  a.B = (int)B; a.I = (int)I; a.K = (int)K; a.J = (int)J; a.L = (int)L;
+  a.nb = (int)best.nb; a.lsp = (int)best.lsp; a.groups = (int)best.groups;
+  a.itb = (int)best.itb; a.jblocks = (int)best.jblocks;
+  a.k4 = (int)best.k4; a.ls = (int)best.ls; a.ls1 = (int)best.ls1; a.ls2 = (int)best.ls2; a.xs = (int)best.xs;
+  auto magic = [](int64_t d) { return (unsigned)(((1ll << 32) + d - 1) / d); };  // dividends and divisors below 2^16
+  a.l_magic = magic(L); a.k_magic = magic(K);
+  const int64_t blocks = best.iblocks * best.jblocks;
+  const dim3 grid((unsigned)std::min<int64_t>(best.groups, std::max<int64_t>(1, best.occ * cus / blocks)), (unsigned)blocks);
+  *st = best.wide ? launch_kron_tile_tj<double>((int)best.tj, a, grid, best.lds, s) : launch_kron_tile_tj<float>((int)best.tj, a, grid, best.lds, s);
+  return true;
 }
 
 // ---- fastest grouped convolution: compile-time width, one workgroup per (image, group) -----
@@ -1144,6 +1246,13 @@ tc_status tc_kron(const float* W1, const float* W2, const float* X, float* Y, in
       kron_lds_kernel<64, 64, 64><<<dim3((unsigned)fgrid), dim3(WG_THREADS), 0, s>>>(f);
       return took("kron:lds", launch_status());
     }
+  }
+  // The shape-generic kernels ("kron:wave"): operands in LDS wherever a block of them fits (up to about 115 of every
+  // extent, more where others are smaller): 22.3 -> 7.9 us at (B,I,K,J,L) = (200,48,50,75,36), 242 -> 47 us at
+  // (500,96,100,100,100), never slower from 8^5 up; the wave-level kernel keeps the rest.
+  {
+    tc_status st = TC_OK;
+    if (try_kron_tile(W1, W2, X, Y, B, I, K, J, L, s, &st)) return took("kron:wave", st);
   }
   constexpr int TJ = 4;
   a.tiles_i = (int)ceil_div(I, 16);
