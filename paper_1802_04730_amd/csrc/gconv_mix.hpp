@@ -55,7 +55,6 @@ struct GconvMixArgs {
 // u / d for magic = ceil(2^31 / d), while 2 u d < 2^32
 __device__ __forceinline__ int div_magic(int u, unsigned magic) { return (int)__umulhi(2u * (unsigned)u, magic); }
 
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // 16-byte load of 4-byte aligned elements
 
 template <int FT, int FQ, int TP>
 __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p) {
@@ -113,7 +112,7 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
   unsigned goff[NU];  // its byte offset in I from the stage's first element
   int loff[NU];       // its LDS offset in doubles
   int decoded = -1;   // number of units that goff / loff were worked out for
-  f4u pre[NU];
+  f4_any pre[NU];
   auto place = [&](int u, int cc, unsigned& go, int& lo) {
     const int sg = div_magic(u, p.upc_magic);
     const int i = min(4 * (u - sg * p.upc), seg - 4);
@@ -136,9 +135,9 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
     }
     const char* in = band_of(s);
 #pragma unroll
-    for (int j = 0; j < NU; j++) pre[j] = *reinterpret_cast<const f4u*>(in + goff[j]);
+    for (int j = 0; j < NU; j++) pre[j] = *reinterpret_cast<const f4_any*>(in + goff[j]);
   };
-  auto put = [&](int lo, const f4u& v) {
+  auto put = [&](int lo, const f4_any& v) {
     double* o = band + lo;
     o[0] = (double)v[0]; o[1] = (double)v[1]; o[2] = (double)v[2]; o[3] = (double)v[3];
   };
@@ -150,13 +149,13 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
     if (units > NU * WG_THREADS) {  // a band of more than 4096 elements: the rest is not fetched ahead
       const char* in = band_of(s);
       for (int u0 = tid + NU * WG_THREADS; u0 < units; u0 += 4 * WG_THREADS) {
-        f4u v[4];
+        f4_any v[4];
         int lo[4];
 #pragma unroll
         for (int j = 0; j < 4; j++) {
           unsigned go;
           place(min(u0 + j * WG_THREADS, units - 1), min(p.cc, p.C - s.c0), go, lo[j]);
-          v[j] = *reinterpret_cast<const f4u*>(in + go);
+          v[j] = *reinterpret_cast<const f4_any*>(in + go);
         }
 #pragma unroll
         for (int j = 0; j < 4; j++) put(lo[j], v[j]);
@@ -180,13 +179,13 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
     const unsigned magic = (0x7fffffffu + (unsigned)steps) / (unsigned)steps;
     auto batch = [&](int u0, auto nb) {  // nb loads in flight per thread
       constexpr int NB = decltype(nb)::value;
-      f4u w[NB];
+      f4_any w[NB];
       int fk[NB];
 #pragma unroll
       for (int j = 0; j < NB; j++) {
         const int u = min(u0 + j * WG_THREADS, units - 1);
         const int f = div_magic(u, magic), k = min(4 * (u - f * steps), kc - 4);
-        w[j] = *reinterpret_cast<const f4u*>(wg + 4u * (unsigned)(f * (p.C * KK) + k));
+        w[j] = *reinterpret_cast<const f4_any*>(wg + 4u * (unsigned)(f * (p.C * KK) + k));
         fk[j] = f << 16 | k;
       }
       if (u0 == tid) {  // (while the first loads are in flight)

@@ -12,8 +12,9 @@
 // LDS reads for 4 MFMAs and no conversion (a vector-ALU instruction costs
 // matrix-pipe time on this chip; widening at staging time is 0.5 conversions per
 // MFMA instead of 2).  One barrier per chunk.  Rows past the extents are clamped
-// on load and masked on store; the reduction tail is staged as zeros.
-// Requires K % 4 == 0 (16-byte loads); other shapes take the wave-level kernel.
+// on load and masked on store.  The last chunk starts at K - 32, so its loads are whole and in bounds at whatever 4-byte
+// alignment the rows have; what it shares with the chunk before is staged as zeros.  A reduction shorter than a chunk
+// (K % 4 == 0 then) is one chunk whose pieces past K are clamped and staged as zeros.
 #pragma once
 #include "gemm_wave.hpp"
 
@@ -34,6 +35,7 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gemm_nt_tile_kernel(GemmArgs p)
   extern __shared__ __attribute__((aligned(16))) double gt_lds[];
 
   const int tid = threadIdx.x;
+  if (EPI == EPI_BIAS_RELU && p.clear && blockIdx.x == 0 && tid == 0) *p.clear = 0;
   const int lane = tid & (WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int r16 = lane & 15, q = lane >> 4;
@@ -51,37 +53,29 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gemm_nt_tile_kernel(GemmArgs p)
   const int b_row0 = tid / B_UPR, b_k = (tid % B_UPR) * 4;
   int aoff[A_LD], boff[B_LD];
 #pragma unroll
-  for (int i = 0; i < A_LD; i++) aoff[i] = min(n0 + a_row0 + i * (WG_THREADS / A_UPR), N - 1) * K + a_k;
+  for (int i = 0; i < A_LD; i++) aoff[i] = min(n0 + a_row0 + i * (WG_THREADS / A_UPR), N - 1) * K + (a_k < K ? a_k : 0);
 #pragma unroll
-  for (int i = 0; i < B_LD; i++) boff[i] = min(m0 + b_row0 + i * (WG_THREADS / B_UPR), M - 1) * K + b_k;
+  for (int i = 0; i < B_LD; i++) boff[i] = min(m0 + b_row0 + i * (WG_THREADS / B_UPR), M - 1) * K + (b_k < K ? b_k : 0);
 
   struct Regs {
     Vec<TA, AV> a[A_LD];
     Vec<float, 4> b[B_LD];
   };
-  // Loads are never skipped per lane: a unit past K re-reads the start of its row and is staged as zeros.
-  auto fetch = [&](Regs& r, int ck) {
-    const int k0 = min(ck, nck - 1) * GT_KC;
-    if (k0 + GT_KC <= K) {  // whole chunk inside the reduction (uniform): lane offset + scalar base, no ALU work
-      const TA* Ak = A + k0;
-      const float* Bk = Bm + k0;
+  auto first_k = [&](int ck) { return K >= GT_KC ? min(ck * GT_KC, K - GT_KC) : 0; };  // uniform
+  auto fetch = [&](Regs& r, int ck) {  // lane offset + scalar base, no ALU work
+    const int k0 = first_k(ck);
+    const TA* Ak = A + k0;
+    const float* Bk = Bm + k0;
 #pragma unroll
-      for (int i = 0; i < A_LD; i++) r.a[i] = load_vec<TA, AV>(Ak + aoff[i]);
+    for (int i = 0; i < A_LD; i++) r.a[i] = load_vec_any<TA, AV>(Ak + aoff[i]);
 #pragma unroll
-      for (int i = 0; i < B_LD; i++) r.b[i] = load_vec<float, 4>(Bk + boff[i]);
-    } else {
-      const bool ain = k0 + a_k < K, bin = k0 + b_k < K;
-#pragma unroll
-      for (int i = 0; i < A_LD; i++) r.a[i] = load_vec<TA, AV>(A + aoff[i] + (ain ? k0 : -a_k));
-#pragma unroll
-      for (int i = 0; i < B_LD; i++) r.b[i] = load_vec<float, 4>(Bm + boff[i] + (bin ? k0 : -b_k));
-    }
+    for (int i = 0; i < B_LD; i++) r.b[i] = load_vec_any<float, 4>(Bk + boff[i]);
   };
   auto stage = [&](const Regs& r, int ck, double* buf) {
-    const int k0 = ck * GT_KC;
+    const int lo = ck * GT_KC - first_k(ck);  // elements of the chunk that the one before has contracted
     double* As = buf + a_row0 * GT_RS + a_k;
     double* Bs = buf + GT_BM * GT_RS + b_row0 * GT_RS + b_k;
-    if (k0 + GT_KC <= K) {  // whole chunk inside the reduction (uniform): widen and store, nothing else
+    if (lo == 0 && K >= GT_KC) {  // every element counts (uniform): widen and store, nothing else
 #pragma unroll
       for (int i = 0; i < A_LD; i++)
 #pragma unroll
@@ -96,20 +90,20 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gemm_nt_tile_kernel(GemmArgs p)
           dbl2 v = {(double)r.b[i].e[e], (double)r.b[i].e[e + 1]};
           *reinterpret_cast<dbl2*>(Bs + i * (WG_THREADS / B_UPR) * GT_RS + e) = v;
         }
-    } else {  // ragged last chunk: what lies past K is staged as zeros
-      const bool ain = k0 + a_k < K, bin = k0 + b_k < K;
+    } else {  // zeros for the rest (in both operands: 0 * Inf would poison the sum)
+      auto in = [&](int k) { return k >= lo && k < K; };
 #pragma unroll
       for (int i = 0; i < A_LD; i++)
 #pragma unroll
         for (int e = 0; e < AV; e += 2) {
-          dbl2 v = {ain ? (double)r.a[i].e[e] : 0.0, ain ? (double)r.a[i].e[e + 1] : 0.0};
+          dbl2 v = {in(a_k + e) ? (double)r.a[i].e[e] : 0.0, in(a_k + e + 1) ? (double)r.a[i].e[e + 1] : 0.0};
           *reinterpret_cast<dbl2*>(As + i * (WG_THREADS / A_UPR) * GT_RS + e) = v;
         }
 #pragma unroll
       for (int i = 0; i < B_LD; i++)
 #pragma unroll
         for (int e = 0; e < 4; e += 2) {
-          dbl2 v = {bin ? (double)r.b[i].e[e] : 0.0, bin ? (double)r.b[i].e[e + 1] : 0.0};
+          dbl2 v = {in(b_k + e) ? (double)r.b[i].e[e] : 0.0, in(b_k + e + 1) ? (double)r.b[i].e[e + 1] : 0.0};
           *reinterpret_cast<dbl2*>(Bs + i * (WG_THREADS / B_UPR) * GT_RS + e) = v;
         }
     }

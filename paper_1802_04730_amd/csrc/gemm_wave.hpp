@@ -20,6 +20,7 @@ struct GemmArgs {
   float* C;           // [batch][N][M] fp32 result, or nullptr
   double* C64;        // [batch][N][M] fp64 copy for a following stage, or nullptr
   int64_t strideA, strideB, strideC;  // elements between batch entries
+  unsigned* clear;    // fcrelu: a word that the launch sets to 0 (the error word of the workspace), or nullptr
   int N, M, K;
   int tiles_n;   // ceil(N / 16)
   int strips_m;  // ceil(M / (16*TM))
@@ -35,6 +36,7 @@ __global__ __launch_bounds__(WG_THREADS) void gemm_nt_wave_kernel(GemmArgs p) {
   const int lane = threadIdx.x & (WAVE - 1);
   const int wave = threadIdx.x / WAVE;
   const int r16 = lane & 15, q = lane >> 4;
+  if (EPI == EPI_BIAS_RELU && p.clear && blockIdx.x == 0 && threadIdx.x == 0) *p.clear = 0;
   const int64_t job = (int64_t)blockIdx.x * WAVES_PER_WG + wave;
   if (job >= p.jobs) return;  // whole wavefront leaves together; no barrier follows
 

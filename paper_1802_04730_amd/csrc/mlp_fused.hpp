@@ -209,28 +209,40 @@ __device__ __forceinline__ void mlp_layer(const TA* __restrict__ A, const float*
   auto load_next = [&](Regs& r) {
     if (ljob >= njobs) return;
     const int k0 = lck * KC;
-    if (k0 + KC <= K) {  // whole chunk inside the reduction: no per-lane checks (uniform branch)
-      const char* Ak = Abase + (size_t)k0 * sizeof(TA);  // uniform
-      const char* Wk = Wbase + (size_t)k0 * 4;
+    if (K >= KC) {  // whole 16-byte loads, also in a ragged last chunk: it starts at K - KC (uniform branches)
+      const int from = min(k0, K - KC), skip = k0 - from;
+      const char* Ak = Abase + (size_t)from * sizeof(TA);  // uniform
+      const char* Wk = Wbase + (size_t)from * 4;
 #pragma unroll
-      for (int i = 0; i < A_LOADS; i++) r.a[i] = load_vec<TA, AV>(reinterpret_cast<const TA*>(Ak + aoff[i]));
+      for (int i = 0; i < A_LOADS; i++) r.a[i] = load_vec_any<TA, AV>(reinterpret_cast<const TA*>(Ak + aoff[i]));
 #pragma unroll
-      for (int i = 0; i < B_LOADS; i++) r.b[i] = load_vec<float, 4>(reinterpret_cast<const float*>(Wk + boff[i]));
-    } else {  // ragged last chunk: clamp the address, zero what lies past K
-      const bool ain = k0 + a_k < K, bin = k0 + b_k < K;
-      const unsigned ashift = ain ? (unsigned)k0 * (unsigned)sizeof(TA) : 0u - (unsigned)a_k * (unsigned)sizeof(TA);
-      const unsigned bshift = bin ? (unsigned)k0 * 4u : 0u - (unsigned)b_k * 4u;
+      for (int i = 0; i < B_LOADS; i++) r.b[i] = load_vec_any<float, 4>(reinterpret_cast<const float*>(Wk + boff[i]));
+      if (skip > 0) {  // what it shares with the chunk before counts as zero, in both operands
+#pragma unroll
+        for (int i = 0; i < A_LOADS; i++)
+#pragma unroll
+          for (int e = 0; e < AV; e++) r.a[i].e[e] = a_k + e >= skip ? r.a[i].e[e] : (TA)0;
+#pragma unroll
+        for (int i = 0; i < B_LOADS; i++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) r.b[i].e[e] = b_k + e >= skip ? r.b[i].e[e] : 0.0f;
+      }
+    } else {
+      // A single short chunk (K >= 4): pieces of 4 elements, the last one moved back to end at K, which brings elements
+      // that the piece before it holds too; those, and pieces that start past K, count as zero.  (An fp64 piece is half
+      // of one.)
+      const int a4 = a_k & ~3, ashift = min(a4, K - 4) - a4, bshift = min(b_k, K - 4) - b_k;
 #pragma unroll
       for (int i = 0; i < A_LOADS; i++) {
-        r.a[i] = load_vec<TA, AV>(reinterpret_cast<const TA*>(Abase + (aoff[i] + ashift)));
+        r.a[i] = load_vec_any<TA, AV>(reinterpret_cast<const TA*>(Abase + (aoff[i] + (unsigned)ashift * (unsigned)sizeof(TA))));
 #pragma unroll
-        for (int e = 0; e < AV; e++) r.a[i].e[e] = ain ? r.a[i].e[e] : (TA)0;
+        for (int e = 0; e < AV; e++) r.a[i].e[e] = a_k + ashift + e >= a4 ? r.a[i].e[e] : (TA)0;
       }
 #pragma unroll
       for (int i = 0; i < B_LOADS; i++) {
-        r.b[i] = load_vec<float, 4>(reinterpret_cast<const float*>(Wbase + (boff[i] + bshift)));
+        r.b[i] = load_vec_any<float, 4>(reinterpret_cast<const float*>(Wbase + (boff[i] + (unsigned)bshift * 4u)));
 #pragma unroll
-        for (int e = 0; e < 4; e++) r.b[i].e[e] = bin ? r.b[i].e[e] : 0.0f;
+        for (int e = 0; e < 4; e++) r.b[i].e[e] = b_k + bshift + e >= b_k ? r.b[i].e[e] : 0.0f;
       }
     }
     if (++lck == nck) { lck = 0; ljob += step; point(); }
@@ -392,13 +404,16 @@ __global__ __launch_bounds__(MLP_TEAMS * WG_THREADS, 2 / MLP_TEAMS) void mlp_fus
   }
 }
 
-// One contraction C[N][M] = sum_k A[N][k] * Bm[M][k] with the layer body above: 16 x 16 output tiles dealt to
-// persistent workgroups whose four wavefronts split every chunk of the reduction.  For one matrix pair (no batch
-// stride) with a long reduction and too few 64 x 64 blocks to fill the chip.
+// One contraction C[N][M] = sum_k A[N][k] * Bm[M][k], or one fcrelu layer (FC), with the layer body above: 16 x 16 output
+// tiles dealt to persistent workgroups whose four wavefronts split every chunk of the reduction.  For one matrix pair (no
+// batch stride) of any K >= 4.  A chain of such launches has no device-wide waits, and it is faster than the chain as one
+// kernel above: a launch costs 1.7 us, a barrier of 256 workgroups 2-3 us and a layer that starts with cold loads behind
+// it (128 x 600 -> 800 -> 400 -> 200: 26.8 us as one kernel, 21.4 as three; 2048 x 512 -> 1000 -> 128: 86 and 68).
+template <typename TA, bool FC>
 __global__ __launch_bounds__(WG_THREADS, 2) void gemm_nt_splitk_kernel(GemmArgs p) {
   extern __shared__ __attribute__((aligned(32))) char smem[];
-  mlp_layer<float, false>(static_cast<const float*>(p.A), p.Bm, nullptr, p.C, nullptr, p.N, p.K, p.M, smem,
-                          (int)blockIdx.x, (int)gridDim.x, -1);
+  if (FC && p.clear && blockIdx.x == 0 && threadIdx.x == 0) *p.clear = 0;
+  mlp_layer<TA, FC>(static_cast<const TA*>(p.A), p.Bm, p.bias, p.C, p.C64, p.N, p.K, p.M, smem, (int)blockIdx.x, (int)gridDim.x, -1);
 }
 
 }  // namespace tc355

@@ -98,10 +98,10 @@ tc_status launch_gemm_tm(GemmArgs a, int64_t batch, int tm, hipStream_t s) {
 // LDS-tiled kernel for big blocks (64 x 64 output tiles); returns false if it does not apply.
 template <typename TA, int EPI>
 bool try_gemm_tile(const GemmArgs& a, int64_t batch, hipStream_t s, tc_status* st) {
-  if (a.K % 4 != 0 || a.N < 48 || a.M < 48) return false;
+  if ((a.K % 4 != 0 && a.K < GT_KC) || a.N < 48 || a.M < 48) return false;
   const int64_t tiles = ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN);
   if (tiles > kMaxGrid || batch > 65535) return false;
-  if (tiles * batch < 128) return false;  // too few blocks to fill the chip: the wave-level kernel spreads wider
+  if (batch > 1 && (a.K % 4 != 0 || tiles * batch < 128)) return false;  // too few blocks to fill the chip: the wave-level kernel spreads wider
   static std::atomic<int> lds_ok{0};  // needs more than the default 64 KiB of dynamic LDS
   if (!lds_ok.load(std::memory_order_acquire)) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_nt_tile_kernel<TA, EPI>),
@@ -164,38 +164,50 @@ bool try_gconv_tiny(const GconvArgs& g, hipStream_t s, tc_status* st) {
   return true;
 }
 
-// Split-reduction kernel (the MLP layer body without its epilogue) for one fp32 matrix pair with a long reduction
-// and too few 64 x 64 blocks for the kernel above; returns false if it does not apply.
-bool try_gemm_splitk(const GemmArgs& a, int64_t batch, hipStream_t s, tc_status* st) {
-  if (batch != 1 || a.K % 4 != 0 || a.K < 2 * MLP_KC || !a.C || a.C64) return false;
-  // the kernel addresses its operands with 32-bit byte offsets
-  if ((int64_t)a.N * a.K * 4 >= (1ll << 32) || (int64_t)a.M * a.K * 4 >= (1ll << 32)) return false;
-  const int64_t jobs = ceil_div(a.N, 16) * ceil_div(a.M, 16);
-  const int cus = device_cus();
-  if (jobs < 64 || cus <= 0) return false;
+// Split-reduction kernel (the MLP layer body as a kernel of its own) for one matrix pair.
+template <typename TA, bool FC>
+tc_status launch_gemm_splitk(const GemmArgs& a, int cus, hipStream_t s) {
   static std::atomic<int> lds_ok{0};  // needs more than the default 64 KiB of dynamic LDS
   if (!lds_ok.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_nt_splitk_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, MLP_LDS_BYTES) != hipSuccess) {
-      *st = TC_ERR_LAUNCH;
-      return true;
-    }
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_nt_splitk_kernel<TA, FC>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, MLP_LDS_BYTES) != hipSuccess)
+      return TC_ERR_LAUNCH;
     lds_ok.store(1, std::memory_order_release);
   }
-  const unsigned nwg = (unsigned)std::min<int64_t>(2 * cus, jobs);
-  gemm_nt_splitk_kernel<<<dim3(nwg), dim3(WG_THREADS), MLP_LDS_BYTES, s>>>(a);
-  *st = launch_status();
-  return true;
+  const unsigned nwg = (unsigned)std::min<int64_t>(2 * cus, ceil_div(a.N, 16) * ceil_div(a.M, 16));
+  gemm_nt_splitk_kernel<TA, FC><<<dim3(nwg), dim3(WG_THREADS), MLP_LDS_BYTES, s>>>(a);
+  return launch_status();
+}
+
+// The two LDS kernels for one matrix pair, in clocks of a compute unit (constants fitted to measured launches).
+// 64 x 64 blocks: 3200 per chunk of 32, one block after the other (two resident blocks take twice as long).  16 x 16 tiles
+// with a split reduction: two teams per compute unit share it at 827 per chunk of 128 and 750 per tile, a team alone takes
+// 990 and 900.  Measured, tiles against blocks: (N,M,K) = (256,3303,3327) 121 / 145 us, (2048,300,700) 27.4 / 33.8,
+// (1000,1000,1000) 52.2 / 47.7, (1500,1500,130) 37 / 24.
+bool splitk_beats_tile(const GemmArgs& a, int cus) {
+  if (a.N < 48 || a.M < 48 || (a.K % 4 != 0 && a.K < GT_KC)) return true;
+  const double tile = (double)ceil_div(ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN), cus) * ceil_div(a.K, GT_KC) * 3200;
+  const int64_t jobs = ceil_div(a.N, 16) * ceil_div(a.M, 16), nck = ceil_div(a.K, MLP_KC), rest = jobs % (2 * cus);
+  const double two = 2.0 * (nck * 827 + 750), one = nck * 990.0 + 900;
+  return jobs / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0.0) < tile;
 }
 
 template <typename TA, int EPI>
 tc_status launch_gemm(const GemmArgs& a, int64_t batch, int tm, hipStream_t s) {
   tc_status st = TC_OK;
   constexpr bool plain = EPI == EPI_NONE;  // tc_tbmm (else: one MLP layer)
-  if (try_gemm_tile<TA, EPI>(a, batch, s, &st)) return took(plain ? "tbmm:tile" : "mlp:layers", st);
-  if constexpr (std::is_same<TA, float>::value && EPI == EPI_NONE) {
-    if (try_gemm_splitk(a, batch, s, &st)) return took("tbmm:splitk", st);
-  }
+  const int cus = device_cus();
+  // (32-bit byte offsets in the split-reduction kernel)
+  const bool splitk = batch == 1 && cus > 0 && a.K >= 4 && (int64_t)a.N * a.K * (int64_t)sizeof(TA) < (1ll << 32) &&
+                      (int64_t)a.M * a.K * 4 < (1ll << 32) && ceil_div(a.N, 16) * ceil_div(a.M, 16) < (1ll << 31);
+  // The wave-level kernel keeps a single tile of a short reduction (7 x 9 x 5: 2.1 us against 2.7) and large products
+  // whose last chunk of 32 would be mostly padding (1500 x 1500 x 130: 22.3 us against 24).
+  const bool wave = batch == 1 && ((a.N <= 16 && a.M <= 16 && a.K <= 16) ||
+                                   (a.K % 4 == 2 && ceil_div(a.K, GT_KC) * GT_KC * 100 >= (int64_t)a.K * 118 &&
+                                    ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN) > 2 * cus));
+  if (wave) t_path = plain ? "tbmm:wave" : "mlp:layers";
+  else if (splitk && splitk_beats_tile(a, cus)) return took(plain ? "tbmm:splitk" : "mlp:tiles", launch_gemm_splitk<TA, !plain>(a, cus, s));
+  else if (try_gemm_tile<TA, EPI>(a, batch, s, &st)) return took(plain ? "tbmm:tile" : "mlp:layers", st);
   t_path = plain ? "tbmm:wave" : "mlp:layers";
   // widest per-lane load that keeps every row start aligned
   if (a.K % 4 == 0) return launch_gemm_tm<TA, 4, EPI>(a, batch, tm, s);
@@ -803,7 +815,9 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
     return took("tbmm:i8", launch_status());
   }
 
-  {
+  // (A single pair with 64 k and more is faster with its reduction split: (N,M,K) = (64,64,64) 5.2 -> 3.0 us, (1000,1000,64)
+  // 8.7 -> 6.2; below, the strips win: (1000,1000,57) 5.9 against 6.3, (128,300,17) 2.7 against 3.1.)
+  if (B > 1 || K < 64) {
     tc_status st = TC_OK;
     if (try_tbmm_lds(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:lds", st);
   }
@@ -927,13 +941,6 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
   // the fused kernel addresses its operands (fp64 activations, fp32 weights) with 32-bit byte offsets
   for (int l = 0; l < n_layers; l++)
     fused = fused && batch * dims[l] * 8 < (1ll << 32) && dims[l + 1] * dims[l] * 4 < (1ll << 32);
-  // Large batches: when every layer fills the chip with 64 x 64 blocks, one LDS-tiled launch per layer (70 % of the
-  // fp64 matrix peak) beats the fused kernel's 16 x 16 tiles (43 %), and the launches no longer matter.
-  if (n_layers > 1 && t_opt.mlp_kernel == TC_MLP_AUTO) {
-    int64_t min_blocks = INT64_MAX;
-    for (int l = 0; l < n_layers; l++) min_blocks = std::min(min_blocks, ceil_div(batch, GT_BM) * ceil_div(dims[l + 1], GT_BN));
-    if (min_blocks >= 256) fused = false;
-  }
   const int cus = device_cus();
   // Small batches with reductions of at most 1024: one workgroup per compute unit, every XCD's workgroups own an eighth
   // of the column tiles of every layer (mlp_rows.hpp).  Option TC_OPT_MLP_KERNEL = TC_MLP_TILES keeps the tile-stream
@@ -976,7 +983,9 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
       return took("mlp:rows", launch_status());
     }
   }
-  if (fused && cus > 0) {
+  // The tile-stream kernel as one persistent kernel only where the caller asks for it: one launch per layer is faster
+  // (mlp_fused.hpp) and waits for nobody.
+  if (fused && cus > 0 && t_opt.mlp_kernel != TC_MLP_AUTO) {
     MlpArgs a{};
     a.I = I;
     int64_t max_jobs = 1;
@@ -1002,20 +1011,23 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
     return took("mlp:tiles", launch_status());
   }
 
-  // Otherwise one launch per layer through the shape-generic contraction.
+  // Otherwise one launch per layer ("mlp:tiles" where one of them is the tile-stream layer, as in the persistent kernel).
   const void* in = I;
+  bool tiles = false;
   for (int l = 0; l < n_layers; l++) {
     GemmArgs a{};
     a.A = in; a.Bm = W[l]; a.bias = bias[l]; a.C = O[l]; a.C64 = act[l];
     a.strideA = 0; a.strideB = 0; a.strideC = 0;
+    a.clear = l == 0 && n_layers > 1 ? reinterpret_cast<unsigned*>(ws) + MLP_SYNC_ERROR : nullptr;  // nothing here can give up
     a.N = (int)batch; a.M = (int)dims[l + 1]; a.K = (int)dims[l];
     const int tm = pick_strip(dims[l + 1], ceil_div(batch, 16) * ceil_div(dims[l + 1], 16));
     const tc_status st = (l == 0) ? launch_gemm<float, EPI_BIAS_RELU>(a, 1, tm, s)
                                   : launch_gemm<double, EPI_BIAS_RELU>(a, 1, tm, s);
     if (st != TC_OK) return st;
+    tiles = tiles || strcmp(t_path, "mlp:tiles") == 0;
     in = act[l];
   }
-  return took("mlp:per_layer", TC_OK);
+  return took(tiles && t_opt.mlp_kernel == TC_MLP_AUTO ? "mlp:tiles" : "mlp:per_layer", TC_OK);
 }
 
 // Strided convolution on the fp64 matrix core (sconv_tile.hpp): blocks of 64 filters x 64 or 32 pixels.

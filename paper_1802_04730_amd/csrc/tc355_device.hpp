@@ -95,4 +95,24 @@ __device__ __forceinline__ Vec<T, V> load_vec(const T* p) {
   return r;
 }
 
+// The same for 16-byte vectors whose elements alone are aligned (global memory; one instruction all the same).
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d2_any __attribute__((ext_vector_type(2), aligned(8)));
+
+template <typename T, int V>
+__device__ __forceinline__ Vec<T, V> load_vec_any(const T* p) {
+  static_assert(sizeof(T) * V == 16, "16-byte vectors");
+  Vec<T, V> r;
+  if constexpr (V == 4) {
+    const f4_any t = *reinterpret_cast<const f4_any*>(p);
+#pragma unroll
+    for (int e = 0; e < V; e++) r.e[e] = t[e];
+  } else {
+    const d2_any t = *reinterpret_cast<const d2_any*>(p);
+#pragma unroll
+    for (int e = 0; e < V; e++) r.e[e] = t[e];
+  }
+  return r;
+}
+
 }  // namespace tc355
