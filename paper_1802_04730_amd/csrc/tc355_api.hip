@@ -34,6 +34,7 @@
 #include "mlp_rows.hpp"
 #include "sconv_tile.hpp"
 #include "sconv_i8.hpp"
+#include "tbmm_any.hpp"
 #include "tbmm_lds.hpp"
 
 using namespace tc355;
@@ -645,6 +646,99 @@ bool try_tbmm_lds(const float* X, const float* Y, float* Z, int64_t B, int64_t N
   return launch_tbmm_lds(pl, a, wgs, lds, s, st);
 }
 
+// ---- transposed batched matmul of small matrices of any size ----
+template <int TN, int TM, int KMAX>
+tc_status launch_tbmm_any(const TbmmAnyArgs& a, unsigned wgs, size_t lds, hipStream_t s) {
+  static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
+  if (!lds_ok.load(std::memory_order_acquire)) {
+    const void* kernels[2] = {reinterpret_cast<const void*>(tbmm_any_kernel<TN, TM, KMAX, false>), reinterpret_cast<const void*>(tbmm_any_kernel<TN, TM, KMAX, true>)};
+    for (const void* k : kernels)
+      if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return TC_ERR_LAUNCH;
+    lds_ok.store(1, std::memory_order_release);
+  }
+  if (a.K % 16 == 0) tbmm_any_kernel<TN, TM, KMAX, true><<<dim3(wgs), dim3(WG_THREADS), lds, s>>>(a);
+  else tbmm_any_kernel<TN, TM, KMAX, false><<<dim3(wgs), dim3(WG_THREADS), lds, s>>>(a);
+  return launch_status();
+}
+
+template <int TN, int KMAX>
+tc_status launch_tbmm_any_tm(int tm, const TbmmAnyArgs& a, unsigned wgs, size_t lds, hipStream_t s) {
+  switch (tm) {
+    case 1: return launch_tbmm_any<TN, 1, KMAX>(a, wgs, lds, s);
+    case 2: return launch_tbmm_any<TN, 2, KMAX>(a, wgs, lds, s);
+    case 3: return launch_tbmm_any<TN, 3, KMAX>(a, wgs, lds, s);
+    case 4: return launch_tbmm_any<TN, 4, KMAX>(a, wgs, lds, s);
+    default: return launch_tbmm_any<TN, 5, KMAX>(a, wgs, lds, s);
+  }
+}
+
+struct TbmmAnyPlan {
+  int64_t strips_n, strips_m, jobs, units, lds;
+  double cost;
+};
+
+// Jobs of tn x tm tiles: what they take, and an estimate of the launch in clocks; false where they do not fit.
+bool plan_tbmm_any(int64_t B, int64_t N, int64_t M, int64_t K, int tn, int tm, TbmmAnyPlan* p) {
+  p->strips_n = ceil_div(ceil_div(N, 16), tn);
+  p->strips_m = ceil_div(ceil_div(M, 16), tm);
+  if (B >= kMaxElems / (p->strips_n * p->strips_m)) return false;  // 32-bit job numbers
+  p->jobs = B * p->strips_n * p->strips_m;
+  const int64_t xrows = std::min<int64_t>(16 * tn, N), yrows = std::min<int64_t>(16 * tm, M);
+  const int64_t pieces = (xrows * K + 6) / 4 + (yrows * K + 6) / 4;
+  p->units = std::max((K % 16 == 0 ? pieces + pieces / 16 : pieces) + 2, (xrows * yrows + 6) / 4 + 1);  // (the last step reads past its row)
+  p->lds = WAVES_PER_WG * p->units * 16;
+  if (p->lds > 160 * 1024) return false;
+  // A job's instructions in clocks of a SIMD (loads, MFMAs, operand reads, results; rows that leave one by one), the round
+  // trip in front of them, the wavefronts that share a SIMD as registers and LDS allow, and what memory delivers.  The
+  // constants are fitted to the measured times of 42 shapes at every (tn, tm): on average 0.3 % from the best choice, 5 %
+  // at worst.
+  const int kmax = K <= 31 ? 31 : K <= 63 ? 63 : 103, steps = (int)ceil_div(K, 4);
+  const int loads = tbmm_any_loads(16 * tn, kmax) + tbmm_any_loads(16 * tm, kmax);
+  const double work = loads * 39.0 + tn * tm * steps * 83.5 + (tn + tm) * steps * (K % 16 == 0 ? 20.1 : 11.2) + tn * tm * 4 * 71.0 +
+                      (yrows == M ? 0.0 : 20.0 * xrows);
+  const int64_t per_simd = ceil_div(p->jobs, 4 * 256);
+  const int64_t w = std::min(per_simd, std::max<int64_t>(1, std::min<int64_t>(512 / (4 * loads + 8 * tn * tm + 44), 160 * 1024 / p->lds)));
+  const double bytes = 4.0 * ((xrows + yrows) * K + xrows * yrows);
+  p->cost = 5430 + std::max({ceil_div(per_simd, w) * (1470 + work), per_simd * work, per_simd * 4 * bytes / 11.0});
+  // (two tiles of rows are a little worse than that: 27 x 61 x 35 24.3 us against 22.3, 94 x 18 x 86 50.1 against 47.9)
+  if (tn == 2 && tm >= 2) p->cost *= tm >= 4 ? 1.15 : K > 63 ? 1.06 : 1.0;
+  return true;
+}
+
+// Reductions up to 103 (what the register file holds of two strips on their way).
+bool try_tbmm_any(const float* X, const float* Y, float* Z, int64_t B, int64_t N, int64_t M, int64_t K, hipStream_t s, tc_status* st) {
+  const int cus = device_cus();
+  if (cus <= 0 || K > 103 || prod_reaches({B, N, K}, 1ll << 40) || prod_reaches({B, M, K}, 1ll << 40) || B * N * K < 4 || B * M * K < 4) return false;
+  const int tiles_n = (int)std::min<int64_t>(2, ceil_div(N, 16)), tiles_m = (int)std::min<int64_t>(5, ceil_div(M, 16));
+  TbmmAnyPlan best{}, pl{};
+  int tn = 0, tm = 0;
+  for (int n = 1; n <= tiles_n; n++)
+    for (int m = 1; m <= std::min(tiles_m, K <= 63 ? 5 : n == 1 ? 4 : 3); m++)  // (registers)
+      if (plan_tbmm_any(B, N, M, K, n, m, &pl) && (tn == 0 || pl.cost < best.cost)) { best = pl; tn = n; tm = m; }
+  if (tn == 0) return false;
+  TbmmAnyArgs a{};
+  a.X = X; a.Y = Y; a.Z = Z;
+  a.N = (int)N; a.M = (int)M; a.K = (int)K;
+  a.strips_n = (int)best.strips_n; a.strips_m = (int)best.strips_m;
+  a.jobs = (int)best.jobs;
+  a.wave_lds_units = (int)best.units;
+  a.xtotal = B * N * K; a.ytotal = B * M * K;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(4, (160 * 1024) / best.lds));
+  const unsigned wgs = (unsigned)std::min<int64_t>(ceil_div(best.jobs, WAVES_PER_WG), per_cu * cus);
+  const size_t lds = (size_t)best.lds;
+  if (K <= 31) {
+    *st = tn == 2 ? launch_tbmm_any_tm<2, 31>(tm, a, wgs, lds, s) : launch_tbmm_any_tm<1, 31>(tm, a, wgs, lds, s);
+  } else if (K <= 63) {
+    *st = tn == 2 ? launch_tbmm_any_tm<2, 63>(tm, a, wgs, lds, s) : launch_tbmm_any_tm<1, 63>(tm, a, wgs, lds, s);
+  } else if (tn == 2) {
+    *st = tm == 1 ? launch_tbmm_any<2, 1, 103>(a, wgs, lds, s) : tm == 2 ? launch_tbmm_any<2, 2, 103>(a, wgs, lds, s) : launch_tbmm_any<2, 3, 103>(a, wgs, lds, s);
+  } else {
+    *st = tm == 1 ? launch_tbmm_any<1, 1, 103>(a, wgs, lds, s) : tm == 2 ? launch_tbmm_any<1, 2, 103>(a, wgs, lds, s)
+        : tm == 3 ? launch_tbmm_any<1, 3, 103>(a, wgs, lds, s) : launch_tbmm_any<1, 4, 103>(a, wgs, lds, s);
+  }
+  return true;
+}
+
 // ---- the same arithmetic for small images with 32 channels per group ----
 template <int H, int W, int MIND>
 bool try_gconv_i8_c32(const GconvArgs& g, hipStream_t s, tc_status* st) {
@@ -817,9 +911,20 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
 
   // (A single pair with 64 k and more is faster with its reduction split: (N,M,K) = (64,64,64) 5.2 -> 3.0 us, (1000,1000,64)
   // 8.7 -> 6.2; below, the strips win: (1000,1000,57) 5.9 against 6.3, (128,300,17) 2.7 against 3.1.)
+  // Batches of small matrices.  The aligned kernel keeps what it is built for, whole batch elements or strips of few rows
+  // at reductions that spread over the LDS banks: (B,N,M,K) = (4000,26,72,26) 17.1 us against 21.5 on the other one,
+  // (105,29,88,48) 4.2 / 4.8, (1000,32,100,32) 12.1 / 13.2; beside that, with results of up to 5 column tiles leaving as
+  // one stream, the other one wins: (5239,42,68,26) 42.8 / 39.2, (2000,48,48,48) 24.7 / 19.7, (3000,40,40,16) 16.1 / 11.5.
+  // 64 x 64 blocks keep large matrices that fill them to four fifths: (1000,64,64,64) 19.3 / 23.5, but (700,96,96,96) 58 / 52.
+  // Everything else ran on the wave-level kernel: (4000,27,61,35) 38.8 / 22.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.
   if (B > 1 || K < 64) {
     tc_status st = TC_OK;
-    if (try_tbmm_lds(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:lds", st);
+    const bool any = B > 1 && M <= 80 && (N > 32 || K % 16 == 0);
+    if (!any && try_tbmm_lds(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:lds", st);
+    const int64_t padded = ceil_div(N, GT_BM) * GT_BM * ceil_div(M, GT_BN) * GT_BN;
+    const bool blocks = K % 4 == 0 && N >= 48 && M >= 48 && 5 * N * M >= 4 * padded && padded / (GT_BM * GT_BN) * B >= 128;
+    const bool tiny = N <= 16 && M <= 16 && K <= 8;  // nothing to stage: (30000,8,8,8) 14.7 us on the wave-level kernel, 15.4 here
+    if (B > 1 && !blocks && !tiny && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:wave", st);
   }
 
   GemmArgs a{};
