@@ -32,6 +32,7 @@
 #include "lut_sum.hpp"
 #include "mlp_fused.hpp"
 #include "mlp_rows.hpp"
+#include "sconv_split.hpp"
 #include "sconv_tile.hpp"
 #include "sconv_i8.hpp"
 #include "tbmm_any.hpp"
@@ -1135,11 +1136,45 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
   return took(tiles && t_opt.mlp_kernel == TC_MLP_AUTO ? "mlp:tiles" : "mlp:per_layer", TC_OK);
 }
 
-// Strided convolution on the fp64 matrix core (sconv_tile.hpp): blocks of 64 filters x 64 or 32 pixels.
+template <int TF, int TP>
+tc_status launch_sconv_split(SconvArgs a, hipStream_t s) {
+  static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
+  if (!lds_ok.load(std::memory_order_acquire)) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(sconv_split_kernel<TF, TP>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+      return TC_ERR_LAUNCH;
+    lds_ok.store(1, std::memory_order_release);
+  }
+  a.tiles_f = (int)ceil_div(a.F, 16 * TF);
+  const int64_t lds = SconvSplitGeom<TF, TP>::STAGES + ceil_div(a.K, SS_KC) * SS_KC * 4;
+  sconv_split_kernel<TF, TP><<<dim3((unsigned)(a.tiles_f * ceil_div(a.P, 16 * TP))), dim3(WG_THREADS), (size_t)lds, s>>>(a);
+  return launch_status();
+}
+
+// Strided convolution on the fp64 matrix core: blocks of 64 filters x 64 or 32 pixels (sconv_tile.hpp), or smaller ones with
+// a split reduction (sconv_split.hpp).
 tc_status launch_sconv_tile(SconvArgs a, hipStream_t s) {
+  const int cus = std::max(1, device_cus());
+  // Which kernel, from what a compute unit would spend in clocks: blocks one after the other when there are several per
+  // unit, a single one bound by its chain of chunks (16 taps, 64 with a split reduction).  The constants are fitted to the
+  // measured times of 46 layers: the faster kernel is taken for each of them.  Measured, (pixels, filters, taps): blocks of
+  // 64 against 16 x 16 with a split reduction (400,64,1029) 40.8 / 10.8 us, (1331,64,9898) 349 / 106, (784,20,425) 19.5 / 6.3;
+  // (11664,100,576) 45.5 / 54.9, (100352,64,64) 31 / 69; against 32 x 16 (867,215,3136) 113 / 51.6, (53312,20,128) 27.4 / 24.
+  const bool offsets = !prod_reaches({a.N, a.C, a.H, a.W}, (int64_t)1 << 30) && !prod_reaches({a.F, a.K}, (int64_t)1 << 30);
+  const int64_t chunks = ceil_div(a.K, SS_KC), table = chunks * SS_KC * 4;
+  if (offsets && SconvSplitGeom<2, 1>::STAGES + table <= 160 * 1024 && ceil_div(a.F, 16) * ceil_div(a.P, 16) <= kMaxGrid) {
+    const bool wide64 = ceil_div(a.F, SC_BF) * ceil_div(a.P, 64) >= 2 * cus;
+    const double blocks = (double)ceil_div(ceil_div(a.F, SC_BF) * ceil_div(a.P, wide64 ? 64 : 32), cus), steps = (double)ceil_div(a.K, SC_KC);
+    const double tile = 9400 + std::max((wide64 ? 2913 : 1303) * steps, blocks * ((wide64 ? 1602 : 816) * steps + 2224));
+    auto split = [&](int tf, double one, double many) {
+      const double n = (double)ceil_div(ceil_div(a.F, 16 * tf) * ceil_div(a.P, 16), cus);
+      return 8175 + (double)a.K + std::max(one * chunks, n * (many * chunks + 752 * tf));
+    };
+    const double s1 = split(1, 921, 688), s2 = split(2, 1510, 1062);
+    if (std::min(s1, s2) < tile) return s1 <= s2 ? launch_sconv_split<1, 1>(a, s) : launch_sconv_split<2, 1>(a, s);
+  }
   a.tiles_f = (int)ceil_div(a.F, SC_BF);
   // 64-pixel blocks when there are at least two of them per compute unit, else 32-pixel blocks (twice as many)
-  const bool wide = (int64_t)a.tiles_f * ceil_div(a.P, 64) >= 2 * (int64_t)std::max(1, device_cus());
+  const bool wide = (int64_t)a.tiles_f * ceil_div(a.P, 64) >= 2 * (int64_t)cus;
   const int64_t grid = (int64_t)a.tiles_f * ceil_div(a.P, wide ? 64 : 32);
   if (grid > kMaxGrid) return TC_ERR_UNSUPPORTED;
   const dim3 gd((unsigned)grid), bd(WG_THREADS);
