@@ -120,12 +120,18 @@ bool try_gemm_tile(const GemmArgs& a, int64_t batch, hipStream_t s, tc_status* s
 
 int device_cus();
 
+bool try_gconv_mix(const GconvArgs& g, hipStream_t s, tc_status* st);
+
 // ---- grouped convolution with 4 or 8 channels per group (4x4x4 MFMA blocks), compile-time width --------
 template <int C, int F, int KH, int KW, int W, int ROWS, int MINW>
 bool try_gconv_quad(const GconvArgs& g, hipStream_t s, tc_status* st) {
   using Gm = GconvQuadGeom<C, F, KH, KW, W, ROWS>;
   if (g.C != C || g.F != F || g.KH != KH || g.KW != KW || g.W != W) return false;
   const int64_t grid = (int64_t)g.N * g.G;
+  // One workgroup per (image, group) leaves the chip idle where there are few: the same 4x4x4 blocks in pieces of an image
+  // (gconv_mix.hpp).  Measured at 32 groups: 4 channels, 56 x 56, batch 1 / 4 / 8 12.7 / 13.3 / 14.4 us here and 6.3 / 11.1 /
+  // 16.3 there; 8 channels, 28 x 28, batch 1 / 2 / 4 7.3 / 7.4 / 7.6 and 5.4 / 6.7 / 7.8.
+  if (grid < (C == 4 ? device_cus() : device_cus() / 2) && try_gconv_mix(g, s, st)) return true;
   if (grid > kMaxGrid) return false;
   static std::atomic<int> lds_ok{0};
   if (!lds_ok.load(std::memory_order_acquire)) {
@@ -1341,7 +1347,16 @@ tc_status tc_group_conv(const float* I, const float* W1, const float* bias, floa
   if (try_gconv_quad<4, 4, 3, 3, 58, 16, 4>(a, s, &st)) return took("gconv:quad", st);    // the same two with a border of one pixel
   if (try_gconv_quad<8, 8, 3, 3, 30, 14, 3>(a, s, &st)) return took("gconv:quad", st);
   if (try_gconv_tiny<32, 32, 3, 3, 7, 7>(a, s, &st)) return took("gconv:tiny", st);       // the paper's (32,32,32,32,7,7)
-  if (try_gconv_lds<16, 16, 3, 3, 7>(a, s, &st)) return took("gconv:lds", st);
+  // 16 channels, any image: blocks of 448 pixels where one or two of them fit the image closely and there are enough, else
+  // blocks of the image's own measure (gconv_mix.hpp).  Measured at 32 groups, batch 16 (lds / mix, us): 22 x 24 26.7 / 29.1,
+  // 30 x 30 48.5 / 53.6, 22 x 22 26.1 / 27.3; 9 x 9 23.5 / 9.2, 28 x 28 48.2 / 42.8, 33 x 33 84.9 / 55.4, 46 x 46 145 / 101,
+  // 56 x 56 156 / 148.
+  {
+    const int64_t npix = OH * OW, pblocks = ceil_div(npix, 448);
+    if (W % 2 == 0 && pblocks <= 2 && npix * 100 >= pblocks * 448 * 85 && !prod_reaches({N, G, pblocks}, kMaxElems) &&
+        N * G * pblocks >= device_cus() && try_gconv_lds<16, 16, 3, 3, 7>(a, s, &st))
+      return took("gconv:lds", st);
+  }
   // G = 1 is the plain convolution of Section 3: the strided convolution's fp64 kernel (implicit contraction over
   // all pixels of the batch in blocks of 64 x 64) where there are at least 64 filters and 64 taps to fill its blocks
   if (G == 1 && F >= 64 && C * KH * KW >= 64 && !prod_reaches({N, C, H, W}, kMaxElems) && !prod_reaches({N, F, OH, OW}, kMaxElems) &&

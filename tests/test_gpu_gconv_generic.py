@@ -69,3 +69,25 @@ def test_gconv_generic_keeps_infinities_out_of_the_padding(oracle_threads):
     got = O.cpu().numpy()
     assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.isposinf(ref).sum() == 12
     assert not np.isnan(got).any()
+
+
+@pytest.mark.parametrize("shape,path", [
+    ((16, 32, 16, 16, 22, 22, 3, 3), "gconv:lds"),   # one block of 448 pixels per image, enough of them
+    ((4, 33, 16, 16, 30, 30, 3, 3), "gconv:lds"),    # two
+    ((3, 32, 16, 16, 30, 30, 3, 3), "gconv:wave"),   # too few of them
+    ((8, 32, 16, 16, 21, 22, 3, 3), "gconv:wave"),   # 380 pixels leave the block 15 % empty
+    ((8, 31, 4, 4, 56, 56, 3, 3), "gconv:quad"),     # fewer (image, group) pairs than compute units: pieces of an image
+    ((8, 32, 4, 4, 56, 56, 3, 3), "gconv:quad"),     # one workgroup for each
+    ((4, 31, 8, 8, 28, 28, 3, 3), "gconv:quad"),
+    ((4, 32, 8, 8, 28, 28, 3, 3), "gconv:quad"),
+])
+def test_gconv_both_sides_of_the_dispatch(shape, path, oracle_threads):
+    from paper_1802_04730_amd import tc355 as tc
+    I, W1, bias = inputs.make_gconv(*shape, seed=shape[0] + shape[4])
+    ref = oracle.group_conv(I, W1, bias)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    O = torch.full(ref.shape, float("nan"), device="cuda")
+    tc.tc_group_conv(dev(I), dev(W1), dev(bias), O)
+    torch.cuda.synchronize()
+    assert tc.last_path() == path
+    assert parity_error(O.cpu().numpy().astype(np.float64), ref) <= TIGHT
