@@ -27,34 +27,10 @@
 #pragma once
 #include <type_traits>
 
-#include "gconv_wave.hpp"
+#include "gconv_mix_plan.hpp"
+#include "tc355_device.hpp"
 
 namespace tc355 {
-
-struct GconvMixArgs {
-  const float* I;     // [N][G][C][H][W]
-  const float* W1;    // [G][F][C][KH][KW]
-  const float* bias;  // [G*F] or nullptr
-  float* O;           // [N][G][F][OH][OW]
-  int N, G, C, F, H, W, KH, KW, OH, OW;
-  int fblocks;         // filter blocks per group
-  int fb;              // filters per block (at most 16*FT + 4*FQ)
-  int imgs;            // images per job (1 unless an image has few pixels)
-  int iblocks;         // ceil(N / imgs)
-  int pblocks;         // pixel blocks per image (1 if imgs > 1)
-  int px;              // pixels per block, a multiple of 16, at most 64*TP
-  int jobs;            // G * fblocks * iblocks * pblocks
-  int cus;             // compute units of the device
-  int cc;              // channels per chunk
-  int rows;            // input rows staged per image (at most H)
-  int ps;              // LDS plane stride in doubles, = 16 (mod 32)
-  int upc;             // 16-byte units per (channel, image): ceil(rows * W / 4)
-  unsigned upc_magic, ow_magic, kk_magic, kw_magic, npix_magic;  // for div_magic; npix's is 0 (quotient 0) if imgs = 1
-};
-
-// u / d for magic = ceil(2^31 / d), while 2 u d < 2^32
-__device__ __forceinline__ int div_magic(int u, unsigned magic) { return (int)__umulhi(2u * (unsigned)u, magic); }
-
 
 template <int FT, int FQ, int TP>
 __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p) {
@@ -68,84 +44,35 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
   const int r16 = lane & 15, q = lane >> 4;
   const int KK = p.KH * p.KW, W = p.W, OW = p.OW, PS = p.ps;
   const int npix = p.OH * OW;
-  const unsigned plane = (unsigned)(p.H * W);
   const int seg = p.rows * W;
   double* band = gm_lds;                                                // [cc][PS], images of a plane `seg` apart
   double* fil = gm_lds + p.cc * PS;                                     // [step][REC]
   int* tab = reinterpret_cast<int*>(fil + ((p.cc * KK + 3) >> 2) * REC);  // [step][4]: byte offset of k slot q's tap; 12 spare entries
 
   // ---- stages (job, chunk of channels), in order
-  struct Stage { int job, pb, ib, gf, c0; };
-  auto advance = [&](Stage& s) {
-    s.c0 += p.cc;
-    if (s.c0 < p.C) return;
-    s.c0 = 0;
-    s.job++;
-    if (++s.pb < p.pblocks) return;
-    s.pb = 0;
-    if (++s.ib < p.iblocks) return;
-    s.ib = 0;
-    s.gf++;
-  };
-  Stage cur;
-  // Workgroups w, w + cus, w + 2 cus, ... share a compute unit: they take neighbouring runs, so that the units' sums
-  // differ by one job at most (in launch order, runs of 3 and 4 jobs fell on units of 9 and of 12).
-  const unsigned per_cu = gridDim.x / (unsigned)p.cus;
-  const unsigned slot = per_cu * (unsigned)p.cus == gridDim.x ? blockIdx.x % (unsigned)p.cus * per_cu + blockIdx.x / (unsigned)p.cus : blockIdx.x;
-  cur.job = (int)((int64_t)p.jobs * slot / gridDim.x);
-  const int job_end = (int)((int64_t)p.jobs * (slot + 1) / gridDim.x);
+  int job_end;
+  GconvMixStage cur = gm_first(p, blockIdx.x, gridDim.x, job_end);
   if (cur.job >= job_end) return;  // (the host launches no more workgroups than jobs)
-  {
-    const int r = cur.job / p.pblocks;
-    cur.pb = cur.job - r * p.pblocks;
-    cur.gf = r / p.iblocks;
-    cur.ib = r - cur.gf * p.iblocks;
-    cur.c0 = 0;
-  }
-  // first input row of a job's band: the last block's band is moved up to end with the image, so all have `rows` rows
-  auto first_row = [&](const Stage& s) {
-    return min(div_magic(s.pb * p.px, p.ow_magic), p.H - p.rows);
-  };
 
-  // ---- band: channels x images, each one contiguous run of `seg` input elements, in units of 4 (the last unit of a
-  // run overlaps its neighbour instead of passing the end).  Unit tid + j * 256 of a stage goes through register j.
-  unsigned goff[NU];  // its byte offset in I from the stage's first element
-  int loff[NU];       // its LDS offset in doubles
-  int decoded = -1;   // number of units that goff / loff were worked out for
+  // ---- band: units of 4 elements (gm_place); the first NU of a thread are fetched a stage ahead
+  GconvMixUnits<NU> at;
   f4_any pre[NU];
-  auto place = [&](int u, int cc, unsigned& go, int& lo) {
-    const int sg = div_magic(u, p.upc_magic);
-    const int i = min(4 * (u - sg * p.upc), seg - 4);
-    int img = 0, c = sg;
-    if (p.imgs > 1) { img = sg / cc; c = sg - img * cc; }
-    go = 4u * ((unsigned)img * (unsigned)(p.G * p.C) * plane + (unsigned)c * plane + (unsigned)i);
-    lo = c * PS + img * seg + i;
-  };
-  auto units_of = [&](const Stage& s) { return min(p.imgs, p.N - s.ib * p.imgs) * min(p.cc, p.C - s.c0) * p.upc; };
-  auto band_of = [&](const Stage& s) {
-    const int g = s.gf / p.fblocks;
-    return reinterpret_cast<const char*>(p.I + (((int64_t)s.ib * p.imgs * p.G + g) * p.C + s.c0) * plane + (int64_t)first_row(s) * W);
-  };
-  auto fetch = [&](const Stage& s) {
-    const int units = units_of(s);
-    if (units != decoded) {  // (same number of units: same number of channels and images)
-      decoded = units;
-#pragma unroll
-      for (int j = 0; j < NU; j++) place(min(tid + j * WG_THREADS, units - 1), min(p.cc, p.C - s.c0), goff[j], loff[j]);
-    }
+  auto band_of = [&](const GconvMixStage& s) { return reinterpret_cast<const char*>(p.I + gm_origin(p, s)); };
+  auto fetch = [&](const GconvMixStage& s) {
+    at.decode(p, s, tid, WG_THREADS);
     const char* in = band_of(s);
 #pragma unroll
-    for (int j = 0; j < NU; j++) pre[j] = *reinterpret_cast<const f4_any*>(in + goff[j]);
+    for (int j = 0; j < NU; j++) pre[j] = *reinterpret_cast<const f4_any*>(in + at.goff[j]);
   };
   auto put = [&](int lo, const f4_any& v) {
     double* o = band + lo;
     o[0] = (double)v[0]; o[1] = (double)v[1]; o[2] = (double)v[2]; o[3] = (double)v[3];
   };
-  auto park = [&](const Stage& s) {
+  auto park = [&](const GconvMixStage& s) {
+    const int units = gm_units(p, s);
 #pragma unroll
     for (int j = 0; j < NU; j++)
-      if (j * WG_THREADS < decoded) put(loff[j], pre[j]);
-    const int units = units_of(s);
+      if (j * WG_THREADS < units) put(at.loff[j], pre[j]);
     if (units > NU * WG_THREADS) {  // a band of more than 4096 elements: the rest is not fetched ahead
       const char* in = band_of(s);
       for (int u0 = tid + NU * WG_THREADS; u0 < units; u0 += 4 * WG_THREADS) {
@@ -154,7 +81,7 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
 #pragma unroll
         for (int j = 0; j < 4; j++) {
           unsigned go;
-          place(min(u0 + j * WG_THREADS, units - 1), min(p.cc, p.C - s.c0), go, lo[j]);
+          gm_place(p, min(u0 + j * WG_THREADS, units - 1), gm_channels(p, s), go, lo[j]);
           v[j] = *reinterpret_cast<const f4_any*>(in + go);
         }
 #pragma unroll
@@ -168,7 +95,7 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
   int staged_gf = -1, staged_c0 = -1;
   d4 bz[FTA];
   double bzq[FQA];
-  auto filters = [&](const Stage& st) {
+  auto filters = [&](const GconvMixStage& st) {
     const int g = st.gf / p.fblocks, f0 = (st.gf - g * p.fblocks) * p.fb, nf = min(p.fb, p.F - f0);
     const int cc = min(p.cc, p.C - st.c0), kc = cc * KK, steps = (kc + 3) >> 2;
     const bool cminor = (cc & 3) == 0;
@@ -253,8 +180,8 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
   filters(cur);
   park(cur);
   for (;;) {
-    Stage nxt = cur;
-    advance(nxt);
+    GconvMixStage nxt = cur;
+    gm_advance(p, nxt);
     const bool more = nxt.job < job_end;
     if (more) fetch(nxt);  // in flight while this stage is contracted
     __syncthreads();
@@ -267,7 +194,7 @@ __global__ __launch_bounds__(WG_THREADS, 2) void gconv_mix_kernel(GconvMixArgs p
     const int tiles = (npx + 15) >> 4, cnt = (tiles + 3 - rank) >> 2;
     const int t0 = rank * (tiles >> 2) + min(rank, tiles & 3);  // this wavefront's tiles: t0 ... t0 + cnt - 1
     if (cur.c0 == 0) {
-      const int h0 = first_row(cur);
+      const int h0 = gm_first_row(p, cur);
 #pragma unroll
       for (int t = 0; t < TP; t++) {  // LDS byte offset of this lane's output pixel in each of its tiles
         int px = min((t0 + t) * 16 + r16, npx - 1) + P0;

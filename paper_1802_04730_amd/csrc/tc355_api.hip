@@ -37,6 +37,7 @@
 #include "sconv_i8.hpp"
 #include "tbmm_any.hpp"
 #include "tbmm_lds.hpp"
+#include "tc355_host.hpp"
 
 using namespace tc355;
 
@@ -46,20 +47,6 @@ constexpr int64_t kMaxElems = (int64_t)1 << 31;  // per-tensor element limit of 
 constexpr int64_t kMaxGrid = 2147483647;
 
 inline bool misaligned(const void* p, size_t a = 16) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
-
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-// True if the product of the (positive) extents reaches `limit`; never overflows: it stops at the first factor
-// that takes the running product there.
-inline bool prod_reaches(std::initializer_list<int64_t> factors, int64_t limit) {
-  int64_t p = 1;
-  for (int64_t f : factors) {
-    if (f >= limit || p > limit / f) return true;  // p * f > limit
-    p *= f;
-    if (p >= limit) return true;
-  }
-  return false;
-}
 
 inline tc_status launch_status() { return hipGetLastError() == hipSuccess ? TC_OK : TC_ERR_LAUNCH; }
 
@@ -262,61 +249,6 @@ bool try_gconv_lds(const GconvArgs& g, hipStream_t s, tc_status* st) {
 }
 
 // ---- grouped convolution for any channel counts and images: 16- and 4-filter MFMA tiles over one LDS band ----
-struct GconvMixPlan {
-  int tp, imgs, pblocks, px, rows, ps, cc, occ;
-  int64_t jobs, lds;
-  double cost;
-};
-
-// Blocks of 64*tp output pixels at `occ` workgroups per compute unit: what they stage, and an estimate of the launch in
-// clocks.  Returns false if the channels of a chunk would not fit.
-bool plan_gconv_mix(const GconvArgs& g, int tp, int occ, int fblocks, int rec, int cus, GconvMixPlan* pl) {
-  const int64_t npix = (int64_t)g.OH * g.OW, KK = (int64_t)g.KH * g.KW;
-  pl->tp = tp;
-  pl->occ = occ;
-  int64_t tiles;  // of an image, or of the images of a job
-  if (npix * 2 <= 64 * tp) {
-    pl->imgs = (int)std::min<int64_t>(g.N, 64 * tp / npix);
-    if (prod_reaches({pl->imgs, g.G, g.C, g.H, g.W}, 1ll << 29) || prod_reaches({pl->imgs, g.G, g.F, g.OH, g.OW}, 1ll << 29)) return false;  // 32-bit byte offsets between a job's images
-    pl->pblocks = 1;
-    tiles = ceil_div(pl->imgs * npix, 16);
-    pl->px = (int)tiles * 16;
-    pl->rows = g.H;
-  } else {
-    pl->imgs = 1;
-    tiles = ceil_div(npix, 16);
-    pl->px = 16 * (int)ceil_div(tiles, ceil_div(tiles, 4 * tp));  // equal blocks
-    pl->pblocks = (int)ceil_div(npix, pl->px);
-    pl->rows = (int)(std::min<int64_t>(g.OH, (pl->px - 2) / g.OW + 2) + g.KH - 1);
-  }
-  const int64_t len = (int64_t)pl->imgs * pl->rows * g.W;
-  if (len > 16384) return false;
-  pl->ps = (int)((len + 15) / 32 * 32 + 16);
-  const int64_t per_c = pl->ps * 8 + (KK * rec * 8 + 3) / 4 + KK * 4, fixed = rec * 8 + 16 + 48;  // (a chunk's last step may be partial; the table is read ahead)
-  const int64_t most = (160 * 1024 / occ - 512 - fixed) / per_c;
-  if (most < 1) return false;
-  int64_t chunks = ceil_div(g.C, most), cc = ceil_div(g.C, chunks);
-  if (chunks > 1 && most >= 4) {  // equal chunks of a multiple of 4 channels (the layout without padded slots)
-    cc = std::min(most / 4 * 4, ceil_div(cc, 4) * 4);
-    chunks = ceil_div(g.C, cc);
-  }
-  if (std::min<int64_t>(cc, g.C - (chunks - 1) * cc) * KK < 4 || cc * KK > 4096) return false;  // filters are staged in units of 4 taps
-  pl->cc = (int)cc;
-  const int64_t steps = ceil_div(cc * KK, 4);
-  pl->lds = cc * pl->ps * 8 + steps * rec * 8 + steps * 16 + 48;
-  pl->jobs = (int64_t)g.G * fblocks * ceil_div(g.N, pl->imgs) * pl->pblocks;
-  // A stage (one chunk of one job) in clocks of a SIMD: its MFMA steps (between the average and the largest share of a
-  // wavefront), and what surrounds them (staging the band, and the filters where they change with every stage), about
-  // half of it vector instructions, which no MFMA overlaps.  `occ` workgroups cover each other's waits but not each
-  // other's instructions; alone, a step is never shorter than the LDS reads of the next one.  (The constants are fitted
-  // to measured times of 16 shapes at every (tp, occ): the choice is on average 2.5 % from the best one.)
-  const double turns = 0.5 * ((double)tiles / (4 * pl->pblocks) + tp), step = turns * rec + 8;
-  const double around = 500 + (double)cc * len / 8 + (chunks > 1 ? 3000 + 0.5 * steps * rec : 0.0);
-  const int64_t per_cu = ceil_div(pl->jobs, cus), share = std::min<int64_t>(occ, per_cu);
-  pl->cost = (double)per_cu / share * chunks * std::max(share * (steps * step + 0.5 * around), steps * std::max(step, 320.0) + around);
-  return pl->jobs < (1ll << 31);
-}
-
 template <int FT, int FQ, int TP>
 tc_status launch_gconv_mix(const GconvMixArgs& a, unsigned grid, int64_t lds, hipStream_t s) {
   static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
@@ -341,34 +273,13 @@ tc_status launch_gconv_mix_tp(int tp, const GconvMixArgs& a, unsigned grid, int6
 }
 
 bool try_gconv_mix(const GconvArgs& g, hipStream_t s, tc_status* st) {
-  const int cus = device_cus();
-  if (cus <= 0 || (int64_t)g.KH * g.W < 4 || (int64_t)g.C * g.KH * g.KW < 4) return false;  // staged in units of 4 elements
-  if (prod_reaches({g.C, g.H, g.W}, 1ll << 29) || prod_reaches({g.F, g.C, g.KH, g.KW}, 1ll << 29) ||
-      prod_reaches({g.F, g.OH, g.OW}, 1ll << 29))
-    return false;  // 32-bit byte offsets
-  const int fblocks = (int)ceil_div(g.F, 32);
-  const int fb = (int)ceil_div(ceil_div(g.F, fblocks), 4) * 4;
-  const int ft = fb / 16, fq = fb % 16 / 4, rec = ft * 64 + fq * 16;
-  GconvMixPlan best{}, pl{};
-  bool any = false;
-  for (int occ = 4; occ >= 1; occ--)
-    for (int tp = 4; tp >= 1; tp--)
-      if (plan_gconv_mix(g, tp, occ, fblocks, rec, cus, &pl) && (!any || pl.cost < best.cost)) { best = pl; any = true; }
-  if (!any) return false;
   GconvMixArgs a{};
   a.I = g.I; a.W1 = g.W1; a.bias = g.bias; a.O = g.O;
   a.N = g.N; a.G = g.G; a.C = g.C; a.F = g.F; a.H = g.H; a.W = g.W; a.KH = g.KH; a.KW = g.KW; a.OH = g.OH; a.OW = g.OW;
-  a.fblocks = fblocks; a.fb = fb;
-  a.px = best.px; a.imgs = best.imgs; a.iblocks = (int)ceil_div(g.N, best.imgs); a.pblocks = best.pblocks;
-  a.jobs = (int)best.jobs; a.cus = cus;
-  a.cc = best.cc; a.rows = best.rows; a.ps = best.ps;
-  a.upc = (int)ceil_div((int64_t)best.rows * g.W, 4);
-  if ((int64_t)g.OH * g.OW >= (1ll << 31) / g.OW) return false;  // divisions by multiplication: 2 * dividend * divisor < 2^32
-  auto magic = [](int64_t d) { return (unsigned)(((1ll << 31) + d - 1) / d); };
-  a.upc_magic = magic(a.upc); a.ow_magic = magic(g.OW); a.kk_magic = magic((int64_t)g.KH * g.KW); a.kw_magic = magic(g.KW);
-  a.npix_magic = best.imgs > 1 ? magic((int64_t)g.OH * g.OW) : 0;
-  const unsigned grid = (unsigned)std::min<int64_t>(best.jobs, (int64_t)best.occ * cus);
-  switch (fb / 4) {
+  GconvMixPlan best{};
+  if (!choose_gconv_mix(a, device_cus(), &best)) return false;
+  const unsigned grid = gconv_mix_grid(a, best);
+  switch (a.fb / 4) {
     case 1: *st = launch_gconv_mix_tp<0, 1>(best.tp, a, grid, best.lds, s); break;
     case 2: *st = launch_gconv_mix_tp<0, 2>(best.tp, a, grid, best.lds, s); break;
     case 3: *st = launch_gconv_mix_tp<0, 3>(best.tp, a, grid, best.lds, s); break;

@@ -32,6 +32,10 @@ SHAPES = [
     (9, 25, 11, 18, 16, 21, 1, 1),    # 1 x 1 filters
     (2, 5, 4, 7, 1, 64, 1, 5),        # a single row
     (2, 3, 10, 6, 64, 3, 3, 3),       # one output column
+    # two images of 6 channels behind one of 12, and the like (tests/test_gconv_mix_plan.py): several images per job and
+    # several chunks, in runs of more than one job
+    (33, 63, 42, 2, 9, 17, 3, 3),
+    (62, 54, 30, 3, 18, 6, 3, 3),
 ]
 
 
