@@ -94,10 +94,16 @@ int64_t tc355_get_option(tc_option key);
 
 /*
  * Which kernel family the calling thread's most recent entry-point call chose,
- * as a static string "op:family" (for example "tbmm:lds", "tbmm:i8",
- * "mlp:rows", "gconv:i8", "gconv:i8_taps", "gconv:band", "gconv:wave" (any shape), "sconv:i8", "sconv:tile",
- * "lut:sum"; ""
- * before the first call).  A debugging and testing aid: tests pick the tolerance of the
+ * as a static string "op:family" ("" before the first call):
+ *   tbmm:   i8, i8_presliced, lds, any, tile, splitk, wave
+ *   mlp:    rows, tiles (one persistent kernel), per_layer (one launch per layer,
+ *           each on the kernel that its extents call for)
+ *   gconv:  i8, i8_small, i8_c32, i8_taps, band, quad, tiny, lds, mix, tile, split,
+ *           wave
+ *   kron:   lds, tile, wave
+ *   sconv:  i8, tile, split
+ *   lut:    sum
+ * A debugging and testing aid: tests pick the tolerance of the
  * arithmetic that actually ran instead of re-deriving the dispatch.
  */
 const char *tc355_last_path(void);

@@ -9,7 +9,6 @@
 #include <chrono>
 #include <cstdint>
 #include <cstdlib>
-#include <cstring>
 #include <initializer_list>
 #include <random>
 #include <type_traits>
@@ -107,9 +106,10 @@ bool try_gemm_tile(const GemmArgs& a, int64_t batch, hipStream_t s, tc_status* s
 
 int device_cus();
 
-bool try_gconv_mix(const GconvArgs& g, hipStream_t s, tc_status* st);
+bool try_gconv_mix(const GconvArgs& g, hipStream_t s, tc_status* st);  // records "gconv:mix"
 
-// ---- grouped convolution with 4 or 8 channels per group (4x4x4 MFMA blocks), compile-time width --------
+// ---- grouped convolution with 4 or 8 channels per group (4x4x4 MFMA blocks), compile-time width; records the path of the
+// kernel that it chose --------
 template <int C, int F, int KH, int KW, int W, int ROWS, int MINW>
 bool try_gconv_quad(const GconvArgs& g, hipStream_t s, tc_status* st) {
   using Gm = GconvQuadGeom<C, F, KH, KW, W, ROWS>;
@@ -120,6 +120,7 @@ bool try_gconv_quad(const GconvArgs& g, hipStream_t s, tc_status* st) {
   // 16.3 there; 8 channels, 28 x 28, batch 1 / 2 / 4 7.3 / 7.4 / 7.6 and 5.4 / 6.7 / 7.8.
   if (grid < (C == 4 ? device_cus() : device_cus() / 2) && try_gconv_mix(g, s, st)) return true;
   if (grid > kMaxGrid) return false;
+  t_path = "gconv:quad";
   static std::atomic<int> lds_ok{0};
   if (!lds_ok.load(std::memory_order_acquire)) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(gconv_quad_kernel<C, F, KH, KW, W, ROWS, MINW>),
@@ -200,10 +201,9 @@ tc_status launch_gemm(const GemmArgs& a, int64_t batch, int tm, hipStream_t s) {
   const bool wave = batch == 1 && ((a.N <= 16 && a.M <= 16 && a.K <= 16) ||
                                    (a.K % 4 == 2 && ceil_div(a.K, GT_KC) * GT_KC * 100 >= (int64_t)a.K * 118 &&
                                     ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN) > 2 * cus));
-  if (wave) t_path = plain ? "tbmm:wave" : "mlp:layers";
-  else if (splitk && splitk_beats_tile(a, cus)) return took(plain ? "tbmm:splitk" : "mlp:tiles", launch_gemm_splitk<TA, !plain>(a, cus, s));
-  else if (try_gemm_tile<TA, EPI>(a, batch, s, &st)) return took(plain ? "tbmm:tile" : "mlp:layers", st);
-  t_path = plain ? "tbmm:wave" : "mlp:layers";
+  if (!wave && splitk && splitk_beats_tile(a, cus)) return took(plain ? "tbmm:splitk" : "mlp:per_layer", launch_gemm_splitk<TA, !plain>(a, cus, s));
+  if (!wave && try_gemm_tile<TA, EPI>(a, batch, s, &st)) return took(plain ? "tbmm:tile" : "mlp:per_layer", st);
+  t_path = plain ? "tbmm:wave" : "mlp:per_layer";
   // widest per-lane load that keeps every row start aligned
   if (a.K % 4 == 0) return launch_gemm_tm<TA, 4, EPI>(a, batch, tm, s);
   if (a.K % 2 == 0) return launch_gemm_tm<TA, 2, EPI>(a, batch, tm, s);
@@ -289,6 +289,7 @@ bool try_gconv_mix(const GconvArgs& g, hipStream_t s, tc_status* st) {
     case 7: *st = launch_gconv_mix_tp<1, 3>(best.tp, a, grid, best.lds, s); break;
     default: *st = launch_gconv_mix_tp<2, 0>(best.tp, a, grid, best.lds, s); break;
   }
+  t_path = "gconv:mix";
   return true;
 }
 
@@ -842,7 +843,7 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
     const int64_t padded = ceil_div(N, GT_BM) * GT_BM * ceil_div(M, GT_BN) * GT_BN;
     const bool blocks = K % 4 == 0 && N >= 48 && M >= 48 && 5 * N * M >= 4 * padded && padded / (GT_BM * GT_BN) * B >= 128;
     const bool tiny = N <= 16 && M <= 16 && K <= 8;  // nothing to stage: (30000,8,8,8) 14.7 us on the wave-level kernel, 15.4 here
-    if (B > 1 && !blocks && !tiny && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:wave", st);
+    if (B > 1 && !blocks && !tiny && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
   }
 
   GemmArgs a{};
@@ -1034,9 +1035,8 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
     return took("mlp:tiles", launch_status());
   }
 
-  // Otherwise one launch per layer ("mlp:tiles" where one of them is the tile-stream layer, as in the persistent kernel).
+  // Otherwise one launch per layer ("mlp:per_layer").
   const void* in = I;
-  bool tiles = false;
   for (int l = 0; l < n_layers; l++) {
     GemmArgs a{};
     a.A = in; a.Bm = W[l]; a.bias = bias[l]; a.C = O[l]; a.C64 = act[l];
@@ -1047,10 +1047,9 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
     const tc_status st = (l == 0) ? launch_gemm<float, EPI_BIAS_RELU>(a, 1, tm, s)
                                   : launch_gemm<double, EPI_BIAS_RELU>(a, 1, tm, s);
     if (st != TC_OK) return st;
-    tiles = tiles || strcmp(t_path, "mlp:tiles") == 0;
     in = act[l];
   }
-  return took(tiles && t_opt.mlp_kernel == TC_MLP_AUTO ? "mlp:tiles" : "mlp:per_layer", TC_OK);
+  return TC_OK;
 }
 
 template <int TF, int TP>
@@ -1068,8 +1067,8 @@ tc_status launch_sconv_split(SconvArgs a, hipStream_t s) {
 }
 
 // Strided convolution on the fp64 matrix core: blocks of 64 filters x 64 or 32 pixels (sconv_tile.hpp), or smaller ones with
-// a split reduction (sconv_split.hpp).
-tc_status launch_sconv_tile(SconvArgs a, hipStream_t s) {
+// a split reduction (sconv_split.hpp).  The caller's operator says how the two are called.
+tc_status launch_sconv_fp64(SconvArgs a, const char* tile_path, const char* split_path, hipStream_t s) {
   const int cus = std::max(1, device_cus());
   // Which kernel, from what a compute unit would spend in clocks: blocks one after the other when there are several per
   // unit, a single one bound by its chain of chunks (16 taps, 64 with a split reduction).  The constants are fitted to the
@@ -1087,7 +1086,7 @@ tc_status launch_sconv_tile(SconvArgs a, hipStream_t s) {
       return 8175 + (double)a.K + std::max(one * chunks, n * (many * chunks + 752 * tf));
     };
     const double s1 = split(1, 921, 688), s2 = split(2, 1510, 1062);
-    if (std::min(s1, s2) < tile) return s1 <= s2 ? launch_sconv_split<1, 1>(a, s) : launch_sconv_split<2, 1>(a, s);
+    if (std::min(s1, s2) < tile) return took(split_path, s1 <= s2 ? launch_sconv_split<1, 1>(a, s) : launch_sconv_split<2, 1>(a, s));
   }
   a.tiles_f = (int)ceil_div(a.F, SC_BF);
   // 64-pixel blocks when there are at least two of them per compute unit, else 32-pixel blocks (twice as many)
@@ -1102,7 +1101,7 @@ tc_status launch_sconv_tile(SconvArgs a, hipStream_t s) {
     if (a.K % 4 == 0) sconv_tile_kernel<4, 32><<<gd, bd, SconvGeom<32>::LDS_BYTES, s>>>(a);
     else sconv_tile_kernel<1, 32><<<gd, bd, SconvGeom<32>::LDS_BYTES, s>>>(a);
   }
-  return launch_status();
+  return took(tile_path, launch_status());
 }
 
 // Strided convolution on the int8 matrix core (sconv_i8.hpp): TF filters against 16 * NT pixels per workgroup.
@@ -1253,10 +1252,10 @@ tc_status tc_group_conv(const float* I, const float* W1, const float* bias, floa
   }
   if (try_gconv_band<16, 3, 3, 58, 8, 2>(a, s, &st)) return took("gconv:band", st);
   if (try_gconv_band<16, 3, 3, 14, 12, 2>(a, s, &st)) return took("gconv:band", st);  // the paper's (32,32,16,16,14,14): the whole image is one band
-  if (try_gconv_quad<4, 4, 3, 3, 56, 16, 4>(a, s, &st)) return took("gconv:quad", st);    // the paper's (32,32,4,4,56,56)
-  if (try_gconv_quad<8, 8, 3, 3, 28, 26, 3>(a, s, &st)) return took("gconv:quad", st);    // the paper's (32,32,8,8,28,28): one band
-  if (try_gconv_quad<4, 4, 3, 3, 58, 16, 4>(a, s, &st)) return took("gconv:quad", st);    // the same two with a border of one pixel
-  if (try_gconv_quad<8, 8, 3, 3, 30, 14, 3>(a, s, &st)) return took("gconv:quad", st);
+  if (try_gconv_quad<4, 4, 3, 3, 56, 16, 4>(a, s, &st)) return st;    // the paper's (32,32,4,4,56,56)
+  if (try_gconv_quad<8, 8, 3, 3, 28, 26, 3>(a, s, &st)) return st;    // the paper's (32,32,8,8,28,28): one band
+  if (try_gconv_quad<4, 4, 3, 3, 58, 16, 4>(a, s, &st)) return st;    // the same two with a border of one pixel
+  if (try_gconv_quad<8, 8, 3, 3, 30, 14, 3>(a, s, &st)) return st;
   if (try_gconv_tiny<32, 32, 3, 3, 7, 7>(a, s, &st)) return took("gconv:tiny", st);       // the paper's (32,32,32,32,7,7)
   // 16 channels, any image: blocks of 448 pixels where one or two of them fit the image closely and there are enough, else
   // blocks of the image's own measure (gconv_mix.hpp).  Measured at 32 groups, batch 16 (lds / mix, us): 22 x 24 26.7 / 29.1,
@@ -1276,13 +1275,13 @@ tc_status tc_group_conv(const float* I, const float* W1, const float* bias, floa
     e.I = I; e.Wt = W1; e.bias = bias; e.O = O;
     e.N = (int)N; e.C = (int)C; e.F = (int)F; e.H = (int)H; e.W = (int)W; e.KH = (int)KH; e.KW = (int)KW;
     e.sh = 1; e.sw = 1; e.OH = (int)OH; e.OW = (int)OW; e.K = (int)(C * KH * KW); e.P = (int)(N * OH * OW);
-    return took("gconv:tile", launch_sconv_tile(e, s));
+    return launch_sconv_fp64(e, "gconv:tile", "gconv:split", s);
   }
-  // The shape-generic kernels ("gconv:wave"): gconv_mix.hpp, except where a reduction is so short that there is nothing
+  // The shape-generic kernels: gconv_mix.hpp ("gconv:mix"), except where a reduction is so short that there is nothing
   // to stage (1 x 1 filters on 4 channels, 32 x 32 x (16 x 21): 5.6 us on the wave kernel, 6.0 on the other) or a
   // launch so small that the shorter chain wins (120 outputs of 12 taps: 3.5 us against 4.0).
   const bool tiny = K <= 4 || (K <= 16 && !prod_reaches({N, G, F, OH, OW}, 256));
-  if (!tiny && try_gconv_mix(a, s, &st)) return took("gconv:wave", st);
+  if (!tiny && try_gconv_mix(a, s, &st)) return st;
   t_path = "gconv:wave";
   // generic kernel: a wavefront takes 16 filters x a strip of 16*TP pixels; small images take a narrower strip
   const int64_t tiles_p = ceil_div(OH * OW, 16);
@@ -1325,12 +1324,12 @@ tc_status tc_kron(const float* W1, const float* W2, const float* X, float* Y, in
       return took("kron:lds", launch_status());
     }
   }
-  // The shape-generic kernels ("kron:wave"): operands in LDS wherever a block of them fits (up to about 115 of every
+  // The shape-generic kernels: operands in LDS ("kron:tile") wherever a block of them fits (up to about 115 of every
   // extent, more where others are smaller): 22.3 -> 7.9 us at (B,I,K,J,L) = (200,48,50,75,36), 242 -> 47 us at
   // (500,96,100,100,100), never slower from 8^5 up; the wave-level kernel keeps the rest.
   {
     tc_status st = TC_OK;
-    if (try_kron_tile(W1, W2, X, Y, B, I, K, J, L, s, &st)) return took("kron:wave", st);
+    if (try_kron_tile(W1, W2, X, Y, B, I, K, J, L, s, &st)) return took("kron:tile", st);
   }
   constexpr int TJ = 4;
   a.tiles_i = (int)ceil_div(I, 16);
@@ -1384,7 +1383,7 @@ tc_status tc_sconv2d(const float* I, const float* Wt, const float* bias, float* 
   a.N = (int)N; a.C = (int)C; a.F = (int)F; a.H = (int)H; a.W = (int)W; a.KH = (int)KH; a.KW = (int)KW;
   a.sh = (int)sh; a.sw = (int)sw; a.OH = (int)OH; a.OW = (int)OW;
   a.K = (int)K; a.P = (int)(N * OH * OW);
-  return took("sconv:tile", launch_sconv_tile(a, s));
+  return launch_sconv_fp64(a, "sconv:tile", "sconv:split", s);
 }
 
 tc_status tc_lut(int32_t n_tables, const float* const* LUT, const int32_t* const* Idx, float* const* O,

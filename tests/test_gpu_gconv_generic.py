@@ -51,7 +51,7 @@ def test_gconv_generic(shape, with_bias, oracle_threads):
     dev = lambda a: torch.from_numpy(a).cuda()
     tc.tc_group_conv(dev(I), dev(W1), dev(bias) if with_bias else None, O)
     torch.cuda.synchronize()
-    assert tc.last_path() == "gconv:wave"
+    assert tc.last_path() == "gconv:mix"
     err = parity_error(O.cpu().numpy().astype(np.float64), ref)
     print("gconv generic %s: parity error %.3e" % (shape, err), flush=True)
     assert err <= TIGHT
@@ -78,12 +78,31 @@ def test_gconv_generic_keeps_infinities_out_of_the_padding(oracle_threads):
 @pytest.mark.parametrize("shape,path", [
     ((16, 32, 16, 16, 22, 22, 3, 3), "gconv:lds"),   # one block of 448 pixels per image, enough of them
     ((4, 33, 16, 16, 30, 30, 3, 3), "gconv:lds"),    # two
-    ((3, 32, 16, 16, 30, 30, 3, 3), "gconv:wave"),   # too few of them
-    ((8, 32, 16, 16, 21, 22, 3, 3), "gconv:wave"),   # 380 pixels leave the block 15 % empty
-    ((8, 31, 4, 4, 56, 56, 3, 3), "gconv:quad"),     # fewer (image, group) pairs than compute units: pieces of an image
+    ((3, 32, 16, 16, 30, 30, 3, 3), "gconv:mix"),    # too few of them
+    ((8, 32, 16, 16, 21, 22, 3, 3), "gconv:mix"),    # 380 pixels leave the block 15 % empty
+    ((8, 31, 4, 4, 56, 56, 3, 3), "gconv:mix"),      # fewer (image, group) pairs than compute units: pieces of an image
     ((8, 32, 4, 4, 56, 56, 3, 3), "gconv:quad"),     # one workgroup for each
-    ((4, 31, 8, 8, 28, 28, 3, 3), "gconv:quad"),
+    ((4, 31, 8, 8, 28, 28, 3, 3), "gconv:mix"),
     ((4, 32, 8, 8, 28, 28, 3, 3), "gconv:quad"),
+    # the 4x4x4-block kernel with a workgroup for each (image, group): last bands of fewer rows, odd heights, a short image,
+    # 8-byte staging loads at widths 58 and 30
+    ((9, 29, 4, 4, 53, 56, 3, 3), "gconv:quad"),
+    ((16, 16, 4, 4, 5, 56, 3, 3), "gconv:quad"),
+    ((8, 32, 4, 4, 58, 58, 3, 3), "gconv:quad"),
+    ((16, 17, 4, 4, 21, 58, 3, 3), "gconv:quad"),
+    ((5, 27, 8, 8, 31, 28, 3, 3), "gconv:quad"),
+    ((4, 32, 8, 8, 30, 30, 3, 3), "gconv:quad"),
+    ((13, 10, 8, 8, 17, 30, 3, 3), "gconv:quad"),
+    ((8, 31, 4, 4, 21, 58, 3, 3), "gconv:mix"),
+    ((4, 31, 8, 8, 17, 30, 3, 3), "gconv:mix"),
+    # too little to stage: the wave-level kernel, in strips of 4, 2 and 1 tiles of 16 pixels
+    ((2, 3, 4, 19, 9, 10, 1, 1), "gconv:wave"),
+    ((2, 3, 4, 5, 6, 7, 1, 1), "gconv:wave"),
+    ((1, 2, 2, 3, 5, 6, 3, 2), "gconv:wave"),
+    ((5, 2, 2, 17, 3, 4, 1, 2), "gconv:wave"),
+    # one group of at least 64 filters: the strided convolution's kernels
+    ((2, 1, 12, 70, 15, 17, 3, 3), "gconv:split"),
+    ((9, 1, 9, 70, 38, 39, 3, 3), "gconv:tile"),
 ])
 def test_gconv_both_sides_of_the_dispatch(shape, path, oracle_threads):
     from paper_1802_04730_amd import tc355 as tc

@@ -34,7 +34,7 @@ SHAPES = [
 ]
 
 
-def run(tc, W1, W2, X):
+def run(tc, W1, W2, X, path="kron:tile"):
     shape = (X.shape[0], W1.shape[0], W2.shape[0])
     size = int(np.prod(shape))
     buf = torch.full((size + 2 * GUARD,), 777.0, device="cuda")
@@ -42,7 +42,7 @@ def run(tc, W1, W2, X):
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
     tc.tc_kron(dev(W1), dev(W2), dev(X), Y)
     torch.cuda.synchronize()
-    assert tc.last_path() == "kron:wave"
+    assert tc.last_path() == path
     assert bool((buf[:GUARD] == 777.0).all()) and bool((buf[GUARD + size:] == 777.0).all())
     return Y.cpu().numpy()
 
@@ -54,6 +54,18 @@ def test_kron_any(shape, oracle_threads):
     err = parity_error(run(tc, W1, W2, X).astype(np.float64), oracle.kron(W1, W2, X))
     print("kron %s: parity error %.3e" % (shape, err), flush=True)
     assert err <= TIGHT
+
+
+@pytest.mark.parametrize("shape", [
+    (3, 20, 1, 30, 17),        # nothing to contract first ...
+    (3, 17, 20, 70, 1),        # ... or second
+    (2, 37, 200, 41, 203),     # one batch element of X is larger than LDS
+    (5, 33, 18, 70, 1200),     # 16 columns of W2 and X are
+])
+def test_kron_beyond_lds(shape, oracle_threads):
+    from paper_1802_04730_amd import tc355 as tc
+    W1, W2, X = inputs.make_kron(*shape, seed=sum(shape))
+    assert parity_error(run(tc, W1, W2, X, "kron:wave").astype(np.float64), oracle.kron(W1, W2, X)) <= TIGHT
 
 
 @pytest.mark.parametrize("shape", [(3, 18, 21, 19, 23), (40, 18, 21, 19, 55)])

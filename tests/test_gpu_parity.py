@@ -60,7 +60,7 @@ TBMM_SHAPES = [
     (5, 40, 200, 30),     # several strips per row tile, K even but not a multiple of 4
     (1, 128, 256, 32),    # transposed matmul of Section 7 (B = 1)
     (7, 5, 81, 64),
-    (40, 100, 130, 68),   # LDS-tiled kernel (>= 128 blocks): ragged 64x64 blocks, reduction not a multiple of the chunk
+    (40, 100, 130, 68),   # strips through wavefront-private LDS: several of rows and columns
     (1, 128, 1024, 1024), # the paper's medium transposed matmul (M,K,N) = (128,1024,1024): split-reduction kernel
     (1, 100, 200, 260),   # split-reduction kernel: ragged 16x16 tiles, reduction tail of 4 past two chunks
     (1, 128, 4096, 96),   # LDS-tiled kernel, one batch element, three chunks
@@ -251,8 +251,8 @@ def test_mlp_shapes_that_the_row_kernel_takes(tc):
     # 512 or 1024, at most two tiles per workgroup in every layer)
     cases = [((128, (1024, 1024, 512, 256)), "mlp:rows"), ((128, (1024, 1024, 1024)), "mlp:rows"),
              ((1024, (128, 128)), "mlp:rows"), ((128, (1024, 1000)), "mlp:rows"), ((100, (512, 256, 1000)), "mlp:rows"),
-             ((1024, (128, 256)), "mlp:tiles"),    # 2 column tiles per XCD x 32 pairs of row tiles: more than 32 workgroups
-             ((256, (1024, 1024)), "mlp:tiles"), ((2048, (128, 128)), "mlp:tiles"), ((128, (384, 128)), "mlp:tiles")]
+             ((1024, (128, 256)), "mlp:per_layer"),  # 2 column tiles per XCD x 32 pairs of row tiles: more than 32 workgroups
+             ((256, (1024, 1024)), "mlp:per_layer"), ((2048, (128, 128)), "mlp:per_layer"), ((128, (384, 128)), "mlp:per_layer")]
     for (batch, dims), path in cases:
         I, Ws, bs = inputs.make_mlp(batch, dims, seed=5)
         run_mlp(tc, I, Ws, bs)
@@ -261,7 +261,7 @@ def test_mlp_shapes_that_the_row_kernel_takes(tc):
 
 def test_mlp_seeded_random_chains_in_the_row_kernels_range(tc, oracle_threads):
     # a seeded draw of chains whose reductions are all 128, 256, 512 or 1024: whatever deal of tiles the host picks
-    # (single jobs, pairs of row tiles, or the tile-stream kernel when neither fits), every layer must agree with the
+    # (single jobs, pairs of row tiles, or one launch per layer when neither fits), every layer must agree with the
     # oracle; ragged batches and ragged last widths included
     rng = np.random.default_rng(20273)  # a draw with 9 chains for the row kernel (4 with pairs in later layers) and 3 for the other
     took = set()
@@ -275,7 +275,7 @@ def test_mlp_seeded_random_chains_in_the_row_kernels_range(tc, oracle_threads):
         took.add(tc.last_path())
         for l in range(n):
             check(O[l], ref[l], "mlp case %d batch %d dims %s layer %d (%s)" % (case, batch, dims, l, tc.last_path()))
-    assert took == {"mlp:rows", "mlp:tiles"}
+    assert took == {"mlp:rows", "mlp:per_layer"}
 
 
 def test_mlp_tile_stream_kernel_by_option(tc, oracle_threads, mlp_option):
@@ -381,7 +381,7 @@ GCONV_SHAPES = [
     (3, 5, 16, 16, 18, 58, 3, 3),   # int8 kernel: 15 (image, group) pairs, two bands
     (1, 3, 16, 16, 10, 58, 3, 3),   # int8 kernel: a single band
     (37, 29, 16, 16, 26, 58, 3, 3), # int8 kernel: 1073 pairs on 512 persistent workgroups (2 or 3 images each)
-    (1, 3, 16, 16, 20, 30, 3, 3),   # 16x16 channels, other width: runtime-width LDS kernel
+    (1, 3, 16, 16, 20, 30, 3, 3),   # 16x16 channels, other width
     (2, 3, 16, 16, 14, 14, 3, 3),   # width-14 band kernel (paper table shape), whole image = one band
     (4, 3, 32, 32, 7, 7, 3, 3),     # int8 kernel for 32-channel small images: three iterations of four images
     (12, 5, 32, 32, 7, 7, 3, 3),    # 15 iterations: runs that cross a group boundary
@@ -389,16 +389,17 @@ GCONV_SHAPES = [
     (12, 5, 16, 16, 14, 14, 3, 3),  # 15 iterations: runs that cross a group boundary
     (2052, 1, 16, 16, 14, 14, 3, 3),  # 513 iterations on 512 workgroups: one run of two
     (1, 2, 16, 16, 17, 14, 3, 3),   # width-14 band kernel: odd height, two bands, unaligned planes
-    (2, 3, 4, 4, 56, 56, 3, 3),     # 4x4x4-block kernel (paper table shape): four bands, last one ragged
-    (1, 2, 4, 4, 5, 56, 3, 3),      # 4x4x4-block kernel: one short band
-    (2, 3, 8, 8, 28, 28, 3, 3),     # 4x4x4-block kernel, 8 channels (paper table shape)
-    (1, 2, 8, 8, 31, 28, 3, 3),     # 4x4x4-block kernel, 8 channels: two bands, ragged tiles
+    # (few images and groups: the shape-generic kernel; the 4x4x4-block kernels themselves: tests/test_gpu_gconv_generic.py)
+    (2, 3, 4, 4, 56, 56, 3, 3),     # the paper's table shapes
+    (1, 2, 4, 4, 5, 56, 3, 3),
+    (2, 3, 8, 8, 28, 28, 3, 3),
+    (1, 2, 8, 8, 31, 28, 3, 3),
     (4, 3, 16, 16, 16, 16, 3, 3),   # int8 kernel for small images at 16 x 16 (the table shape with a border): 13 tiles, the last a quarter full
     (8, 5, 16, 16, 16, 16, 3, 3),   # the same, runs that cross a group boundary
-    (2, 3, 4, 4, 58, 58, 3, 3),     # 4x4x4-block kernel at width 58 (the table shape with a border): 8-byte staging loads
-    (1, 2, 4, 4, 21, 58, 3, 3),     # the same, odd height: two bands, the second ragged
-    (2, 3, 8, 8, 30, 30, 3, 3),     # 4x4x4-block kernel, 8 channels at width 30: the whole image one band
-    (1, 2, 8, 8, 17, 30, 3, 3),     # the same, a short image
+    (2, 3, 4, 4, 58, 58, 3, 3),     # the same with a border of one pixel
+    (1, 2, 4, 4, 21, 58, 3, 3),
+    (2, 3, 8, 8, 30, 30, 3, 3),
+    (1, 2, 8, 8, 17, 30, 3, 3),
     (2, 2, 32, 64, 12, 13, 3, 3),   # big groups (64 filters, 288 taps): the int8 kernel over gathered taps, one grid plane per group
     (1, 1, 64, 128, 20, 20, 3, 3),  # G = 1 at 64 -> 128 channels: the plain convolution of Section 3 on that kernel
     (3, 3, 36, 64, 9, 9, 3, 3),     # three groups, 324 taps, 147 pixels

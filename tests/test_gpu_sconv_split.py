@@ -25,10 +25,19 @@ SHAPES = [
     (1, 1500, 36, 8, 9, 3, 3, 2, 2),      # 13500 taps: the table of tap offsets takes a third of the LDS
 ]
 
+# enough blocks of 64 filters for the kernel without a split (sconv_tile.hpp)
+TILE_SHAPES = [
+    (15, 3, 70, 33, 36, 3, 3, 1, 1),      # 27 taps: one chunk and 11; 15810 pixels; the second filter block has 6
+    (9, 7, 129, 27, 24, 3, 3, 1, 1),      # 63 taps; three filter blocks, the last one a single filter
+    (13, 13, 65, 25, 55, 5, 1, 1, 2),     # 65 taps, strides 1 and 2
+    (1, 64, 100, 110, 110, 3, 3, 1, 1),   # 576 taps in fours, two blocks
+    (3, 5, 256, 112, 109, 2, 2, 1, 1),    # 20 taps, blocks of 64 pixels
+]
 
-@pytest.mark.parametrize("shape", SHAPES)
+
+@pytest.mark.parametrize("shape,path", [(s, "sconv:split") for s in SHAPES] + [(s, "sconv:tile") for s in TILE_SHAPES])
 @pytest.mark.parametrize("with_bias", [True, False])
-def test_sconv_split(shape, with_bias, oracle_threads):
+def test_sconv_split(shape, path, with_bias, oracle_threads):
     from paper_1802_04730_amd import tc355 as tc
     N, C, F, H, W, KH, KW, sh, sw = shape
     I, Wt, bias = inputs.make_sconv2d(N, C, F, H, W, KH, KW, seed=C + F)
@@ -38,7 +47,7 @@ def test_sconv_split(shape, with_bias, oracle_threads):
     dev = lambda a: torch.from_numpy(a).cuda()
     tc.tc_sconv2d(dev(I), dev(Wt), dev(bias) if with_bias else None, O, sh, sw)
     torch.cuda.synchronize()
-    assert tc.last_path() == "sconv:tile"
+    assert tc.last_path() == path
     err = parity_error(O.cpu().numpy().astype(np.float64), ref)
     print("sconv %s: parity error %.3e" % (shape, err), flush=True)
     assert err <= TIGHT

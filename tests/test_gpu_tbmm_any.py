@@ -37,8 +37,21 @@ SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("shape", SHAPES)
-def test_tbmm_any(shape, oracle_threads):
+# what stays on other kernels: (B, N, M, K), path
+OTHERS = [
+    ((5, 20, 30, 131), "tbmm:wave"),     # reductions too long for a strip in registers: loads of 1,
+    ((3, 37, 33, 150), "tbmm:wave"),     # 2
+    ((3, 17, 19, 300), "tbmm:wave"),     # and 4 elements
+    ((3, 5, 200, 131), "tbmm:wave"),     # several strips of columns
+    ((30, 9, 7, 5), "tbmm:wave"),        # nothing to stage
+    ((40, 120, 125, 68), "tbmm:tile"),   # 64 x 64 blocks: ragged ones, a reduction of two chunks and 4
+    ((130, 64, 64, 4), "tbmm:tile"),     # a single short chunk
+    ((500, 26, 72, 26), "tbmm:lds"),
+]
+
+
+@pytest.mark.parametrize("shape,path", [(s, "tbmm:any") for s in SHAPES] + OTHERS)
+def test_tbmm_any(shape, path, oracle_threads):
     from paper_1802_04730_amd import tc355 as tc
     B, N, M, K = shape
     X, Y = inputs.make_tbmm(B, N, M, K, seed=sum(shape))
@@ -48,7 +61,7 @@ def test_tbmm_any(shape, oracle_threads):
     dev = lambda a: torch.from_numpy(a).cuda()
     tc.tc_tbmm(dev(X), dev(Y), Z)
     torch.cuda.synchronize()
-    assert tc.last_path() == "tbmm:wave"
+    assert tc.last_path() == path
     err = parity_error(Z.cpu().numpy().astype(np.float64), ref)
     print("tbmm %s: parity error %.3e" % (shape, err), flush=True)
     assert err <= TIGHT
