@@ -844,6 +844,9 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
     const bool blocks = K % 4 == 0 && N >= 48 && M >= 48 && 5 * N * M >= 4 * padded && padded / (GT_BM * GT_BN) * B >= 128;
     const bool tiny = N <= 16 && M <= 16 && K <= 8;  // nothing to stage: (30000,8,8,8) 14.7 us on the wave-level kernel, 15.4 here
     if (B > 1 && !blocks && !tiny && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
+    // (reductions beyond 103, which the other one refuses: (1000,8,8,128) 4.3 us here, 5.1 on the wave-level kernel,
+    // (1000,4,4,256) 5.4 / 6.8, (1000,17,18,112) 7.8 / 8.9)
+    if (any && !blocks && !tiny && try_tbmm_lds(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:lds", st);
   }
 
   GemmArgs a{};

@@ -47,6 +47,9 @@ OTHERS = [
     ((40, 120, 125, 68), "tbmm:tile"),   # 64 x 64 blocks: ragged ones, a reduction of two chunks and 4
     ((130, 64, 64, 4), "tbmm:tile"),     # a single short chunk
     ((500, 26, 72, 26), "tbmm:lds"),
+    ((100, 8, 8, 128), "tbmm:lds"),      # reductions that are too long for the kernel of any alignment
+    ((50, 4, 4, 256), "tbmm:lds"),
+    ((1000, 17, 18, 112), "tbmm:lds"),
 ]
 
 
