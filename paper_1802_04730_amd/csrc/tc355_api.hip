@@ -489,6 +489,8 @@ bool try_gconv_i8(const GconvArgs& g, int force13, hipStream_t s, tc_status* st)
 // ---- transposed batched matmul on small per-batch matrices: flat coalesced strips through per-wavefront LDS ----
 struct TbmmLdsPlan {
   int tn, tm, nx, ny, store, ks;  // what a job is and what it needs: load instructions per strip, store mode, k steps
+  int64_t strips_n, strips_m, jobs;
+  size_t wave_units, lds;         // LDS per wavefront in 16-byte units, per workgroup in bytes
 };
 
 // The instantiations that exist; a shape takes the first one that covers its plan.  (KS = 0: any reduction length.)
@@ -506,39 +508,37 @@ struct TbmmLdsPlan {
   V(1, 1, 4, 4, TBMM_STORE_PIECES, 0) \
   V(1, 1, 4, 4, TBMM_STORE_SCALAR, 0)
 
-bool launch_tbmm_lds(const TbmmLdsPlan& pl, const TbmmLdsArgs& a, int64_t wgs, size_t lds, hipStream_t s, tc_status* st) {
+tc_status launch_tbmm_lds(const TbmmLdsPlan& pl, const TbmmLdsArgs& a, int64_t wgs, hipStream_t s) {
 #define TC355_TBMM_LDS_TRY(TN_, TM_, NX_, NY_, ST_, KS_)                                                       \
   if (pl.tn == TN_ && pl.tm == TM_ && pl.nx <= NX_ && pl.ny <= NY_ && pl.store == ST_ && (KS_ == 0 || pl.ks == KS_)) { \
-    tbmm_lds_kernel<TN_, TM_, NX_, NY_, 1, ST_, KS_><<<dim3((unsigned)wgs), dim3(WG_THREADS), lds, s>>>(a);     \
-    *st = launch_status();                                                                                     \
-    return true;                                                                                               \
+    tbmm_lds_kernel<TN_, TM_, NX_, NY_, 1, ST_, KS_><<<dim3((unsigned)wgs), dim3(WG_THREADS), pl.lds, s>>>(a);  \
+    return launch_status();                                                                                    \
   }
   TC355_TBMM_LDS_VARIANTS(TC355_TBMM_LDS_TRY)
 #undef TC355_TBMM_LDS_TRY
-  return false;
+  return TC_ERR_LAUNCH;  // (the plan has looked)
 }
 
 // Returns false if the shape is not one for this kernel (the caller then takes the shape-generic kernels).
-bool try_tbmm_lds(const float* X, const float* Y, float* Z, int64_t B, int64_t N, int64_t M, int64_t K, hipStream_t s,
-                  tc_status* st) {
+bool plan_tbmm_lds(int64_t B, int64_t N, int64_t M, int64_t K, TbmmLdsPlan* plan) {
   if ((N * K) % 4 != 0 || (M * K) % 4 != 0 || K > 256) return false;  // strips must start and end on 16-byte boundaries
   const int cus = device_cus();
   if (cus <= 0) return false;
   const int64_t tiles_n = ceil_div(N, 16), tiles_m = ceil_div(M, 16);
-  TbmmLdsPlan pl{};
+  TbmmLdsPlan& pl = *plan;
   pl.tn = tiles_n >= 2 ? 2 : 1;
-  const int64_t strips_n = ceil_div(tiles_n, pl.tn);
+  pl.strips_n = ceil_div(tiles_n, pl.tn);
   // A whole row of tiles per job (most reuse of the X strip, contiguous results) when that still leaves two
   // wavefronts for every SIMD of the chip; with few jobs, fewer tiles per job: a shorter chain from launch to the
   // last store.
   pl.tm = 1;
   for (int c : {5, 2}) {
-    if ((c == 5 ? tiles_m <= 5 && M % 4 == 0 : c <= tiles_m) && B * strips_n * ceil_div(tiles_m, c) >= 8 * (int64_t)cus) {
+    if ((c == 5 ? tiles_m <= 5 && M % 4 == 0 : c <= tiles_m) && B * pl.strips_n * ceil_div(tiles_m, c) >= 8 * (int64_t)cus) {
       pl.tm = c;
       break;
     }
   }
-  const int64_t strips_m = ceil_div(tiles_m, pl.tm);
+  pl.strips_m = ceil_div(tiles_m, pl.tm);
   const int64_t xrows = std::min<int64_t>(16 * pl.tn, N), yrows = std::min<int64_t>(16 * pl.tm, M);
   const int64_t xu = xrows * K / 4, yu = yrows * K / 4;  // 16-byte pieces per strip
   pl.nx = (int)ceil_div(xu, WAVE);
@@ -547,22 +547,32 @@ bool try_tbmm_lds(const float* X, const float* Y, float* Z, int64_t B, int64_t N
   pl.ks = (int)ceil_div(K, 4);
   // LDS per wavefront: both strips (one spare piece: the last step of a ragged reduction reads past its row); in
   // the flat store mode the same region then holds the job's block of Z
-  size_t wave_units = (size_t)(xu + yu) + 1;
-  if (pl.store == TBMM_STORE_FLAT) wave_units = std::max<size_t>(wave_units, (size_t)(xrows * M / 4));
-  const size_t lds = WAVES_PER_WG * wave_units * 16;
-  if (lds > 64 * 1024) return false;
-  if (B >= kMaxElems / (strips_n * strips_m)) return false;  // 32-bit job numbers
+  pl.wave_units = (size_t)(xu + yu) + 1;
+  if (pl.store == TBMM_STORE_FLAT) pl.wave_units = std::max<size_t>(pl.wave_units, (size_t)(xrows * M / 4));
+  pl.lds = WAVES_PER_WG * pl.wave_units * 16;
+  if (pl.lds > 64 * 1024) return false;
+  if (B >= kMaxElems / (pl.strips_n * pl.strips_m)) return false;  // 32-bit job numbers
+  pl.jobs = B * pl.strips_n * pl.strips_m;
+#define TC355_TBMM_LDS_COVERS(TN_, TM_, NX_, NY_, ST_, KS_) \
+  if (pl.tn == TN_ && pl.tm == TM_ && pl.nx <= NX_ && pl.ny <= NY_ && pl.store == ST_ && (KS_ == 0 || pl.ks == KS_)) return true;
+  TC355_TBMM_LDS_VARIANTS(TC355_TBMM_LDS_COVERS)
+#undef TC355_TBMM_LDS_COVERS
+  return false;
+}
+
+tc_status run_tbmm_lds(const TbmmLdsPlan& pl, const float* X, const float* Y, float* Z, int64_t N, int64_t M, int64_t K, hipStream_t s) {
+  const int cus = device_cus();
   TbmmLdsArgs a{};
   a.X = X; a.Y = Y; a.Z = Z;
   a.N = (int)N; a.M = (int)M; a.K = (int)K;
-  a.strips_n = (int)strips_n; a.strips_m = (int)strips_m;
-  a.jobs = (int)(B * strips_n * strips_m);
-  a.wave_lds_units = (int)wave_units;
+  a.strips_n = (int)pl.strips_n; a.strips_m = (int)pl.strips_m;
+  a.jobs = (int)pl.jobs;
+  a.wave_lds_units = (int)pl.wave_units;
   // persistent wavefronts, two workgroups per compute unit (the kernel is compiled for two wavefronts per SIMD);
   // small jobs take fewer registers and less LDS, so more of their workgroups are resident at once
-  const int64_t per_cu = pl.tm == 5 ? 2 : std::max<int64_t>(2, std::min<int64_t>(4, (160 * 1024) / (int64_t)lds));
+  const int64_t per_cu = pl.tm == 5 ? 2 : std::max<int64_t>(2, std::min<int64_t>(4, (160 * 1024) / (int64_t)pl.lds));
   const int64_t wgs = std::min<int64_t>(ceil_div((int64_t)a.jobs, WAVES_PER_WG), per_cu * cus);
-  return launch_tbmm_lds(pl, a, wgs, lds, s, st);
+  return launch_tbmm_lds(pl, a, wgs, s);
 }
 
 // ---- transposed batched matmul of small matrices of any size ----
@@ -830,23 +840,33 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
 
   // (A single pair with 64 k and more is faster with its reduction split: (N,M,K) = (64,64,64) 5.2 -> 3.0 us, (1000,1000,64)
   // 8.7 -> 6.2; below, the strips win: (1000,1000,57) 5.9 against 6.3, (128,300,17) 2.7 against 3.1.)
-  // Batches of small matrices.  The aligned kernel keeps what it is built for, whole batch elements or strips of few rows
-  // at reductions that spread over the LDS banks: (B,N,M,K) = (4000,26,72,26) 17.1 us against 21.5 on the other one,
-  // (105,29,88,48) 4.2 / 4.8, (1000,32,100,32) 12.1 / 13.2; beside that, with results of up to 5 column tiles leaving as
-  // one stream, the other one wins: (5239,42,68,26) 42.8 / 39.2, (2000,48,48,48) 24.7 / 19.7, (3000,40,40,16) 16.1 / 11.5.
-  // 64 x 64 blocks keep large matrices that fill them to four fifths: (1000,64,64,64) 19.3 / 23.5, but (700,96,96,96) 58 / 52.
-  // Everything else ran on the wave-level kernel: (4000,27,61,35) 38.8 / 22.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.
+  // Batches of small matrices; times in us.  The rules were drawn from every kernel's time at 2036 shapes (two random draws).
   if (B > 1 || K < 64) {
     tc_status st = TC_OK;
-    const bool any = B > 1 && M <= 80 && (N > 32 || K % 16 == 0);
-    if (!any && try_tbmm_lds(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:lds", st);
+    TbmmLdsPlan pl{};
+    if (plan_tbmm_lds(B, N, M, K, &pl)) {
+      // The aligned kernel keeps what it takes ((B,N,M,K) = (6300,64,60,4) 19.5, 57.6 on 64 x 64 blocks; (1000,64,64,48)
+      // 13.8 / 17.2; (134,68,75,48) 6.4, 7.0 on the other one; (1000,4,4,256) 5.4, 6.8 on the wave-level kernel) except
+      // where its jobs fit badly: rows of 5 column tiles of which M has 3 or fewer ((1265,64,16,48) 17.8 / 8.0,
+      // (2000,48,48,48) 24.7 / 19.7), results stored element by element that could leave as one stream
+      // ((6035,58,30,12) 29.3 / 15.5, (1323,76,65,44) 31.2 / 26.8), and its longest strips where there are too few
+      // wavefronts to hide their loads ((41,60,81,32) 4.4 / 3.7; from 2 jobs per compute unit on 3.7 / 4.1 at (102,52,52,37)).
+      const bool any = B > 1 && (pl.tm == 5 ? ceil_div(M, 16) <= 3
+                                 : pl.tm == 2 ? M % 4 != 0 && M <= 80 && K % 16 != 0
+                                              : pl.tn == 2 && (pl.nx > 3 || pl.ny > 2) && pl.jobs <= 2 * device_cus());
+      if (any && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
+      return took("tbmm:lds", run_tbmm_lds(pl, X, Y, Z, N, M, K, s));
+    }
+    // What it does not take ran on 64 x 64 blocks or on the wave-level kernel.  The blocks keep matrices that fill them to
+    // four fifths ((1000,64,64,64) 19.3, 23.5 on the other one, but (700,96,96,96) 58 / 52), all from K = 80 on
+    // ((984,53,56,88) 23.3 / 28.2).  The wave-level kernel keeps what is too short to stage ((30000,8,8,8) 14.7 / 15.4,
+    // (7513,11,18,3) 6.2 / 7.8), long reductions whose rows share LDS banks ((2126,6,32,64) 8.3 / 9.6, (5709,51,5,96) 38 / 46)
+    // and long ones against one column tile ((5805,32,6,92) 21.5 / 23.8).  Everything else is the other one's:
+    // (4000,27,61,35) 38.8 / 22.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.
     const int64_t padded = ceil_div(N, GT_BM) * GT_BM * ceil_div(M, GT_BN) * GT_BN;
-    const bool blocks = K % 4 == 0 && N >= 48 && M >= 48 && 5 * N * M >= 4 * padded && padded / (GT_BM * GT_BN) * B >= 128;
-    const bool tiny = N <= 16 && M <= 16 && K <= 8;  // nothing to stage: (30000,8,8,8) 14.7 us on the wave-level kernel, 15.4 here
-    if (B > 1 && !blocks && !tiny && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
-    // (reductions beyond 103, which the other one refuses: (1000,8,8,128) 4.3 us here, 5.1 on the wave-level kernel,
-    // (1000,4,4,256) 5.4 / 6.8, (1000,17,18,112) 7.8 / 8.9)
-    if (any && !blocks && !tiny && try_tbmm_lds(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:lds", st);
+    const bool blocks = K % 4 == 0 && N >= 48 && M >= 48 && (K >= 80 || 5 * N * M >= 4 * padded) && padded / (GT_BM * GT_BN) * B >= 128;
+    const bool wave = (N <= 16 && M <= 16 && K <= 8) || (K % 2 != 0 && K <= 9) || (K % 16 == 0 && K >= 48) || (K >= 90 && M <= 16);
+    if (B > 1 && !blocks && !wave && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
   }
 
   GemmArgs a{};

@@ -64,7 +64,7 @@ TBMM_SHAPES = [
     (1, 128, 1024, 1024), # the paper's medium transposed matmul (M,K,N) = (128,1024,1024): split-reduction kernel
     (1, 100, 200, 260),   # split-reduction kernel: ragged 16x16 tiles, reduction tail of 4 past two chunks
     (1, 128, 4096, 96),   # LDS-tiled kernel, one batch element, three chunks
-    (130, 64, 64, 4),     # LDS-tiled kernel: a single short chunk
+    (130, 64, 64, 4),     # a reduction of one step
     (1, 128, 8192, 256),  # int8 matrix-core kernel (128 rows, >= 128 blocks of 64 columns): two reduction blocks of 128
     (2, 128, 4096, 384),  # the same, two batch elements, three reduction blocks
     (3, 128, 3072, 640),
