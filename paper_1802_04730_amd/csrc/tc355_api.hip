@@ -180,12 +180,29 @@ tc_status launch_gemm_splitk(const GemmArgs& a, int cus, hipStream_t s) {
 // with a split reduction: two teams per compute unit share it at 827 per chunk of 128 and 750 per tile, a team alone takes
 // 990 and 900.  Measured, tiles against blocks: (N,M,K) = (256,3303,3327) 121 / 145 us, (2048,300,700) 27.4 / 33.8,
 // (1000,1000,1000) 52.2 / 47.7, (1500,1500,130) 37 / 24.
-bool splitk_beats_tile(const GemmArgs& a, int cus) {
-  if (a.N < 48 || a.M < 48 || (a.K % 4 != 0 && a.K < GT_KC)) return true;
-  const double tile = (double)ceil_div(ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN), cus) * ceil_div(a.K, GT_KC) * 3200;
+double gemm_tile_clocks(const GemmArgs& a, int cus) {
+  if (a.N < 48 || a.M < 48 || (a.K % 4 != 0 && a.K < GT_KC)) return 1e30;
+  return (double)ceil_div(ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN), cus) * ceil_div(a.K, GT_KC) * 3200;
+}
+
+double gemm_splitk_clocks(const GemmArgs& a, int cus) {
   const int64_t jobs = ceil_div(a.N, 16) * ceil_div(a.M, 16), nck = ceil_div(a.K, MLP_KC), rest = jobs % (2 * cus);
   const double two = 2.0 * (nck * 827 + 750), one = nck * 990.0 + 900;
-  return jobs / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0.0) < tile;
+  return jobs / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0.0);
+}
+
+// Does the wave-level kernel beat the better one of these for a plain fp32 product?  Their last chunk (of 128, of 32) is padding
+// where a reduction is short or a little longer than whole chunks; the wave-level kernel has no chunks: a wavefront per 16 x 16
+// tile, four of them at a time on a compute unit, 43 clocks per k (85 where rows have odd lengths and every operand is a load of
+// its own), 1800 more than the tiles and 400 less than the blocks before the first and behind the last.  Fitted to the three
+// kernels' times at 600 shapes; measured, wave / tiles / blocks, us: (N,M,K) = (666,773,7) 3.6 / 8.3 / -, (1708,121,21) 3.9 / 5.2 / -,
+// (2405,629,29) 11.7 / 19.6 / -, (1219,411,134) 8.4 / 11.2 / 10.3, (115,1632,148) 5.9 / 6.5 / 9.8, (285,1098,54) 5.1 / 5.9 / 5.9,
+// but (650,456,144) 8.4 / 7.6 / 10.0 and (1012,1571,43) 13.5 / 20.5 / 9.4.
+bool gemm_wave_beats(const GemmArgs& a, double splitk, double tile, int cus) {
+  const int64_t jobs = ceil_div(a.N, 16) * ceil_div(a.M, 16);
+  if (a.M <= 80 || (a.K % 2 != 0 && a.K >= 32)) return false;  // (a narrow result is one wavefront per 16 rows)
+  if (jobs >= 4096) return splitk < tile && a.K < 32;          // (several tiles per wavefront there)
+  return 1800 + (double)ceil_div(jobs, 4 * cus) * a.K * (a.K % 2 == 0 ? 43 : 85) < (splitk < tile ? splitk : tile + 2200);
 }
 
 template <typename TA, int EPI>
@@ -196,12 +213,15 @@ tc_status launch_gemm(const GemmArgs& a, int64_t batch, int tm, hipStream_t s) {
   // (32-bit byte offsets in the split-reduction kernel)
   const bool splitk = batch == 1 && cus > 0 && a.K >= 4 && (int64_t)a.N * a.K * (int64_t)sizeof(TA) < (1ll << 32) &&
                       (int64_t)a.M * a.K * 4 < (1ll << 32) && ceil_div(a.N, 16) * ceil_div(a.M, 16) < (1ll << 31);
+  const double split = splitk ? gemm_splitk_clocks(a, cus) : 1e30, tile = batch == 1 && cus > 0 ? gemm_tile_clocks(a, cus) : 0.0;
   // The wave-level kernel keeps a single tile of a short reduction (7 x 9 x 5: 2.1 us against 2.7) and large products
-  // whose last chunk of 32 would be mostly padding (1500 x 1500 x 130: 22.3 us against 24).
+  // whose last chunk of 32 would be mostly padding ((N,M,K) = (2136,1047,38) 11.0 us against 13.7, (1082,2329,22) 8.1 / 29.6,
+  // (1500,1500,130) 22.3 / 24; at 18 % padding it is even: (1143,2514,130) 26.8 / 25.2).
   const bool wave = batch == 1 && ((a.N <= 16 && a.M <= 16 && a.K <= 16) ||
                                    (a.K % 4 == 2 && ceil_div(a.K, GT_KC) * GT_KC * 100 >= (int64_t)a.K * 118 &&
-                                    ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN) > 2 * cus));
-  if (!wave && splitk && splitk_beats_tile(a, cus)) return took(plain ? "tbmm:splitk" : "mlp:per_layer", launch_gemm_splitk<TA, !plain>(a, cus, s));
+                                    ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN) > 2 * cus) ||
+                                   (plain && splitk && gemm_wave_beats(a, split, tile, cus)));
+  if (!wave && split < tile) return took(plain ? "tbmm:splitk" : "mlp:per_layer", launch_gemm_splitk<TA, !plain>(a, cus, s));
   if (!wave && try_gemm_tile<TA, EPI>(a, batch, s, &st)) return took(plain ? "tbmm:tile" : "mlp:per_layer", st);
   t_path = plain ? "tbmm:wave" : "mlp:per_layer";
   // widest per-lane load that keeps every row start aligned

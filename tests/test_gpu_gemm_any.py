@@ -44,6 +44,14 @@ PRODUCTS = [
     ((1101, 1000, 33), "tbmm:tile"),    # the last chunk of 32 shares 31 elements with the first
     ((1100, 1001, 67), "tbmm:tile"),
     ((1500, 1500, 66), "tbmm:wave"),
+    # short reductions, or little more than whole chunks: with enough tiles the wave-level kernel, by its estimate
+    ((601, 203, 7), "tbmm:wave"),       # odd rows: loads of one element
+    ((115, 1632, 148), "tbmm:wave"),    # of four
+    ((1219, 411, 134), "tbmm:wave"),   # of two
+    ((650, 456, 144), "tbmm:splitk"),
+    ((601, 79, 7), "tbmm:splitk"),      # a narrow result would be a wavefront per 16 rows
+    ((1005, 1050, 21), "tbmm:wave"),    # several tiles per wavefront
+    ((1012, 1571, 43), "tbmm:tile"),
 ]
 
 
