@@ -116,9 +116,17 @@ bool try_gconv_quad(const GconvArgs& g, hipStream_t s, tc_status* st) {
   if (g.C != C || g.F != F || g.KH != KH || g.KW != KW || g.W != W) return false;
   const int64_t grid = (int64_t)g.N * g.G;
   // One workgroup per (image, group) leaves the chip idle where there are few: the same 4x4x4 blocks in pieces of an image
-  // (gconv_mix.hpp).  Measured at 32 groups: 4 channels, 56 x 56, batch 1 / 4 / 8 12.7 / 13.3 / 14.4 us here and 6.3 / 11.1 /
-  // 16.3 there; 8 channels, 28 x 28, batch 1 / 2 / 4 7.3 / 7.4 / 7.6 and 5.4 / 6.7 / 7.8.
-  if (grid < (C == 4 ? device_cus() : device_cus() / 2) && try_gconv_mix(g, s, st)) return true;
+  // (gconv_mix.hpp).  Here a launch takes as long as one workgroup's bands, there as long as the pixels per compute unit
+  // say: lines through the times of both at 456 (pairs, height), the slower kernel is taken for one of them (7.8 us against
+  // 7.3) and 0.7 % given away on average.  Measured, here / there in us, 56 x 56 with 4 channels: 64 pairs 13.0 / 8.2, 128
+  // 13.4 / 11.3, 176 13.8 / 14.5, 255 14.7 / 17.4, 255 pairs of 28 x 56 8.2 / 11.7; 28 x 28 with 8 channels: 48 7.5 / 6.7,
+  // 80 7.5 / 8.0, 127 7.7 / 8.1.
+  if (grid < device_cus()) {
+    const double px = (double)grid * g.OH * g.OW / device_cus();
+    const double bands = (C == 4 ? 2.1 : 2.5) + (C == 4 ? (W == 56 ? 2.75 : 2.95) : (W == 28 ? 4.85 : 3.45)) * ceil_div(g.OH, ROWS);
+    const double pieces = C == 4 ? 4.2 + std::min(0.0125 * px, 1.5 + 0.0043 * px) : 4.6 + std::min(0.016 * px, 1.4 + 0.0085 * px);
+    if (pieces < bands && try_gconv_mix(g, s, st)) return true;
+  }
   if (grid > kMaxGrid) return false;
   t_path = "gconv:quad";
   static std::atomic<int> lds_ok{0};

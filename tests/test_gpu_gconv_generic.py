@@ -80,20 +80,21 @@ def test_gconv_generic_keeps_infinities_out_of_the_padding(oracle_threads):
     ((4, 33, 16, 16, 30, 30, 3, 3), "gconv:lds"),    # two
     ((3, 32, 16, 16, 30, 30, 3, 3), "gconv:mix"),    # too few of them
     ((8, 32, 16, 16, 21, 22, 3, 3), "gconv:mix"),    # 380 pixels leave the block 15 % empty
-    ((8, 31, 4, 4, 56, 56, 3, 3), "gconv:mix"),      # fewer (image, group) pairs than compute units: pieces of an image
-    ((8, 32, 4, 4, 56, 56, 3, 3), "gconv:quad"),     # one workgroup for each
-    ((4, 31, 8, 8, 28, 28, 3, 3), "gconv:mix"),
-    ((4, 32, 8, 8, 28, 28, 3, 3), "gconv:quad"),
+    ((4, 31, 4, 4, 56, 56, 3, 3), "gconv:mix"),      # few (image, group) pairs: pieces of an image
+    ((8, 31, 4, 4, 56, 56, 3, 3), "gconv:quad"),     # one workgroup for each
+    ((2, 31, 8, 8, 28, 28, 3, 3), "gconv:mix"),
+    ((4, 31, 8, 8, 28, 28, 3, 3), "gconv:quad"),
     # the 4x4x4-block kernel with a workgroup for each (image, group): last bands of fewer rows, odd heights, a short image,
     # 8-byte staging loads at widths 58 and 30
     ((9, 29, 4, 4, 53, 56, 3, 3), "gconv:quad"),
     ((16, 16, 4, 4, 5, 56, 3, 3), "gconv:quad"),
     ((8, 32, 4, 4, 58, 58, 3, 3), "gconv:quad"),
     ((16, 17, 4, 4, 21, 58, 3, 3), "gconv:quad"),
-    ((5, 27, 8, 8, 31, 28, 3, 3), "gconv:quad"),
-    ((4, 32, 8, 8, 30, 30, 3, 3), "gconv:quad"),
-    ((13, 10, 8, 8, 17, 30, 3, 3), "gconv:quad"),
-    ((8, 31, 4, 4, 21, 58, 3, 3), "gconv:mix"),
+    ((9, 29, 8, 8, 31, 28, 3, 3), "gconv:quad"),
+    ((8, 32, 8, 8, 30, 30, 3, 3), "gconv:quad"),
+    ((16, 17, 8, 8, 17, 30, 3, 3), "gconv:quad"),
+    ((8, 31, 4, 4, 21, 58, 3, 3), "gconv:quad"),     # few rows: one workgroup's two bands are done before the pieces are
+    ((3, 31, 4, 4, 58, 58, 3, 3), "gconv:mix"),
     ((4, 31, 8, 8, 17, 30, 3, 3), "gconv:mix"),
     # too little to stage: the wave-level kernel, in strips of 4, 2 and 1 tiles of 16 pixels
     ((2, 3, 4, 19, 9, 10, 1, 1), "gconv:wave"),
