@@ -31,6 +31,8 @@ SHAPES = [
     (2, 33, 10, 140, 20),      # two blocks of columns
     (2, 150, 12, 20, 18),      # two blocks of rows
     (1, 40, 300, 24, 40),      # a long first reduction
+    (4, 128, 128, 128, 128),   # one block of rows does not fit LDS
+    (515, 40, 700, 9, 20),     # ... with more batch elements than two workgroups per compute unit
 ]
 
 
