@@ -1133,8 +1133,11 @@ tc_status launch_sconv_split(SconvArgs a, hipStream_t s) {
 tc_status launch_sconv_fp64(SconvArgs a, const char* tile_path, const char* split_path, hipStream_t s) {
   const int cus = std::max(1, device_cus());
   // Which kernel, from what a compute unit would spend in clocks: blocks one after the other when there are several per
-  // unit, a single one bound by its chain of chunks (16 taps, 64 with a split reduction).  The constants are fitted to the
-  // measured times of 46 layers: the faster kernel is taken for each of them.  Measured, (pixels, filters, taps): blocks of
+  // unit, a single one bound by its chain of chunks (16 taps, 64 with a split reduction); small blocks read a third again
+  // as long where strides step over the filters (lines of the input that nobody else reads).  The split has to be 4 % better:
+  // that is what the estimate is worth.  Of 1500 random layers measured on every kernel, 2 take one that is more than 3 % slower
+  // than the blocks of 64 (9 % at most; without the 4 % and the third 10, and 15.0 -> 16.4 us at (2415,256,174)), and
+  // the choice is on average 0.7 % from the fastest.  Measured, (pixels, filters, taps): blocks of
   // 64 against 16 x 16 with a split reduction (400,64,1029) 40.8 / 10.8 us, (1331,64,9898) 349 / 106, (784,20,425) 19.5 / 6.3;
   // (11664,100,576) 45.5 / 54.9, (100352,64,64) 31 / 69; against 32 x 16 (867,215,3136) 113 / 51.6, (53312,20,128) 27.4 / 24.
   const bool offsets = !prod_reaches({a.N, a.C, a.H, a.W}, (int64_t)1 << 30) && !prod_reaches({a.F, a.K}, (int64_t)1 << 30);
@@ -1143,12 +1146,13 @@ tc_status launch_sconv_fp64(SconvArgs a, const char* tile_path, const char* spli
     const bool wide64 = ceil_div(a.F, SC_BF) * ceil_div(a.P, 64) >= 2 * cus;
     const double blocks = (double)ceil_div(ceil_div(a.F, SC_BF) * ceil_div(a.P, wide64 ? 64 : 32), cus), steps = (double)ceil_div(a.K, SC_KC);
     const double tile = 9400 + std::max((wide64 ? 2913 : 1303) * steps, blocks * ((wide64 ? 1602 : 816) * steps + 2224));
+    const double gather = a.sw > a.KW ? 1.35 : 1.0;
     auto split = [&](int tf, double one, double many) {
       const double n = (double)ceil_div(ceil_div(a.F, 16 * tf) * ceil_div(a.P, 16), cus);
-      return 8175 + (double)a.K + std::max(one * chunks, n * (many * chunks + 752 * tf));
+      return 8175 + (double)a.K + std::max(one * chunks, n * (gather * many * chunks + 752 * tf));
     };
     const double s1 = split(1, 921, 688), s2 = split(2, 1510, 1062);
-    if (std::min(s1, s2) < tile) return took(split_path, s1 <= s2 ? launch_sconv_split<1, 1>(a, s) : launch_sconv_split<2, 1>(a, s));
+    if (1.04 * std::min(s1, s2) < tile) return took(split_path, s1 <= s2 ? launch_sconv_split<1, 1>(a, s) : launch_sconv_split<2, 1>(a, s));
   }
   a.tiles_f = (int)ceil_div(a.F, SC_BF);
   // 64-pixel blocks when there are at least two of them per compute unit, else 32-pixel blocks (twice as many)

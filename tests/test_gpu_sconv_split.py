@@ -32,6 +32,8 @@ TILE_SHAPES = [
     (13, 13, 65, 25, 55, 5, 1, 1, 2),     # 65 taps, strides 1 and 2
     (1, 64, 100, 110, 110, 3, 3, 1, 1),   # 576 taps in fours, two blocks
     (3, 5, 256, 112, 109, 2, 2, 1, 1),    # 20 taps, blocks of 64 pixels
+    (1, 174, 256, 35, 69, 1, 1, 1, 1),    # both estimated alike
+    (9, 163, 155, 35, 47, 1, 1, 2, 2),    # strides that step over the filters
 ]
 
 
