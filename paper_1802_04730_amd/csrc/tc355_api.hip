@@ -646,7 +646,7 @@ struct TbmmAnyPlan {
 };
 
 // Jobs of tn x tm tiles: what they take, and an estimate of the launch in clocks; false where they do not fit.
-bool plan_tbmm_any(int64_t B, int64_t N, int64_t M, int64_t K, int tn, int tm, TbmmAnyPlan* p) {
+bool plan_tbmm_any(int64_t B, int64_t N, int64_t M, int64_t K, int tn, int tm, int cus, TbmmAnyPlan* p) {
   p->strips_n = ceil_div(ceil_div(N, 16), tn);
   p->strips_m = ceil_div(ceil_div(M, 16), tm);
   if (B >= kMaxElems / (p->strips_n * p->strips_m)) return false;  // 32-bit job numbers
@@ -664,7 +664,7 @@ bool plan_tbmm_any(int64_t B, int64_t N, int64_t M, int64_t K, int tn, int tm, T
   const int loads = tbmm_any_loads(16 * tn, kmax) + tbmm_any_loads(16 * tm, kmax);
   const double work = loads * 39.0 + tn * tm * steps * 83.5 + (tn + tm) * steps * (K % 16 == 0 ? 20.1 : 11.2) + tn * tm * 4 * 71.0 +
                       (yrows == M ? 0.0 : 20.0 * xrows);
-  const int64_t per_simd = ceil_div(p->jobs, 4 * 256);
+  const int64_t per_simd = ceil_div(p->jobs, 4 * cus);
   const int64_t w = std::min(per_simd, std::max<int64_t>(1, std::min<int64_t>(512 / (4 * loads + 8 * tn * tm + 44), 160 * 1024 / p->lds)));
   const double bytes = 4.0 * ((xrows + yrows) * K + xrows * yrows);
   p->cost = 5430 + std::max({ceil_div(per_simd, w) * (1470 + work), per_simd * work, per_simd * 4 * bytes / 11.0});
@@ -682,7 +682,7 @@ bool try_tbmm_any(const float* X, const float* Y, float* Z, int64_t B, int64_t N
   int tn = 0, tm = 0;
   for (int n = 1; n <= tiles_n; n++)
     for (int m = 1; m <= std::min(tiles_m, K <= 63 ? 5 : n == 1 ? 4 : 3); m++)  // (registers)
-      if (plan_tbmm_any(B, N, M, K, n, m, &pl) && (tn == 0 || pl.cost < best.cost)) { best = pl; tn = n; tm = m; }
+      if (plan_tbmm_any(B, N, M, K, n, m, cus, &pl) && (tn == 0 || pl.cost < best.cost)) { best = pl; tn = n; tm = m; }
   if (tn == 0) return false;
   TbmmAnyArgs a{};
   a.X = X; a.Y = Y; a.Z = Z;
