@@ -33,6 +33,9 @@ EXPORTS = ["tc_status_string", "tc355_version", "tc355_set_option", "tc355_get_o
            "tc_group_conv", "tc_group_conv_infer", "tc_kron", "tc_sconv2d", "tc_sconv2d_infer", "tc_lut"]
 
 
+_RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 class TcError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -140,8 +143,11 @@ def _ptr(t, name: str, index=None) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
-        # torch.cuda.current_stream().cuda_stream without the Stream object (2.6 us, a third of a small call's host time)
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        # torch.cuda.current_stream().cuda_stream without the Stream object (2.6 us, a third of a small call's host time);
+        # not a public name, so not relied on
+        if _RAW_STREAM is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _RAW_STREAM(torch.cuda.current_device())
     return int(stream)
 
 

@@ -198,3 +198,17 @@ def test_product_package_does_not_reach_the_oracle():
                 text = open(os.path.join(dirpath, f)).read()
                 assert "import oracle" not in text and "from oracle" not in text, f
                 assert "tc_oracle" not in text, f
+
+
+def test_the_stream_of_a_call_without_torchs_private_symbol(monkeypatch):
+    import types
+
+    import torch
+
+    from paper_1802_04730_amd import tc355
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    monkeypatch.setattr(tc355, "_RAW_STREAM", lambda device: 0x4560 + device)
+    assert tc355._stream(None) == 0x4563 and tc355._stream(0x70) == 0x70
+    monkeypatch.setattr(tc355, "_RAW_STREAM", None)
+    assert tc355._stream(None) == 0x1230
