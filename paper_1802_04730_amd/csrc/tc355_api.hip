@@ -658,8 +658,7 @@ bool plan_tbmm_any(int64_t B, int64_t N, int64_t M, int64_t K, int tn, int tm, i
   if (p->lds > 160 * 1024) return false;
   // A job's instructions in clocks of a SIMD (loads, MFMAs, operand reads, results; rows that leave one by one), the round
   // trip in front of them, the wavefronts that share a SIMD as registers and LDS allow, and what memory delivers.  The
-  // constants are fitted to the measured times of 42 shapes at every (tn, tm): on average 0.3 % from the best choice, 5 %
-  // at worst.
+  // constants are fitted to the measured times of 42 shapes at every (tn, tm): on average 0.3 % from the best choice there.
   const int kmax = K <= 31 ? 31 : K <= 63 ? 63 : 103, steps = (int)ceil_div(K, 4);
   const int loads = tbmm_any_loads(16 * tn, kmax) + tbmm_any_loads(16 * tm, kmax);
   const double work = loads * 39.0 + tn * tm * steps * 83.5 + (tn + tm) * steps * (K % 16 == 0 ? 20.1 : 11.2) + tn * tm * 4 * 71.0 +
@@ -668,8 +667,12 @@ bool plan_tbmm_any(int64_t B, int64_t N, int64_t M, int64_t K, int tn, int tm, i
   const int64_t w = std::min(per_simd, std::max<int64_t>(1, std::min<int64_t>(512 / (4 * loads + 8 * tn * tm + 44), 160 * 1024 / p->lds)));
   const double bytes = 4.0 * ((xrows + yrows) * K + xrows * yrows);
   p->cost = 5430 + std::max({ceil_div(per_simd, w) * (1470 + work), per_simd * work, per_simd * 4 * bytes / 11.0});
-  // (two tiles of rows are a little worse than that: 27 x 61 x 35 24.3 us against 22.3, 94 x 18 x 86 50.1 against 47.9)
-  if (tn == 2 && tm >= 2) p->cost *= tm >= 4 ? 1.15 : K > 63 ? 1.06 : 1.0;
+  // Two tiles of rows are a little worse than that: (2176,109,60,14) 23.9 us against 20.7, (4000,94,18,86) 50.1 / 47.9.  Over 400
+  // other random shapes measured at every (tn, tm) the choice is on average 1.6 % from the best one, 1.75 % without these
+  // factors.  The large one helps batches of a few thousand, which stream ((4000,27,61,35) 24.3 / 22.3, (5182,28,58,35) 30.3 /
+  // 27.5, (5630,21,51,46) 36.0 / 32.4), and gives some smaller ones away ((1991,26,55,35) 11.3 / 12.5, (1601,28,59,53) 13.9 / 15.7).
+  if (tn == 2 && tm >= 4) p->cost *= K > 31 ? 1.15 : 1.06;
+  else if (tn == 2 && tm >= 2 && K > 63) p->cost *= 1.06;
   return true;
 }
 
