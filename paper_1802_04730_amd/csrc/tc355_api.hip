@@ -882,33 +882,43 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
 
   // (A single pair with 64 k and more is faster with its reduction split: (N,M,K) = (64,64,64) 5.2 -> 3.0 us, (1000,1000,64)
   // 8.7 -> 6.2; below, the strips win: (1000,1000,57) 5.9 against 6.3, (128,300,17) 2.7 against 3.1.)
-  // Batches of small matrices; times in us.  The rules were drawn from every kernel's time at 2036 shapes (two random draws).
+  // Batches of small matrices; times in us.  The rules were drawn from every kernel's time at 2036 random shapes; at 1527 others
+  // the kernel taken is on average 1.3 % from the fastest.
   if (B > 1 || K < 64) {
     tc_status st = TC_OK;
     TbmmLdsPlan pl{};
+    const int64_t tiles_m = ceil_div(M, 16);
     if (plan_tbmm_lds(B, N, M, K, &pl)) {
       // The aligned kernel keeps what it takes ((B,N,M,K) = (6300,64,60,4) 19.5, 57.6 on 64 x 64 blocks; (1000,64,64,48)
       // 13.8 / 17.2; (134,68,75,48) 6.4, 7.0 on the other one; (1000,4,4,256) 5.4, 6.8 on the wave-level kernel) except
-      // where its jobs fit badly: rows of 5 column tiles of which M has 3 or fewer ((1265,64,16,48) 17.8 / 8.0,
-      // (2000,48,48,48) 24.7 / 19.7), results stored element by element that could leave as one stream
-      // ((6035,58,30,12) 29.3 / 15.5, (1323,76,65,44) 31.2 / 26.8), and its longest strips where there are too few
-      // wavefronts to hide their loads ((41,60,81,32) 4.4 / 3.7; from 2 jobs per compute unit on 3.7 / 4.1 at (102,52,52,37)).
-      const bool any = B > 1 && (pl.tm == 5 ? ceil_div(M, 16) <= 3
-                                 : pl.tm == 2 ? M % 4 != 0 && M <= 80 && K % 16 != 0
-                                              : pl.tn == 2 && (pl.nx > 3 || pl.ny > 2) && pl.jobs <= 2 * device_cus());
-      if (any && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
+      // where its jobs fit badly: rows of 5 or pairs of column tiles of which M fills three quarters at most
+      // ((1265,64,16,48) 17.8 / 8.0, (2000,48,48,48) 24.7 / 19.7, (773,48,48,40) 10.6 / 8.4); results that it stores element
+      // by element while the reduction is short ((5274,113,46,8) 70 / 30, (934,70,123,4) 23 / 14) or there are more than two
+      // tiles of rows and at most four of columns ((1187,57,38,60) 18.0 / 14.9, but (228,89,67,40) 8.4 / 9.8); its longest strips
+      // where there are too few wavefronts to hide their loads ((41,60,81,32) 4.4 / 3.7; from 2 jobs per compute unit on, 4 with
+      // such stores, (102,52,52,37) 3.8 / 4.1).
+      const bool scalar = pl.store == TBMM_STORE_SCALAR;
+      const int64_t cols = pl.tm * pl.strips_m;
+      const bool any = cols >= 2 * tiles_m ||
+                       (pl.tn == 2 && pl.tm > 1 && (scalar ? K <= 25 || (N > 32 && M <= 64 && K % 16 != 0) : 10 * cols >= 13 * tiles_m)) ||
+                       (pl.tn == 2 && pl.tm == 1 && (pl.nx > 3 || pl.ny > 2) && pl.jobs <= (scalar ? 4 : 2) * device_cus());
+      if (B > 1 && any && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
       return took("tbmm:lds", run_tbmm_lds(pl, X, Y, Z, N, M, K, s));
     }
     // What it does not take ran on 64 x 64 blocks or on the wave-level kernel.  The blocks keep matrices that fill them to
-    // four fifths ((1000,64,64,64) 19.3, 23.5 on the other one, but (700,96,96,96) 58 / 52), all from K = 80 on
-    // ((984,53,56,88) 23.3 / 28.2).  The wave-level kernel keeps what is too short to stage ((30000,8,8,8) 14.7 / 15.4,
-    // (7513,11,18,3) 6.2 / 7.8), long reductions whose rows share LDS banks ((2126,6,32,64) 8.3 / 9.6, (5709,51,5,96) 38 / 46)
-    // and long ones against one column tile ((5805,32,6,92) 21.5 / 23.8).  Everything else is the other one's:
-    // (4000,27,61,35) 38.8 / 22.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.
-    const int64_t padded = ceil_div(N, GT_BM) * GT_BM * ceil_div(M, GT_BN) * GT_BN;
-    const bool blocks = K % 4 == 0 && N >= 48 && M >= 48 && (K >= 80 || 5 * N * M >= 4 * padded) && padded / (GT_BM * GT_BN) * B >= 128;
-    const bool wave = (N <= 16 && M <= 16 && K <= 8) || (K % 2 != 0 && K <= 9) || (K % 16 == 0 && K >= 48) || (K >= 90 && M <= 16);
-    if (B > 1 && !blocks && !wave && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
+    // four fifths ((1000,64,64,64) 19.3, 23.5 on the other one, but (700,96,96,96) 58 / 52), and from K = 88 on also where
+    // three fifths of the chip's time would be spent on results ((984,53,56,88) 23.3 / 28.2, (124,108,99,92) 12.6 / 15.9, but
+    // (311,64,48,88) 11.3 / 8.5).  The wave-level kernel keeps what is too short to stage ((30000,8,8,8) 14.7 / 15.4,
+    // (1175,77,4,1) 4.0 / 4.9), results that are as wide as one tile or wider than 5 while the rows share LDS banks
+    // ((5709,51,5,96) 38 / 46, (6,51,120,80) 4.3 / 4.7) or the wide ones' odd reductions are short ((3129,12,92,5) 8.8 / 9.3).
+    // Everything else is the other one's: (4000,27,61,35) 38.8 / 22.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.
+    const int64_t cus = std::max(1, device_cus()), blocks = ceil_div(N, GT_BM) * ceil_div(M, GT_BN) * B, tiles = ceil_div(N, 16) * tiles_m * B;
+    const double full = (double)N * M / (ceil_div(N, GT_BM) * GT_BM * ceil_div(M, GT_BN) * GT_BN);
+    const bool block = K % 4 == 0 && N >= 48 && M >= 48 && blocks >= 128 &&
+                       (full >= 0.8 || (K >= 88 && full * blocks >= 0.575 * (ceil_div(blocks, cus) * cus)));
+    const bool wave = (N <= 16 && M <= 16 && K <= 8) || (M <= 18 && K <= 18 && tiles > 114) ||
+                      (K % 16 == 0 && K >= 32 && (M <= 18 || (M > 80 && tiles <= 3229))) || (M > 80 && K % 2 != 0 && K <= 14);
+    if (B > 1 && !block && !wave && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
   }
 
   GemmArgs a{};

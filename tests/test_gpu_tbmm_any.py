@@ -16,27 +16,27 @@ GUARD = 64
 # (B, N, M, K)
 SHAPES = [
     (2, 1, 17, 2),           # X holds a single 16-byte piece
-    (3, 17, 33, 11),         # the tensors end 1 and 1 elements into a piece
-    (3, 15, 31, 13),         # 1 and 1 ... of another length
-    (3, 13, 27, 17),         # 3 and 1
+    (5, 1, 17, 1),
+    (3, 17, 33, 7),          # the tensors end 1 and 1 elements into a piece
+    (3, 15, 31, 9),          # 1 and 1 ... of another length
+    (3, 13, 27, 5),          # 3 and 1
     (2, 17, 7, 15),          # 2 and 2
     (7, 17, 17, 31),
     (4000, 27, 61, 35),      # several jobs per wavefront; blocks of Z that share pieces
     (900, 9, 74, 12),        # five column tiles
-    (300, 57, 16, 10),       # two tiles of rows per job
+    (300, 57, 19, 10),       # two tiles of rows per job
     (3000, 40, 40, 16),      # a reduction of one LDS bank's period
     (3000, 48, 48, 48),      # of three: rows of five column tiles would be mostly padding
     (1200, 58, 30, 12),      # results at any alignment as one stream
     (41, 60, 81, 32),        # long strips, few of them
     (300, 33, 65, 34),
-    (200, 86, 98, 94),       # strips of columns: results row by row
+    (200, 96, 96, 96),       # strips of columns: results row by row
     (60, 86, 92, 70),
     (40, 100, 100, 103),     # the longest reduction
     (40, 50, 99, 63),
     (40, 50, 17, 62),
     (64, 19, 83, 31),
 ]
-
 
 # what stays on other kernels: (B, N, M, K), path
 OTHERS = [
@@ -45,18 +45,18 @@ OTHERS = [
     ((3, 17, 19, 300), "tbmm:wave"),     # and 4 elements
     ((3, 5, 200, 131), "tbmm:wave"),     # several strips of columns
     ((30, 9, 7, 5), "tbmm:wave"),        # nothing to stage
+    ((300, 57, 16, 10), "tbmm:wave"),    # little to stage, one column tile
+    ((40, 50, 99, 80), "tbmm:wave"),     # rows that share LDS banks: a wide result,
+    ((40, 50, 17, 80), "tbmm:wave"),     # a narrow one
+    ((60, 21, 101, 13), "tbmm:wave"),    # a wide result of a short odd reduction
     ((40, 120, 125, 68), "tbmm:tile"),   # 64 x 64 blocks: ragged ones, a reduction of two chunks and 4
+    ((984, 53, 56, 88), "tbmm:tile"),    # three quarters full
     ((500, 26, 72, 26), "tbmm:lds"),
     ((130, 64, 64, 16), "tbmm:lds"),     # ... but short reductions stay with the strips
     ((700, 64, 60, 4), "tbmm:lds"),
     ((400, 48, 48, 48), "tbmm:lds"),     # enough long strips to hide their loads
     ((3000, 48, 56, 32), "tbmm:lds"),    # four of five column tiles
-    ((200, 96, 96, 96), "tbmm:tile"),
-    ((5, 1, 17, 1), "tbmm:wave"),        # odd reductions too short for pieces of four
-    ((3, 17, 33, 7), "tbmm:wave"),
-    ((3, 13, 27, 5), "tbmm:wave"),
-    ((520, 4, 116, 48), "tbmm:wave"),    # rows that share LDS banks
-    ((40, 33, 9, 94), "tbmm:wave"),      # a long reduction against one column tile
+    ((5, 40, 40, 16), "tbmm:lds"),
     ((100, 8, 8, 128), "tbmm:lds"),      # reductions that are too long for the kernel of any alignment
     ((50, 4, 4, 256), "tbmm:lds"),
     ((1000, 17, 18, 112), "tbmm:lds"),
@@ -81,7 +81,7 @@ def test_tbmm_any(shape, path, oracle_threads):
     assert bool((buf[:GUARD] == 777.0).all()) and bool((buf[GUARD + ref.size:] == 777.0).all())
 
 
-@pytest.mark.parametrize("shape", [(3, 17, 33, 7), (3, 17, 33, 11), (5, 40, 40, 16), (4, 96, 90, 50)])
+@pytest.mark.parametrize("shape", [(3, 17, 33, 7), (3, 17, 33, 11), (5, 40, 40, 16), (41, 60, 81, 32), (4, 96, 90, 50)])
 def test_tbmm_keeps_infinities_in_their_rows(shape, oracle_threads):
     """Slots past K of a last step hold the next row's data: an Inf there reaches nothing."""
     from paper_1802_04730_amd import tc355 as tc
