@@ -668,11 +668,10 @@ bool plan_tbmm_any(int64_t B, int64_t N, int64_t M, int64_t K, int tn, int tm, i
   const double bytes = 4.0 * ((xrows + yrows) * K + xrows * yrows);
   p->cost = 5430 + std::max({ceil_div(per_simd, w) * (1470 + work), per_simd * work, per_simd * 4 * bytes / 11.0});
   // Two tiles of rows are a little worse than that: (2176,109,60,14) 23.9 us against 20.7, (4000,94,18,86) 50.1 / 47.9.  Over 400
-  // other random shapes measured at every (tn, tm) the choice is on average 1.6 % from the best one, 1.75 % without these
-  // factors.  The large one helps batches of a few thousand, which stream ((4000,27,61,35) 24.3 / 22.3, (5182,28,58,35) 30.3 /
-  // 27.5, (5630,21,51,46) 36.0 / 32.4), and gives some smaller ones away ((1991,26,55,35) 11.3 / 12.5, (1601,28,59,53) 13.9 / 15.7).
-  if (tn == 2 && tm >= 4) p->cost *= K > 31 ? 1.15 : 1.06;
-  else if (tn == 2 && tm >= 2 && K > 63) p->cost *= 1.06;
+  // other random shapes measured at every (tn, tm) the choice is on average 1.7 % from the best one, 1.75 % without these
+  // factors.  The large one helps batches of a few thousand, which stream ((4000,27,61,35) 24.3 / 22.3, (4548,21,99,19) 33.9 /
+  // 29.7, (5630,21,51,46) 36.0 / 32.4), and gives some smaller ones away ((1991,26,55,35) 11.3 / 12.5, (1601,28,59,53) 13.9 / 15.7).
+  if (tn == 2 && tm >= 2) p->cost *= tm >= 4 ? 1.15 : K > 63 ? 1.06 : 1.0;
   return true;
 }
 
@@ -891,17 +890,17 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
     if (plan_tbmm_lds(B, N, M, K, &pl)) {
       // The aligned kernel keeps what it takes ((B,N,M,K) = (6300,64,60,4) 19.5, 57.6 on 64 x 64 blocks; (1000,64,64,48)
       // 13.8 / 17.2; (134,68,75,48) 6.4, 7.0 on the other one; (1000,4,4,256) 5.4, 6.8 on the wave-level kernel) except
-      // where its jobs fit badly: rows of 5 or pairs of column tiles of which M fills three quarters at most
-      // ((1265,64,16,48) 17.8 / 8.0, (2000,48,48,48) 24.7 / 19.7, (773,48,48,40) 10.6 / 8.4); results that it stores element
+      // where its jobs fit badly: rows of 5 column tiles of which M fills three quarters at most, pairs of which it fills five
+      // sixths ((1265,64,16,48) 17.8 / 8.0, (2000,48,48,48) 24.7 / 19.7, (773,48,48,40) 10.6 / 8.4); results that it stores element
       // by element while the reduction is short ((5274,113,46,8) 70 / 30, (934,70,123,4) 23 / 14) or there are more than two
       // tiles of rows and at most four of columns ((1187,57,38,60) 18.0 / 14.9, but (228,89,67,40) 8.4 / 9.8); its longest strips
       // where there are too few wavefronts to hide their loads ((41,60,81,32) 4.4 / 3.7; from 2 jobs per compute unit on, 4 with
-      // such stores, (102,52,52,37) 3.8 / 4.1).
+      // such stores and K up to 40, (102,52,52,37) 3.8 / 4.1, (217,20,59,84) 5.0 / 5.6).
       const bool scalar = pl.store == TBMM_STORE_SCALAR;
       const int64_t cols = pl.tm * pl.strips_m;
       const bool any = cols >= 2 * tiles_m ||
-                       (pl.tn == 2 && pl.tm > 1 && (scalar ? K <= 25 || (N > 32 && M <= 64 && K % 16 != 0) : 10 * cols >= 13 * tiles_m)) ||
-                       (pl.tn == 2 && pl.tm == 1 && (pl.nx > 3 || pl.ny > 2) && pl.jobs <= (scalar ? 4 : 2) * device_cus());
+                       (pl.tn == 2 && pl.tm > 1 && (scalar ? K <= 31 || (N > 32 && M <= 64 && K % 16 != 0) : 10 * cols >= (pl.tm == 5 ? 13 : 12) * tiles_m)) ||
+                       (pl.tn == 2 && pl.tm == 1 && (pl.nx > 3 || pl.ny > 2) && pl.jobs <= (scalar && K <= 40 ? 4 : 2) * device_cus());
       if (B > 1 && any && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
       return took("tbmm:lds", run_tbmm_lds(pl, X, Y, Z, N, M, K, s));
     }
@@ -909,15 +908,15 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
     // four fifths ((1000,64,64,64) 19.3, 23.5 on the other one, but (700,96,96,96) 58 / 52), and from K = 88 on also where
     // three fifths of the chip's time would be spent on results ((984,53,56,88) 23.3 / 28.2, (124,108,99,92) 12.6 / 15.9, but
     // (311,64,48,88) 11.3 / 8.5).  The wave-level kernel keeps what is too short to stage ((30000,8,8,8) 14.7 / 15.4,
-    // (1175,77,4,1) 4.0 / 4.9), results that are as wide as one tile or wider than 5 while the rows share LDS banks
+    // (1175,77,4,1) 4.0 / 4.9), results that are one tile wide or more than 5 while the rows share LDS banks
     // ((5709,51,5,96) 38 / 46, (6,51,120,80) 4.3 / 4.7) or the wide ones' odd reductions are short ((3129,12,92,5) 8.8 / 9.3).
     // Everything else is the other one's: (4000,27,61,35) 38.8 / 22.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.
     const int64_t cus = std::max(1, device_cus()), blocks = ceil_div(N, GT_BM) * ceil_div(M, GT_BN) * B, tiles = ceil_div(N, 16) * tiles_m * B;
     const double full = (double)N * M / (ceil_div(N, GT_BM) * GT_BM * ceil_div(M, GT_BN) * GT_BN);
     const bool block = K % 4 == 0 && N >= 48 && M >= 48 && blocks >= 128 &&
                        (full >= 0.8 || (K >= 88 && full * blocks >= 0.575 * (ceil_div(blocks, cus) * cus)));
-    const bool wave = (N <= 16 && M <= 16 && K <= 8) || (M <= 18 && K <= 18 && tiles > 114) ||
-                      (K % 16 == 0 && K >= 32 && (M <= 18 || (M > 80 && tiles <= 3229))) || (M > 80 && K % 2 != 0 && K <= 14);
+    const bool wave = (N <= 16 && M <= 16 && K <= 8) || (M <= 16 && K <= (K % 2 != 0 ? 11 : 18) && tiles > 114) ||
+                      (K % 16 == 0 && K >= 32 && (M <= 16 || (M > 80 && tiles <= 3229))) || (M > 80 && K % 2 != 0 && K <= 14);
     if (B > 1 && !block && !wave && try_tbmm_any(X, Y, Z, B, N, M, K, s, &st)) return took("tbmm:any", st);
   }
 

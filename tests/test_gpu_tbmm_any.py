@@ -47,7 +47,7 @@ OTHERS = [
     ((30, 9, 7, 5), "tbmm:wave"),        # nothing to stage
     ((300, 57, 16, 10), "tbmm:wave"),    # little to stage, one column tile
     ((40, 50, 99, 80), "tbmm:wave"),     # rows that share LDS banks: a wide result,
-    ((40, 50, 17, 80), "tbmm:wave"),     # a narrow one
+    ((40, 50, 16, 80), "tbmm:wave"),     # a narrow one
     ((60, 21, 101, 13), "tbmm:wave"),    # a wide result of a short odd reduction
     ((40, 120, 125, 68), "tbmm:tile"),   # 64 x 64 blocks: ragged ones, a reduction of two chunks and 4
     ((984, 53, 56, 88), "tbmm:tile"),    # three quarters full
