@@ -18,8 +18,8 @@
 // All loads are 16 bytes of 4-byte aligned elements: no size is rounded up in memory.
 //
 // Bound by the fp64 matrix pipe and by the vector instructions that do not overlap it (counters at
-// (N,G,C,F,H,W) = (16,24,12,20,33,45), 3 x 3: pipe busy 60 % of the cycles, vector instructions 17 %).  Measured there
-// 54 us = 41 TFLOP/s, 25 of it without the MFMAs, where gconv_wave.hpp (operands gathered from global memory, 32 filters' worth of
+// (N,G,C,F,H,W) = (16,24,12,20,33,45), 3 x 3: pipe busy 54 % of the cycles, vector instructions 16 %, LDS bank conflicts 12 %).
+// Measured there 53 us = 41 TFLOP/s, 25 of it without the MFMAs, where gconv_wave.hpp (operands gathered from global memory, 32 filters' worth of
 // MFMAs) takes 200 us; (2,22,23,31,27,48) 5 x 5: 54 us against 132, (7,32,8,8,58,58) 3 x 3: 28 against 99, a small
 // (2,1,7,4,17,20) 3 x 2: 4.2 against 12.2.  Deals of tiles and workgroups: equal blocks of pixels with the longer shares
 // rotating over the wavefronts instead of 64*TP pixels each: (13,6,40,40,20,28) 35 us against 41; neighbouring runs on

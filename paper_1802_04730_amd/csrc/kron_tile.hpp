@@ -12,9 +12,9 @@
 //     stride of 4 (mod 8) elements spreads them over all banks; the last, partial group takes k = 4s + q.
 //   * A row of fewer than 8 tiles in all (few rows i, few batch elements) is split over its l tiles (`lsp` wavefronts
 //     per tile, combined through LDS in a fixed order), so that a single batch element keeps 8 wavefronts busy.
-// Measured, wave-level kernel -> this one: (B,I,K,J,L) = (200,48,50,75,36) 22.3 -> 7.9 us (252 MFMAs per batch element, one
+// Measured, wave-level kernel -> this one: (B,I,K,J,L) = (200,48,50,75,36) 22.7 -> 7.8 us (252 MFMAs per batch element, one
 // per compute unit: 1.6 us of launch, 2 of staging, 84 MFMAs in the longest wavefront), (40,79,89,29,74) 52.7 -> 7.2,
-// (2000,18,98,40,48) 63 -> 26, (500,96,100,100,100) 242 -> 47 us (62 % of the fp64 matrix peak, padding not counted),
+// (2000,18,98,40,48) 63 -> 26, (500,96,100,100,100) 243 -> 49 us (matrix pipe busy 56 % of it),
 // (8,8,8,8,8) 4.0 -> 3.3.
 // Registers decide the occupancy (two workgroups per compute unit up to four column tiles): everything that is uniform
 // over a wavefront is kept scalar, and few loads are in flight while accumulators live.  A read-ahead by a whole group

@@ -1403,7 +1403,7 @@ tc_status tc_kron(const float* W1, const float* W2, const float* X, float* Y, in
     }
   }
   // The shape-generic kernels: operands in LDS ("kron:tile") wherever a block of them fits (up to about 140 of every
-  // extent, more where others are smaller): 22.3 -> 7.9 us at (B,I,K,J,L) = (200,48,50,75,36), 242 -> 47 us at
+  // extent, more where others are smaller): 22.7 -> 7.8 us at (B,I,K,J,L) = (200,48,50,75,36), 243 -> 49 us at
   // (500,96,100,100,100), 528 -> 193 at (600,128,128,128,128), never slower from 8^5 up; the wave-level kernel keeps the rest.
   {
     tc_status st = TC_OK;
