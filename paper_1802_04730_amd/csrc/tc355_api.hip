@@ -1489,16 +1489,24 @@ tc_status tc_lut(int32_t n_tables, const float* const* LUT, const int32_t* const
     a.LUT[t] = LUT[t]; a.Idx[t] = Idx[t]; a.O[t] = O[t]; a.E[t] = E[t]; a.L[t] = (int)L[t];
   }
   a.D = (int)D; a.B = (int)B;
-  const int v = (D % 4 == 0) ? 4 : 1;
-  const int64_t units = D / v;
+  // (the limit of the entry point)
+  if ((int64_t)n_tables * B * ceil_div(D % 4 == 0 ? D / 4 : D, WG_THREADS) > kMaxGrid) return TC_ERR_UNSUPPORTED;
+  const int v = D >= 4 ? 4 : 1;
+  const int64_t units = ceil_div(D, v);
   int cpw = 1;
   while (cpw < units && cpw < WG_THREADS) cpw *= 2;
   a.cpw = cpw;
   a.blocks = (int)ceil_div(units, cpw);
-  const int64_t grid = (int64_t)n_tables * B * a.blocks;
+  // as many slots as leave no thread more than one round of lookups
+  const int64_t longest = *std::max_element(L, L + n_tables);
+  int slots = 1;
+  while (slots * cpw < WG_THREADS && ceil_div(longest, slots) > LUT_NB) slots *= 2;
+  a.slots = slots;
+  const int64_t grid = ceil_div(B, WG_THREADS / (slots * cpw)) * a.blocks;
   if (grid > kMaxGrid) return TC_ERR_UNSUPPORTED;
-  if (v == 4) lut_sum_kernel<4><<<dim3((unsigned)grid), dim3(WG_THREADS), 0, s>>>(a);
-  else lut_sum_kernel<1><<<dim3((unsigned)grid), dim3(WG_THREADS), 0, s>>>(a);
+  const dim3 g((unsigned)grid, (unsigned)n_tables);
+  if (v == 4) lut_sum_kernel<4><<<g, dim3(WG_THREADS), 0, s>>>(a);
+  else lut_sum_kernel<1><<<g, dim3(WG_THREADS), 0, s>>>(a);
   return took("lut:sum", launch_status());
 }
 
