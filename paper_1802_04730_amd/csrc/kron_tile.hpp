@@ -7,6 +7,12 @@
 // and `nb` batch elements at a time, widened to fp64 (as fp32, widened at the read, where fp64 would not fit), and a
 // wavefront owns 16 rows i of one of them.  As in kron_lds.hpp the first contraction is computed transposed, so that
 // its result registers are the A operands of the second one: T never moves and is never rounded.
+//   * Either factor may go first.  SECOND computes T(b,k,j) = sum_l X(b,k,l) W2(j,l) and Y(b,i,j) = sum_k W1(i,k) T(b,k,j): the
+//     same loops with (I, W1, K) and (J, W2, L) exchanged (the host passes them so, and all names below follow), where the
+//     streamed tiles are rows of X as they lie in memory, T's result registers are B operands, and the partial group's k slots
+//     serve all groups.  The host takes the order whose estimate is 10 % lower; multiply-adds are I L (K + J) against K J (L + I).
+//     At 400 random layers: 1.106 times faster on average, 4 of them slower by 3-7 % (5-7 us each); (1647,77,68,13,88)
+//     61.5 -> 25.6 us, (454,89,96,10,100) 34.3 -> 12.6, (1828,89,26,31,87) 45.3 -> 21.6.
 //   * Two tiles of 16 l advance together, so a W1 operand feeds two MFMAs.
 //   * k slot q of step e of a group is k = 4q + e: the four k slots of an X read are then 4 rows apart, and a row
 //     stride of 4 (mod 8) elements spreads them over all banks; the last, partial group takes k = 4s + q.
@@ -18,7 +24,7 @@
 // (8,8,8,8,8) 4.0 -> 3.3.
 // Registers decide the occupancy (two workgroups per compute unit up to four column tiles): everything that is uniform
 // over a wavefront is kept scalar, and few loads are in flight while accumulators live.  A read-ahead by a whole group
-// of 16 k was slower for that reason (9.9 -> 13 us at the first shape, with spills).
+// of 16 k was slower for that reason (9.9 -> 13 us at the first shape, with spills); so were five column tiles at two workgroups.
 #pragma once
 #include "tc355_device.hpp"
 
@@ -89,46 +95,50 @@ struct KronCopy {
 
 template <typename TS>
 struct KronTileJob {
-  const TS* x;   // Xs of this batch element + r16, row 4q of a group
-  const TS* xt;  // the same, row q of the partial group
-  const TS* w1;  // W1s row of this lane + 4q
+  const TS* x;   // Xs of this batch element: + r16, row 4q of a group (SECOND: + q)
+  const TS* xt;  // the same, row (column) q of the partial group
+  const TS* w1;  // W1s row of this lane + 4q (SECOND: + q)
   const TS* w1t; // W1s row of this lane + first k of the partial group + q
 };
 
 // One or two tiles of 16 l from l0 on: T, then its share of all TJ column tiles.  FULL: every l of the tiles is below L.
-template <typename TS, int TJ, int NL, bool FULL>
-__device__ __forceinline__ void kron_l_tiles(const KronTileJob<TS>& jb, const TS* w2, int cs, int l0, int L, int K, int ls, int q, d4 (&acc)[TJ]) {
+template <typename TS, int TJ, bool SECOND, int NL, bool FULL>
+__device__ __forceinline__ void kron_l_tiles(const KronTileJob<TS>& jb, const TS* w2, int cs, int l0, int L, int K, int ls, int r16, int q, d4 (&acc)[TJ]) {
   d4 T[NL];
+  int xo[NL];  // first element of tile n; rows beyond the last repeat it (their T is replaced by zeros)
 #pragma unroll
-  for (int n = 0; n < NL; n++) T[n] = d4_zero();
+  for (int n = 0; n < NL; n++) {
+    T[n] = d4_zero();
+    xo[n] = SECOND ? (FULL ? l0 + 16 * n + r16 : min(l0 + 16 * n + r16, L - 1)) * ls : 16 * n;
+  }
   const int k16 = K >> 4;
-  const TS* xp = jb.x + l0;
+  const TS* xp = SECOND ? jb.x : jb.x + l0;
   const TS* wp = jb.w1;
 #pragma unroll 1
   for (int g = 0; g < k16; g++) {
     TS a[NL][4], w[4];
 #pragma unroll
     for (int e = 0; e < 4; e++) {
-      w[e] = wp[e];
+      w[e] = wp[SECOND ? 4 * e : e];
 #pragma unroll
-      for (int n = 0; n < NL; n++) a[n][e] = xp[e * ls + 16 * n];
+      for (int n = 0; n < NL; n++) a[n][e] = xp[xo[n] + e * (SECOND ? 4 : ls)];
     }
 #pragma unroll
     for (int e = 0; e < 4; e++)
 #pragma unroll
       for (int n = 0; n < NL; n++) T[n] = mfma_f64((double)a[n][e], (double)w[e], T[n]);
-    xp += 16 * ls;
+    xp += SECOND ? 16 : 16 * ls;
     wp += 16;
   }
   {
-    const TS* xt = jb.xt + l0;
+    const TS* xt = SECOND ? jb.xt : jb.xt + l0;
     const TS* wt = jb.w1t;
 #pragma unroll 1
     for (int k = k16 * 16; k < K; k += 4) {
       const double w = (double)*wt;
 #pragma unroll
-      for (int n = 0; n < NL; n++) T[n] = mfma_f64((double)xt[16 * n], w, T[n]);
-      xt += 4 * ls;
+      for (int n = 0; n < NL; n++) T[n] = mfma_f64((double)xt[xo[n]], w, T[n]);
+      xt += SECOND ? 4 : 4 * ls;
       wt += 4;
     }
   }
@@ -152,7 +162,7 @@ __device__ __forceinline__ void kron_l_tiles(const KronTileJob<TS>& jb, const TS
           for (int c = 0; c < TJ; c++) wn[c] = wl[c * cs + 4 * s + 4];
         }
 #pragma unroll
-        for (int c = 0; c < TJ; c++) acc[c] = mfma_f64(t, (double)w[c], acc[c]);
+        for (int c = 0; c < TJ; c++) acc[c] = SECOND ? mfma_f64((double)w[c], t, acc[c]) : mfma_f64(t, (double)w[c], acc[c]);
         __builtin_amdgcn_sched_barrier(0);
         if (s < 4 * NL - 1) {
 #pragma unroll
@@ -162,7 +172,7 @@ __device__ __forceinline__ void kron_l_tiles(const KronTileJob<TS>& jb, const TS
     }
 }
 
-template <typename TS, int TJ>
+template <typename TS, int TJ, bool SECOND>
 __global__ __launch_bounds__(KT_THREADS, TJ <= 4 ? 4 : 2) void kron_tile_kernel(KronTileArgs p) {
   extern __shared__ __attribute__((aligned(16))) char kron_smem[];
   const int tid = threadIdx.x;
@@ -179,9 +189,14 @@ __global__ __launch_bounds__(KT_THREADS, TJ <= 4 ? 4 : 2) void kron_tile_kernel(
   // zeros that the partial last steps read: k in [K, k4) of X and W1, l in [L, l4) of W2
   const int zrows = p.k4 - K;
   auto zero_rows = [&] {
-    for (int e = tid; e < zrows * ls * p.nb; e += KT_THREADS) {
-      const int b = e / (zrows * ls);
-      Xs[(b * p.k4 + K) * ls + e - b * zrows * ls] = (TS)0;
+    if constexpr (SECOND) {  // the ends of all rows
+      for (int r = tid; r < L * p.nb; r += KT_THREADS)
+        for (int k = K; k < p.k4; k++) Xs[r * ls + k] = (TS)0;
+    } else {
+      for (int e = tid; e < zrows * ls * p.nb; e += KT_THREADS) {
+        const int b = e / (zrows * ls);
+        Xs[(b * p.k4 + K) * ls + e - b * zrows * ls] = (TS)0;
+      }
     }
   };
   zero_rows();
@@ -191,7 +206,8 @@ __global__ __launch_bounds__(KT_THREADS, TJ <= 4 ? 4 : 2) void kron_tile_kernel(
     for (int l = L; l < l4; l++) W2s[tid * p.ls2 + l] = (TS)0;
   // the first loads of all three operands go out together: one round trip to memory before the first MFMA
   auto x_copy = [&](int g) {
-    return KronCopy<TS, true>{p.X + (int64_t)g * p.nb * K * L, Xs, min(p.nb, p.B - g * p.nb) * K * L, L, ls, zrows * ls, tid, p.l_magic, p.k_magic};
+    return KronCopy<TS, !SECOND>{p.X + (int64_t)g * p.nb * K * L, Xs, min(p.nb, p.B - g * p.nb) * K * L, SECOND ? K : L, ls, zrows * ls, tid,
+                                 SECOND ? p.k_magic : p.l_magic, p.k_magic};
   };
   float vx[KT_BATCH];
   {
@@ -213,7 +229,7 @@ __global__ __launch_bounds__(KT_THREADS, TJ <= 4 ? 4 : 2) void kron_tile_kernel(
   for (int g = blockIdx.x; g < p.groups; g += gridDim.x) {
     const int b0 = g * p.nb, nb = min(p.nb, p.B - b0);
     {
-      const KronCopy<TS, true> cx = x_copy(g);
+      const KronCopy<TS, !SECOND> cx = x_copy(g);
       cx.store(vx, 0);
       cx.rest();
     }
@@ -229,17 +245,17 @@ __global__ __launch_bounds__(KT_THREADS, TJ <= 4 ? 4 : 2) void kron_tile_kernel(
       for (int c = 0; c < TJ; c++) acc[c] = d4_zero();
       if (mine) {
         KronTileJob<TS> jb;
-        const TS* xb = Xs + bi * p.k4 * ls + r16;
+        const TS* xb = SECOND ? Xs + bi * L * ls : Xs + bi * p.k4 * ls + r16;
         const TS* wr = W1s + min(16 * it + r16, irows - 1) * p.ls1;
-        jb.x = xb + 4 * q * ls;
-        jb.xt = xb + ((K & ~15) + q) * ls;
-        jb.w1 = wr + 4 * q;
+        jb.x = xb + (SECOND ? q : 4 * q * ls);
+        jb.xt = xb + ((K & ~15) + q) * (SECOND ? 1 : ls);
+        jb.w1 = wr + (SECOND ? q : 4 * q);
         jb.w1t = wr + (K & ~15) + q;
         const int lend = min(L, 16 * per_part * (part + 1));
         int l0 = 16 * per_part * part;
-        for (; l0 + 32 <= lend; l0 += 32) kron_l_tiles<TS, TJ, 2, true>(jb, w2, 16 * p.ls2, l0, L, K, ls, q, acc);
-        if (lend - l0 > 16) kron_l_tiles<TS, TJ, 2, false>(jb, w2, 16 * p.ls2, l0, L, K, ls, q, acc);
-        else if (lend > l0) kron_l_tiles<TS, TJ, 1, false>(jb, w2, 16 * p.ls2, l0, L, K, ls, q, acc);
+        for (; l0 + 32 <= lend; l0 += 32) kron_l_tiles<TS, TJ, SECOND, 2, true>(jb, w2, 16 * p.ls2, l0, L, K, ls, r16, q, acc);
+        if (lend - l0 > 16) kron_l_tiles<TS, TJ, SECOND, 2, false>(jb, w2, 16 * p.ls2, l0, L, K, ls, r16, q, acc);
+        else if (lend > l0) kron_l_tiles<TS, TJ, SECOND, 1, false>(jb, w2, 16 * p.ls2, l0, L, K, ls, r16, q, acc);
       }
       if (p.lsp > 1) {
         __syncthreads();  // X is no longer read: the region takes the partial sums
@@ -264,14 +280,32 @@ __global__ __launch_bounds__(KT_THREADS, TJ <= 4 ? 4 : 2) void kron_tile_kernel(
         }
       }
       if (mine && part == 0) {
-        float* Y = p.Y + (int64_t)(b0 + bi) * I * J + (int64_t)(i0 + 16 * it) * J + j0 + r16;
+        float* Y = p.Y + (int64_t)(b0 + bi) * I * J;
+        if constexpr (SECOND) {  // (the extents are exchanged: Y's rows are J and its columns I here)
+          // a scalar row pointer plus the lane's own offset: pointers per lane would cost the registers of the second
+          // workgroup per compute unit
+          Y += (int64_t)j0 * I + i0 + 16 * it;
+          const unsigned own = (unsigned)(q * I + r16);
+          const bool col = 16 * it + r16 < irows;
 #pragma unroll
-        for (int v = 0; v < 4; v++) {
-          const int i = d_row(q, v);
-          if (16 * it + i < irows) {
+          for (int c = 0; c < TJ; c++) {
 #pragma unroll
-            for (int c = 0; c < TJ; c++)
-              if (16 * c + r16 < jrows) Y[(int64_t)i * J + 16 * c] = (float)acc[c][v];
+            for (int v = 0; v < 4; v++) {
+              if (col && 16 * c + d_row(q, v) < jrows) Y[own] = (float)acc[c][v];
+              Y += 4 * (int64_t)I;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+          Y += (int64_t)(i0 + 16 * it) * J + j0 + r16;
+#pragma unroll
+          for (int v = 0; v < 4; v++) {
+            const int i = d_row(q, v);
+            if (16 * it + i < irows) {
+#pragma unroll
+              for (int c = 0; c < TJ; c++)
+                if (16 * c + r16 < jrows) Y[(int64_t)i * J + 16 * c] = (float)acc[c][v];
+            }
           }
         }
       }
