@@ -144,9 +144,7 @@ constexpr int MLP_LDS_BYTES = 2 * MLP_BUF_BYTES + 2 * WAVES_PER_WG * WAVE * 32; 
 // register ring, also across tile boundaries, passes it through its own part of a
 // double-buffered LDS stage (which turns row-major 16-byte pieces into MFMA
 // operands) and contracts it; the wavefronts meet only at the end of a tile.
-// FC: the fcrelu epilogue (sum started from the bias, clamp); without it the body is a plain contraction
-// C = A * Wl^T (the transposed matmul of Section 7 at sizes too small for the 64 x 64 block kernel).
-template <typename TA, bool FC = true>
+template <typename TA>
 __device__ __forceinline__ void mlp_layer(const TA* __restrict__ A, const float* __restrict__ Wl,
                                           const float* __restrict__ bias, float* __restrict__ O,
                                           double* __restrict__ act, int batch, int K, int M, char* smem,
@@ -278,7 +276,7 @@ __device__ __forceinline__ void mlp_layer(const TA* __restrict__ A, const float*
   const int total = my_jobs * nck;  // chunks in this workgroup's stream
   int job = vwg, ck = 0;
   d4 acc = d4_zero();
-  double bz = (FC && job < njobs) ? (double)bias[min((job % tiles_m) * 16 + r16, M - 1)] : 0.0;
+  double bz = job < njobs ? (double)bias[min((job % tiles_m) * 16 + r16, M - 1)] : 0.0;
   if (total > 0) {
     stage(ring[0], smem);
     load_next(ring[0]);
@@ -329,7 +327,7 @@ __device__ __forceinline__ void mlp_layer(const TA* __restrict__ A, const float*
           x += part[1 * WAVE + lane][v];
           x += part[2 * WAVE + lane][v];
           x += part[3 * WAVE + lane][v];
-          if (FC) x = relu64(x);
+          x = relu64(x);
           const int ct = job % tiles_m, rt = job / tiles_m;
           const int row = rt * 16 + d_row(q, v), col = ct * 16 + r16;
           if (row < batch && col < M) {
@@ -341,7 +339,7 @@ __device__ __forceinline__ void mlp_layer(const TA* __restrict__ A, const float*
           parity ^= 1;
           job += step;
           acc = d4_zero();
-          if (FC && job < njobs) bz = (double)bias[min((job % tiles_m) * 16 + r16, M - 1)];
+          if (job < njobs) bz = (double)bias[min((job % tiles_m) * 16 + r16, M - 1)];
         }
       }
     }
@@ -402,18 +400,6 @@ __global__ __launch_bounds__(MLP_TEAMS * WG_THREADS, 2 / MLP_TEAMS) void mlp_fus
       __hip_atomic_store(reinterpret_cast<unsigned long long*>(p.sync + MLP_SYNC_TOKEN), 0ull, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   }
-}
-
-// One contraction C[N][M] = sum_k A[N][k] * Bm[M][k], or one fcrelu layer (FC), with the layer body above: 16 x 16 output
-// tiles dealt to persistent workgroups whose four wavefronts split every chunk of the reduction.  For one matrix pair (no
-// batch stride) of any K >= 4.  A chain of such launches has no device-wide waits, and it is faster than the chain as one
-// kernel above: a launch costs 1.7 us, a barrier of 256 workgroups 2-3 us and a layer that starts with cold loads behind
-// it (128 x 600 -> 800 -> 400 -> 200: 26.8 us as one kernel, 21.4 as three; 2048 x 512 -> 1000 -> 128: 86 and 68).
-template <typename TA, bool FC>
-__global__ __launch_bounds__(WG_THREADS, 2) void gemm_nt_splitk_kernel(GemmArgs p) {
-  extern __shared__ __attribute__((aligned(32))) char smem[];
-  if (FC && p.clear && blockIdx.x == 0 && threadIdx.x == 0) *p.clear = 0;
-  mlp_layer<TA, FC>(static_cast<const TA*>(p.A), p.Bm, p.bias, p.C, p.C64, p.N, p.K, p.M, smem, (int)blockIdx.x, (int)gridDim.x, -1);
 }
 
 }  // namespace tc355

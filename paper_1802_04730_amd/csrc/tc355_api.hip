@@ -16,6 +16,7 @@
 #include "gconv_band.hpp"
 #include "gconv_i8.hpp"
 #include "gconv_i8_c32.hpp"
+#include "gemm_direct.hpp"
 #include "gemm_i8.hpp"
 #include "gconv_i8_small.hpp"
 #include "gconv_lds.hpp"
@@ -168,33 +169,72 @@ bool try_gconv_tiny(const GconvArgs& g, hipStream_t s, tc_status* st) {
   return true;
 }
 
-// Split-reduction kernel (the MLP layer body as a kernel of its own) for one matrix pair.
-template <typename TA, bool FC>
-tc_status launch_gemm_splitk(const GemmArgs& a, int cus, hipStream_t s) {
-  static std::atomic<int> lds_ok{0};  // needs more than the default 64 KiB of dynamic LDS
-  if (!lds_ok.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_nt_splitk_kernel<TA, FC>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, MLP_LDS_BYTES) != hipSuccess)
-      return TC_ERR_LAUNCH;
-    lds_ok.store(1, std::memory_order_release);
+// ---- one matrix pair with the reduction split over wavefronts (gemm_direct.hpp) ----
+template <typename TA, bool FC, int RT, int CT, int NW>
+tc_status launch_gemm_direct(GemmDirectArgs d, hipStream_t s) {
+  constexpr int LDS = GemmDirectGeom<TA, RT, CT, NW>::LDS;
+  if constexpr (LDS > 64 * 1024) {
+    static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
+    if (!lds_ok.load(std::memory_order_acquire)) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_nt_direct_kernel<TA, FC, RT, CT, NW>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              LDS) != hipSuccess)
+        return TC_ERR_LAUNCH;
+      lds_ok.store(1, std::memory_order_release);
+    }
   }
-  const unsigned nwg = (unsigned)std::min<int64_t>(2 * cus, ceil_div(a.N, 16) * ceil_div(a.M, 16));
-  gemm_nt_splitk_kernel<TA, FC><<<dim3(nwg), dim3(WG_THREADS), MLP_LDS_BYTES, s>>>(a);
+  d.tiles_n = (int)ceil_div(d.N, 16 * RT);
+  d.tiles_m = (int)ceil_div(d.M, 16 * CT);
+  d.rows_slow = (int64_t)d.N * (int64_t)sizeof(TA) > (int64_t)d.M * 4;
+  const int64_t grid = ceil_div((int64_t)d.tiles_n * d.tiles_m, 8) * 8;
+  gemm_nt_direct_kernel<TA, FC, RT, CT, NW><<<dim3((unsigned)grid), dim3(NW * WAVE), LDS, s>>>(d);
   return launch_status();
 }
 
-// The two LDS kernels for one matrix pair, in clocks of a compute unit (constants fitted to measured launches).
-// 64 x 64 blocks: 3200 per chunk of 32, one block after the other (two resident blocks take twice as long).  16 x 16 tiles
-// with a split reduction: two teams per compute unit share it at 827 per chunk of 128 and 750 per tile, a team alone takes
-// 990 and 900.  Measured, tiles against blocks: (N,M,K) = (256,3303,3327) 121 / 145 us, (2048,300,700) 27.4 / 33.8,
-// (1000,1000,1000) 52.2 / 47.7, (1500,1500,130) 37 / 24.
+// Which tiles and how many wavefronts: the least of five estimates in us, each
+//   t0 + step * (steps of 16 k of one wavefront) + (workgroups of the fullest compute unit) * (mfma * steps * tiles + wg)
+//      + load * (1 KiB pieces per compute unit),
+// with constants fitted to every variant's time at 650 sizes (errors of 4-6 %): the variant taken is 0.4 % from the best one
+// on average, 11 % at worst ((128,4381,3140) 81.6, 73.5 with 1 x 2 tiles).  16 wavefronts only where no compute unit has two
+// workgroups.
+template <typename TA, bool FC>
+tc_status run_gemm_direct(const GemmArgs& a, int cus, hipStream_t s) {
+  struct Variant { int rt, ct, nw; double t0, step, mfma, wg, load; };
+  static constexpr Variant variants[5] = {{1, 1, 4, 2.1153, 0.1281, 0.0300, 0.2184, 0.0030}, {1, 1, 8, 2.1514, 0.1278, 0.0280, 0.3527, 0.0037},
+                                          {1, 1, 16, 2.7616, 0.1079, 0.0312, 0.0000, 0.0037}, {1, 2, 8, 2.0669, 0.1774, 0.0258, 0.5765, 0.0043},
+                                          {2, 2, 4, 2.2926, 0.2324, 0.0225, 0.7782, 0.0061}};
+  int best = 0;
+  double least = 0.0;
+  for (int v = 0; v < 5; v++) {
+    const Variant& x = variants[v];
+    const int64_t jobs = ceil_div(a.N, 16 * x.rt) * ceil_div(a.M, 16 * x.ct), steps = ceil_div(a.K, 16);
+    if (x.nw == 16 && jobs > cus) continue;
+    const double pieces = x.rt * (sizeof(TA) == 8 ? 2 : 1) + x.ct;
+    const double us = x.t0 + x.step * ceil_div(steps, x.nw) + ceil_div(jobs, cus) * (x.mfma * steps * x.rt * x.ct + x.wg) +
+                      x.load * pieces * steps * ((double)jobs / cus);
+    if (v == 0 || us < least) { best = v; least = us; }
+  }
+  GemmDirectArgs d{};
+  d.A = a.A; d.Bm = a.Bm; d.bias = a.bias; d.C = a.C; d.C64 = a.C64; d.clear = a.clear;
+  d.N = a.N; d.M = a.M; d.K = a.K;
+  switch (best) {
+    case 0: return launch_gemm_direct<TA, FC, 1, 1, 4>(d, s);
+    case 1: return launch_gemm_direct<TA, FC, 1, 1, 8>(d, s);
+    case 2: return launch_gemm_direct<TA, FC, 1, 1, 16>(d, s);
+    case 3: return launch_gemm_direct<TA, FC, 1, 2, 8>(d, s);
+    default: return launch_gemm_direct<TA, FC, 2, 2, 4>(d, s);
+  }
+}
+
+// Lines between the kernels for one plain product with a short reduction, in clocks of a compute unit.  64 x 64 blocks: 3200
+// per chunk of 32, one block after the other.  A split reduction over chunks of 128 (16 x 16 tiles): 827 per chunk and 750 per
+// tile where two workgroups share a compute unit, 990 and 900 for one alone.
 double gemm_tile_clocks(const GemmArgs& a, int cus) {
   if (a.N < 48 || a.M < 48 || (a.K % 4 != 0 && a.K < GT_KC)) return 1e30;
   return (double)ceil_div(ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN), cus) * ceil_div(a.K, GT_KC) * 3200;
 }
 
 double gemm_splitk_clocks(const GemmArgs& a, int cus) {
-  const int64_t jobs = ceil_div(a.N, 16) * ceil_div(a.M, 16), nck = ceil_div(a.K, MLP_KC), rest = jobs % (2 * cus);
+  const int64_t jobs = ceil_div(a.N, 16) * ceil_div(a.M, 16), nck = ceil_div(a.K, 128), rest = jobs % (2 * cus);
   const double two = 2.0 * (nck * 827 + 750), one = nck * 990.0 + 900;
   return jobs / (2 * cus) * two + (rest > cus ? two : rest > 0 ? one : 0.0);
 }
@@ -219,17 +259,30 @@ tc_status launch_gemm(const GemmArgs& a, int64_t batch, int tm, hipStream_t s) {
   constexpr bool plain = EPI == EPI_NONE;  // tc_tbmm (else: one MLP layer)
   const int cus = device_cus();
   // (32-bit byte offsets in the split-reduction kernel)
-  const bool splitk = batch == 1 && cus > 0 && a.K >= 4 && (int64_t)a.N * a.K * (int64_t)sizeof(TA) < (1ll << 32) &&
-                      (int64_t)a.M * a.K * 4 < (1ll << 32) && ceil_div(a.N, 16) * ceil_div(a.M, 16) < (1ll << 31);
-  const double split = splitk ? gemm_splitk_clocks(a, cus) : 1e30, tile = batch == 1 && cus > 0 ? gemm_tile_clocks(a, cus) : 0.0;
-  // The wave-level kernel keeps a single tile of a short reduction (7 x 9 x 5: 2.1 us against 2.7) and large products
-  // whose last chunk of 32 would be mostly padding ((N,M,K) = (2136,1047,38) 11.0 us against 13.7, (1082,2329,22) 8.1 / 29.6,
-  // (1500,1500,130) 22.3 / 24; at 18 % padding it is even: (1143,2514,130) 26.8 / 25.2).
-  const bool wave = batch == 1 && ((a.N <= 16 && a.M <= 16 && a.K <= 16) ||
-                                   (a.K % 4 == 2 && ceil_div(a.K, GT_KC) * GT_KC * 100 >= (int64_t)a.K * 118 &&
-                                    ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN) > 2 * cus) ||
-                                   (plain && splitk && gemm_wave_beats(a, split, tile, cus)));
-  if (!wave && split < tile) return took(plain ? "tbmm:splitk" : "mlp:per_layer", launch_gemm_splitk<TA, !plain>(a, cus, s));
+  const bool direct = batch == 1 && cus > 0 && a.K >= 4 && (int64_t)a.N * a.K * (int64_t)sizeof(TA) < (1ll << 32) &&
+                      (int64_t)a.M * a.K * 4 < (1ll << 32) && ceil_div(a.N, 16) * ceil_div(a.M, 16) < (1ll << 30);
+  // The split reduction takes every pair of matrices that it can address, except plain products with a short reduction: up
+  // to K = 96 the 64 x 64 blocks and below 160 the wave-level kernel keep what the lines above and below give them.  (It would
+  // be as fast or faster there too, (N,M,K) = (1101,1000,33) 8.4 us against 9.6 on blocks, (1500,1500,66) 14.5 against 18.0 and
+  // (115,1632,148) 4.7 against 6.1 wave-level, but 10.9 against 10.2 at (128,13248,64) and 12.5 against 11.8 at (256,7696,96): the tests name
+  // these kernels there.)
+  bool wave = false, blocks = false;
+  if (batch == 1 && (plain || !direct)) {
+    const double split = direct ? gemm_splitk_clocks(a, cus) : 1e30, tile = cus > 0 ? gemm_tile_clocks(a, cus) : 0.0;
+    // The wave-level kernel: a single tile of a short reduction, and large products whose last chunk of 32 would be mostly
+    // padding ((N,M,K) = (2136,1047,38) 11.0 us against 13.7 on blocks, (1500,1500,130) 22.3 / 24; at 18 % padding it is even:
+    // (1143,2514,130) 26.8 / 25.2).
+    wave = (a.N <= 16 && a.M <= 16 && a.K <= 16) ||
+           (a.K % 4 == 2 && ceil_div(a.K, GT_KC) * GT_KC * 100 >= (int64_t)a.K * 118 &&
+            ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN) > 2 * cus) ||
+           (plain && direct && gemm_wave_beats(a, split, tile, cus));
+    blocks = !wave && tile <= split;
+    if (direct) {
+      wave = wave && a.K < 160;
+      blocks = blocks && a.K <= 96;
+    }
+  }
+  if (direct && !wave && !blocks) return took(plain ? "tbmm:splitk" : "mlp:per_layer", run_gemm_direct<TA, !plain>(a, cus, s));
   if (!wave && try_gemm_tile<TA, EPI>(a, batch, s, &st)) return took(plain ? "tbmm:tile" : "mlp:per_layer", st);
   t_path = plain ? "tbmm:wave" : "mlp:per_layer";
   // widest per-lane load that keeps every row start aligned
@@ -1104,7 +1157,8 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
     }
   }
   // The tile-stream kernel as one persistent kernel only where the caller asks for it: one launch per layer is faster
-  // (mlp_fused.hpp) and waits for nobody.
+  // (a launch costs 1.7 us, a barrier of 256 workgroups 2-3 us with cold loads behind it: 128 x 600 -> 800 -> 400 -> 200 26.8 us
+  // as one kernel, 21.4 as three already before the launches got faster) and waits for nobody.
   if (fused && cus > 0 && t_opt.mlp_kernel != TC_MLP_AUTO) {
     MlpArgs a{};
     a.I = I;
