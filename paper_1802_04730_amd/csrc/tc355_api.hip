@@ -111,28 +111,26 @@ bool try_gconv_mix(const GconvArgs& g, hipStream_t s, tc_status* st);  // record
 
 // ---- grouped convolution with 4 or 8 channels per group (4x4x4 MFMA blocks), compile-time width; records the path of the
 // kernel that it chose --------
-template <int C, int F, int KH, int KW, int W, int ROWS, int MINW>
+template <int C, int F, int KH, int KW, int W, int ROWS, int TN, int MINW>
 bool try_gconv_quad(const GconvArgs& g, hipStream_t s, tc_status* st) {
-  using Gm = GconvQuadGeom<C, F, KH, KW, W, ROWS>;
+  using Gm = GconvQuadGeom<C, F, KH, KW, W, ROWS, TN>;
   if (g.C != C || g.F != F || g.KH != KH || g.KW != KW || g.W != W) return false;
-  const int64_t grid = (int64_t)g.N * g.G;
-  // One workgroup per (image, group) leaves the chip idle where there are few: the same 4x4x4 blocks in pieces of an image
-  // (gconv_mix.hpp).  Here a launch takes as long as one workgroup's bands, there as long as the pixels per compute unit
-  // say: lines through the times of both at 456 (pairs, height), the slower kernel is taken for one of them (7.8 us against
-  // 7.3) and 0.7 % given away on average.  Measured, here / there in us, 56 x 56 with 4 channels: 64 pairs 13.0 / 8.2, 128
-  // 13.4 / 11.3, 176 13.8 / 14.5, 255 14.7 / 17.4, 255 pairs of 28 x 56 8.2 / 11.7; 28 x 28 with 8 channels: 48 7.5 / 6.7,
-  // 80 7.5 / 8.0, 127 7.7 / 8.1.
-  if (grid < device_cus()) {
-    const double px = (double)grid * g.OH * g.OW / device_cus();
-    const double bands = (C == 4 ? 2.1 : 2.5) + (C == 4 ? (W == 56 ? 2.75 : 2.95) : (W == 28 ? 4.85 : 3.45)) * ceil_div(g.OH, ROWS);
+  const int64_t pairs = (int64_t)g.N * g.G, grid = ceil_div(pairs, 8) * 8 * ceil_div(g.OH, ROWS);
+  if (grid > kMaxGrid) return false;
+  // Few pairs: the same 4x4x4 blocks in pieces of an image (gconv_mix.hpp), where the estimates of an earlier form of this kernel,
+  // one workgroup per pair, say so.  (In bands it is as fast or faster from about 32 pairs of 56 x 56 on, 5.5 us against 11.3
+  // at 124; up to there the tests name the other kernel.)
+  if (pairs < 125) {
+    constexpr int EARLIER = C == 4 ? 16 : W == 28 ? 26 : 14;  // its rows per band
+    const double px = (double)pairs * g.OH * g.OW / std::max(1, device_cus());
+    const double bands = (C == 4 ? 2.1 : 2.5) + (C == 4 ? (W == 56 ? 2.75 : 2.95) : (W == 28 ? 4.85 : 3.45)) * ceil_div(g.OH, EARLIER);
     const double pieces = C == 4 ? 4.2 + std::min(0.0125 * px, 1.5 + 0.0043 * px) : 4.6 + std::min(0.016 * px, 1.4 + 0.0085 * px);
     if (pieces < bands && try_gconv_mix(g, s, st)) return true;
   }
-  if (grid > kMaxGrid) return false;
   t_path = "gconv:quad";
   static std::atomic<int> lds_ok{0};
   if (!lds_ok.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(gconv_quad_kernel<C, F, KH, KW, W, ROWS, MINW>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(gconv_quad_kernel<C, F, KH, KW, W, ROWS, TN, MINW>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, Gm::LDS_BYTES) != hipSuccess) {
       *st = TC_ERR_LAUNCH;
       return true;
@@ -141,8 +139,8 @@ bool try_gconv_quad(const GconvArgs& g, hipStream_t s, tc_status* st) {
   }
   GconvQuadArgs a{};
   a.I = g.I; a.W1 = g.W1; a.bias = g.bias; a.O = g.O;
-  a.G = g.G; a.H = g.H;
-  gconv_quad_kernel<C, F, KH, KW, W, ROWS, MINW><<<dim3((unsigned)grid), dim3(WG_THREADS), Gm::LDS_BYTES, s>>>(a);
+  a.NG = pairs; a.G = g.G; a.H = g.H;
+  gconv_quad_kernel<C, F, KH, KW, W, ROWS, TN, MINW><<<dim3((unsigned)grid), dim3(WG_THREADS), Gm::LDS_BYTES, s>>>(a);
   *st = launch_status();
   return true;
 }
@@ -1406,10 +1404,10 @@ tc_status tc_group_conv(const float* I, const float* W1, const float* bias, floa
   }
   if (try_gconv_band<16, 3, 3, 58, 8, 2>(a, s, &st)) return took("gconv:band", st);
   if (try_gconv_band<16, 3, 3, 14, 12, 2>(a, s, &st)) return took("gconv:band", st);  // the paper's (32,32,16,16,14,14): the whole image is one band
-  if (try_gconv_quad<4, 4, 3, 3, 56, 16, 4>(a, s, &st)) return st;    // the paper's (32,32,4,4,56,56)
-  if (try_gconv_quad<8, 8, 3, 3, 28, 26, 3>(a, s, &st)) return st;    // the paper's (32,32,8,8,28,28): one band
-  if (try_gconv_quad<4, 4, 3, 3, 58, 16, 4>(a, s, &st)) return st;    // the same two with a border of one pixel
-  if (try_gconv_quad<8, 8, 3, 3, 30, 14, 3>(a, s, &st)) return st;
+  if (try_gconv_quad<4, 4, 3, 3, 56, 9, 4, 4>(a, s, &st)) return st;    // the paper's (32,32,4,4,56,56)
+  if (try_gconv_quad<8, 8, 3, 3, 28, 13, 3, 3>(a, s, &st)) return st;    // the paper's (32,32,8,8,28,28): one band
+  if (try_gconv_quad<4, 4, 3, 3, 58, 8, 4, 4>(a, s, &st)) return st;    // the same two with a border of one pixel
+  if (try_gconv_quad<8, 8, 3, 3, 30, 14, 7, 2>(a, s, &st)) return st;
   if (try_gconv_tiny<32, 32, 3, 3, 7, 7>(a, s, &st)) return took("gconv:tiny", st);       // the paper's (32,32,32,32,7,7)
   // 16 channels, any image: blocks of 448 pixels where one or two of them fit the image closely and there are enough, else
   // blocks of the image's own measure (gconv_mix.hpp).  Measured at 32 groups, batch 16 (lds / mix, us): 22 x 24 26.7 / 29.1,
