@@ -1,15 +1,20 @@
-"""Build libtc355.so in-tree with hipcc for gfx950."""
+"""Build libtc355.so (hipcc, gfx950) and the binding's native calls _fast.so (g++) in-tree."""
 from __future__ import annotations
 
 import glob
 import hashlib
 import os
 import subprocess
+import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtc355.so")
 STAMP = LIB + ".srchash"  # hash of the sources the library was built from
+FAST = os.path.join(HERE, "_fast.so")  # the binding's calls in native code
+FAST_SOURCE = os.path.join(CSRC, "fast_call.cpp")
+FAST_STAMP = FAST + ".srchash"
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -52,8 +57,48 @@ def have_hipcc() -> bool:
     return os.access(hipcc_path(), os.X_OK)
 
 
+def fast_hash() -> str:
+    """Hash of what _fast.so is compiled from: its source, and the interpreter and torch whose headers it uses."""
+    import torch
+
+    h = hashlib.sha256(("%s %s" % (sys.version, torch.__version__)).encode())
+    with open(FAST_SOURCE, "rb") as f:
+        h.update(f.read())
+    return h.hexdigest()
+
+
+def fast_is_stale() -> bool:
+    if not os.path.exists(FAST) or not os.path.exists(FAST_STAMP):
+        return True
+    with open(FAST_STAMP) as f:
+        return f.read().strip() != fast_hash()
+
+
+def build_fast(verbose: bool = False) -> str:
+    """Compile the binding's native calls against torch's headers; returns the module's path."""
+    import torch
+
+    t = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(hipcc_path()))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + os.path.join(t, "include"), "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"], "-o", FAST, FAST_SOURCE,
+           "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + r.stdout + r.stderr)
+    with open(FAST_STAMP, "w") as f:
+        f.write(fast_hash() + "\n")
+    return FAST
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every HIP source into libtc355.so; returns the library path."""
+    """Compile every HIP source into libtc355.so, and _fast.so; returns the library path."""
+    if force or fast_is_stale():
+        build_fast(verbose)
     if not force and not is_stale():
         return LIB
     hipcc = hipcc_path()

@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libtc355.so: argument marshalling only.
+"""Thin binding of libtc355.so: argument marshalling only, in native code (csrc/fast_call.cpp) for the arguments that calls are
+made with in earnest and through ctypes for the rest, errors among them.
 
 Every function has the name and argument order of the C entry point in
 include/tc355.h.  Tensors are torch CUDA tensors (device memory owned by the
@@ -10,7 +11,9 @@ loaded the import of this module's functions fails loudly.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import shutil
 import struct
 
 import torch
@@ -18,6 +21,8 @@ import torch
 from . import build as _build
 
 _LIB = None
+_FAST = None  # csrc/fast_call.cpp, from the moment the library is loaded; None where it cannot be built
+_AT = {}  # addresses of the entry points
 
 TC_OK = 0
 STATUS_NAMES = {0: "TC_OK", 1: "TC_ERR_NULL", 2: "TC_ERR_SHAPE", 3: "TC_ERR_ALIAS", 4: "TC_ERR_ALIGN",
@@ -84,8 +89,24 @@ def lib() -> ctypes.CDLL:
     L.tc_sconv2d_infer.restype = ctypes.c_int
     L.tc_lut.argtypes = [i32, vp, vp, vp, vp, vp, i64, i64, vp]
     L.tc_lut.restype = ctypes.c_int
+    _load_fast(L)
     _LIB = L
     return L
+
+
+def _load_fast(L) -> None:
+    """The native calls, built first if they are missing or older than their source (and a compiler is there)."""
+    global _FAST
+    if _build.fast_is_stale():
+        if shutil.which(os.environ.get("CXX", "g++")) is None:
+            return
+        _build.build_fast()
+    spec = importlib.util.spec_from_file_location("_fast", _build.FAST)
+    fast = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(fast)
+    for name in ("tc_tbmm", "tc_tbmm_ws", "tc_mlp_fcrelu", "tc_group_conv", "tc_kron", "tc_sconv2d", "tc_lut"):
+        _AT[name] = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
+    _FAST = fast
 
 
 def status_string(status: int) -> str:
@@ -165,6 +186,10 @@ def _check(status: int, where: str) -> None:
 
 def tc_tbmm(X, Y, Z, stream=None) -> None:
     """Z[B,N,M] = sum_k X[B,N,K] * Y[B,M,K]; Z is written in place."""
+    if _FAST is not None:
+        status = _FAST.tbmm(_AT["tc_tbmm"], X, Y, Z, stream)
+        if status >= 0:
+            return _check(status, "tc_tbmm")
     B, N, K = X.shape
     B2, M, K2 = Y.shape
     if (B, K) != (B2, K2) or tuple(Z.shape) != (B, N, M):
@@ -178,6 +203,10 @@ def tc_tbmm_workspace_bytes(B: int, N: int, M: int, K: int) -> int:
 
 def tc_tbmm_ws(X, Y, Z, workspace, stream=None) -> None:
     """tc_tbmm with a workspace (a uint8 tensor of at least tc_tbmm_workspace_bytes bytes, or None)."""
+    if _FAST is not None:
+        status = _FAST.tbmm_ws(_AT["tc_tbmm_ws"], X, Y, Z, workspace, stream)
+        if status >= 0:
+            return _check(status, "tc_tbmm_ws")
     B, N, K = X.shape
     B2, M, K2 = Y.shape
     if (B, K) != (B2, K2) or tuple(Z.shape) != (B, N, M):
@@ -216,6 +245,10 @@ def tc_mlp_fcrelu(I, W, bias, O, workspace=None, stream=None) -> None:
     ``workspace`` is a torch CUDA uint8 tensor of at least
     tc_mlp_fcrelu_workspace_bytes(batch, dims) bytes (None only when that is 0).
     """
+    if _FAST is not None:
+        status = _FAST.mlp(_AT["tc_mlp_fcrelu"], I, W, bias, O, workspace, stream)
+        if status >= 0:
+            return _check(status, "tc_mlp_fcrelu")
     batch, n, dm, Wp, bp, Op = _mlp_args(I, W, bias, O, "tc_mlp_fcrelu")
     ws_ptr, ws_bytes = None, 0
     if workspace is not None:
@@ -241,6 +274,10 @@ def tc_group_conv_infer(H: int, W: int, KH: int, KW: int):
 
 def tc_group_conv(I, W1, bias, O, stream=None) -> None:
     """O[N,G,F,OH,OW] = grouped conv of I[N,G,C,H,W] with W1[G,F,C,KH,KW] plus bias[G*F] (or None)."""
+    if _FAST is not None:
+        status = _FAST.gconv(_AT["tc_group_conv"], I, W1, bias, O, stream)
+        if status >= 0:
+            return _check(status, "tc_group_conv")
     N, G, C, H, W = I.shape
     G2, F, C2, KH, KW = W1.shape
     if (G, C) != (G2, C2):
@@ -255,6 +292,10 @@ def tc_group_conv(I, W1, bias, O, stream=None) -> None:
 
 def tc_kron(W1, W2, X, Y, stream=None) -> None:
     """Y[B,I,J] = sum_{k,l} W1[I,K] * W2[J,L] * X[B,K,L]."""
+    if _FAST is not None:
+        status = _FAST.kron(_AT["tc_kron"], W1, W2, X, Y, stream)
+        if status >= 0:
+            return _check(status, "tc_kron")
     I, K = W1.shape
     J, L = W2.shape
     B, K2, L2 = X.shape
@@ -272,6 +313,10 @@ def tc_sconv2d_infer(H: int, W: int, KH: int, KW: int, sh: int, sw: int):
 
 def tc_sconv2d(I, Wt, bias, O, sh: int, sw: int, stream=None) -> None:
     """O[N,F,OH,OW] = bias[F] + convolution of I[N,C,H,W] with Wt[F,C,KH,KW], strides (sh, sw), no padding."""
+    if _FAST is not None:
+        status = _FAST.sconv(_AT["tc_sconv2d"], I, Wt, bias, O, sh, sw, stream)
+        if status >= 0:
+            return _check(status, "tc_sconv2d")
     N, C, H, W = I.shape
     F, C2, KH, KW = Wt.shape
     if C != C2:
@@ -289,6 +334,10 @@ def tc_sconv2d(I, Wt, bias, O, sh: int, sw: int, stream=None) -> None:
 
 def tc_lut(LUT, Idx, O, stream=None) -> None:
     """O[t][B,D] = sum_k LUT[t][Idx[t][B,k], :] for every table t; LUT, Idx, O are lists of equal length."""
+    if _FAST is not None:
+        status = _FAST.lut(_AT["tc_lut"], LUT, Idx, O, stream)
+        if status >= 0:
+            return _check(status, "tc_lut")
     n = len(LUT)
     if n == 0 or len(Idx) != n or len(O) != n:
         raise ValueError("tc_lut: LUT, Idx and O must be lists of the same, non-zero length")
