@@ -17,18 +17,12 @@
 // additions; the result is rounded to fp32 once.
 //
 // One workgroup of 8 wavefronts = 128 rows of X against 64 rows of Y.
-// Without a workspace both operands are sliced by the workgroup that uses them:
-// X is sliced again by every workgroup, and slicing plus the per-block scaling
-// of the sums is about 475 vector-ALU instructions per wavefront and block
-// beside its 104 MFMAs (13 digit products).  With a workspace (PRE = true) X is
-// sliced ONCE by gemm_i8_slice_x_kernel, which runs the X half of the slicing
-// code and writes the digit records and the rows' inverse scales to global
-// memory in exactly the order in which this kernel's threads pick them up (one
-// 16-byte load per record, 8 KiB of consecutive addresses per instruction of
-// the workgroup): 184 of the vector instructions per wavefront and block go.  On this chip the vector ALU and the matrix core of a SIMD do
-// not work at the same time (the time of this kernel is the sum of its two
-// halves whatever their order or interleaving), so the kernel is bound by that
-// sum; blocks of 128 instead of 64 halve the per-block scaling work.
+// Both operands are sliced by the workgroup that uses them: X is sliced again by every workgroup, and slicing plus the per-block
+// scaling of the sums is about 475 vector-ALU instructions per wavefront and block beside its 104 MFMAs (13 digit products).
+// With a workspace X is sliced ONCE by gemm_i8_slice_x_kernel, which runs the X half of the slicing code and writes the
+// digits to global memory in operand order, and gemm_i8_presliced_kernel (below) contracts them.  The vector ALU and the
+// matrix core of a SIMD overlap little on this chip (the time of this kernel is the sum of its two halves whatever their
+// order or interleaving), so the kernel is bound by that sum; blocks of 128 instead of 64 halve the per-block scaling work.
 // Per block a thread owns 32 elements of one X row (four lanes per row) and 16
 // of one Y row (eight lanes per row): row maximum across those lanes
 // (data-parallel primitives), scale = S / max by a reciprocal and two Newton
@@ -58,10 +52,9 @@ struct GemmI8Args {
   const float* Y;  // [B][M][K]
   float* Z;        // [B][N][M]
   int M, K;
-  // X sliced beforehand (PRE = true): per block of 128 rows and block of 128 k, 8 record groups (MFMA step s, digit
-  // plane k) of 512 records of 16 bytes, record t being what thread t of the contracting workgroup stages; then
-  // the 128 inverse scales of the block (fp64)
-  const i4* Xd;        // [B * N / 128][K / 128][2][4][512]
+  // X sliced beforehand: per block of 128 rows and block of 128 k, for every MFMA step, tile of 16 rows and digit plane the
+  // 16 bytes of each lane of the operand; the 128 inverse scales of the block (fp64)
+  const i4* Xd;        // [B * N / 128][K / 128][2][8][4][64]
   const double* Xinv;  // [B * N / 128][K / 128][128]
 };
 // bytes of pre-sliced X per block of 128 rows x 128 k
@@ -111,8 +104,7 @@ __device__ __forceinline__ void gi8_absmax4(const f4& v, int& smax, unsigned& um
 }
 __device__ __forceinline__ int gi8_magnitude(int smax, unsigned umax) { return max(max(smax, 0), (int)(umax & 0x7fffffffu)); }
 
-// X sliced once: one workgroup per (block of 128 k, block of 128 rows), thread t = (row t / 4, chunk t % 4) exactly
-// as in the contracting kernel, which later reads record t of every group with one 16-byte load.
+// X sliced once: one workgroup per (block of 128 k, block of 128 rows), thread t = (row t / 4, chunk t % 4).
 __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_slice_x_kernel(const float* X, int K, i4* Xd, double* Xinv) {
   const int tid = threadIdx.x, blk = blockIdx.x, nb = (K + GI8_KB - 1) / GI8_KB;
   const int64_t rb = blockIdx.y;
@@ -137,7 +129,7 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_slice_x_kernel(const f
   v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
   double scale, inverse;
   gi8_scales((unsigned)v, scale, inverse);
-  i4* dst = Xd + (rb * nb + blk) * (int64_t)(GI8_STEPS * 4 * GI8_THREADS) + tid;
+  i4* dst = Xd + (rb * nb + blk) * (int64_t)(GI8_STEPS * 4 * GI8_THREADS) + (xrow >> 4) * (4 * WAVE) + cx * 16 + (xrow & 15);
 #pragma unroll
   for (int s = 0; s < GI8_STEPS; s++) {
     int y[4][4];
@@ -147,14 +139,13 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_slice_x_kernel(const f
     for (int k = 0; k < 4; k++) {
       i4 rec;
       rec.x = y[0][k]; rec.y = y[1][k]; rec.z = y[2][k]; rec.w = y[3][k];
-      dst[(s * 4 + k) * GI8_THREADS] = rec;
+      dst[s * (GI8_TN / 16 * 4 * WAVE) + k * WAVE] = rec;
     }
   }
   if (cx == 0) Xinv[(rb * nb + blk) * GI8_TN + xrow] = inverse;
 }
 
-// PRE: X arrives sliced (Xd, Xinv) instead of as fp32.
-template <int MIND = 2, bool PRE = false>
+template <int MIND = 2>
 __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_kernel(GemmI8Args p) {
   static_assert(MIND == 2 || MIND == 3, "13 or 10 digit products");
   extern __shared__ __attribute__((aligned(16))) char gi8g_lds[];
@@ -179,20 +170,10 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_kernel(GemmI8Args p) {
   const float* xsrc = X + (int64_t)xrow * K + 4 * cx;
   const float* ysrc = Y + (int64_t)yrow * K + 32 * hy + 4 * cyc;
   f4 rx[GI8_STEPS][4], ry[GI8_STEPS][2];
-  i4 xd[GI8_STEPS][4];  // PRE: this thread's digit records of the block
-  double xinv = 0.0;    // PRE: inverse scale of row xrow in the block
-  const int64_t rb = b * gridDim.z + blockIdx.z;  // block of 128 rows of X
   auto fetch = [&](int blk) {
     const float* ys = ysrc + blk * GI8_KB;
     const bool whole = blk * GI8_KB + GI8_KB <= K;  // K is a multiple of 4: 16-byte pieces are inside or outside as a whole
-    if constexpr (PRE) {
-      const i4* xr = p.Xd + (rb * nb + blk) * (int64_t)(GI8_STEPS * 4 * GI8_THREADS) + tid;
-#pragma unroll
-      for (int s = 0; s < GI8_STEPS; s++)
-#pragma unroll
-        for (int k = 0; k < 4; k++) xd[s][k] = xr[(s * 4 + k) * GI8_THREADS];
-      xinv = p.Xinv[(rb * nb + blk) * GI8_TN + xrow];
-    } else {
+    {
       const float* xs = xsrc + blk * GI8_KB;
       if (whole) {
 #pragma unroll
@@ -225,15 +206,7 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_kernel(GemmI8Args p) {
     }
   };
   auto slice = [&]() {
-    if constexpr (PRE) {  // X: the records as they came
-#pragma unroll
-      for (int s = 0; s < GI8_STEPS; s++) {
-        char* dst = gi8g_lds + xrow * GI8_RS + 16 * (4 * s + cx);
-#pragma unroll
-        for (int k = 0; k < 4; k++) *reinterpret_cast<i4*>(dst + k * GI8_PLANE) = xd[s][k];
-      }
-      invs[xrow] = xinv;
-    } else {  // X: 16 elements per step, row shared by the 4 lanes of a quad
+    {  // X: 16 elements per step, row shared by the 4 lanes of a quad
       int sm = 0;
       unsigned um = 0;
 #pragma unroll
@@ -372,6 +345,168 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_kernel(GemmI8Args p) {
     f4 o;
     o.x = (float)acc[j][0]; o.y = (float)acc[j][1]; o.z = (float)acc[j][2]; o.w = (float)acc[j][3];
     *reinterpret_cast<f4*>(Z + (int64_t)(64 * nh + 16 * j + r16) * M + m0 + 16 * mt + 4 * q) = o;
+  }
+}
+
+// The same product with X sliced beforehand.  Per block a SIMD has 104 MFMAs of each of its two wavefronts and about 280 vector
+// instructions (slicing Y, scaling the sums) to issue, 2.5 us at 2.4 GHz; the first form of this kernel, which staged X's
+// records through registers and one LDS buffer, took 4.0: 40 operand reads and 16 writes per wavefront, and two barriers at
+// which all wavefronts changed between a phase for the vector ALU and one for the matrix core.  Here X never enters LDS: its
+// digits lie in global memory in operand order, a wavefront's operand is 1 KiB of consecutive addresses that L2 has (2.1 MB
+// for 128 x 4096), and the next block's replace this block's in registers as soon as their last MFMA is issued.  That leaves LDS
+// to two buffers of Y and one barrier per block: block t + 1 is sliced into one of them before block t is contracted from
+// the other.  A wavefront contracts all 64 rows of Y against 16 rows of X, which a compute unit then loads once (32 x 32 per
+// wavefront loads them twice: 115 us).
+// (M,K,N) = (128,4096,16384): 128-131 -> 107 us and 5 for slicing X.  Taken back: half of the wavefronts slicing behind their
+// contraction instead of before (109; with both orders as loops of their own it spills: 145).
+constexpr int GP_PLANE = GI8_TM * GI8_RS;                     // a digit plane of Y
+constexpr int GP_BUF = 4 * GP_PLANE + GI8_TM * 8;             // four of them and the rows' inverse scales
+constexpr int GP_LDS_BYTES = 2 * GP_BUF;
+static_assert(GP_BUF % 16 == 0, "16-byte LDS accesses");
+
+template <int MIND>
+__global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_presliced_kernel(GemmI8Args p) {
+  static_assert(MIND == 2 || MIND == 3, "13 or 10 digit products");
+  extern __shared__ __attribute__((aligned(16))) char gi8p_lds[];
+  const int tid = threadIdx.x;
+  const int lane = tid & (WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  const int r16 = lane & 15, q = lane >> 4;
+  const int M = p.M, K = p.K, nb = (K + GI8_KB - 1) / GI8_KB;
+  const int m0 = blockIdx.x * GI8_TM;
+  const int64_t b = blockIdx.y, rb = b * gridDim.z + blockIdx.z;  // rb: block of 128 rows of X
+  const float* Y = p.Y + (b * M + m0) * (int64_t)K;
+  float* Z = p.Z + rb * GI8_TN * M;
+
+  // ---- staging Y: see gemm_i8_kernel
+  const int yrow = tid >> 3, cyc = (tid & 7) >> 1, hy = tid & 1;
+  const float* ysrc = Y + (int64_t)yrow * K + 32 * hy + 4 * cyc;
+  f4 ry[GI8_STEPS][2];
+  auto fetch = [&](int blk) {
+    const float* ys = ysrc + blk * GI8_KB;
+    if (blk * GI8_KB + GI8_KB <= K) {
+#pragma unroll
+      for (int s = 0; s < GI8_STEPS; s++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) ry[s][j] = *reinterpret_cast<const f4*>(ys + 64 * s + 16 * j);
+    } else {
+#pragma unroll
+      for (int s = 0; s < GI8_STEPS; s++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          const bool in = blk * GI8_KB + 64 * s + 16 * j + 32 * hy + 4 * cyc < K;
+          ry[s][j] = in ? *reinterpret_cast<const f4*>(ys + 64 * s + 16 * j) : f4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  };
+  auto slice = [&](int buf) {
+    int sm = 0;
+    unsigned um = 0;
+#pragma unroll
+    for (int s = 0; s < GI8_STEPS; s++) {
+      gi8_absmax4(ry[s][0], sm, um);
+      gi8_absmax4(ry[s][1], sm, um);
+    }
+    int v = gi8_magnitude(sm, um);
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+    v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false));  // row_half_mirror: the other quad
+    double scale, inverse;
+    gi8_scales((unsigned)v, scale, inverse);
+    char* base = gi8p_lds + buf * GP_BUF;
+#pragma unroll
+    for (int s = 0; s < GI8_STEPS; s++) {
+      int y[2][4];
+#pragma unroll
+      for (int j = 0; j < 2; j++) gi8_digits4(ry[s][j], scale, y[j]);
+      char* dst = base + yrow * GI8_RS + 16 * (4 * s + cyc) + 8 * hy;
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        int2 rec;
+        rec.x = y[0][k]; rec.y = y[1][k];
+        *reinterpret_cast<int2*>(dst + k * GP_PLANE) = rec;
+      }
+    }
+    reinterpret_cast<double*>(base + 4 * GP_PLANE)[yrow] = inverse * 16777216.0;  // 2^24: the weight of the lowest kept diagonal
+  };
+
+  // ---- contraction: all four tiles of Y against tile `wave` of X
+  i4 xa[GI8_STEPS][4];  // this block's operands of X: [step][plane]
+  double fx;            // inverse scale of the lane's row of X
+  const i4* xsrc = p.Xd + rb * nb * (int64_t)(GI8_STEPS * 4 * GI8_THREADS) + wave * (4 * WAVE) + lane;
+  const double* xisrc = p.Xinv + rb * nb * GI8_TN + 16 * wave + r16;
+  auto load_x = [&](int blk) {
+    const i4* src = xsrc + (int64_t)blk * (GI8_STEPS * 4 * GI8_THREADS);
+#pragma unroll
+    for (int s = 0; s < GI8_STEPS; s++)
+#pragma unroll
+      for (int k = 0; k < 4; k++) xa[s][k] = src[s * (GI8_TN / 16 * 4 * WAVE) + k * WAVE];
+  };
+  constexpr int YT = GI8_TM / 16;
+  double acc[YT][4];
+#pragma unroll
+  for (int j = 0; j < YT; j++)
+#pragma unroll
+    for (int v = 0; v < 4; v++) acc[j][v] = 0.0;
+  constexpr int ND = 7 - MIND, NP = MIND == 3 ? 10 : 13;
+  auto contract = [&](int buf, int next) {
+    // order: no two consecutive products on one diagonal
+    constexpr int PK[13] = {3, 2, 3, 3, 2, 1, 2, 1, 0, 3, 2, 1, 0};  // the last three: the diagonal k + l = 2
+    constexpr int PL[13] = {0, 1, 1, 2, 2, 2, 3, 3, 3, 3, 0, 1, 2};
+    const char* base = gi8p_lds + buf * GP_BUF;
+    const double* invs = reinterpret_cast<const double*>(base + 4 * GP_PLANE) + 4 * q;
+    i4 d[ND];  // d[i]: diagonal k + l = MIND + i
+#pragma unroll
+    for (int j = 0; j < YT; j++) {
+      const char* at = base + (16 * j + r16) * GI8_RS + 16 * q;
+      bool begun[ND] = {};  // (compile-time after unrolling) the first product of a diagonal starts from a literal zero
+#pragma unroll
+      for (int s = 0; s < GI8_STEPS; s++) {
+        i4 ya[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) ya[k] = *reinterpret_cast<const i4*>(at + 64 * s + k * GP_PLANE);
+#pragma unroll
+        for (int pr = 0; pr < NP; pr++) {
+          const int dg = PK[pr] + PL[pr] - MIND;
+          d[dg] = mfma_i8(ya[PK[pr]], xa[s][PL[pr]], begun[dg] ? d[dg] : i4{0, 0, 0, 0});
+          begun[dg] = true;
+        }
+      }
+      if (j == YT - 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_x(next);  // (their last use here was just issued)
+      }
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        // 128 terms of at most 2^14 per digit pair: 2^21 x 256 + 2 x 2^21 and 3 x 2^21 x 256 + 4 x 2^21, below 2^31
+        const int hi = d[ND - 1][v] * 256 + d[ND - 2][v], lo = d[ND - 3][v] * 256 + d[ND - 4][v];
+        double rr = __builtin_fma((double)hi, 65536.0, (double)lo);
+        if constexpr (MIND == 2) rr = __builtin_fma((double)d[0][v], 0.00390625, rr);
+        acc[j][v] = __builtin_fma(rr, invs[16 * j + v] * fx, acc[j][v]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    fx = xisrc[(int64_t)next * GI8_TN];
+  };
+
+  fetch(0);
+  load_x(0);
+  fx = xisrc[0];
+  slice(0);
+  fetch(min(1, nb - 1));
+  __syncthreads();
+  for (int t = 0; t < nb; t++) {
+    slice((t + 1) & 1);  // (behind the last block: once more, into the buffer that nobody reads)
+    fetch(min(t + 2, nb - 1));
+    __builtin_amdgcn_sched_barrier(0);
+    contract(t & 1, min(t + 1, nb - 1));
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < YT; j++) {
+    f4 o;
+    o.x = (float)acc[j][0]; o.y = (float)acc[j][1]; o.z = (float)acc[j][2]; o.w = (float)acc[j][3];
+    *reinterpret_cast<f4*>(Z + (int64_t)(16 * wave + r16) * M + m0 + 16 * j + 4 * q) = o;
   }
 }
 

@@ -924,10 +924,10 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
   if (tbmm_i8_shape(B, N, M, K) && t_opt.int8 != TC_INT8_OFF) {
     static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
     if (!lds_ok.load(std::memory_order_acquire)) {
-      const void* kernels[4] = {reinterpret_cast<const void*>(gemm_i8_kernel<2, false>), reinterpret_cast<const void*>(gemm_i8_kernel<3, false>),
-                                reinterpret_cast<const void*>(gemm_i8_kernel<2, true>), reinterpret_cast<const void*>(gemm_i8_kernel<3, true>)};
+      const void* kernels[4] = {reinterpret_cast<const void*>(gemm_i8_kernel<2>), reinterpret_cast<const void*>(gemm_i8_kernel<3>),
+                                reinterpret_cast<const void*>(gemm_i8_presliced_kernel<2>), reinterpret_cast<const void*>(gemm_i8_presliced_kernel<3>)};
       for (const void* k : kernels)
-        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, GI8_LDS_BYTES) != hipSuccess) return TC_ERR_LAUNCH;
+        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, std::max(GI8_LDS_BYTES, GP_LDS_BYTES)) != hipSuccess) return TC_ERR_LAUNCH;
       lds_ok.store(1, std::memory_order_release);
     }
     GemmI8Args g{};
@@ -943,12 +943,12 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
       const tc_status st = launch_status();
       if (st != TC_OK) return st;
       g.Xd = xd; g.Xinv = xinv;
-      if (ten) gemm_i8_kernel<3, true><<<grid, dim3(GI8_THREADS), GI8_LDS_BYTES, s>>>(g);
-      else gemm_i8_kernel<2, true><<<grid, dim3(GI8_THREADS), GI8_LDS_BYTES, s>>>(g);
+      if (ten) gemm_i8_presliced_kernel<3><<<grid, dim3(GI8_THREADS), GP_LDS_BYTES, s>>>(g);
+      else gemm_i8_presliced_kernel<2><<<grid, dim3(GI8_THREADS), GP_LDS_BYTES, s>>>(g);
       return took("tbmm:i8_presliced", launch_status());
     }
-    if (ten) gemm_i8_kernel<3, false><<<grid, dim3(GI8_THREADS), GI8_LDS_BYTES, s>>>(g);
-    else gemm_i8_kernel<2, false><<<grid, dim3(GI8_THREADS), GI8_LDS_BYTES, s>>>(g);
+    if (ten) gemm_i8_kernel<3><<<grid, dim3(GI8_THREADS), GI8_LDS_BYTES, s>>>(g);
+    else gemm_i8_kernel<2><<<grid, dim3(GI8_THREADS), GI8_LDS_BYTES, s>>>(g);
     return took("tbmm:i8", launch_status());
   }
 
