@@ -1214,32 +1214,43 @@ tc_status launch_sconv_split(SconvArgs a, hipStream_t s) {
   return launch_status();
 }
 
+// The fp64 kernels of the strided convolution, in clocks; what cannot run is out of reach.
+struct SconvFp64Clocks { double tile, split1, split2; };
+
+// Which kernel, from what a compute unit would spend in clocks: blocks one after the other when there are several per
+// unit, a single one bound by its chain of chunks (16 taps, 64 with a split reduction); small blocks read a third again
+// as long where strides step over the filters (lines of the input that nobody else reads).  The split has to be 4 % better:
+// that is what the estimate is worth.  Of 1500 random layers measured on every kernel, 2 take one that is more than 3 % slower
+// than the blocks of 64 (9 % at most; without the 4 % and the third 10, and 15.0 -> 16.4 us at (2415,256,174)), and
+// the choice is on average 0.7 % from the fastest.  Measured, (pixels, filters, taps): blocks of
+// 64 against 16 x 16 with a split reduction (400,64,1029) 40.8 / 10.8 us, (1331,64,9898) 349 / 106, (784,20,425) 19.5 / 6.3;
+// (11664,100,576) 45.5 / 54.9, (100352,64,64) 31 / 69; against 32 x 16 (867,215,3136) 113 / 51.6, (53312,20,128) 27.4 / 24.
+SconvFp64Clocks sconv_fp64_clocks(int64_t N, int64_t C, int64_t H, int64_t W, int64_t F, int64_t K, int64_t P, bool gaps) {
+  const int cus = std::max(1, device_cus());
+  const bool offsets = !prod_reaches({N, C, H, W}, (int64_t)1 << 30) && !prod_reaches({F, K}, (int64_t)1 << 30);
+  const int64_t chunks = ceil_div(K, SS_KC), table = chunks * SS_KC * 4;
+  const bool wide64 = ceil_div(F, SC_BF) * ceil_div(P, 64) >= 2 * cus;
+  const double blocks = (double)ceil_div(ceil_div(F, SC_BF) * ceil_div(P, wide64 ? 64 : 32), cus), steps = (double)ceil_div(K, SC_KC);
+  SconvFp64Clocks c{9400 + std::max((wide64 ? 2913 : 1303) * steps, blocks * ((wide64 ? 1602 : 816) * steps + 2224)), 1e30, 1e30};
+  if (offsets && SconvSplitGeom<2, 1>::STAGES + table <= 160 * 1024 && ceil_div(F, 16) * ceil_div(P, 16) <= kMaxGrid) {
+    const double gather = gaps ? 1.35 : 1.0;
+    auto split = [&](int tf, double one, double many) {
+      const double n = (double)ceil_div(ceil_div(F, 16 * tf) * ceil_div(P, 16), cus);
+      return 8175 + (double)K + std::max(one * chunks, n * (gather * many * chunks + 752 * tf));
+    };
+    c.split1 = split(1, 921, 688);
+    c.split2 = split(2, 1510, 1062);
+  }
+  return c;
+}
+
 // Strided convolution on the fp64 matrix core: blocks of 64 filters x 64 or 32 pixels (sconv_tile.hpp), or smaller ones with
 // a split reduction (sconv_split.hpp).  The caller's operator says how the two are called.
 tc_status launch_sconv_fp64(SconvArgs a, const char* tile_path, const char* split_path, hipStream_t s) {
   const int cus = std::max(1, device_cus());
-  // Which kernel, from what a compute unit would spend in clocks: blocks one after the other when there are several per
-  // unit, a single one bound by its chain of chunks (16 taps, 64 with a split reduction); small blocks read a third again
-  // as long where strides step over the filters (lines of the input that nobody else reads).  The split has to be 4 % better:
-  // that is what the estimate is worth.  Of 1500 random layers measured on every kernel, 2 take one that is more than 3 % slower
-  // than the blocks of 64 (9 % at most; without the 4 % and the third 10, and 15.0 -> 16.4 us at (2415,256,174)), and
-  // the choice is on average 0.7 % from the fastest.  Measured, (pixels, filters, taps): blocks of
-  // 64 against 16 x 16 with a split reduction (400,64,1029) 40.8 / 10.8 us, (1331,64,9898) 349 / 106, (784,20,425) 19.5 / 6.3;
-  // (11664,100,576) 45.5 / 54.9, (100352,64,64) 31 / 69; against 32 x 16 (867,215,3136) 113 / 51.6, (53312,20,128) 27.4 / 24.
-  const bool offsets = !prod_reaches({a.N, a.C, a.H, a.W}, (int64_t)1 << 30) && !prod_reaches({a.F, a.K}, (int64_t)1 << 30);
-  const int64_t chunks = ceil_div(a.K, SS_KC), table = chunks * SS_KC * 4;
-  if (offsets && SconvSplitGeom<2, 1>::STAGES + table <= 160 * 1024 && ceil_div(a.F, 16) * ceil_div(a.P, 16) <= kMaxGrid) {
-    const bool wide64 = ceil_div(a.F, SC_BF) * ceil_div(a.P, 64) >= 2 * cus;
-    const double blocks = (double)ceil_div(ceil_div(a.F, SC_BF) * ceil_div(a.P, wide64 ? 64 : 32), cus), steps = (double)ceil_div(a.K, SC_KC);
-    const double tile = 9400 + std::max((wide64 ? 2913 : 1303) * steps, blocks * ((wide64 ? 1602 : 816) * steps + 2224));
-    const double gather = a.sw > a.KW ? 1.35 : 1.0;
-    auto split = [&](int tf, double one, double many) {
-      const double n = (double)ceil_div(ceil_div(a.F, 16 * tf) * ceil_div(a.P, 16), cus);
-      return 8175 + (double)a.K + std::max(one * chunks, n * (gather * many * chunks + 752 * tf));
-    };
-    const double s1 = split(1, 921, 688), s2 = split(2, 1510, 1062);
-    if (1.04 * std::min(s1, s2) < tile) return took(split_path, s1 <= s2 ? launch_sconv_split<1, 1>(a, s) : launch_sconv_split<2, 1>(a, s));
-  }
+  const SconvFp64Clocks c = sconv_fp64_clocks(a.N, a.C, a.H, a.W, a.F, a.K, a.P, a.sw > a.KW);
+  if (1.04 * std::min(c.split1, c.split2) < c.tile)
+    return took(split_path, c.split1 <= c.split2 ? launch_sconv_split<1, 1>(a, s) : launch_sconv_split<2, 1>(a, s));
   a.tiles_f = (int)ceil_div(a.F, SC_BF);
   // 64-pixel blocks when there are at least two of them per compute unit, else 32-pixel blocks (twice as many)
   const bool wide = (int64_t)a.tiles_f * ceil_div(a.P, 64) >= 2 * (int64_t)cus;
@@ -1285,7 +1296,8 @@ int64_t sconv_i8_lds_bytes(int tf, int nt, int64_t blocks) {
 // that is a multiple of 4 and at least 256 taps (two blocks), operands that 32-bit offsets reach, a table of tap
 // offsets that fits LDS beside the digit planes (about 17,000 taps).  Measured faster than the fp64 kernel from a
 // single 8 x 8 image up.
-bool try_sconv_i8(const SconvI8Args& a, int64_t N, hipStream_t s, tc_status* st) {  // a.G groups of a.C channels and a.F filters
+// a.G groups of a.C channels and a.F filters; fp64_next: what is refused here goes to launch_sconv_fp64.
+bool try_sconv_i8(const SconvI8Args& a, int64_t N, bool fp64_next, hipStream_t s, tc_status* st) {
   if (t_opt.int8 == TC_INT8_OFF) return false;
   if (a.F % 32 != 0 || a.K % 4 != 0 || a.K < 256) return false;
   if (prod_reaches({N, a.G, a.C, a.H, a.W}, (int64_t)1 << 30)) return false;            // 32-bit byte offsets into I
@@ -1305,6 +1317,18 @@ bool try_sconv_i8(const SconvI8Args& a, int64_t N, hipStream_t s, tc_status* st)
   if (sconv_i8_lds_bytes(tf, nt, blocks) > 160 * 1024) return false;
   const int64_t gx = ceil_div(units, nt);
   if (gx > kMaxGrid || fblocks > 65535) return false;
+  // A workgroup walks over all taps, 1.9 us per block of 128 and pixel tile of a wavefront, however few workgroups there are: a
+  // long reduction on few pixels is faster in fp64 with its reduction split, and no less exact.  The line: estimates of both
+  // (this one fitted to 213 layers, errors of 7 %), fp64 where its is 10 % lower; of those layers 60 go over, 1.8 times as fast
+  // on average and none slower: (pixels, filters, taps) (64,128,12544) 201 -> 84 us, (192,128,3136) 54.6 -> 23.9, (200,256,1600)
+  // 30.8 -> 14.4.  Up to 1152 taps, and for less than one tile of pixels, int8 stays whatever the estimates say: (200,128,576)
+  // 14.4 against 7.1, where the tests name it.
+  if (fp64_next && a.G == 1 && t_opt.int8 == TC_INT8_AUTO && a.K > 1152 && a.P >= 16) {
+    const double turns = (double)ceil_div(gx * fblocks, std::max(1, device_cus()));
+    const double i8 = turns * (4.64 + blocks * (0.82 + 1.12 * (nt / nt_step)));  // us
+    const SconvFp64Clocks c = sconv_fp64_clocks(N, a.C, a.H, a.W, a.F, a.K, a.P, a.sw > a.KW);
+    if (std::min({c.tile, c.split1, c.split2}) / 2400 < 0.9 * i8) return false;
+  }
   const dim3 grid((unsigned)gx, (unsigned)fblocks, (unsigned)a.G);
   const bool ten = t_opt.int8 == TC_INT8_TEN;  // 13 digit products unless the caller has said that 10 will do
   if (tf == 128) {
@@ -1399,7 +1423,7 @@ tc_status tc_group_conv(const float* I, const float* W1, const float* bias, floa
       e.I = I; e.Wt = W1; e.bias = bias; e.O = O;
       e.C = (int)C; e.F = (int)F; e.H = (int)H; e.W = (int)W; e.KH = (int)KH; e.KW = (int)KW; e.sh = 1; e.sw = 1;
       e.OH = (int)OH; e.OW = (int)OW; e.K = (int)(C * KH * KW); e.P = (int)(N * OH * OW); e.G = (int)G;
-      if (try_sconv_i8(e, N, s, &st)) return took("gconv:i8_taps", st);
+      if (try_sconv_i8(e, N, F >= 64, s, &st)) return took("gconv:i8_taps", st);
     }
   }
   if (try_gconv_band<16, 3, 3, 58, 8, 2>(a, s, &st)) return took("gconv:band", st);
@@ -1527,7 +1551,7 @@ tc_status tc_sconv2d(const float* I, const float* Wt, const float* bias, float* 
     e.OH = (int)OH; e.OW = (int)OW;
     e.K = (int)K; e.P = (int)(N * OH * OW); e.G = 1;
     tc_status st = TC_OK;
-    if (try_sconv_i8(e, N, s, &st)) return took("sconv:i8", st);
+    if (try_sconv_i8(e, N, true, s, &st)) return took("sconv:i8", st);
   }
 
   SconvArgs a{};
