@@ -24,6 +24,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "gemm_direct_plan.hpp"
 #include "gemm_wave.hpp"
 
 namespace tc355 {
@@ -118,13 +119,13 @@ __global__ __launch_bounds__(NW * WAVE, RT * CT == 4 ? 3 : 4) void gemm_nt_direc
   const int steps = (K + 15) / 16;
   const int s0 = (int)((int64_t)steps * wave / NW), n = (int)((int64_t)steps * (wave + 1) / NW) - s0;  // this wavefront's steps
 
-  // ---- loading: byte offsets of the lane's parts from the operands (32 bits: the host checks)
+  // ---- loading: byte offsets of the lane's parts from the operands (32 bits: the host asks gd_reaches)
   const int lr = lane >> 2, lp = (lane & 3) ^ (lane >> 4);
   unsigned aoff[RT], boff[CT];
 #pragma unroll
-  for (int i = 0; i < RT; i++) aoff[i] = ((unsigned)min(n0 + 16 * i + lr, N - 1) * (unsigned)K + (unsigned)(PE * lp)) * (unsigned)sizeof(TA);
+  for (int i = 0; i < RT; i++) aoff[i] = gd_offset(min(n0 + 16 * i + lr, N - 1), PE * lp, K, sizeof(TA));
 #pragma unroll
-  for (int j = 0; j < CT; j++) boff[j] = ((unsigned)min(m0 + 16 * j + lr, M - 1) * (unsigned)K + 4u * lp) * 4u;
+  for (int j = 0; j < CT; j++) boff[j] = gd_offset(min(m0 + 16 * j + lr, M - 1), 4 * lp, K, 4);
   const char* A = static_cast<const char*>(p.A);
   const char* B = reinterpret_cast<const char*>(p.Bm);
   const unsigned ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)gd_lds + (unsigned)wave * Gm::WAVE_BYTES;
@@ -146,10 +147,10 @@ __global__ __launch_bounds__(NW * WAVE, RT * CT == 4 ? 3 : 4) void gemm_nt_direc
 #pragma unroll
         for (int z = 0; z < AI; z++) {
           const int group = A64 ? 4 * ((4 * z + lp) >> 1) : 4 * lp;  // first k of the group that this part belongs to
-          load_to_lds(Ak + aoff[i] + 64 * z + (int64_t)min(0, K - 4 - (k0 + group)) * (int)sizeof(TA), base + (i * AI + z) * 1024);
+          load_to_lds(Ak + aoff[i] + 64 * z + gd_end_shift(k0, group, K, sizeof(TA)), base + (i * AI + z) * 1024);
         }
 #pragma unroll
-      for (int j = 0; j < CT; j++) load_to_lds(Bk + boff[j] + (int64_t)min(0, K - 4 - (k0 + 4 * lp)) * 4, base + (RT * AI + j) * 1024);
+      for (int j = 0; j < CT; j++) load_to_lds(Bk + boff[j] + gd_end_shift(k0, 4 * lp, K, 4), base + (RT * AI + j) * 1024);
     }
   };
 

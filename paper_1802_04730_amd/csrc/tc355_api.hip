@@ -257,8 +257,8 @@ tc_status launch_gemm(const GemmArgs& a, int64_t batch, int tm, hipStream_t s) {
   constexpr bool plain = EPI == EPI_NONE;  // tc_tbmm (else: one MLP layer)
   const int cus = device_cus();
   // (32-bit byte offsets in the split-reduction kernel)
-  const bool direct = batch == 1 && cus > 0 && a.K >= 4 && (int64_t)a.N * a.K * (int64_t)sizeof(TA) < (1ll << 32) &&
-                      (int64_t)a.M * a.K * 4 < (1ll << 32) && ceil_div(a.N, 16) * ceil_div(a.M, 16) < (1ll << 30);
+  const bool direct = batch == 1 && cus > 0 && a.K >= 4 && gd_reaches(a.N, a.K, sizeof(TA)) && gd_reaches(a.M, a.K, 4) &&
+                      ceil_div(a.N, 16) * ceil_div(a.M, 16) < (1ll << 30);
   // The split reduction takes every pair of matrices that it can address, except plain products with a short reduction: up
   // to K = 96 the 64 x 64 blocks and below 160 the wave-level kernel keep what the lines above and below give them.  (It would
   // be as fast or faster there too, (N,M,K) = (1101,1000,33) 8.4 us against 9.6 on blocks, (1500,1500,66) 14.5 against 18.0 and
