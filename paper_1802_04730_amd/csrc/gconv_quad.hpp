@@ -43,6 +43,7 @@ struct GconvQuadArgs {
   float* O;
   int64_t NG;  // images times groups
   int G, H;
+  unsigned first;  // number of the launch's first workgroup (a multiple of 8)
 };
 
 template <int C, int F, int KH, int KW, int W, int ROWS, int TN>
@@ -82,10 +83,10 @@ __global__ __launch_bounds__(WG_THREADS, MINW) void gconv_quad_kernel(GconvQuadA
   const int H = p.H, OH = H - KH + 1;
   const int npix = OH * OW;
   // the bands of a pair are on one XCD (workgroups equal modulo 8), whose L2 keeps the rows that two bands read
-  const unsigned nbands = (unsigned)((OH + ROWS - 1) / ROWS), oct = blockIdx.x / (8 * nbands);
-  const int64_t ng = (int64_t)oct * 8 + blockIdx.x % 8;  // n*G + g
+  const unsigned nbands = (unsigned)((OH + ROWS - 1) / ROWS), wg = p.first + blockIdx.x, oct = wg / (8 * nbands);
+  const int64_t ng = (int64_t)oct * 8 + wg % 8;  // n*G + g
   if (ng >= p.NG) return;  // (the whole workgroup)
-  const int h0 = (int)((blockIdx.x - oct * 8 * nbands) / 8) * ROWS;
+  const int h0 = (int)((wg - oct * 8 * nbands) / 8) * ROWS;
   const int g = (int)(ng % p.G);
   const int64_t plane = (int64_t)H * W;
 

@@ -39,6 +39,7 @@ struct GemmDirectArgs {
   int N, M, K;
   int tiles_n, tiles_m;  // blocks of 16 RT rows, of 16 CT columns
   int rows_slow;         // order of the tiles: those of one block of rows follow each other
+  unsigned first;        // number of the launch's first workgroup (a multiple of 8)
 };
 
 // RT x CT tiles of 16 x 16 per workgroup, NW wavefronts
@@ -112,7 +113,9 @@ __global__ __launch_bounds__(NW * WAVE, RT * CT == 4 ? 3 : 4) void gemm_nt_direc
   const int r16 = lane & 15, q = lane >> 4;
   const int N = p.N, M = p.M, K = p.K;
   // every XCD (workgroups equal modulo 8) takes a run of tiles: all of the smaller operand and an eighth of the larger one
-  const int jobs = p.tiles_n * p.tiles_m, share = (jobs + 7) / 8, job = (int)(blockIdx.x % 8) * share + (int)(blockIdx.x / 8);
+  const int jobs = p.tiles_n * p.tiles_m, share = (jobs + 7) / 8;
+  const unsigned wg = p.first + blockIdx.x;
+  const int job = (int)(wg % 8) * share + (int)(wg / 8);
   if (job >= jobs) return;  // (the whole workgroup)
   const int per = p.rows_slow ? p.tiles_m : p.tiles_n, slow = job / per, fast = job - slow * per;
   const int n0 = (p.rows_slow ? slow : fast) * 16 * RT, m0 = (p.rows_slow ? fast : slow) * 16 * CT;

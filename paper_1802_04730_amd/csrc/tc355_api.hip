@@ -140,8 +140,12 @@ bool try_gconv_quad(const GconvArgs& g, hipStream_t s, tc_status* st) {
   GconvQuadArgs a{};
   a.I = g.I; a.W1 = g.W1; a.bias = g.bias; a.O = g.O;
   a.NG = pairs; a.G = g.G; a.H = g.H;
-  gconv_quad_kernel<C, F, KH, KW, W, ROWS, TN, MINW><<<dim3((unsigned)grid), dim3(WG_THREADS), Gm::LDS_BYTES, s>>>(a);
-  *st = launch_status();
+  for (int64_t at = 0; at < grid; at += next_launch(grid - at, WG_THREADS)) {
+    a.first = (unsigned)at;
+    gconv_quad_kernel<C, F, KH, KW, W, ROWS, TN, MINW><<<dim3((unsigned)next_launch(grid - at, WG_THREADS)), dim3(WG_THREADS), Gm::LDS_BYTES, s>>>(a);
+    *st = launch_status();
+    if (*st != TC_OK) break;
+  }
   return true;
 }
 
@@ -184,8 +188,13 @@ tc_status launch_gemm_direct(GemmDirectArgs d, hipStream_t s) {
   d.tiles_m = (int)ceil_div(d.M, 16 * CT);
   d.rows_slow = (int64_t)d.N * (int64_t)sizeof(TA) > (int64_t)d.M * 4;
   const int64_t grid = ceil_div((int64_t)d.tiles_n * d.tiles_m, 8) * 8;
-  gemm_nt_direct_kernel<TA, FC, RT, CT, NW><<<dim3((unsigned)grid), dim3(NW * WAVE), LDS, s>>>(d);
-  return launch_status();
+  tc_status st = TC_OK;
+  for (int64_t at = 0; at < grid && st == TC_OK; at += next_launch(grid - at, NW * WAVE)) {
+    d.first = (unsigned)at;
+    gemm_nt_direct_kernel<TA, FC, RT, CT, NW><<<dim3((unsigned)next_launch(grid - at, NW * WAVE)), dim3(NW * WAVE), LDS, s>>>(d);
+    st = launch_status();
+  }
+  return st;
 }
 
 // Which tiles and how many wavefronts: the least of five estimates in us, each

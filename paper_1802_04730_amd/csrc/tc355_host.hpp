@@ -19,4 +19,12 @@ inline bool prod_reaches(std::initializer_list<int64_t> factors, int64_t limit) 
   return false;
 }
 
+// HIP refuses a launch of 2^32 threads or more in one dimension.  Kernels that may need more take the number of the launch's first
+// workgroup and run in several launches: workgroups of `threads` threads for the next one, of `left` that are left.  (A
+// multiple of 8 unless it is the last: workgroups equal modulo 8 share an XCD.)
+inline int64_t next_launch(int64_t left, int threads) {
+  const int64_t most = ((int64_t)1 << 31) / threads / 8 * 8;
+  return left < most ? left : most;
+}
+
 }  // namespace tc355
