@@ -74,17 +74,22 @@ def fast_is_stale() -> bool:
         return f.read().strip() != fast_hash()
 
 
-def build_fast(verbose: bool = False) -> str:
-    """Compile the binding's native calls against torch's headers; returns the module's path."""
+def torch_module_command(source: str, out: str) -> list:
+    """g++ line of a Python module that uses torch's headers."""
     import torch
 
     t = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(hipcc_path()))
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
-           "-I" + os.path.join(t, "include"), "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"),
-           "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"], "-o", FAST, FAST_SOURCE,
-           "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+            "-I" + os.path.join(t, "include"), "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"),
+            "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"], "-o", out, source,
+            "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
+def build_fast(verbose: bool = False) -> str:
+    """Compile the binding's native calls against torch's headers; returns the module's path."""
+    cmd = torch_module_command(FAST_SOURCE, FAST)
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

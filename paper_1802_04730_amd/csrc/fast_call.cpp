@@ -66,9 +66,12 @@ PyObject** items(PyObject* o, Py_ssize_t n) {
   return PySequence_Fast_GET_SIZE(o) == n ? PySequence_Fast_ITEMS(o) : nullptr;
 }
 
+// An entry point from its address.
 template <typename T>
-T entry(PyObject* o) {
-  return reinterpret_cast<T>(PyLong_AsVoidPtr(o));
+bool entry_of(PyObject* o, T* entry) {
+  if (!PyLong_CheckExact(o)) return false;
+  *entry = reinterpret_cast<T>(PyLong_AsVoidPtr(o));
+  return *entry || !PyErr_Occurred();
 }
 
 // Runs `body`, which returns a status or -1; what throws (a tensor without memory, for one) is left to the general path.
@@ -84,12 +87,16 @@ PyObject* guarded(F body) {
   return PyLong_FromLong(st);
 }
 
-#define CALL(expr)               \
-  int st;                        \
-  Py_BEGIN_ALLOW_THREADS         \
-  st = (expr);                   \
-  Py_END_ALLOW_THREADS           \
-  return st
+// The call itself, without the interpreter's lock; its arguments are evaluated with it.
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <typename... P, typename... A>
+int call(int (*entry)(P...), A... args) {
+  Unlocked u;
+  return entry(args...);
+}
 
 inline const float* f(const Arg& a) { return static_cast<const float*>(a.data); }
 inline float* out(const Arg& a) { return static_cast<float*>(a.data); }
@@ -102,7 +109,9 @@ PyObject* call_tbmm(PyObject*, PyObject* const* v, Py_ssize_t n) {
     if (n != 5 || !take(v[1], 3, &X) || !take(v[2], 3, &Y) || !take(v[3], 3, &Z) || !stream_of(v[4], &s)) return -1;
     const int64_t B = X.size[0], N = X.size[1], K = X.size[2], M = Y.size[1];
     if (Y.size[0] != B || Y.size[2] != K || Z.size[0] != B || Z.size[1] != N || Z.size[2] != M) return -1;
-    CALL(entry<tbmm_t>(v[0])(f(X), f(Y), out(Z), B, N, M, K, s));
+    tbmm_t entry;
+    if (!entry_of(v[0], &entry)) return -1;
+    return call(entry, f(X), f(Y), out(Z), B, N, M, K, s);
   });
 }
 
@@ -114,7 +123,9 @@ PyObject* call_tbmm_ws(PyObject*, PyObject* const* v, Py_ssize_t n) {
     if (n != 6 || !take(v[1], 3, &X) || !take(v[2], 3, &Y) || !take(v[3], 3, &Z) || !take(v[4], c10::kByte, 1, &W) || !stream_of(v[5], &s)) return -1;
     const int64_t B = X.size[0], N = X.size[1], K = X.size[2], M = Y.size[1];
     if (Y.size[0] != B || Y.size[2] != K || Z.size[0] != B || Z.size[1] != N || Z.size[2] != M) return -1;
-    CALL(entry<tbmm_ws_t>(v[0])(f(X), f(Y), out(Z), B, N, M, K, W.data, (size_t)W.size[0], s));
+    tbmm_ws_t entry;
+    if (!entry_of(v[0], &entry)) return -1;
+    return call(entry, f(X), f(Y), out(Z), B, N, M, K, W.data, (size_t)W.size[0], s);
   });
 }
 
@@ -143,7 +154,9 @@ PyObject* call_mlp(PyObject*, PyObject* const* v, Py_ssize_t n) {
     }
     if ((v[5] != Py_None && !take(v[5], c10::kByte, 1, &ws)) || !stream_of(v[6], &s)) return -1;
     const size_t bytes = ws.size ? (size_t)ws.size[0] : 0;
-    CALL(entry<mlp_t>(v[0])(f(I), batch, (int32_t)layers, dims, Wp, bp, Op, ws.data, bytes, s));
+    mlp_t entry;
+    if (!entry_of(v[0], &entry)) return -1;
+    return call(entry, f(I), batch, (int32_t)layers, dims, Wp, bp, Op, ws.data, bytes, s);
   });
 }
 
@@ -157,7 +170,9 @@ PyObject* call_gconv(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int64_t N = I.size[0], G = I.size[1], C = I.size[2], H = I.size[3], Wd = I.size[4], F = W.size[1], KH = W.size[3], KW = W.size[4];
     if (W.size[0] != G || W.size[2] != C || (b.size && b.size[0] != G * F)) return -1;
     if (O.size[0] != N || O.size[1] != G || O.size[2] != F || O.size[3] != H - KH + 1 || O.size[4] != Wd - KW + 1) return -1;
-    CALL(entry<gconv_t>(v[0])(f(I), f(W), f(b), out(O), N, G, C, F, H, Wd, KH, KW, s));
+    gconv_t entry;
+    if (!entry_of(v[0], &entry)) return -1;
+    return call(entry, f(I), f(W), f(b), out(O), N, G, C, F, H, Wd, KH, KW, s);
   });
 }
 
@@ -169,7 +184,9 @@ PyObject* call_kron(PyObject*, PyObject* const* v, Py_ssize_t n) {
     if (n != 6 || !take(v[1], 2, &W1) || !take(v[2], 2, &W2) || !take(v[3], 3, &X) || !take(v[4], 3, &Y) || !stream_of(v[5], &s)) return -1;
     const int64_t I = W1.size[0], K = W1.size[1], J = W2.size[0], L = W2.size[1], B = X.size[0];
     if (X.size[1] != K || X.size[2] != L || Y.size[0] != B || Y.size[1] != I || Y.size[2] != J) return -1;
-    CALL(entry<kron_t>(v[0])(f(W1), f(W2), f(X), out(Y), B, I, K, J, L, s));
+    kron_t entry;
+    if (!entry_of(v[0], &entry)) return -1;
+    return call(entry, f(W1), f(W2), f(X), out(Y), B, I, K, J, L, s);
   });
 }
 
@@ -185,7 +202,9 @@ PyObject* call_sconv(PyObject*, PyObject* const* v, Py_ssize_t n) {
     const int64_t N = I.size[0], C = I.size[1], H = I.size[2], Wd = I.size[3], F = W.size[0], KH = W.size[2], KW = W.size[3];
     if (W.size[1] != C || (b.size && b.size[0] != F) || sh < 1 || sw < 1 || KH < 1 || KH > H || KW < 1 || KW > Wd) return -1;
     if (O.size[0] != N || O.size[1] != F || O.size[2] != (H - KH) / sh + 1 || O.size[3] != (Wd - KW) / sw + 1) return -1;
-    CALL(entry<sconv_t>(v[0])(f(I), f(W), f(b), out(O), N, C, F, H, Wd, KH, KW, sh, sw, s));
+    sconv_t entry;
+    if (!entry_of(v[0], &entry)) return -1;
+    return call(entry, f(I), f(W), f(b), out(O), N, C, F, H, Wd, KH, KW, sh, sw, s);
   });
 }
 
@@ -217,7 +236,9 @@ PyObject* call_lut(PyObject*, PyObject* const* v, Py_ssize_t n) {
       L[t] = x.size[1];
     }
     if (!stream_of(v[4], &s)) return -1;
-    CALL(entry<lut_t>(v[0])((int32_t)tables, Tp, Xp, Op, E, L, D, B, s));
+    lut_t entry;
+    if (!entry_of(v[0], &entry)) return -1;
+    return call(entry, (int32_t)tables, Tp, Xp, Op, E, L, D, B, s);
   });
 }
 
