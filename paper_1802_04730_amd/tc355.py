@@ -15,13 +15,14 @@ import importlib.util
 import os
 import shutil
 import struct
+import warnings
 
 import torch
 
 from . import build as _build
 
 _LIB = None
-_FAST = None  # csrc/fast_call.cpp, from the moment the library is loaded; None where it cannot be built
+_FAST = None  # csrc/fast_call.cpp, from the moment the library is loaded; None where it cannot be built or loaded
 _AT = {}  # addresses of the entry points
 
 TC_OK = 0
@@ -95,15 +96,21 @@ def lib() -> ctypes.CDLL:
 
 
 def _load_fast(L) -> None:
-    """The native calls, built first if they are missing or older than their source (and a compiler is there)."""
+    """The native calls, built first if they are missing or older than their source (and a compiler is there).  The general path
+    does all that they do: what keeps them from being built or loaded here costs host time and nothing else."""
     global _FAST
-    if _build.fast_is_stale():
-        if shutil.which(os.environ.get("CXX", "g++")) is None:
-            return
-        _build.build_fast()
-    spec = importlib.util.spec_from_file_location("_fast", _build.FAST)
-    fast = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(fast)
+    try:
+        if _build.fast_is_stale():
+            if shutil.which(os.environ.get("CXX", "g++")) is None:
+                return
+            _build.build_fast()
+        spec = importlib.util.spec_from_file_location("_fast", _build.FAST)
+        fast = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(fast)
+    except (RuntimeError, OSError, ImportError) as e:
+        warnings.warn("the binding's native calls are not available: calls go through ctypes, some microseconds slower (%s)" % e,
+                      RuntimeWarning, stacklevel=3)
+        return
     for name in ("tc_tbmm", "tc_tbmm_ws", "tc_mlp_fcrelu", "tc_group_conv", "tc_kron", "tc_sconv2d", "tc_lut"):
         _AT[name] = ctypes.cast(getattr(L, name), ctypes.c_void_p).value
     _FAST = fast
