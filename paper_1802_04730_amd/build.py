@@ -7,6 +7,7 @@ import os
 import subprocess
 import sys
 import sysconfig
+import threading
 import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -75,8 +76,25 @@ def fast_is_stale() -> bool:
         return f.read().strip() != fast_hash()
 
 
-def torch_module_command(source: str, out: str) -> list:
-    """g++ line of a Python module that uses torch's headers."""
+def _compile(cmd: list, out: str, compiler: str, verbose: bool) -> str:
+    """Run a compiler line that ends before its output's name and write `out` as a whole: another process may be loading it, or
+    making it too.  Returns what the compiler said."""
+    if verbose:
+        print(" ".join(cmd + ["-o", out]), flush=True)
+    part = "%s.%d.%d.part" % (out, os.getpid(), threading.get_ident())
+    try:
+        r = subprocess.run(cmd + ["-o", part], capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(compiler + " failed:\n" + r.stdout + r.stderr)
+        os.replace(part, out)
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
+    return r.stderr
+
+
+def torch_module_command(source: str) -> list:
+    """g++ line, but for the output's name, of a Python module that uses torch's headers."""
     import torch
 
     t = os.path.dirname(torch.__file__)
@@ -84,18 +102,13 @@ def torch_module_command(source: str, out: str) -> list:
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
             "-I" + os.path.join(t, "include"), "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"),
-            "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"], "-o", out, source,
+            "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"], source,
             "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
 
 
 def build_fast(verbose: bool = False) -> str:
     """Compile the binding's native calls against torch's headers; returns the module's path."""
-    cmd = torch_module_command(FAST_SOURCE, FAST)
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("g++ failed:\n" + r.stdout + r.stderr)
+    _compile(torch_module_command(FAST_SOURCE), FAST, "g++", verbose)
     with open(FAST_STAMP, "w") as f:
         f.write(fast_hash() + "\n")
     return FAST
@@ -106,18 +119,12 @@ def build(force: bool = True, verbose: bool = False) -> str:
 
     _fast.so only saves host time: where it cannot be built, that is a warning."""
     if force or is_stale():
-        hipcc = hipcc_path()
-        cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB] + sources()
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        if r.returncode != 0:
-            raise RuntimeError("hipcc failed:\n" + r.stdout + r.stderr)
+        said = _compile([hipcc_path()] + HIPCC_FLAGS + sources(), LIB, "hipcc", verbose)
         with open(STAMP, "w") as f:
             f.write(source_hash() + "\n")
         if verbose:
             noise = "is not a recognized feature for this target"
-            for line in r.stderr.splitlines():
+            for line in said.splitlines():
                 if noise not in line:
                     print(line)
     if force or fast_is_stale():

@@ -70,3 +70,20 @@ def test_the_library_is_built_without_them(fresh, monkeypatch):
     with pytest.warns(RuntimeWarning, match="_fast.so"):
         assert tcbuild.build(force=True) == str(fresh / "lib.so")
     assert (fresh / "lib.so").read_text() == "built\n" and not tcbuild.is_stale() and tcbuild.fast_is_stale()
+
+
+def test_a_module_is_written_as_a_whole(fresh, monkeypatch):
+    """What another process may be loading is replaced, never written into; a compiler that fails half-way leaves it alone."""
+    out = fresh / "_fast.so"
+    out.write_text("the one before")
+    to_output = 'while [ "$1" != -o ]; do shift; done\necho half > "$2"\n'
+    monkeypatch.setenv("CXX", script(fresh / "cxx", to_output + "exit 1\n"))
+    with pytest.raises(RuntimeError):
+        tcbuild.build_fast()
+    assert out.read_text() == "the one before" and tcbuild.fast_is_stale()
+    monkeypatch.setenv("CXX", script(fresh / "cxx", to_output + 'echo whole > "$2"\n'))
+    with open(out) as before:
+        tcbuild.build_fast()
+        assert before.read() == "the one before"
+    assert out.read_text() == "whole\n" and not tcbuild.fast_is_stale()
+    assert sorted(p.name for p in fresh.iterdir()) == ["_fast.so", "_fast.so.srchash", "cxx"]

@@ -46,7 +46,7 @@ def host(tmp_path_factory):
     from paper_1802_04730_amd import build
 
     out = str(tmp_path_factory.mktemp("fast") / "fast_call_host.so")
-    subprocess.run(build.torch_module_command(os.path.join(ROOT, "tests", "fast_call_host.cpp"), out), check=True)
+    subprocess.run(build.torch_module_command(os.path.join(ROOT, "tests", "fast_call_host.cpp")) + ["-o", out], check=True)
     return out
 
 
