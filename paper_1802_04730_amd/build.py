@@ -17,6 +17,7 @@ STAMP = LIB + ".srchash"  # hash of the sources the library was built from
 FAST = os.path.join(HERE, "_fast.so")  # the binding's calls in native code
 FAST_SOURCE = os.path.join(CSRC, "fast_call.cpp")
 FAST_STAMP = FAST + ".srchash"
+FAST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -60,10 +61,10 @@ def have_hipcc() -> bool:
 
 
 def fast_hash() -> str:
-    """Hash of what _fast.so is compiled from: its source, and the interpreter and torch whose headers it uses."""
+    """Hash of what _fast.so is compiled from: its source, the flags, and the interpreter and torch whose headers it uses."""
     import torch
 
-    h = hashlib.sha256(("%s %s" % (sys.version, torch.__version__)).encode())
+    h = hashlib.sha256(("%s %s %s" % (sys.version, torch.__version__, " ".join(FAST_FLAGS))).encode())
     with open(FAST_SOURCE, "rb") as f:
         h.update(f.read())
     return h.hexdigest()
@@ -99,7 +100,7 @@ def torch_module_command(source: str) -> list:
 
     t = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(hipcc_path()))
-    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    return [os.environ.get("CXX", "g++")] + FAST_FLAGS + [
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
             "-I" + os.path.join(t, "include"), "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"),
             "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"], source,
@@ -108,9 +109,10 @@ def torch_module_command(source: str) -> list:
 
 def build_fast(verbose: bool = False) -> str:
     """Compile the binding's native calls against torch's headers; returns the module's path."""
+    made_from = fast_hash()  # (of the source as the compiler finds it)
     _compile(torch_module_command(FAST_SOURCE), FAST, "g++", verbose)
     with open(FAST_STAMP, "w") as f:
-        f.write(fast_hash() + "\n")
+        f.write(made_from + "\n")
     return FAST
 
 
@@ -119,9 +121,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
 
     _fast.so only saves host time: where it cannot be built, that is a warning."""
     if force or is_stale():
+        made_from = source_hash()  # (of the sources as the compiler finds them)
         said = _compile([hipcc_path()] + HIPCC_FLAGS + sources(), LIB, "hipcc", verbose)
         with open(STAMP, "w") as f:
-            f.write(source_hash() + "\n")
+            f.write(made_from + "\n")
         if verbose:
             noise = "is not a recognized feature for this target"
             for line in said.splitlines():

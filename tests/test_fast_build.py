@@ -87,3 +87,19 @@ def test_a_module_is_written_as_a_whole(fresh, monkeypatch):
         assert before.read() == "the one before"
     assert out.read_text() == "whole\n" and not tcbuild.fast_is_stale()
     assert sorted(p.name for p in fresh.iterdir()) == ["_fast.so", "_fast.so.srchash", "cxx"]
+
+
+def test_a_stamp_names_what_the_compiler_read(fresh, monkeypatch):
+    """Other flags, or a source that is edited while it compiles, leave the module stale."""
+    source = fresh / "fast_call.cpp"
+    source.write_text("// one\n")
+    monkeypatch.setattr(tcbuild, "FAST_SOURCE", str(source))
+    compiler = 'while [ "$1" != -o ]; do shift; done\necho module > "$2"\n'
+    monkeypatch.setenv("CXX", script(fresh / "cxx", compiler + "echo // two > %s\n" % source))
+    tcbuild.build_fast()
+    assert tcbuild.fast_is_stale()
+    monkeypatch.setenv("CXX", script(fresh / "cxx", compiler))
+    tcbuild.build_fast()
+    assert not tcbuild.fast_is_stale()
+    monkeypatch.setattr(tcbuild, "FAST_FLAGS", tcbuild.FAST_FLAGS + ["-g"])
+    assert tcbuild.fast_is_stale()
