@@ -26,12 +26,12 @@
 // over a wavefront is kept scalar, and few loads are in flight while accumulators live.  A read-ahead by a whole group
 // of 16 k was slower for that reason (9.9 -> 13 us at the first shape, with spills); so were five column tiles at two workgroups.
 #pragma once
+#include "kron_tile_plan.hpp"
 #include "tc355_device.hpp"
 
 namespace tc355 {
 
-constexpr int KT_WAVES = 8;
-constexpr int KT_THREADS = KT_WAVES * WAVE;
+static_assert(KT_WAVE == WAVE, "lanes of a wavefront");
 constexpr int KT_BATCH = 4;  // first loads of each operand, per thread
 constexpr int KT_REST = 12;  // loads in flight per thread behind them
 

@@ -197,33 +197,12 @@ tc_status launch_gemm_direct(GemmDirectArgs d, hipStream_t s) {
   return st;
 }
 
-// Which tiles and how many wavefronts: the least of five estimates in us, each
-//   t0 + step * (steps of 16 k of one wavefront) + (workgroups of the fullest compute unit) * (mfma * steps * tiles + wg)
-//      + load * (1 KiB pieces per compute unit),
-// with constants fitted to every variant's time at 650 sizes (errors of 4-6 %): the variant taken is 0.4 % from the best one
-// on average, 11 % at worst ((128,4381,3140) 81.6, 73.5 with 1 x 2 tiles).  16 wavefronts only where no compute unit has two
-// workgroups.
 template <typename TA, bool FC>
 tc_status run_gemm_direct(const GemmArgs& a, int cus, hipStream_t s) {
-  struct Variant { int rt, ct, nw; double t0, step, mfma, wg, load; };
-  static constexpr Variant variants[5] = {{1, 1, 4, 2.1153, 0.1281, 0.0300, 0.2184, 0.0030}, {1, 1, 8, 2.1514, 0.1278, 0.0280, 0.3527, 0.0037},
-                                          {1, 1, 16, 2.7616, 0.1079, 0.0312, 0.0000, 0.0037}, {1, 2, 8, 2.0669, 0.1774, 0.0258, 0.5765, 0.0043},
-                                          {2, 2, 4, 2.2926, 0.2324, 0.0225, 0.7782, 0.0061}};
-  int best = 0;
-  double least = 0.0;
-  for (int v = 0; v < 5; v++) {
-    const Variant& x = variants[v];
-    const int64_t jobs = ceil_div(a.N, 16 * x.rt) * ceil_div(a.M, 16 * x.ct), steps = ceil_div(a.K, 16);
-    if (x.nw == 16 && jobs > cus) continue;
-    const double pieces = x.rt * (sizeof(TA) == 8 ? 2 : 1) + x.ct;
-    const double us = x.t0 + x.step * ceil_div(steps, x.nw) + ceil_div(jobs, cus) * (x.mfma * steps * x.rt * x.ct + x.wg) +
-                      x.load * pieces * steps * ((double)jobs / cus);
-    if (v == 0 || us < least) { best = v; least = us; }
-  }
   GemmDirectArgs d{};
   d.A = a.A; d.Bm = a.Bm; d.bias = a.bias; d.C = a.C; d.C64 = a.C64; d.clear = a.clear;
   d.N = a.N; d.M = a.M; d.K = a.K;
-  switch (best) {
+  switch (choose_gemm_direct(a.N, a.M, a.K, sizeof(TA), cus)) {
     case 0: return launch_gemm_direct<TA, FC, 1, 1, 4>(d, s);
     case 1: return launch_gemm_direct<TA, FC, 1, 1, 8>(d, s);
     case 2: return launch_gemm_direct<TA, FC, 1, 1, 16>(d, s);
@@ -441,92 +420,12 @@ tc_status launch_kron_tile_tj(int tj, const KronTileArgs& a, dim3 grid, int64_t 
   }
 }
 
-struct KronTilePlan {
-  int64_t nb, lsp, itb, iblocks, jblocks, tj, k4, ls, ls1, ls2, xs, lds, groups, occ;
-  bool wide, second;
-  double cost;
-};
-
-// A plan from its free choices, and an estimate of the launch in clocks; false where it does not fit LDS.
-bool plan_kron_tile(int64_t B, int64_t I, int64_t K, int64_t J, int64_t L, int64_t iblocks, int64_t nb, int64_t lsp, bool wide, bool second, int cus, KronTilePlan* p) {
-  const int64_t size = wide ? 8 : 4, ltiles = ceil_div(L, 16);
-  p->nb = nb; p->lsp = lsp; p->wide = wide; p->second = second;
-  p->itb = ceil_div(ceil_div(I, 16), iblocks);
-  p->iblocks = ceil_div(ceil_div(I, 16), p->itb);
-  p->jblocks = ceil_div(ceil_div(J, 16), 8);
-  p->tj = ceil_div(ceil_div(J, 16), p->jblocks);
-  if (p->iblocks * p->jblocks > 65535 || p->itb > 8) return false;
-  p->k4 = ceil_div(K, 4) * 4;
-  // Bank spread of the operand reads: 4 k rows (columns l in the second order) and 16 neighbours of the other index at a time.
-  auto up = [](int64_t n, int64_t rem, int64_t mod) { return n + ((rem - n) % mod + mod) % mod; };
-  p->ls = !second ? up(L, 4, 8) : wide ? up(p->k4, 2, 4) : up(p->k4, 4, 8);
-  p->ls1 = second && wide ? up(p->k4, 2, 4) : up(p->k4, 4, 8);
-  p->ls2 = wide ? up(ceil_div(L, 4) * 4, 2, 4) : up(ceil_div(L, 4) * 4, 4, 8);
-  const int64_t xrows = second ? L : p->k4;
-  if (prod_reaches({nb, xrows, p->ls}, 1 << 16)) return false;
-  const int64_t x = nb * xrows * p->ls + 16;  // (the last row is read up to 15 elements past its end)
-  const int64_t sums = nb * p->itb * (lsp - 1) * p->tj * 4 * WAVE * 8 / size;
-  p->xs = ceil_div(std::max(x, sums), 16) * 16;
-  p->lds = (p->xs + 16 * p->tj * p->ls2 + std::min<int64_t>(16 * p->itb, I) * p->ls1 + 16) * size;  // (operands are read up to 7 elements ahead)
-  if (p->lds > 160 * 1024) return false;
-  p->groups = ceil_div(B, nb);
-  p->occ = std::max<int64_t>(1, std::min<int64_t>(p->tj <= 4 ? 2 : 1, 160 * 1024 / (p->lds + 512)));
-  // What a launch costs in clocks, as far as the choices change it: MFMAs (74 clocks each with what surrounds them, 79 where
-  // operands are widened at the read), staging, the exchange of partial sums.  A wavefront's chain is two tiles' time
-  // while the other half of the workgroup shares its SIMD; `occ` workgroups cover part of each other's staging.  The
-  // constants are fitted to the measured times of 45 shapes at every choice of (iblocks, nb, lsp, wide): the plan taken
-  // is on average 0.3 % from the best one, 2.4 % at worst.
-  const int64_t blocks = p->iblocks * p->jblocks, jobs = nb * p->itb * lsp, per_cu = ceil_div(p->groups * blocks, cus);
-  const double tile = (double)ceil_div(ltiles, lsp) * (p->k4 / 4 + 4 * p->tj) * (wide ? 74.0 : 79.0) + 355;
-  const double stage = 2500 + (double)nb * K * L / KT_THREADS * 130 + (lsp > 1 ? 107.0 * lsp * p->tj : 0.0);
-  const int64_t share = std::min(p->occ, per_cu), rest = jobs % KT_WAVES;
-  const double chain = (jobs / KT_WAVES * 2 + (rest > 4 ? 2 : rest > 0 ? 1 : 0)) * tile + stage;
-  p->cost = (double)(std::min<int64_t>(16 * p->itb, I) * K + 16 * p->tj * L) / KT_THREADS * 145 +
-            (double)ceil_div(per_cu, share) * std::max(chain, share * (std::max(jobs / 4.0, 1.0) * tile + 0.72 * stage));
-  return true;
-}
-
-// The best plan for one order of the two contractions (`second`: the extents come exchanged).
-// More blocks of rows than needed only until one fits and while there are fewer than two workgroups per compute unit, more
-// batch elements per stage only while there is a workgroup for half of them and they fit.  (At most 46 plans, 11 on average,
-// over 200,000 random layers.)
-bool best_kron_plan(int64_t B, int64_t I, int64_t K, int64_t J, int64_t L, bool second, int cus, KronTilePlan* best, bool any) {
-  KronTilePlan pl{};
-  const int64_t tiles_i = ceil_div(I, 16), least = ceil_div(tiles_i, 8), jblocks = ceil_div(ceil_div(J, 16), 8);
-  bool here = false;
-  for (int64_t itb = ceil_div(tiles_i, least); itb >= 1; itb--) {
-    const int64_t iblocks = ceil_div(tiles_i, itb);
-    if (here && (iblocks >= least + 8 || B * (iblocks - 1) * jblocks >= 2 * cus)) break;
-    if (ceil_div(tiles_i, iblocks) != itb) continue;  // (the same blocks as with fewer tiles each)
-    bool fits = true;
-    for (int64_t nb = 1; fits && nb <= 8 && (nb == 1 || (nb <= B && ceil_div(B, nb) * iblocks * jblocks >= cus / 2)); nb++) {
-      fits = false;
-      for (int64_t lsp = 1; lsp <= 8 && (lsp == 1 || (nb * itb * lsp <= KT_WAVES && lsp <= ceil_div(L, 16))); lsp *= 2)
-        for (int wide = 1; wide >= 0; wide--)
-          if (plan_kron_tile(B, I, K, J, L, iblocks, nb, lsp, wide, second, cus, &pl)) {
-            fits = here = true;
-            if (!any || pl.cost < best->cost) { *best = pl; any = true; }
-          }
-    }
-  }
-  return any;
-}
-
 // Returns false where no block of 16 rows, of columns and one batch element fit LDS.
 bool try_kron_tile(const float* W1, const float* W2, const float* X, float* Y, int64_t B, int64_t I, int64_t K, int64_t J, int64_t L,
                    hipStream_t s, tc_status* st) {
   const int cus = device_cus();
-  if (cus <= 0 || K < 2 || L < 2 || K > 40000 || L > 40000) return false;
   KronTilePlan best{};
-  bool any = best_kron_plan(B, I, K, J, L, false, cus, &best, false);
-  // The other order of the contractions where the estimate is 10 % lower: at 700 layers measured both ways no layer was more
-  // than 3 % slower than in the first order with that margin (24 without it), for 0.1 % of the gain.
-  KronTilePlan other{};
-  if (best_kron_plan(B, J, L, I, K, true, cus, &other, false) && (!any || 1.1 * other.cost < best.cost)) {
-    best = other;
-    any = true;
-  }
-  if (!any) return false;
+  if (!choose_kron_tile(B, I, K, J, L, cus, &best)) return false;
   if (best.second) {
     std::swap(W1, W2);
     std::swap(I, J);
@@ -540,8 +439,7 @@ bool try_kron_tile(const float* W1, const float* W2, const float* X, float* Y, i
   a.k4 = (int)best.k4; a.ls = (int)best.ls; a.ls1 = (int)best.ls1; a.ls2 = (int)best.ls2; a.xs = (int)best.xs;
   auto magic = [](int64_t d) { return (unsigned)(((1ll << 32) + d - 1) / d); };  // dividends and divisors below 2^16
   a.l_magic = magic(L); a.k_magic = magic(K);
-  const int64_t blocks = best.iblocks * best.jblocks;
-  const dim3 grid((unsigned)std::min<int64_t>(best.groups, std::max<int64_t>(1, best.occ * cus / blocks)), (unsigned)blocks);
+  const dim3 grid((unsigned)kron_tile_workgroups(best, cus), (unsigned)(best.iblocks * best.jblocks));
   const int tj = (int)best.tj;
   if (best.second) *st = best.wide ? launch_kron_tile_tj<double, true>(tj, a, grid, best.lds, s) : launch_kron_tile_tj<float, true>(tj, a, grid, best.lds, s);
   else *st = best.wide ? launch_kron_tile_tj<double, false>(tj, a, grid, best.lds, s) : launch_kron_tile_tj<float, false>(tj, a, grid, best.lds, s);

@@ -13,18 +13,32 @@ pytestmark = pytest.mark.gpu
 TIGHT = 2.5e-7
 GUARD = 64
 
-# (B, I, K, J, L): I and L large against K and J
-SHAPES = [
-    (40, 100, 16, 8, 100),    # one tile of k, eight row tiles of the result in two accumulator sets
-    (300, 64, 17, 16, 96),    # one row of k in the second tile; whole groups of l
+# (B, I, K, J, L): I and L large against K and J.  tests/test_variant_plans.py holds them to what is said here.
+SECOND = [
+    (300, 64, 17, 16, 96),    # one row of k in the second tile; whole groups of l; two wavefronts per tile
     (300, 65, 31, 17, 95),    # partial everything; one column of the second tile of j
-    (7, 33, 5, 3, 131),       # a tile of 5 k; l in 8 groups and a partial one of 3
-    (3, 128, 33, 9, 66),      # eight row tiles; three tiles of k: a pair and one
-    (2, 140, 20, 33, 90),     # two blocks of rows
     (2100, 40, 9, 10, 97),    # several batch elements per stage, the last stage with fewer
-    (1, 96, 64, 16, 200),     # one batch element: the tiles of k are split over wavefronts
-    (2, 120, 10, 40, 1000),   # fp32 in LDS
+    (2, 120, 10, 40, 1000),   # fp32 in LDS, eight accumulators
+    (1, 29, 4, 61, 85),       # one batch element; a tile of 4 k; l in 5 groups and a partial one of 5; blocks of rows
+    (1, 42, 3, 73, 56),       # a tile of 3 k
+    (300, 41, 40, 25, 23),    # three tiles of k: a pair and one
+    (1, 30, 35, 45, 38),      # three tiles of k split over two wavefronts
+    (1, 24, 31, 21, 43),      # two tiles of k split over two wavefronts, the second one partial
+    (1, 150, 9, 69, 22),      # two blocks of columns of the result, five of its rows
+    (253, 153, 19, 28, 22),   # two blocks of columns, two batch elements per stage, the last stage with one
+    (523, 22, 65, 15, 226),   # partial sums where X lay, and then X again: six workgroups take two stages; fp32
+    (1181, 24, 90, 5, 83),    # the same in fp64, two and three stages
+    (258, 19, 110, 47, 282),  # the same with four wavefronts per tile, blocks of rows, fp32
 ]
+# ... and where the first one goes first all the same
+FIRST = [
+    (40, 100, 16, 8, 100),
+    (7, 33, 5, 3, 131),
+    (3, 128, 33, 9, 66),
+    (2, 140, 20, 33, 90),
+    (1, 96, 64, 16, 200),
+]
+POISONED = [(300, 65, 31, 17, 95), (700, 18, 37, 12, 61), (300, 151, 17, 4, 18)]  # (partial tiles of k, second factor first)
 
 
 def both(shape, poison=False):
@@ -46,7 +60,7 @@ def both(shape, poison=False):
     return Y.cpu().numpy(), oracle.kron(W1, W2, X)
 
 
-@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("shape", SECOND + FIRST)
 def test_kron_second_factor_first(shape, oracle_threads):
     got, ref = both(shape)
     err = parity_error(got.astype(np.float64), ref)
@@ -54,7 +68,7 @@ def test_kron_second_factor_first(shape, oracle_threads):
     assert err <= TIGHT
 
 
-@pytest.mark.parametrize("shape", [SHAPES[2], SHAPES[3]])
+@pytest.mark.parametrize("shape", POISONED)
 def test_kron_second_factor_first_keeps_infinities_apart(shape, oracle_threads):
     got, ref = both(shape, poison=True)
     finite = np.isfinite(ref)
