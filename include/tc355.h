@@ -280,7 +280,8 @@ tc_status tc_mlp_fcrelu_static(const float *I, int64_t batch, int32_t n_layers,
  * int8 kernel of tc_sconv2d with stride 1, one group after the other in one
  * launch: its arithmetic (blocks of 128 taps, a scale per filter and per
  * output pixel in every block, 13 digit products; TC_INT8_TEN: 10), its
- * limits and its Inf/NaN behaviour are described there.
+ * limits and its Inf/NaN behaviour are described there, and for G = 1 and F at
+ * least 64 the long reductions on few pixels that take fp64 instead.
  */
 tc_status tc_group_conv(const float *I, const float *W1, const float *bias,
                         float *O, int64_t N, int64_t G, int64_t C, int64_t F,
@@ -300,8 +301,18 @@ tc_status tc_group_conv_infer(int64_t H, int64_t W, int64_t KH, int64_t KW,
  * Section 3):
  *     Y(b,i,j) +=! W1(i,k) * W2(j,l) * X(b,k,l)
  * W1: [I,K]   W2: [J,L]   X: [B,K,L]   Y: [B,I,J].
- * Evaluated as two chained contractions, T(b,i,l) = sum_k W1(i,k) X(b,k,l)
- * then Y(b,i,j) = sum_l T(b,i,l) W2(j,l); T stays on chip in fp64.
+ * Evaluated as two chained contractions, either
+ *     T(b,i,l) = sum_k W1(i,k) X(b,k,l), then Y(b,i,j) = sum_l T(b,i,l) W2(j,l)
+ * or, where that is estimated to be 10 % cheaper (I and L large against K and
+ * J),
+ *     T(b,k,j) = sum_l X(b,k,l) W2(j,l), then Y(b,i,j) = sum_k W1(i,k) T(b,k,j);
+ * T stays on chip in fp64.  All extents, B among them, and the device decide.
+ * For finite sums both orders give the exact result rounded to fp32 once, up to
+ * fp64 rounding: the last bit of an element may differ between batch sizes.
+ * Inf or NaN: the factor that goes first meets the elements of X one by one,
+ * so that an Inf in it gives NaN where it meets a zero or both signs; the other
+ * factor meets their sums T only, so that an Inf in it gives an Inf where the
+ * sum is not zero.
  */
 tc_status tc_kron(const float *W1, const float *W2, const float *X, float *Y,
                   int64_t B, int64_t I, int64_t K, int64_t J, int64_t L,
@@ -319,9 +330,14 @@ tc_status tc_kron(const float *W1, const float *W2, const float *X, float *Y,
  * products and sums, one rounding per output -- except for F a multiple of 32
  * with C*KH*KW a multiple of 4, at least 256 and at most about 17,000 (I below
  * 2^30 elements, O below 2^31), which run on the int8 matrix core by the scheme of
- * tc_tbmm: the reduction index (c,kh,kw), in W's order, is cut into blocks of
- * 128 (the last one filled with zeros); in every block each filter and each
- * output pixel's taps are scaled to 0x7F7F7F7E by their own largest magnitude,
+ * tc_tbmm, unless the reduction is long and the pixels are few: with more than
+ * 1152 taps and at least 16 output pixels (N*OH*OW) the fp64 kernels take what
+ * they are estimated to do in 10 % less time, by all extents, N among them, and
+ * the device, so that a layer may change its arithmetic with the batch
+ * (TC_INT8_TEN and TC_INT8_THIRTEEN ask for int8 whatever the estimate).  On
+ * int8 the reduction index (c,kh,kw), in W's order, is cut into blocks of 128
+ * (the last one filled with zeros); in every block each filter and each output
+ * pixel's taps are scaled to 0x7F7F7F7E by their own largest magnitude,
  * rounded to a 32-bit integer and cut into four signed 8-bit digits; the 13
  * digit products of weight 256^2 and above are summed exactly in int32, scaled
  * back and added over the blocks in fp64; bias added in fp64, one rounding to

@@ -348,7 +348,7 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_kernel(GemmI8Args p) {
   }
 }
 
-// The same product with X sliced beforehand.  Per block a SIMD has 104 MFMAs of each of its two wavefronts and about 280 vector
+// The same product with X sliced beforehand.  Per block a SIMD has 104 MFMAs of each of its two wavefronts and 286 vector
 // instructions (slicing Y, scaling the sums) to issue, 2.5 us at 2.4 GHz; the first form of this kernel, which staged X's
 // records through registers and one LDS buffer, took 4.0: 40 operand reads and 16 writes per wavefront, and two barriers at
 // which all wavefronts changed between a phase for the vector ALU and one for the matrix core.  Here X never enters LDS: its
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_kernel(GemmI8Args p) {
 // to two buffers of Y and one barrier per block: block t + 1 is sliced into one of them before block t is contracted from
 // the other.  A wavefront contracts all 64 rows of Y against 16 rows of X, which a compute unit then loads once (32 x 32 per
 // wavefront loads them twice: 115 us).
-// (M,K,N) = (128,4096,16384): 128-131 -> 107 us and 5 for slicing X.  Taken back: half of the wavefronts slicing behind their
+// (M,K,N) = (128,4096,16384): 128-131 -> 107 us and 6.9 for slicing X.  Taken back: half of the wavefronts slicing behind their
 // contraction instead of before (109; with both orders as loops of their own it spills: 145).
 constexpr int GP_PLANE = GI8_TM * GI8_RS;                     // a digit plane of Y
 constexpr int GP_BUF = 4 * GP_PLANE + GI8_TM * 8;             // four of them and the rows' inverse scales

@@ -213,7 +213,8 @@ tc_status run_gemm_direct(const GemmArgs& a, int cus, hipStream_t s) {
 
 // Lines between the kernels for one plain product with a short reduction, in clocks of a compute unit.  64 x 64 blocks: 3200
 // per chunk of 32, one block after the other.  A split reduction over chunks of 128 (16 x 16 tiles): 827 per chunk and 750 per
-// tile where two workgroups share a compute unit, 990 and 900 for one alone.
+// tile where two workgroups share a compute unit, 990 and 900 for one alone.  That is the kernel that gemm_direct.hpp took over
+// from: the lines between the other two were drawn with it in the middle and have not been drawn again.
 double gemm_tile_clocks(const GemmArgs& a, int cus) {
   if (a.N < 48 || a.M < 48 || (a.K % 4 != 0 && a.K < GT_KC)) return 1e30;
   return (double)ceil_div(ceil_div(a.N, GT_BM) * ceil_div(a.M, GT_BN), cus) * ceil_div(a.K, GT_KC) * 3200;
@@ -802,9 +803,11 @@ bool tbmm_i8_shape(int64_t B, int64_t N, int64_t M, int64_t K) {
          (M / GI8_TM) * (N / GI8_TN) * B >= 128;
 }
 
-// Does slicing X once, in a kernel of its own, pay?  The extra launch costs 2-3 us; what it saves grows with the number
-// of workgroups that would each slice X (M / 64) and with the length of the reduction.  Measured: 138 -> 128 us at
-// (B,N,M,K) = (1,128,16384,4096), 19.8 -> 22.3 us at (2,256,4096,512).
+// Does slicing X once, in a kernel of its own, pay?  The extra launch costs 5-7 us; what it saves grows with the number
+// of workgroups that would each slice X (M / 64) and with the length of the reduction.  Measured, every workgroup / once, us:
+// (B,N,M,K) = (1,128,16384,4096) 133.8 / 109.3, (1,128,8192,2048) 64.0 / 50.8, (1,128,16384,512) 21.1 / 22.1, (2,256,4096,512)
+// 20.3 / 22.1.  The line was drawn where an earlier form of the contraction gained less, and leaves some out from K = 1024 on:
+// (1,128,16384,1024) 37.7 / 34.3, (1,256,4096,2048) 64.2 / 51.7, (1,512,2048,4096) 122.6 / 93.6.
 bool tbmm_presliced_pays(int64_t B, int64_t N, int64_t M, int64_t K) {
   return M / GI8_TM >= 128 && K / GI8_KB >= 16 && B * (N / GI8_TN) <= 65535 && ceil_div(K, GI8_KB) <= kMaxGrid;
 }
@@ -1022,7 +1025,9 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
   const int cus = device_cus();
   // Small batches with reductions of at most 1024: one workgroup per compute unit, every XCD's workgroups own an eighth
   // of the column tiles of every layer (mlp_rows.hpp).  Option TC_OPT_MLP_KERNEL = TC_MLP_TILES keeps the tile-stream
-  // kernel below.
+  // kernel below.  (The line was drawn against one launch per layer as it was before gemm_direct.hpp.  Against that, here / one
+  // launch per layer, us: 128 x 1024 -> 1024 -> 512 -> 256 19.8 / 18.1, 16 rows of it 15.9 / 14.3, 128 x 1024 -> 1024 9.0 / 7.6,
+  // 512 x 256 -> 256 -> 128 11.9 / 6.6, 128 x 256 -> 1024 4.8 / 3.7.)
   if (fused && cus >= MR_SHARES) {
     const int64_t G = ceil_div(batch, 16);
     const int64_t nwg = std::min<int64_t>(cus, MR_MAX_WG) / MR_SHARES * MR_SHARES;
@@ -1201,8 +1206,8 @@ int64_t sconv_i8_lds_bytes(int tf, int nt, int64_t blocks) {
 
 // Takes the call if the shape is one the int8 kernel is built for: a multiple of 32 filters, a reduction C * KH * KW
 // that is a multiple of 4 and at least 256 taps (two blocks), operands that 32-bit offsets reach, a table of tap
-// offsets that fits LDS beside the digit planes (about 17,000 taps).  Measured faster than the fp64 kernel from a
-// single 8 x 8 image up.
+// offsets that fits LDS beside the digit planes (about 17,000 taps); long reductions on few pixels go to fp64 all the same
+// (below).
 // a.G groups of a.C channels and a.F filters; fp64_next: what is refused here goes to launch_sconv_fp64.
 bool try_sconv_i8(const SconvI8Args& a, int64_t N, bool fp64_next, hipStream_t s, tc_status* st) {
   if (t_opt.int8 == TC_INT8_OFF) return false;
@@ -1336,7 +1341,7 @@ tc_status tc_group_conv(const float* I, const float* W1, const float* bias, floa
   if (try_gconv_band<16, 3, 3, 58, 8, 2>(a, s, &st)) return took("gconv:band", st);
   if (try_gconv_band<16, 3, 3, 14, 12, 2>(a, s, &st)) return took("gconv:band", st);  // the paper's (32,32,16,16,14,14): the whole image is one band
   if (try_gconv_quad<4, 4, 3, 3, 56, 9, 4, 4>(a, s, &st)) return st;    // the paper's (32,32,4,4,56,56)
-  if (try_gconv_quad<8, 8, 3, 3, 28, 13, 3, 3>(a, s, &st)) return st;    // the paper's (32,32,8,8,28,28): one band
+  if (try_gconv_quad<8, 8, 3, 3, 28, 13, 3, 3>(a, s, &st)) return st;    // the paper's (32,32,8,8,28,28): two bands
   if (try_gconv_quad<4, 4, 3, 3, 58, 8, 4, 4>(a, s, &st)) return st;    // the same two with a border of one pixel
   if (try_gconv_quad<8, 8, 3, 3, 30, 14, 7, 2>(a, s, &st)) return st;
   if (try_gconv_tiny<32, 32, 3, 3, 7, 7>(a, s, &st)) return took("gconv:tiny", st);       // the paper's (32,32,32,32,7,7)

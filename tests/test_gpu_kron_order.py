@@ -74,3 +74,24 @@ def test_kron_second_factor_first_keeps_infinities_apart(shape, oracle_threads):
     finite = np.isfinite(ref)
     assert np.array_equal(np.isfinite(got), finite)
     assert parity_error(got[finite].astype(np.float64), ref[finite]) <= TIGHT
+
+
+@pytest.mark.parametrize("shape", [SECOND[1], FIRST[0]])
+@pytest.mark.parametrize("factor", [1, 2])
+def test_infinity_in_a_factor(shape, factor):
+    """The factor that goes first meets the elements of X one by one (Inf times a zero is NaN), the other one their sums."""
+    from paper_1802_04730_amd import tc355 as tc
+    B, I, K, J, L = shape
+    W = [np.abs(a) + 0.01 for a in inputs.make_kron(*shape, seed=5)]
+    W[factor - 1][0, 0] = np.inf
+    W[2][0, 0, 0] = 0.0
+    W1, W2, X = (torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda() for a in W)
+    Y = torch.empty((B, I, J), device="cuda")
+    tc.tc_kron(W1, W2, X, Y)
+    assert tc.last_path() == "kron:tile"
+    first = 2 if shape in SECOND else 1  # the factor that goes first
+    hit = Y[:, 0, :] if factor == 1 else Y[:, :, 0]  # what reads the infinity
+    assert bool(hit[1:].isposinf().all())
+    assert bool((hit[0].isnan() if factor == first else hit[0].isposinf()).all())
+    rest = Y[:, 1:, :] if factor == 1 else Y[:, :, 1:]
+    assert bool(rest.isfinite().all())
