@@ -3,21 +3,28 @@
 //
 //     Z(b,n,m) = sum_k X(b,n,k) * Y(b,m,k)
 //
-// What bounds it: HBM at large batches (27 x 61 x 35: 18.9 KB and 72 MFMAs per batch element), which the wave-level
-// kernel did not reach because it fetched operands row by row, 4 bytes per lane where K is odd.
-// A job is one batch element, a strip of 16 TN rows of X_b and a strip of 16 TM rows of Y_b, done by one wavefront in its
-// private LDS region, without barriers; the next job's operands travel in registers meanwhile.
-//   * A strip is a contiguous run of memory that may start and end anywhere.  It is fetched as 16-byte pieces from the
-//     16-byte boundary before it (tensors start on one), parked as it comes, and read from its first element on.  The
-//     piece that holds a tensor's last elements is loaded from 4 elements before the end and moved into place: nothing
-//     beyond the tensor is read.
-//   * PAD (K a multiple of 16): 16 rows at such a stride share a few LDS banks, so a spare piece follows every 16.
-//   * Results are laid out in the region and leave as contiguous streams: 16-byte pieces of the whole block where the
-//     strip covers all of M (first and last piece element by element where they are shared), else row by row.
-// MFMA roles and the order of m inside a tile are those of tbmm_lds.hpp.
-// Measured, wave-level kernel -> this one: (B,N,M,K) = (4000,27,61,35) 37.1 -> 22.3 us (3.4 TB/s; 18.9 KB per element travel
-// once, 8 % of the MFMA work is padding), (5972,36,47,73) 108 -> 60, (13047,58,14,17) 49 -> 23, (35,55,75,81) 13.5 -> 4.1.
+// What bounds it: HBM at large batches, the launch and one chain load -> MFMAs -> store at small ones, the fp64 matrix core where the
+// matrices approach 100 x 100.
+// A workgroup owns a strip of rows of X_b and a strip of rows of Y_b -- all of both where they are small, several batch elements
+// where they are smaller still -- and its wavefronts share the strips' 16 x 16 tiles out.  The strips are contiguous runs of
+// memory.  They travel straight to LDS (no registers, no LDS writes), every wavefront requests its part, and one barrier later
+// every wavefront reads what it needs.  Nothing is pipelined inside a workgroup: 34-110 registers and the LDS of one strip pair
+// leave room for several workgroups per compute unit, whose loads, MFMAs and stores cover each other.
+//   * 16-byte pieces from the strip's first element on (4-byte alignment is enough), its last 1 .. 3 elements one by one: nothing
+//     beyond a strip is read.
+//   * VEC (K a multiple of 4: rows start on pieces): an operand read is one piece, whose four elements feed four MFMA steps, and
+//     piece p of a strip lies in slot p ^ (p / 16 % 16), so that 16 rows at any such stride fall into different banks.
+//     Otherwise an operand read is one element per lane, and rows at odd or singly even strides spread by themselves.
+//   * Results are laid out in LDS and leave as contiguous streams: 16-byte pieces of the whole block where the strip covers
+//     all of M (first and last piece element by element where they are shared), else row by row.  Where there are few, or the
+//     reduction is long, they leave from the registers instead: two barriers less (4.2 -> 3.6 us at (17,27,55,86)).
+// Against one wavefront per strip pair with a private LDS region and the next strips on their way in registers (us):
+// (B,N,M,K) = (4000,27,61,35) 21.8 -> 17.3 (4.4 TB/s), (5117,46,61,72) 87 -> 52, (904,88,89,77) 43.6 -> 34, (2097,16,28,83)
+// 10.7 -> 8.0, (207,39,49,73) 8.1 -> 5.3, (14,9,68,41) 3.5 -> 3.1; over 268 random shapes 1.14 times as fast, 4 of them 6-10 %
+// slower (4-8 us each: (107,44,44,95) 4.4 -> 4.9).  That one held two strips per wavefront in registers, so a SIMD had two or
+// three wavefronts and little to cover a round trip with.  Taken back: 16 wavefronts per workgroup (within 2 %).
 #pragma once
+#include "tbmm_any_plan.hpp"
 #include "tc355_device.hpp"
 
 namespace tc355 {
@@ -26,177 +33,195 @@ struct TbmmAnyArgs {
   const float* X;  // [B][N][K]
   const float* Y;  // [B][M][K]
   float* Z;        // [B][N][M]
-  int N, M, K;
-  int strips_n, strips_m;
-  int jobs;              // B * strips_n * strips_m  (< 2^31, checked by the host)
-  int wave_lds_units;    // 16-byte units of LDS per wavefront
-  int64_t xtotal, ytotal;  // elements of X and Y, at least 4
+  int B, N, M, K;          // B * strips_n * strips_m < 2^31
+  int strips_n, strips_m;  // strips of 16 TN gn rows of X, of 16 TM gm rows of Y
+  int direct;              // results straight from the registers
+  unsigned first;          // number of the launch's first workgroup
 };
+// workgroup: gm wavefronts in x, gn in y, nb batch elements in z (1 where there are several strips)
 
-// 16-byte pieces of a strip of `rows` rows of K elements at the worst alignment, in load instructions of a wavefront.
-constexpr int tbmm_any_loads(int rows, int kmax) { return (rows * kmax + 6) / 4 / WAVE + 1; }
+// where piece p of a strip lies: 16 pieces in another order per 256 bytes
+template <bool VEC>
+__device__ __forceinline__ int ta_slot(int p) { return VEC ? p ^ ((p >> 4) & 15) : p; }
 
-// Requests one strip: pieces 64*i + lane from element `first` (a multiple of 4) of a tensor of `total` elements on; lanes
-// past the strip's end repeat its last piece (same address, same value, same LDS slot).
-template <int U>
-__device__ __forceinline__ void tbmm_any_fetch(f4 (&r)[U], const float* base, int64_t first, int64_t total, int pieces, int lane) {
-  const char* at = reinterpret_cast<const char*>(base + first);
-  if (first + 4 * (int64_t)pieces <= total) {  // uniform
-#pragma unroll
-    for (int i = 0; i < U; i++) r[i] = *reinterpret_cast<const f4*>(at + 16u * (unsigned)min(i * WAVE + lane, pieces - 1));
-  } else {  // the strip ends with the tensor, inside a piece: that piece is loaded from total - 4
-    const int back = (int)(first + 4 * (int64_t)pieces - total);  // 1 .. 3
-#pragma unroll
-    for (int i = 0; i < U; i++) {
-      const int u = min(i * WAVE + lane, pieces - 1);
-      const bool end = u == pieces - 1;
-      const f4_any t = *reinterpret_cast<const f4_any*>(at + (16 * u - (end ? 4 * back : 0)));
-      f4 v = t;
-      if (end) {
-        v[0] = back == 1 ? t[1] : back == 2 ? t[2] : t[3];
-        v[1] = back == 1 ? t[2] : t[3];
-        v[2] = t[3];
-      }
-      r[i] = v;
-    }
-  }
+// lane l's 16 (4) bytes to lds + 16 l (4 l); a uniform address
+__device__ __forceinline__ void ta_load16(const char* g, unsigned lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(uintptr_t)g,
+                                   (__attribute__((address_space(3))) void*)(uintptr_t)lds, 16, 0, 0);
+}
+__device__ __forceinline__ void ta_load4(const char* g, unsigned lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(uintptr_t)g,
+                                   (__attribute__((address_space(3))) void*)(uintptr_t)lds, 4, 0, 0);
 }
 
-template <int TN, int TM, int KMAX, bool PAD>
-__global__ __launch_bounds__(WG_THREADS, 2) void tbmm_any_kernel(TbmmAnyArgs p) {
-  constexpr int NX = tbmm_any_loads(16 * TN, KMAX), NY = tbmm_any_loads(16 * TM, KMAX);
-  extern __shared__ __attribute__((aligned(16))) char tbmm_smem[];
+template <int TN, int TM, bool VEC>
+__global__ __launch_bounds__(TA_MAX_WAVES * WAVE, TN * TM <= 2 ? 6 : TN * TM <= 5 ? 4 : 3) void tbmm_any_kernel(TbmmAnyArgs p) {
+  extern __shared__ __attribute__((aligned(16))) char ta_lds[];
+  float* ldsf = reinterpret_cast<float*>(ta_lds);
   const int lane = threadIdx.x & (WAVE - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int gm = blockDim.x / WAVE, gn = blockDim.y, nb = blockDim.z, waves = gm * gn * nb;
+  const int wm = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), wn = __builtin_amdgcn_readfirstlane(threadIdx.y),
+            e = __builtin_amdgcn_readfirstlane(threadIdx.z);
+  const int wave = (e * gn + wn) * gm + wm;
   const int r16 = lane & 15, q = lane >> 4;
   const int N = p.N, M = p.M, K = p.K;
-  char* lds = tbmm_smem + (size_t)wave * p.wave_lds_units * 16;
-  float* ldsf = reinterpret_cast<float*>(lds);
-  const unsigned stride = gridDim.x * WAVES_PER_WG;
-  unsigned job = blockIdx.x * WAVES_PER_WG + wave;
-  if (job >= (unsigned)p.jobs) return;  // whole wavefront leaves together; there is no barrier in this kernel
 
-  struct Geo {
-    unsigned b;
-    int n0, m0;
-    int xoff, yoff;  // elements between the 16-byte boundary and the strip
-    int xu, yu;      // 16-byte pieces of the strips
-  };
-  struct Pre {
-    f4 x[NX];
-    f4 y[NY];
-  };
-  auto geometry = [&](unsigned j) {
-    Geo g;
-    const unsigned rest = j / (unsigned)p.strips_m;
-    const int sm = (int)(j - rest * (unsigned)p.strips_m);
-    g.b = rest / (unsigned)p.strips_n;
-    g.n0 = (int)(rest - g.b * (unsigned)p.strips_n) * 16 * TN;
-    g.m0 = sm * 16 * TM;
-    g.xoff = (int)(((g.b * (unsigned)N + (unsigned)g.n0) * (unsigned)K) & 3u);  // (the low bits survive the wrap)
-    g.yoff = (int)(((g.b * (unsigned)M + (unsigned)g.m0) * (unsigned)K) & 3u);
-    g.xu = (g.xoff + min(16 * TN, N - g.n0) * K + 3) >> 2;
-    g.yu = (g.yoff + min(16 * TM, M - g.m0) * K + 3) >> 2;
-    return g;
-  };
-  auto fetch = [&](const Geo& g, Pre& r) {
-    tbmm_any_fetch(r.x, p.X, ((int64_t)g.b * N + g.n0) * K - g.xoff, p.xtotal, g.xu, lane);
-    tbmm_any_fetch(r.y, p.Y, ((int64_t)g.b * M + g.m0) * K - g.yoff, p.ytotal, g.yu, lane);
-  };
-  auto slot = [](int piece) { return PAD ? piece + (piece >> 4) : piece; };
-  auto word = [](int w) { return PAD ? w + ((w >> 6) << 2) : w; };
-  auto park = [&](const Geo& g, const Pre& r) {
-#pragma unroll
-    for (int i = 0; i < NX; i++) *reinterpret_cast<f4*>(lds + 16 * slot(min(i * WAVE + lane, g.xu - 1))) = r.x[i];
-#pragma unroll
-    for (int i = 0; i < NY; i++) *reinterpret_cast<f4*>(lds + 16 * slot(g.xu + min(i * WAVE + lane, g.yu - 1))) = r.y[i];
-  };
-  const int ksteps = (K + 3) >> 2;
-
-  Geo geo = geometry(job);
-  Pre pre;
-  fetch(geo, pre);
-  for (;;) {
-    const Geo g = geo;
-    park(g, pre);
-    const unsigned next = job + stride;
-    const bool more = next < (unsigned)p.jobs && next > job;  // uniform (32-bit wrap: no further job)
-    if (more) {
-      geo = geometry(next);
-      fetch(geo, pre);  // in flight while this job is contracted
-    }
-
-    // LDS word of element k = q of this lane's rows (row clamped into the strip; such rows are never stored)
-    int aidx[TM], bidx[TN];
-#pragma unroll
-    for (int t = 0; t < TM; t++) aidx[t] = 4 * g.xu + g.yoff + min(16 * t + 4 * (r16 & 3) + (r16 >> 2), M - 1 - g.m0) * K + q;
-#pragma unroll
-    for (int t = 0; t < TN; t++) bidx[t] = g.xoff + min(16 * t + r16, N - 1 - g.n0) * K + q;
-
-    d4 acc[TN][TM];
-#pragma unroll
-    for (int tn = 0; tn < TN; tn++)
-#pragma unroll
-      for (int tm = 0; tm < TM; tm++) acc[tn][tm] = d4_zero();
-
-    // One step = 4 reduction elements; in the last one the slots past K are zeroed in BOTH operands: what was read there
-    // is the next row's data, possibly an Inf.
-    auto step = [&](int s, bool last) {
-      float af[TM], bf[TN];
-#pragma unroll
-      for (int t = 0; t < TM; t++) af[t] = ldsf[word(aidx[t] + 4 * s)];
-#pragma unroll
-      for (int t = 0; t < TN; t++) bf[t] = ldsf[word(bidx[t] + 4 * s)];
-      if (last && 4 * s + q >= K) {
-#pragma unroll
-        for (int t = 0; t < TM; t++) af[t] = 0.0f;
-#pragma unroll
-        for (int t = 0; t < TN; t++) bf[t] = 0.0f;
-      }
-#pragma unroll
-      for (int tm = 0; tm < TM; tm++)
-#pragma unroll
-        for (int tn = 0; tn < TN; tn++) acc[tn][tm] = mfma_f64((double)af[tm], (double)bf[tn], acc[tn][tm]);
+  // ---- the workgroup's strips
+  int b0 = (int)(p.first + blockIdx.x), n0 = 0, m0 = 0, ne = 1;
+  if (p.strips_n * p.strips_m == 1) {
+    b0 *= nb;
+    ne = min(nb, p.B - b0);
+  } else {
+    const unsigned rest = (unsigned)b0 / (unsigned)p.strips_m;
+    m0 = (b0 - (int)rest * p.strips_m) * 16 * TM * gm;
+    b0 = (int)(rest / (unsigned)p.strips_n);
+    n0 = ((int)rest - b0 * p.strips_n) * 16 * TN * gn;
+  }
+  const int rows = min(16 * TN * gn, N - n0), cols = min(16 * TM * gm, M - m0);
+  const int xlen = ne * rows * K, ylen = ne * cols * K;  // elements
+  const int xslots = VEC ? ((xlen >> 2) + 15) & ~15 : (xlen + 3) >> 2;
+  const int yslots = VEC ? ((ylen >> 2) + 15) & ~15 : ylen >> 2;
+  {
+    const char* x = reinterpret_cast<const char*>(p.X + ((int64_t)b0 * N + n0) * K);
+    const char* y = reinterpret_cast<const char*>(p.Y + ((int64_t)b0 * M + m0) * K);
+    const unsigned base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)ta_lds;
+    auto copy = [&](const char* src, int slots, int pieces, unsigned at, int g) {  // 64 slots from 64 g on
+      const int s = WAVE * g + lane, u = ta_slot<VEC>(s);
+      if (s < slots && u < pieces) ta_load16(src + 16u * (unsigned)u, at + 1024u * (unsigned)g);
     };
-    for (int s = 0; s < ksteps - 1; s++) step(s, false);
-    step(ksteps - 1, true);
+    const int gx = ((VEC ? xslots : xlen >> 2) + WAVE - 1) / WAVE, gy = (yslots + WAVE - 1) / WAVE;
+    for (int g = wave; g < gx; g += waves) copy(x, VEC ? xslots : xlen >> 2, xlen >> 2, base, g);
+    for (int g = wave; g < gy; g += waves) copy(y, yslots, ylen >> 2, base + 16u * (unsigned)xslots, g);
+    if (!VEC && wave == waves - 1) {  // what a strip holds beyond whole pieces
+      if (lane < (xlen & 3)) ta_load4(x + 16u * (unsigned)(xlen >> 2) + 4 * lane, base + 16u * (unsigned)(xlen >> 2));
+      if (lane < (ylen & 3)) ta_load4(y + 16u * (unsigned)(ylen >> 2) + 4 * lane, base + 16u * (unsigned)(xslots + (ylen >> 2)));
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
 
-    // write-back: Z[b][n0 + 16*tn + r16][m0 + 16*tm + 4*q + v] = acc[tn][tm][v], through the region
-    const int rows = min(16 * TN, N - g.n0), cols = min(16 * TM, M - g.m0);
-    const bool flat = cols == M;  // one contiguous block (uniform)
-    const int64_t z0 = ((int64_t)g.b * N + g.n0) * M + g.m0;
-    const int zoff = flat ? (int)((g.b * (unsigned)N + (unsigned)g.n0) * (unsigned)M & 3u) : 0;
+  // ---- contraction: MFMA rows = rows of X, columns = rows of Y (clamped into the strip; such results are not stored)
+  d4 acc[TN][TM];
 #pragma unroll
-    for (int tn = 0; tn < TN; tn++)
+  for (int i = 0; i < TN; i++)
 #pragma unroll
-      for (int tm = 0; tm < TM; tm++)
+    for (int j = 0; j < TM; j++) acc[i][j] = d4_zero();
+  if (e < ne) {
+    int arow[TN], brow[TM];  // first element of the lane's rows
 #pragma unroll
-        for (int v = 0; v < 4; v++)
-          if (16 * tn + r16 < rows && 16 * tm + 4 * q + v < cols)
-            ldsf[zoff + (16 * tn + r16) * cols + 16 * tm + 4 * q + v] = (float)acc[tn][tm][v];
-    if (flat) {
-      const int end = zoff + rows * M, zu = (end + 3) >> 2;
-      float* zs = p.Z + (z0 - zoff);
-      for (int u = lane; u < zu; u += WAVE) {
-        const f4 v = *reinterpret_cast<const f4*>(lds + 16 * u);
-        if (4 * u >= zoff && 4 * u + 4 <= end) {
-          store_stream(reinterpret_cast<f4*>(zs + 4 * u), v);
-        } else {
+    for (int i = 0; i < TN; i++) arow[i] = (e * rows + min(16 * (TN * wn + i) + r16, rows - 1)) * K;
 #pragma unroll
-          for (int e = 0; e < 4; e++)
-            if (4 * u + e >= zoff && 4 * u + e < end) zs[4 * u + e] = v[e];
+    for (int j = 0; j < TM; j++) brow[j] = (e * cols + min(16 * (TM * wm + j) + r16, cols - 1)) * K;
+    const int yword = 4 * xslots;
+    auto mma = [&](const float (&a)[TN], const float (&b)[TM]) {
+#pragma unroll
+      for (int i = 0; i < TN; i++)
+#pragma unroll
+        for (int j = 0; j < TM; j++) acc[i][j] = mfma_f64((double)a[i], (double)b[j], acc[i][j]);
+    };
+    int k = 0;
+    if constexpr (VEC) {
+      for (; k + 16 <= K; k += 16) {  // lane (r16, q): k + 4 q .. + 3
+        f4 a4[TN], b4[TM];
+#pragma unroll
+        for (int i = 0; i < TN; i++) a4[i] = *reinterpret_cast<const f4*>(ta_lds + 16 * ta_slot<true>(((arow[i] + k) >> 2) + q));
+#pragma unroll
+        for (int j = 0; j < TM; j++) b4[j] = *reinterpret_cast<const f4*>(ta_lds + 16 * (xslots + ta_slot<true>(((brow[j] + k) >> 2) + q)));
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+          float a[TN], b[TM];
+#pragma unroll
+          for (int i = 0; i < TN; i++) a[i] = a4[i][c];
+#pragma unroll
+          for (int j = 0; j < TM; j++) b[j] = b4[j][c];
+          mma(a, b);
         }
       }
     } else {
-      // 16*TM columns (fewer in the last strip): whole rows by 64 lanes, or 2 or 4 rows side by side
-      constexpr int RP = TM == 1 ? 4 : TM == 2 ? 2 : 1;
-      const int r0 = lane / (WAVE / RP), c0 = lane % (WAVE / RP);
-      float* zs = p.Z + z0;
-      for (int r = r0; r < rows; r += RP)
-        for (int c = c0; c < cols; c += WAVE / RP) zs[(int64_t)r * M + c] = ldsf[r * cols + c];
+      for (; k + 16 <= K; k += 16) {
+        float a[4][TN], b[4][TM];
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+#pragma unroll
+          for (int i = 0; i < TN; i++) a[c][i] = ldsf[arow[i] + q + k + 4 * c];
+#pragma unroll
+          for (int j = 0; j < TM; j++) b[c][j] = ldsf[yword + brow[j] + q + k + 4 * c];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; c++) mma(a[c], b[c]);
+      }
     }
-    if (!more) return;
-    job = next;
+    for (; k < K; k += 4) {  // single steps; slots past K are zeroed in BOTH operands: what lies there may be an Inf
+      float a[TN], b[TM];
+      const bool in = VEC || k + q < K;
+      const int at = in ? q : 0;  // (k itself is in)
+#pragma unroll
+      for (int i = 0; i < TN; i++) {
+        const float v = VEC ? ldsf[4 * ta_slot<true>((arow[i] + k) >> 2) + q] : ldsf[arow[i] + k + at];
+        a[i] = in ? v : 0.f;
+      }
+#pragma unroll
+      for (int j = 0; j < TM; j++) {
+        const float v = VEC ? ldsf[yword + 4 * ta_slot<true>((brow[j] + k) >> 2) + q] : ldsf[yword + brow[j] + k + at];
+        b[j] = in ? v : 0.f;
+      }
+      mma(a, b);
+    }
+  }
+
+  const int64_t z0 = ((int64_t)b0 * N + n0) * M + m0;
+  if (p.direct) {
+    if (e >= ne) return;
+    float* z = p.Z + z0 + (int64_t)e * N * M;
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        const int row = 16 * (TN * wn + i) + d_row(q, v);
+#pragma unroll
+        for (int j = 0; j < TM; j++) {
+          const int col = 16 * (TM * wm + j) + r16;
+          if (row < rows && col < cols) z[(int64_t)row * M + col] = (float)acc[i][j][v];
+        }
+      }
+    return;
+  }
+
+  // ---- results through LDS
+  const bool flat = cols == M;  // one contiguous block (uniform)
+  const int zoff = flat ? (int)(z0 & 3) : 0;
+  __syncthreads();
+  if (e < ne) {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        const int row = 16 * (TN * wn + i) + d_row(q, v);
+#pragma unroll
+        for (int j = 0; j < TM; j++) {
+          const int col = 16 * (TM * wm + j) + r16;
+          if (row < rows && col < cols) ldsf[zoff + (e * rows + row) * cols + col] = (float)acc[i][j][v];
+        }
+      }
+  }
+  __syncthreads();
+  if (flat) {
+    const int end = zoff + ne * rows * M, zu = (end + 3) >> 2;
+    float* zs = p.Z + (z0 - zoff);
+    for (int u = WAVE * wave + lane; u < zu; u += WAVE * waves) {
+      const f4 v = *reinterpret_cast<const f4*>(ta_lds + 16 * u);
+      if (4 * u >= zoff && 4 * u + 4 <= end) {
+        store_stream(reinterpret_cast<f4*>(zs + 4 * u), v);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+          if (4 * u + c >= zoff && 4 * u + c < end) zs[4 * u + c] = v[c];
+      }
+    }
+  } else {
+    float* zs = p.Z + z0;
+    for (int r = wave; r < rows; r += waves)
+      for (int c = lane; c < cols; c += WAVE) store_stream(zs + (int64_t)r * M + c, ldsf[r * cols + c]);
   }
 }
 

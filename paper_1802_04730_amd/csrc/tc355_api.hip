@@ -596,96 +596,68 @@ tc_status run_tbmm_lds(const TbmmLdsPlan& pl, const float* X, const float* Y, fl
 }
 
 // ---- transposed batched matmul of small matrices of any size ----
-template <int TN, int TM, int KMAX>
-tc_status launch_tbmm_any(const TbmmAnyArgs& a, unsigned wgs, size_t lds, hipStream_t s) {
+template <int TN, int TM>
+tc_status launch_tbmm_any(const TbmmAnyPlan& pl, TbmmAnyArgs a, hipStream_t s) {
   static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
   if (!lds_ok.load(std::memory_order_acquire)) {
-    const void* kernels[2] = {reinterpret_cast<const void*>(tbmm_any_kernel<TN, TM, KMAX, false>), reinterpret_cast<const void*>(tbmm_any_kernel<TN, TM, KMAX, true>)};
+    const void* kernels[2] = {reinterpret_cast<const void*>(tbmm_any_kernel<TN, TM, false>), reinterpret_cast<const void*>(tbmm_any_kernel<TN, TM, true>)};
     for (const void* k : kernels)
-      if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return TC_ERR_LAUNCH;
+      if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)TA_MAX_LDS) != hipSuccess) return TC_ERR_LAUNCH;
     lds_ok.store(1, std::memory_order_release);
   }
-  if (a.K % 16 == 0) tbmm_any_kernel<TN, TM, KMAX, true><<<dim3(wgs), dim3(WG_THREADS), lds, s>>>(a);
-  else tbmm_any_kernel<TN, TM, KMAX, false><<<dim3(wgs), dim3(WG_THREADS), lds, s>>>(a);
-  return launch_status();
-}
-
-template <int TN, int KMAX>
-tc_status launch_tbmm_any_tm(int tm, const TbmmAnyArgs& a, unsigned wgs, size_t lds, hipStream_t s) {
-  switch (tm) {
-    case 1: return launch_tbmm_any<TN, 1, KMAX>(a, wgs, lds, s);
-    case 2: return launch_tbmm_any<TN, 2, KMAX>(a, wgs, lds, s);
-    case 3: return launch_tbmm_any<TN, 3, KMAX>(a, wgs, lds, s);
-    case 4: return launch_tbmm_any<TN, 4, KMAX>(a, wgs, lds, s);
-    default: return launch_tbmm_any<TN, 5, KMAX>(a, wgs, lds, s);
+  const dim3 bd((unsigned)(pl.gm * WAVE), (unsigned)pl.gn, (unsigned)pl.nb);
+  for (int64_t at = 0; at < pl.groups;) {
+    const int64_t n = next_launch(pl.groups - at, pl.gm * pl.gn * pl.nb * WAVE);
+    a.first = (unsigned)at;
+    if (a.K % 4 == 0) tbmm_any_kernel<TN, TM, true><<<dim3((unsigned)n), bd, (size_t)pl.lds, s>>>(a);
+    else tbmm_any_kernel<TN, TM, false><<<dim3((unsigned)n), bd, (size_t)pl.lds, s>>>(a);
+    const tc_status st = launch_status();
+    if (st != TC_OK) return st;
+    at += n;
   }
+  return TC_OK;
 }
 
-struct TbmmAnyPlan {
-  int64_t strips_n, strips_m, jobs, units, lds;
-  double cost;
-};
-
-// Jobs of tn x tm tiles: what they take, and an estimate of the launch in clocks; false where they do not fit.
-bool plan_tbmm_any(int64_t B, int64_t N, int64_t M, int64_t K, int tn, int tm, int cus, TbmmAnyPlan* p) {
-  p->strips_n = ceil_div(ceil_div(N, 16), tn);
-  p->strips_m = ceil_div(ceil_div(M, 16), tm);
-  if (B >= kMaxElems / (p->strips_n * p->strips_m)) return false;  // 32-bit job numbers
-  p->jobs = B * p->strips_n * p->strips_m;
-  const int64_t xrows = std::min<int64_t>(16 * tn, N), yrows = std::min<int64_t>(16 * tm, M);
-  const int64_t pieces = (xrows * K + 6) / 4 + (yrows * K + 6) / 4;
-  p->units = std::max((K % 16 == 0 ? pieces + pieces / 16 : pieces) + 2, (xrows * yrows + 6) / 4 + 1);  // (the last step reads past its row)
-  p->lds = WAVES_PER_WG * p->units * 16;
-  if (p->lds > 160 * 1024) return false;
-  // A job's instructions in clocks of a SIMD (loads, MFMAs, operand reads, results; rows that leave one by one), the round
-  // trip in front of them, the wavefronts that share a SIMD as registers and LDS allow, and what memory delivers.  The
-  // constants are fitted to the measured times of 42 shapes at every (tn, tm): on average 0.3 % from the best choice there.
-  const int kmax = K <= 31 ? 31 : K <= 63 ? 63 : 103, steps = (int)ceil_div(K, 4);
-  const int loads = tbmm_any_loads(16 * tn, kmax) + tbmm_any_loads(16 * tm, kmax);
-  const double work = loads * 39.0 + tn * tm * steps * 83.5 + (tn + tm) * steps * (K % 16 == 0 ? 20.1 : 11.2) + tn * tm * 4 * 71.0 +
-                      (yrows == M ? 0.0 : 20.0 * xrows);
-  const int64_t per_simd = ceil_div(p->jobs, 4 * cus);
-  const int64_t w = std::min(per_simd, std::max<int64_t>(1, std::min<int64_t>(512 / (4 * loads + 8 * tn * tm + 44), 160 * 1024 / p->lds)));
-  const double bytes = 4.0 * ((xrows + yrows) * K + xrows * yrows);
-  p->cost = 5430 + std::max({ceil_div(per_simd, w) * (1470 + work), per_simd * work, per_simd * 4 * bytes / 11.0});
-  // Two tiles of rows are a little worse than that: (2176,109,60,14) 23.9 us against 20.7, (4000,94,18,86) 50.1 / 47.9.  Over 400
-  // other random shapes measured at every (tn, tm) the choice is on average 1.7 % from the best one, 1.75 % without these
-  // factors.  The large one helps batches of a few thousand, which stream ((4000,27,61,35) 24.3 / 22.3, (4548,21,99,19) 33.9 /
-  // 29.7, (5630,21,51,46) 36.0 / 32.4), and gives some smaller ones away ((1991,26,55,35) 11.3 / 12.5, (1601,28,59,53) 13.9 / 15.7).
-  if (tn == 2 && tm >= 2) p->cost *= tm >= 4 ? 1.15 : K > 63 ? 1.06 : 1.0;
-  return true;
+// The plan of the thread's last shapes: choosing one takes 1-4 us of host time.
+const TbmmAnyPlan* tbmm_any_plan(int64_t B, int64_t N, int64_t M, int64_t K, int cus) {
+  struct Entry {
+    int64_t B, N, M, K;
+    int cus;
+    bool any;
+    TbmmAnyPlan plan;
+  };
+  static thread_local Entry last[8] = {};
+  Entry& e = last[(uint64_t)(B * 31 + N * 7 + M * 3 + K) % 8];
+  if (e.B != B || e.N != N || e.M != M || e.K != K || e.cus != cus) {
+    e.any = choose_tbmm_any(B, N, M, K, cus, &e.plan);
+    e.B = B; e.N = N; e.M = M; e.K = K; e.cus = cus;
+  }
+  return e.any ? &e.plan : nullptr;
 }
 
-// Reductions up to 103 (what the register file holds of two strips on their way).
+// Reductions up to 103: beyond, LDS holds too few workgroups.
 bool try_tbmm_any(const float* X, const float* Y, float* Z, int64_t B, int64_t N, int64_t M, int64_t K, hipStream_t s, tc_status* st) {
   const int cus = device_cus();
-  if (cus <= 0 || K > 103 || prod_reaches({B, N, K}, 1ll << 40) || prod_reaches({B, M, K}, 1ll << 40) || B * N * K < 4 || B * M * K < 4) return false;
-  const int tiles_n = (int)std::min<int64_t>(2, ceil_div(N, 16)), tiles_m = (int)std::min<int64_t>(5, ceil_div(M, 16));
-  TbmmAnyPlan best{}, pl{};
-  int tn = 0, tm = 0;
-  for (int n = 1; n <= tiles_n; n++)
-    for (int m = 1; m <= std::min(tiles_m, K <= 63 ? 5 : n == 1 ? 4 : 3); m++)  // (registers)
-      if (plan_tbmm_any(B, N, M, K, n, m, cus, &pl) && (tn == 0 || pl.cost < best.cost)) { best = pl; tn = n; tm = m; }
-  if (tn == 0) return false;
+  if (cus <= 0 || K > 103 || prod_reaches({B, N, K}, 1ll << 40) || prod_reaches({B, M, K}, 1ll << 40)) return false;
+  const TbmmAnyPlan* pl = tbmm_any_plan(B, N, M, K, cus);
+  if (!pl) return false;
   TbmmAnyArgs a{};
   a.X = X; a.Y = Y; a.Z = Z;
-  a.N = (int)N; a.M = (int)M; a.K = (int)K;
-  a.strips_n = (int)best.strips_n; a.strips_m = (int)best.strips_m;
-  a.jobs = (int)best.jobs;
-  a.wave_lds_units = (int)best.units;
-  a.xtotal = B * N * K; a.ytotal = B * M * K;
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(4, (160 * 1024) / best.lds));
-  const unsigned wgs = (unsigned)std::min<int64_t>(ceil_div(best.jobs, WAVES_PER_WG), per_cu * cus);
-  const size_t lds = (size_t)best.lds;
-  if (K <= 31) {
-    *st = tn == 2 ? launch_tbmm_any_tm<2, 31>(tm, a, wgs, lds, s) : launch_tbmm_any_tm<1, 31>(tm, a, wgs, lds, s);
-  } else if (K <= 63) {
-    *st = tn == 2 ? launch_tbmm_any_tm<2, 63>(tm, a, wgs, lds, s) : launch_tbmm_any_tm<1, 63>(tm, a, wgs, lds, s);
-  } else if (tn == 2) {
-    *st = tm == 1 ? launch_tbmm_any<2, 1, 103>(a, wgs, lds, s) : tm == 2 ? launch_tbmm_any<2, 2, 103>(a, wgs, lds, s) : launch_tbmm_any<2, 3, 103>(a, wgs, lds, s);
-  } else {
-    *st = tm == 1 ? launch_tbmm_any<1, 1, 103>(a, wgs, lds, s) : tm == 2 ? launch_tbmm_any<1, 2, 103>(a, wgs, lds, s)
-        : tm == 3 ? launch_tbmm_any<1, 3, 103>(a, wgs, lds, s) : launch_tbmm_any<1, 4, 103>(a, wgs, lds, s);
+  a.B = (int)B; a.N = (int)N; a.M = (int)M; a.K = (int)K;
+  a.strips_n = (int)pl->strips_n; a.strips_m = (int)pl->strips_m;
+  a.direct = pl->direct;
+  switch (10 * pl->tn + pl->tm) {
+    case 11: *st = launch_tbmm_any<1, 1>(*pl, a, s); break;
+    case 12: *st = launch_tbmm_any<1, 2>(*pl, a, s); break;
+    case 13: *st = launch_tbmm_any<1, 3>(*pl, a, s); break;
+    case 15: *st = launch_tbmm_any<1, 5>(*pl, a, s); break;
+    case 21: *st = launch_tbmm_any<2, 1>(*pl, a, s); break;
+    case 22: *st = launch_tbmm_any<2, 2>(*pl, a, s); break;
+    case 23: *st = launch_tbmm_any<2, 3>(*pl, a, s); break;
+    case 31: *st = launch_tbmm_any<3, 1>(*pl, a, s); break;
+    case 32: *st = launch_tbmm_any<3, 2>(*pl, a, s); break;
+    case 33: *st = launch_tbmm_any<3, 3>(*pl, a, s); break;
+    default: return false;
   }
   return true;
 }
@@ -893,7 +865,9 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
     // (311,64,48,88) 11.3 / 8.5).  The wave-level kernel keeps what is too short to stage ((30000,8,8,8) 14.7 / 15.4,
     // (1175,77,4,1) 4.0 / 4.9), results that are one tile wide or more than 5 while the rows share LDS banks
     // ((5709,51,5,96) 38 / 46, (6,51,120,80) 4.3 / 4.7) or the wide ones' odd reductions are short ((3129,12,92,5) 8.8 / 9.3).
-    // Everything else is the other one's: (4000,27,61,35) 38.8 / 22.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.
+    // Everything else is the other one's: (4000,27,61,35) 38.8 / 17.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.  (The lines
+    // here and above were drawn against its earlier form, a wavefront per strip pair; it is 1.14 times as fast by now, and the wave-level
+    // kernel's share above would be 1.14 times as fast on it, the aligned kernel's 1.06 times: 15 and 76 shapes.)
     const int64_t cus = std::max(1, device_cus()), blocks = ceil_div(N, GT_BM) * ceil_div(M, GT_BN) * B, tiles = ceil_div(N, 16) * tiles_m * B;
     const double full = (double)N * M / (ceil_div(N, GT_BM) * GT_BM * ceil_div(M, GT_BN) * GT_BN);
     const bool block = K % 4 == 0 && N >= 48 && M >= 48 && blocks >= 128 &&
