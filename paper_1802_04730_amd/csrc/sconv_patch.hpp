@@ -1,0 +1,347 @@
+// Strided convolution (Section 3, listing sconv2d) on the int8 matrix core for filters of nine taps over a multiple of 32
+// channels and a multiple of 32 filters:
+//
+//   O(n,f,h,w) = B(f) + sum_{c,kh,kw} I(n,c, sh*h + kh, sw*w + kw) * W(f,c,kh,kw)
+//
+// sconv_i8.hpp gathers every tap of every pixel and slices it: an element of the input as often as there are taps over it, the
+// filters as often as there are workgroups.  Here a workgroup slices the rows of the input that its pixels touch ONCE, where they
+// lie, and a tap is an offset into them.
+//
+// A workgroup of 8 wavefronts owns TF filters and a run of up to 16 NTW PG pixels of one image (PG = 8 / (TF / 16) wavefronts
+// per filter tile) and walks over the channels, 32 at a time:
+//   * Patch: the input rows under the run, whole rows, so that a channel's part is one contiguous run of memory.  A thread slices
+//     pieces of 4 positions x 4 channels (four 16-byte loads, requested a stage ahead); LDS holds [16 channels][digit][position][16
+//     bytes].  One scale for the patch of a stage.
+//   * Filters: a wavefront slices the 16 filters of its own tile, in registers, in operand order; nobody else has them.  Their taps
+//     lie channel by channel in memory; pieces of 4 channels x 2 travel to a private LDS ring (global_load_lds) and are read back
+//     tap by tap.  Scale per filter and stage.
+//   * Contraction: an MFMA step is 2 taps x 32 channels (lane (r16, q): tap 2 s + q / 2, channels 16 (q % 2) ..), rows =
+//     pixels, columns = filters.  An operand read touches 16 positions sw apart: at 16 bytes a position all strides but
+//     multiples of 3 and 4 read at full speed (measured: row strides of 1, and of 2 modulo 4, pieces of 16 bytes take 5
+//     clocks, others 9 and more).  The 13 digit products of a tile are summed over all taps of the stage before they are
+//     scaled: 9 taps x 32 channels instead of 128 taps.
+// The arithmetic is that of sconv_i8.hpp (32-bit fixed point, four signed 8-bit digits, the products with k + l >= 2 summed
+// exactly in int32, fp64 over the stages, one rounding), but that scales are powers of two: what is above 2^-7 of the largest
+// magnitude is not rounded at all, which more than makes up for scales that many more elements share (errors on the metric
+// 1.1e-7 .. 1.8e-7 against 1.9e-7 .. 3.5e-7 on Gaussian data, 7e-7 .. 8e-7 on heavy-tailed).  Inf and NaN reach what they reach there: a position that holds one is
+// left out of the patch (and of its scale) and marked, and pixels whose window touches a mark become NaN; a filter that holds one
+// gives NaN everywhere.
+// (N,C,F,H,W) at stride s, sconv_i8.hpp -> this, us: (32,64,128,56,56) at 2 46.7 -> 36.0, (32,64,64,56,56) at 1 112 -> 69,
+// (3,128,256,58,58) at 1 73 -> 52, (15,128,192,13,72) at 1 82 -> 55.  What bounds it: a stage of 6 tiles is 8 us, 5.2 of them MFMAs at
+// their rate; the 4 to 5 us in front of it are vector instructions (the filters' slicing above all) and LDS round trips that
+// nothing covers, so layers with few pixels per compute unit stay with sconv_i8.hpp.  Filters straight from memory in
+// operand order would touch 32 lines per load; scratch registers (one 64-bit address per load kept over the loop) cost 9 us.
+#pragma once
+#include "sconv_i8.hpp"
+#include "sconv_patch_plan.hpp"
+
+namespace tc355 {
+
+struct SconvPatchArgs {
+  const float* I;     // [N][G][C][H][W]
+  const float* Wt;    // [G][F][C][KH][KW]
+  const float* bias;  // [G * F] or nullptr
+  float* O;           // [N][G][F][OH][OW]
+  int C, F, H, W, KH, KW, sh, sw, OH, OW, G;
+  int px, blocks;     // pixels per workgroup, runs of them per image (blockIdx.x = image * blocks + run)
+  unsigned ow_magic, kw_magic;  // sp_magic of OW, KW
+};
+
+constexpr int SP_THREADS = SP_WAVES * WAVE;
+constexpr int SP_PLANE = SP_POSITIONS * 16;    // one digit of 16 channels
+constexpr int SP_GROUP = 4 * SP_PLANE;
+constexpr int SP_UNITS = (2 * SP_POSITIONS + SP_THREADS - 1) / SP_THREADS;  // (4 positions, 4 channels) per thread
+constexpr int SP_RAW = 32 * SP_TAPS * 16;  // 16 filters x 4 channels x 2, all taps
+constexpr int SP_RING = 2 * SP_GROUP;          // 8 wavefronts x 2 of them
+constexpr int SP_MAXIMA = SP_RING + SP_WAVES * 2 * SP_RAW;  // [2] largest magnitude of a stage's patch; [1] without Inf and NaN
+constexpr int SP_MARKS = SP_MAXIMA + 16;       // [position] holds Inf or NaN in some channel
+constexpr int SP_LDS_BYTES = SP_MARKS + SP_POSITIONS;
+static_assert(SP_LDS_BYTES <= 160 * 1024, "one workgroup per compute unit");
+
+// The power of two that takes the largest magnitude (its bits) just below the largest number of four signed digits, 0x7F7F7F7F,
+// and its inverse: elements above 2^-7 of the maximum become integers without rounding.
+__device__ __forceinline__ void sp_scales(unsigned mbits, double& scale, double& inverse) {
+  const int e = (int)max((mbits + 0x10101u) >> 23, 1u);  // (significands above 0xFEFEFE count as the next binade's)
+  scale = __hiloint2double((1023 + 157 - e) << 20, 0);
+  inverse = i8_nonfinite(mbits) ? __longlong_as_double(0x7ff8000000000000ll) : __hiloint2double((1023 - 157 + e) << 20, 0);
+}
+
+// n / d for n and d below 2^12 and magic = sp_magic(d)
+__device__ __forceinline__ int sp_div(int n, unsigned magic) { return (int)(((unsigned)n * magic) >> SP_MAGIC_SHIFT); }
+
+// 16 bytes per lane to LDS: lane l's to lds + 16 l.  In assembly: the compiler would wait for such loads before any LDS read.
+__device__ __forceinline__ void sp_load_to_lds(const char* base, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory", "m0");
+}
+
+template <int TF, int NTW>
+__global__ __launch_bounds__(SP_THREADS, 1) void sconv_patch_kernel(SconvPatchArgs p) {
+  constexpr int FT = TF / 16, PG = SP_WAVES / FT;
+  constexpr int STEPS = (SP_TAPS + 1) / 2;
+  extern __shared__ __attribute__((aligned(16))) char sp_lds[];
+  const int tid = threadIdx.x;
+  const int lane = tid & (WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  const int r16 = lane & 15, q = lane >> 4;
+  const int W = p.W, HW = p.H * W, OW = p.OW, OHW = p.OH * OW, C = p.C;
+  constexpr int KHW = SP_TAPS;
+  const int grp = blockIdx.z, f0 = blockIdx.y * TF;
+  const int img = blockIdx.x / p.blocks, p0 = ((int)blockIdx.x - img * p.blocks) * p.px;
+  const int npx = min(p.px, OHW - p0);
+  const int row0 = p0 / OW, col0 = p0 - row0 * OW;                       // the first pixel
+  const int rows = sp_div(col0 + npx - 1, p.ow_magic) * p.sh + p.KH;      // input rows
+  const int npos = rows * W;                                             // at most SP_POSITIONS (the host asks)
+  const int ft = wave % FT, pg = wave / FT;
+  unsigned* maxima = reinterpret_cast<unsigned*>(sp_lds + SP_MAXIMA);
+  unsigned char* marks = reinterpret_cast<unsigned char*>(sp_lds + SP_MARKS);
+  if (tid < 4) maxima[tid] = 0;
+  for (int i = tid; i < SP_POSITIONS / 4; i += SP_THREADS) reinterpret_cast<int*>(marks)[i] = 0;
+
+  // ---- patch: unit j of this thread is 4 positions (the last ones moved back to end with the run) x 4 channels: quad cq of 8
+  const int quads = (npos + 3) >> 2, rounds = (8 * quads + SP_THREADS - 1) / SP_THREADS;  // (uniform)
+  unsigned goff[SP_UNITS];
+  int loff[SP_UNITS];
+#pragma unroll
+  for (int j = 0; j < SP_UNITS; j++) {
+    const int u = min(j * SP_THREADS + tid, 8 * quads - 1), cq = u & 7, pos = min(4 * (u >> 3), npos - 4);
+    goff[j] = 4u * (unsigned)(4 * cq * HW + pos);
+    loff[j] = (cq >> 2) * SP_GROUP + pos * 16 + 4 * (cq & 3);
+  }
+  const float* in = p.I + ((int64_t)img * p.G + grp) * C * HW + (int64_t)row0 * p.sh * W;
+  f4 pre[SP_UNITS][4];  // [channel][position]
+  auto fetch = [&](int c0) {  // (every register gets a value on every way: a kept one would stay live all along)
+    const char* at = reinterpret_cast<const char*>(in + (int64_t)c0 * HW);
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+      const char* plane = at + 4 * (int64_t)c * HW;
+      asm volatile("" : "+s"(plane));  // (a scalar base and a 32-bit offset: not 64-bit addresses kept over the loop)
+#pragma unroll
+      for (int j = 0; j < SP_UNITS; j++) {
+        pre[j][c] = f4{0.f, 0.f, 0.f, 0.f};
+        if (j < rounds && c0 < C) pre[j][c] = *reinterpret_cast<const f4_any*>(plane + goff[j]);
+      }
+    }
+  };
+  auto patch_max = [&]() {
+    int sm = 0;
+    unsigned um = 0;
+#pragma unroll
+    for (int j = 0; j < SP_UNITS; j++)
+      if (j < rounds) {
+#pragma unroll
+        for (int c = 0; c < 4; c++) gi8_absmax4(pre[j][c], sm, um);
+      }
+    return i8_wave_max((unsigned)gi8_magnitude(sm, um));
+  };
+  auto post = [&](unsigned* to) {
+    const unsigned m = patch_max();
+    if (lane == 0) __hip_atomic_fetch_max(to, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+
+  // ---- filters of this wavefront's tile: pieces of quarter j of a stage (channels 4 j .. + 3 of both groups), filter by filter
+  const unsigned ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)sp_lds + SP_RING + (unsigned)wave * (2 * SP_RAW);
+  const char* wt = reinterpret_cast<const char*>(p.Wt + ((int64_t)grp * p.F + f0 + 16 * ft) * C * KHW);
+  unsigned woff[STEPS];  // byte offset of the lane's pieces from the quarter's first one
+#pragma unroll
+  for (int i = 0; i < STEPS; i++) {
+    const int u = min(WAVE * i + lane, 32 * KHW - 1), fg = u / KHW;
+    woff[i] = 4u * (unsigned)((fg >> 1) * C * KHW + (fg & 1) * 16 * KHW) + 16u * (unsigned)(u - fg * KHW);
+  }
+  auto load_raw = [&](int c0, int j) {
+    const char* at = wt + (int64_t)(c0 + 4 * j) * KHW * 4;
+#pragma unroll
+    for (int i = 0; i < STEPS; i++)
+      if (WAVE * i + lane < 32 * KHW) sp_load_to_lds(at, woff[i], ring + (unsigned)(j & 1) * SP_RAW + 1024u * i);
+  };
+  f4 raw[STEPS][4];
+  auto read_raw = [&](int j) {
+    const float* src = reinterpret_cast<const float*>(sp_lds + SP_RING + wave * (2 * SP_RAW) + (j & 1) * SP_RAW) + (2 * r16 + (q & 1)) * 4 * KHW + (q >> 1);
+#pragma unroll
+    for (int s = 0; s < STEPS; s++) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const float v = src[2 * s + e * KHW];
+        raw[s][j][e] = 2 * s + 1 < KHW || q < 2 ? v : 0.f;  // (the last step has one tap)
+      }
+    }
+  };
+
+  // ---- contraction: pixel tiles pg, pg + PG, .. against the wavefront's filter tile
+  unsigned base[NTW], toff[STEPS];
+#pragma unroll
+  for (int i = 0; i < NTW; i++) {
+    const int px = min(16 * (pg + PG * i) + r16, npx - 1) + col0, oh = sp_div(px, p.ow_magic), ow = px - oh * OW;
+    base[i] = 16u * (unsigned)(oh * p.sh * W + ow * p.sw);
+  }
+#pragma unroll
+  for (int s = 0; s < STEPS; s++) {
+    const int tap = min(2 * s + (q >> 1), KHW - 1), kh = sp_div(tap, p.kw_magic), kw = tap - kh * p.KW;
+    toff[s] = 16u * (unsigned)(kh * W + kw) + (unsigned)(q & 1) * SP_GROUP;
+  }
+  double acc[NTW][4];
+#pragma unroll
+  for (int i = 0; i < NTW; i++)
+#pragma unroll
+    for (int v = 0; v < 4; v++) acc[i][v] = 0.0;
+  bool marked = false;  // (uniform) some position is
+
+  fetch(0);
+  load_raw(0, 0);
+  load_raw(0, 1);
+  __syncthreads();  // the cleared words
+  for (int c0 = 0, t = 0; c0 < C; c0 += 32, t ^= 1) {
+    post(maxima + t);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    read_raw(0);
+    read_raw(1);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    load_raw(c0, 2);
+    load_raw(c0, 3);
+    __syncthreads();  // (also: everybody has contracted the stage before)
+    unsigned m = __builtin_amdgcn_readfirstlane(maxima[t]);
+    if (i8_nonfinite(m)) {  // (uniform) leave such elements out, mark their positions
+      marked = true;
+#pragma unroll
+      for (int j = 0; j < SP_UNITS; j++)
+        if (j < rounds) {
+#pragma unroll
+          for (int c = 0; c < 4; c++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+              if (i8_nonfinite(__float_as_uint(pre[j][c][e]) & 0x7fffffffu)) {
+                pre[j][c][e] = 0.f;
+                marks[(loff[j] >> 4) % SP_POSITIONS + e] = 1;  // (a group is 4 SP_POSITIONS records)
+              }
+        }
+      post(maxima + 2);
+      __syncthreads();
+      m = __builtin_amdgcn_readfirstlane(maxima[2]);
+      __syncthreads();
+      if (tid == 0) maxima[2] = 0;
+    }
+    if (tid == 0) maxima[t ^ 1] = 0;  // read a stage ago, written behind the next barrier
+    double pscale, pinverse;
+    sp_scales(m, pscale, pinverse);
+#pragma unroll
+    for (int j = 0; j < SP_UNITS; j++)
+      if (j < rounds) {
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          int y[4];
+          gi8_digits4(f4{pre[j][0][e], pre[j][1][e], pre[j][2][e], pre[j][3][e]}, pscale, y);
+#pragma unroll
+          for (int k = 0; k < 4; k++) *reinterpret_cast<int*>(sp_lds + loff[j] + 16 * e + k * SP_PLANE) = y[k];
+        }
+      }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    read_raw(2);
+    read_raw(3);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (c0 + 32 < C) {
+      load_raw(c0 + 32, 0);
+      load_raw(c0 + 32, 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // the filters' scale and digits, in operand order
+    i4 wd[STEPS][4];
+    double factor;
+    {
+      int sm = 0;
+      unsigned um = 0;
+#pragma unroll
+      for (int s = 0; s < STEPS; s++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) gi8_absmax4(raw[s][j], sm, um);
+      int v = gi8_magnitude(sm, um);
+      v = max(v, __shfl_xor(v, 16));
+      v = max(v, __shfl_xor(v, 32));
+      double scale, inverse;
+      sp_scales((unsigned)v, scale, inverse);
+      factor = inverse * pinverse * 16777216.0;  // 2^24: the weight of the lowest kept diagonal
+#pragma unroll
+      for (int s = 0; s < STEPS; s++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+          int y[4];
+          gi8_digits4(raw[s][j], scale, y);
+#pragma unroll
+          for (int k = 0; k < 4; k++) wd[s][k][j] = y[k];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    fetch(c0 + 32);  // (registers: not before the filters are digits)
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();  // the patch's digits
+#pragma unroll
+    for (int i = 0; i < NTW; i++) {
+      __builtin_amdgcn_sched_barrier(0);
+      // order: no two consecutive products on one diagonal
+      constexpr int PK[13] = {3, 2, 3, 3, 2, 1, 2, 1, 0, 3, 2, 1, 0};
+      constexpr int PL[13] = {0, 1, 1, 2, 2, 2, 3, 3, 3, 3, 0, 1, 2};
+      i4 d[5];  // d[x]: diagonal k + l = 2 + x
+      bool begun[5] = {};  // (compile-time after unrolling)
+#pragma unroll
+      for (int s = 0; s < STEPS; s++) {
+        const char* at = sp_lds + (base[i] + toff[s]);
+        i4 ya[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) ya[k] = *reinterpret_cast<const i4*>(at + k * SP_PLANE);
+#pragma unroll
+        for (int pr = 0; pr < 13; pr++) {
+          const int dg = PK[pr] + PL[pr] - 2;
+          d[dg] = mfma_i8(ya[PK[pr]], wd[s][PL[pr]], begun[dg] ? d[dg] : i4{0, 0, 0, 0});
+          begun[dg] = true;
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        // 288 terms of at most 2^14 per digit pair: 288 x 2^14 x 256 + 2 x 288 x 2^14 stays below 2^31, the next pair of
+        // diagonals (three and four digit pairs) would not
+        const int hi = d[4][v] * 256 + d[3][v];
+        double rr = __builtin_fma((double)d[2][v], 256.0, (double)d[1][v]);
+        rr = __builtin_fma((double)hi, 65536.0, rr);
+        rr = __builtin_fma((double)d[0][v], 0.00390625, rr);
+        acc[i][v] = __builtin_fma(rr, factor, acc[i][v]);
+      }
+    }
+  }
+
+  if (marked) {  // (uniform) pixels whose window touches a mark
+#pragma unroll 1
+    for (int i = 0; i < NTW; i++)
+#pragma unroll 1
+      for (int v = 0; v < 4; v++) {
+        const int px = min(16 * (pg + PG * i) + 4 * q + v, npx - 1) + col0, oh = sp_div(px, p.ow_magic), ow = px - oh * OW;
+        const unsigned char* at = marks + (oh * p.sh * W + ow * p.sw);
+        bool hit = false;
+        for (int kh = 0; kh < p.KH; kh++)
+          for (int kw = 0; kw < p.KW; kw++) hit |= at[kh * W + kw] != 0;
+#pragma unroll
+        for (int a = 0; a < NTW; a++)
+#pragma unroll
+          for (int b = 0; b < 4; b++)
+            if (hit && a == i && b == v) acc[a][b] = __longlong_as_double(0x7ff8000000000000ll);
+      }
+  }
+
+  // ---- outputs: staged in the patch's LDS as [filter][pixel], written as runs of consecutive pixels of one filter
+  constexpr int TP = 16 * NTW * PG, OS = TP + 1;  // odd: the 16 filters of a wavefront's write fall into 16 banks
+  static_assert(TF * OS * 4 <= SP_RING, "the output stage fits the patch");
+  float* ostage = reinterpret_cast<float*>(sp_lds);
+  __syncthreads();
+  {
+    const double bz = p.bias ? (double)p.bias[grp * p.F + f0 + 16 * ft + r16] : 0.0;
+#pragma unroll
+    for (int i = 0; i < NTW; i++)
+#pragma unroll
+      for (int v = 0; v < 4; v++) ostage[(16 * ft + r16) * OS + 16 * (pg + PG * i) + 4 * q + v] = (float)(acc[i][v] + bz);
+  }
+  __syncthreads();
+  float* out = p.O + (((int64_t)img * p.G + grp) * p.F + f0) * OHW + p0;
+  for (int idx = tid; idx < TF * TP; idx += SP_THREADS) {
+    const int fl = idx / TP, px = idx - fl * TP;
+    if (px < npx) store_stream(out + (int64_t)fl * OHW + px, ostage[fl * OS + px]);
+  }
+}
+
+}  // namespace tc355

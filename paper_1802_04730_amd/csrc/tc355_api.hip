@@ -35,6 +35,7 @@
 #include "sconv_split.hpp"
 #include "sconv_tile.hpp"
 #include "sconv_i8.hpp"
+#include "sconv_patch.hpp"
 #include "tbmm_any.hpp"
 #include "tbmm_lds.hpp"
 #include "tc355_host.hpp"
@@ -1172,10 +1173,40 @@ tc_status launch_sconv_i8(const SconvI8Args& a, int64_t blocks, dim3 grid, bool 
   return launch_status();
 }
 
-// LDS bytes of the kernel for tf filters and nt pixel tiles per workgroup (the geometry depends on tf + 16 nt only)
-int64_t sconv_i8_lds_bytes(int tf, int nt, int64_t blocks) {
-  const int64_t rows = tf + 16 * nt;
-  return 4 * rows * SI8_RS + rows * 8 + 2 * 16 * nt * 4 + blocks * SI8_KB * 4;
+// The same for 3 x 3 taps over a multiple of 32 channels, the input sliced where it lies (sconv_patch.hpp).
+template <int TF, int NTW>
+tc_status launch_sconv_patch(const SconvPatchArgs& a, dim3 grid, hipStream_t s) {
+  static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
+  if (!lds_ok.load(std::memory_order_acquire)) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(sconv_patch_kernel<TF, NTW>), hipFuncAttributeMaxDynamicSharedMemorySize, SP_LDS_BYTES) != hipSuccess)
+      return TC_ERR_LAUNCH;
+    lds_ok.store(1, std::memory_order_release);
+  }
+  sconv_patch_kernel<TF, NTW><<<grid, dim3(SP_THREADS), SP_LDS_BYTES, s>>>(a);
+  return launch_status();
+}
+
+template <int TF>
+tc_status launch_sconv_patch_tiles(int tiles, const SconvPatchArgs& a, dim3 grid, hipStream_t s) {
+  switch (tiles) {
+    case 2: return launch_sconv_patch<TF, 2>(a, grid, s);
+    case 3: return launch_sconv_patch<TF, 3>(a, grid, s);
+    case 4: return launch_sconv_patch<TF, 4>(a, grid, s);
+    case 5: return launch_sconv_patch<TF, 5>(a, grid, s);
+    default: return launch_sconv_patch<TF, 6>(a, grid, s);
+  }
+}
+
+tc_status run_sconv_patch(const SconvI8Args& e, int64_t N, const SconvPatchPlan& pl, hipStream_t s) {
+  SconvPatchArgs a{};
+  a.I = e.I; a.Wt = e.Wt; a.bias = e.bias; a.O = e.O;
+  a.C = e.C; a.F = e.F; a.H = e.H; a.W = e.W; a.KH = e.KH; a.KW = e.KW; a.sh = e.sh; a.sw = e.sw; a.OH = e.OH; a.OW = e.OW; a.G = e.G;
+  a.px = pl.px; a.blocks = pl.blocks;
+  a.ow_magic = sp_magic(e.OW); a.kw_magic = sp_magic(e.KW);
+  const dim3 grid((unsigned)(N * pl.blocks), (unsigned)(e.F / pl.tf), (unsigned)e.G);
+  if (pl.tf == 128) return launch_sconv_patch_tiles<128>(pl.tiles, a, grid, s);
+  if (pl.tf == 64) return launch_sconv_patch_tiles<64>(pl.tiles, a, grid, s);
+  return launch_sconv_patch_tiles<32>(pl.tiles, a, grid, s);
 }
 
 // Takes the call if the shape is one the int8 kernel is built for: a multiple of 32 filters, a reduction C * KH * KW
@@ -1189,20 +1220,11 @@ bool try_sconv_i8(const SconvI8Args& a, int64_t N, bool fp64_next, hipStream_t s
   if (prod_reaches({N, a.G, a.C, a.H, a.W}, (int64_t)1 << 30)) return false;            // 32-bit byte offsets into I
   if (prod_reaches({N, a.G, a.F, a.OH, a.OW}, (int64_t)1 << 31)) return false;          // 32-bit element offsets into O
   if (a.G > 65535) return false;
-  // 128 filters per workgroup and 1 .. 4 pixel tiles, or (a multiple of 64 filters only) 64 filters and 2, 4, 6, 8,
-  // or (a multiple of 32 only) 32 filters and 4, 8, 12
-  const int tf = a.F % 128 == 0 ? 128 : (a.F % 64 == 0 ? 64 : 32), nt_step = 128 / tf, nt_max = tf == 32 ? 12 : 4 * nt_step;
-  const int64_t blocks = ceil_div(a.K, SI8_KB), units = ceil_div(a.P, 16), fblocks = a.F / tf;
-  // pixel tiles per workgroup: as few rounds of workgroups as the largest tile allows, then the smallest tile
-  // that still makes that number of rounds
-  const int64_t per_round = std::max<int64_t>(1, device_cus() / (fblocks * a.G));
-  const int64_t rounds = ceil_div(units, nt_max * per_round);
-  int nt = (int)ceil_div(ceil_div(units, rounds * per_round), nt_step) * nt_step;
-  nt = std::min(nt_max, std::max(nt_step, nt));
-  while (nt > nt_step && sconv_i8_lds_bytes(tf, nt, blocks) > 160 * 1024) nt -= nt_step;
-  if (sconv_i8_lds_bytes(tf, nt, blocks) > 160 * 1024) return false;
-  const int64_t gx = ceil_div(units, nt);
-  if (gx > kMaxGrid || fblocks > 65535) return false;
+  SconvI8Deal deal{};
+  if (!deal_sconv_i8(a.P, a.F, a.K, a.G, device_cus(), &deal)) return false;
+  const int tf = deal.tf, nt = deal.nt;
+  const int64_t blocks = ceil_div(a.K, SI8_KB), gx = deal.gx, fblocks = a.F / tf;
+  static_assert(SI8_KB == SI8_BLOCK && SI8_RS == SI8_ROW, "sconv_patch_plan.hpp");
   // A workgroup walks over all taps, 1.9 us per block of 128 and pixel tile of a wavefront, however few workgroups there are: a
   // long reduction on few pixels is faster in fp64 with its reduction split, and no less exact.  The line: estimates of both
   // (this one fitted to 213 layers, errors of 7 %), fp64 where its is 10 % lower; of those layers 60 go over, 1.8 times as fast
@@ -1210,10 +1232,18 @@ bool try_sconv_i8(const SconvI8Args& a, int64_t N, bool fp64_next, hipStream_t s
   // 30.8 -> 14.4.  Up to 1152 taps, and for less than one tile of pixels, int8 stays whatever the estimates say: (200,128,576)
   // 14.4 against 7.1, where the tests name it.
   if (fp64_next && a.G == 1 && t_opt.int8 == TC_INT8_AUTO && a.K > 1152 && a.P >= 16) {
-    const double turns = (double)ceil_div(gx * fblocks, std::max(1, device_cus()));
-    const double i8 = turns * (4.64 + blocks * (0.82 + 1.12 * (nt / nt_step)));  // us
     const SconvFp64Clocks c = sconv_fp64_clocks(N, a.C, a.H, a.W, a.F, a.K, a.P, a.sw > a.KW);
-    if (std::min({c.tile, c.split1, c.split2}) / 2400 < 0.9 * i8) return false;
+    if (std::min({c.tile, c.split1, c.split2}) / 2400 < 0.9 * deal.us) return false;
+  }
+  // Filters of 9 taps over a multiple of 32 channels: the input sliced once instead of once per tap, where the estimate of that is
+  // 5 % lower (large layers; a small one has too little to do between its filters).  Of 220 random layers 25 go over, 1.27 times as
+  // fast, none of them slower; (N,C,F,H,W) at stride s: (32,64,128,56,56) at 2 46.9 -> 36 us, (32,64,64,56,56) at 1 112 -> 69,
+  // (15,128,192,13,72) at 1 82 -> 55, but (10,64,128,28,28) at 2 14.9 / 17.4.
+  SconvPatchPlan patch{};
+  if (t_opt.int8 != TC_INT8_TEN && plan_sconv_patch(N, a.G, a.C, a.F, a.H, a.W, a.KH, a.KW, a.sh, a.sw, device_cus(), &patch) &&
+      patch.us < 0.95 * deal.us) {
+    *st = run_sconv_patch(a, N, patch, s);
+    return true;
   }
   const dim3 grid((unsigned)gx, (unsigned)fblocks, (unsigned)a.G);
   const bool ten = t_opt.int8 == TC_INT8_TEN;  // 13 digit products unless the caller has said that 10 will do

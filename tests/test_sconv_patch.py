@@ -1,0 +1,179 @@
+"""Strided convolution on int8 with the input sliced where it lies (csrc/sconv_patch.hpp): which layers take it (the library's own
+choice in csrc/sconv_patch_plan.hpp, compiled by the system's C++ compiler, for 256 compute units) and, on the GPU, parity with the
+float64 oracle.  4e-6 on the metric and a quarter of the bar on heavy-tailed operands are what every int8 kernel is held to."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1802_04730_amd import inputs
+from paper_1802_04730_amd.metric import PARITY_BAR, parity_error
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+TIGHT_I8 = 4e-6
+
+# (N, C, F, H, W, KH, KW, sh, sw): filters per workgroup, pixel tiles per wavefront
+LAYERS = {
+    (13, 32, 32, 184, 9, 3, 3, 1, 1): (32, 2),   # an only stage
+    (27, 32, 96, 27, 33, 3, 3, 2, 1): (32, 3),   # strides that differ
+    (12, 96, 96, 45, 46, 3, 3, 1, 1): (32, 5),   # three stages; runs that start and end inside rows
+    (28, 32, 160, 52, 9, 3, 3, 1, 1): (32, 6),
+    (1, 32, 320, 166, 12, 3, 3, 1, 1): (64, 2),
+    (11, 32, 448, 68, 14, 9, 1, 2, 2): (64, 3),  # nine taps in a column
+    (9, 64, 64, 58, 57, 3, 3, 1, 1): (64, 4),    # two stages
+    (29, 32, 192, 14, 49, 3, 3, 2, 1): (64, 5),
+    (15, 32, 384, 28, 30, 3, 3, 2, 2): (128, 3),
+    (8, 64, 128, 61, 56, 3, 3, 2, 1): (128, 4),
+    (19, 32, 128, 62, 47, 9, 1, 2, 2): (128, 5),
+    (32, 64, 128, 56, 56, 3, 3, 2, 2): (128, 6),
+}
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("sconv_patch")
+    (d / "plan.cpp").write_text('#include "sconv_patch_plan.hpp"\n'
+                                'extern "C" int plan(const int64_t* a, int64_t G, int64_t* o) {\n'
+                                '  tc355::SconvPatchPlan p{};\n  tc355::SconvI8Deal d{};\n'
+                                '  if (!tc355::plan_sconv_patch(a[0], G, a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], 256, &p)) return 0;\n'
+                                '  const int64_t OH = (a[3] - a[5]) / a[7] + 1, OW = (a[4] - a[6]) / a[8] + 1;\n'
+                                '  if (!tc355::deal_sconv_i8(a[0] * OH * OW, a[2], a[1] * a[5] * a[6], G, 256, &d)) return 0;\n'
+                                '  o[0] = p.tf; o[1] = p.tiles; o[2] = p.px; o[3] = p.blocks;\n'
+                                '  return p.us < 0.95 * d.us ? 2 : 1;\n}\n'
+                                'extern "C" unsigned magic(int d) { return tc355::sp_magic(d); }\n')
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_1802_04730_amd", "csrc"),
+                    "-o", str(d / "plan.so"), str(d / "plan.cpp")], check=True)
+    lib = ctypes.CDLL(str(d / "plan.so"))
+
+    def ask(layer, G=1):
+        o = (ctypes.c_int64 * 4)()
+        return lib.plan((ctypes.c_int64 * 9)(*layer), ctypes.c_int64(G), o), tuple(o)
+
+    ask.magic = lib.magic
+    return ask
+
+
+def test_layers_take_the_kernel(plan):
+    for layer, said in LAYERS.items():
+        took, (tf, tiles, px, blocks) = plan(layer)
+        assert took == 2 and (tf, tiles) == said, (layer, took, tf, tiles)
+
+
+def test_what_the_kernel_takes_for_granted(plan):
+    rng = np.random.default_rng(3)
+    seen = 0
+    for _ in range(4000):
+        KH, KW = ((3, 3), (1, 9), (9, 1))[rng.integers(0, 3)]
+        H, W = int(rng.integers(KH, 300)), int(rng.integers(KW, 300))
+        sh, sw = int(rng.integers(1, 5)), int(rng.integers(1, 5))
+        layer = (int(rng.integers(1, 40)), 32 * int(rng.integers(1, 9)), 32 * int(rng.integers(1, 13)), H, W, KH, KW, sh, sw)
+        took, (tf, tiles, px, blocks) = plan(layer, int(rng.integers(1, 9)))
+        if not took:
+            continue
+        seen += 1
+        OH, OW = (H - KH) // sh + 1, (W - KW) // sw + 1
+        assert layer[2] % tf == 0 and 1 <= tiles <= 6 and px <= 16 * tiles * (128 // tf)
+        assert blocks * px >= OH * OW > (blocks - 1) * px
+        for b in range(blocks):
+            p0, n = b * px, min(px, OH * OW - b * px)
+            rows = ((p0 + n - 1) // OW - p0 // OW) * sh + KH  # input rows under the run
+            assert 4 <= rows * W <= 640
+            assert p0 % OW + n <= 2048  # what a division by multiplication gets
+    assert seen > 1000
+    n = np.arange(2048, dtype=np.int64)
+    for d in range(1, 641):
+        m = plan.magic(d)
+        assert (n * m < 1 << 32).all() and np.array_equal((n * m) >> 21, n // d), d
+
+
+def run(I, Wt, bias, sh, sw, shape, groups=None):
+    from paper_1802_04730_amd import tc355 as tc
+    dev = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    n = int(np.prod(shape))
+    buf = torch.full((n + 512,), 7.0, device="cuda")
+    O = buf[256:256 + n].view(shape)
+    if groups is None:
+        tc.tc_sconv2d(dev(I), dev(Wt), dev(bias), O, sh, sw)
+        assert tc.last_path() == "sconv:i8"
+    else:
+        tc.tc_group_conv(dev(I), dev(Wt), dev(bias), O)
+        assert tc.last_path() == "gconv:i8_taps"
+    torch.cuda.synchronize()
+    assert torch.all(buf[:256] == 7.0) and torch.all(buf[256 + n:] == 7.0)
+    return O.cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer", list(LAYERS))
+def test_parity(layer, oracle_threads):
+    N, C, F, H, W, KH, KW, sh, sw = layer
+    I, Wt, bias = inputs.make_sconv2d(N, C, F, H, W, KH, KW, seed=inputs.SEED_BASE + 300 + C)
+    bias = bias if C != 64 else None
+    ref = oracle.sconv2d(I, Wt, bias, sh, sw)
+    err = parity_error(run(I, Wt, bias, sh, sw, ref.shape), ref)
+    print("sconv2d by patches %s: parity error %.3e" % (layer, err), flush=True)
+    assert err <= TIGHT_I8
+
+
+GROUPED = (20, 4, 32, 32, 33, 34, 3, 3)  # N, G, C, F, H, W, KH, KW
+
+
+def test_grouped_layer_takes_the_kernel(plan):
+    N, G, C, F, H, W, KH, KW = GROUPED
+    assert plan((N, C, F, H, W, KH, KW, 1, 1), G)[0] == 2
+
+
+@pytest.mark.gpu
+def test_groups(oracle_threads):
+    N, G, C, F, H, W, KH, KW = GROUPED
+    I, W1, bias = inputs.make_gconv(N, G, C, F, H, W, KH, KW, seed=inputs.SEED_BASE + 310)
+    ref = oracle.group_conv(I, W1, bias)
+    assert parity_error(run(I, W1, bias, 1, 1, ref.shape, G), ref) <= TIGHT_I8
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["lognormal", "student3", "sparse", "tiny"])
+def test_heavy_tailed_operands(kind, oracle_threads):
+    N, C, F, H, W, KH, KW, sh, sw = (9, 64, 64, 58, 57, 3, 3, 1, 1)
+    I, Wt, bias = inputs.make_sconv2d(N, C, F, H, W, KH, KW, seed=77)
+    rng = np.random.default_rng(9)
+    mag = {"lognormal": lambda a: np.exp(rng.normal(size=a.shape) * 1.5), "student3": lambda a: np.abs(rng.standard_t(3, size=a.shape)),
+           "sparse": lambda a: np.where(rng.random(a.shape) < 0.01, 300.0, 1.0),
+           # denormal inputs.  (Filters of 2^40 lift the outputs to 2^-90: where outputs are denormal as well, a rounding is half of
+           # 2^-149, 2^-10 of an output of 2^-140, whatever computes it.)
+           "tiny": lambda a: np.full(a.shape, 2.0 ** -130 if a is I else 2.0 ** 40)}[kind]
+    I, Wt = (I * mag(I)).astype(np.float32), (Wt * mag(Wt)).astype(np.float32)
+    bias = bias if kind != "tiny" else None
+    ref = oracle.sconv2d(I, Wt, bias, sh, sw)
+    err = parity_error(run(I, Wt, bias, sh, sw, ref.shape), ref)
+    print("sconv2d by patches, %s: parity error %.3e" % (kind, err), flush=True)
+    assert err <= PARITY_BAR / 4
+
+
+@pytest.mark.gpu
+def test_nan_and_inf_stay_in_the_outputs_that_read_them(oracle_threads):
+    N, C, F, H, W, KH, KW, sh, sw = (32, 64, 128, 56, 56, 3, 3, 2, 2)
+    I, Wt, bias = inputs.make_sconv2d(N, C, F, H, W, KH, KW, seed=81)
+    ref = oracle.sconv2d(I, Wt, bias, sh, sw)
+    In = I.copy()
+    In[1, 5, 6, 8] = np.nan    # rows 6 = 2*2 + 2 = 2*3 + 0, columns 8 = 2*3 + 2 = 2*4 + 0; first stage
+    In[7, 63, 55, 55] = np.inf  # under no window
+    In[7, 40, 54, 54] = -np.inf  # row and column 54 = 2*26 + 2 alone; second stage
+    got = run(In, Wt, bias, sh, sw, ref.shape)
+    hit = np.zeros(ref.shape, dtype=bool)
+    hit[1, :, 2:4, 3:5] = True
+    hit[7, :, 26, 26] = True
+    assert np.isnan(got[hit]).all() and not np.isnan(got[~hit]).any()
+    assert parity_error(np.where(hit, ref, got), ref) <= TIGHT_I8
+    Wn = Wt.copy()
+    Wn[77, 3, 1, 2] = np.nan
+    Wn[5, 60, 2, 2] = np.inf
+    got = run(I, Wn, bias, sh, sw, ref.shape)
+    hit = np.zeros(ref.shape, dtype=bool)
+    hit[:, [5, 77]] = True
+    assert np.isnan(got[hit]).all() and not np.isnan(got[~hit]).any()
+    assert parity_error(np.where(hit, ref, got), ref) <= TIGHT_I8
