@@ -21,9 +21,8 @@
 //     clocks, others 9 and more).  The 13 digit products of a tile are summed over all taps of the stage before they are
 //     scaled: 9 taps x 32 channels instead of 128 taps.
 // The arithmetic is that of sconv_i8.hpp (32-bit fixed point, four signed 8-bit digits, the products with k + l >= 2 summed
-// exactly in int32, fp64 over the stages, one rounding), but that scales are powers of two: what is above 2^-7 of the largest
-// magnitude is not rounded at all, which more than makes up for scales that many more elements share (errors on the metric
-// 1.1e-7 .. 1.8e-7 against 1.9e-7 .. 3.5e-7 on Gaussian data, 7e-7 .. 8e-7 on heavy-tailed).  Inf and NaN reach what they reach there: a position that holds one is
+// exactly in int32, fp64 over the stages, one rounding); what is above 2^-7 of the largest magnitude is not rounded, so scales that
+// many elements share cost little (errors on the metric 1.1e-7 .. 1.8e-7 on Gaussian data, 7e-7 .. 8e-7 on heavy-tailed).  Inf and NaN reach what they reach there: a position that holds one is
 // left out of the patch (and of its scale) and marked, and pixels whose window touches a mark become NaN; a filter that holds one
 // gives NaN everywhere.
 // (N,C,F,H,W) at stride s, sconv_i8.hpp -> this, us: (32,64,128,56,56) at 2 46.7 -> 36.0, (32,64,64,56,56) at 1 112 -> 69,
@@ -57,14 +56,6 @@ constexpr int SP_MAXIMA = SP_RING + SP_WAVES * 2 * SP_RAW;  // [2] largest magni
 constexpr int SP_MARKS = SP_MAXIMA + 16;       // [position] holds Inf or NaN in some channel
 constexpr int SP_LDS_BYTES = SP_MARKS + SP_POSITIONS;
 static_assert(SP_LDS_BYTES <= 160 * 1024, "one workgroup per compute unit");
-
-// The power of two that takes the largest magnitude (its bits) just below the largest number of four signed digits, 0x7F7F7F7F,
-// and its inverse: elements above 2^-7 of the maximum become integers without rounding.
-__device__ __forceinline__ void sp_scales(unsigned mbits, double& scale, double& inverse) {
-  const int e = (int)max((mbits + 0x10101u) >> 23, 1u);  // (significands above 0xFEFEFE count as the next binade's)
-  scale = __hiloint2double((1023 + 157 - e) << 20, 0);
-  inverse = i8_nonfinite(mbits) ? __longlong_as_double(0x7ff8000000000000ll) : __hiloint2double((1023 - 157 + e) << 20, 0);
-}
 
 // n / d for n and d below 2^12 and magic = sp_magic(d)
 __device__ __forceinline__ int sp_div(int n, unsigned magic) { return (int)(((unsigned)n * magic) >> SP_MAGIC_SHIFT); }
@@ -221,7 +212,7 @@ __global__ __launch_bounds__(SP_THREADS, 1) void sconv_patch_kernel(SconvPatchAr
     }
     if (tid == 0) maxima[t ^ 1] = 0;  // read a stage ago, written behind the next barrier
     double pscale, pinverse;
-    sp_scales(m, pscale, pinverse);
+    gi8_scales<2>(m, pscale, pinverse);
 #pragma unroll
     for (int j = 0; j < SP_UNITS; j++)
       if (j < rounds) {
@@ -256,7 +247,7 @@ __global__ __launch_bounds__(SP_THREADS, 1) void sconv_patch_kernel(SconvPatchAr
       v = max(v, __shfl_xor(v, 16));
       v = max(v, __shfl_xor(v, 32));
       double scale, inverse;
-      sp_scales((unsigned)v, scale, inverse);
+      gi8_scales<2>((unsigned)v, scale, inverse);
       factor = inverse * pinverse * 16777216.0;  // 2^24: the weight of the lowest kept diagonal
 #pragma unroll
       for (int s = 0; s < STEPS; s++)
