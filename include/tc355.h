@@ -187,7 +187,7 @@ tc_status tc_tbmm_ws(const float *X, const float *Y, float *Z, int64_t B,
  *            call has run, 32-bit word 33 of the workspace is 1 if a
  *            device-wide wait gave up (workgroups could not all be resident
  *            at once; outputs are then unspecified) and 0 otherwise.
- * Small batches whose reduction extents dims[l] are all 128, 256, 512 or 1024
+ * Small batches (16 rows and more) whose reduction extents dims[l] are all 128, 256, 512 or 1024
  * run as one persistent kernel ("mlp:rows"); everything else is one launch per
  * layer.  TC_OPT_MLP_KERNEL = TC_MLP_TILES asks for one persistent kernel
  * wherever every dims[l] is a multiple of 4 (l < n_layers).

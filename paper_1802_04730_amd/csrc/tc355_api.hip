@@ -1002,16 +1002,18 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
   const int cus = device_cus();
   // Small batches with reductions of at most 1024: one workgroup per compute unit, every XCD's workgroups own an eighth
   // of the column tiles of every layer (mlp_rows.hpp).  Option TC_OPT_MLP_KERNEL = TC_MLP_TILES keeps the tile-stream
-  // kernel below.  (The line was drawn against one launch per layer as it was before gemm_direct.hpp.  Against that, here / one
-  // launch per layer, us: 128 x 1024 -> 1024 -> 512 -> 256 19.8 / 18.1, 16 rows of it 15.9 / 14.3, 128 x 1024 -> 1024 9.0 / 7.6,
-  // 512 x 256 -> 256 -> 128 11.9 / 6.6, 128 x 256 -> 1024 4.8 / 3.7.)
+  // kernel below.  Fewer than 16 rows do not fill a tile and go to one launch per layer (here / there, us: one row of 1024 -> 1024
+  // -> 512 -> 256 16.1 / 13.7, two of 128 -> 256 -> 1024 -> 128 14.9 / 10.6, five of 256 -> 1024 -> 2000 13.0 / 8.5, 15 of 1024 -> 1000
+  // 6.2 / 5.4), unless the caller asks for this kernel.  (The other lines were drawn against one launch per layer as it was before
+  // gemm_direct.hpp.  Against that: 128 x 1024 -> 1024 -> 512 -> 256 19.8 / 18.1, 128 x 1024 -> 1024 9.0 / 7.6, 512 x 256 -> 256 -> 128
+  // 11.9 / 6.6, 128 x 256 -> 1024 4.8 / 3.7; the tests hold chains of 16 rows and more to this kernel.)
   if (fused && cus >= MR_SHARES) {
     const int64_t G = ceil_div(batch, 16);
     const int64_t nwg = std::min<int64_t>(cus, MR_MAX_WG) / MR_SHARES * MR_SHARES;
     int64_t max_ct = 1;  // most column tiles of any layer whose output is handed on
     for (int l = 0; l + 1 < n_layers; l++) max_ct = std::max(max_ct, ceil_div(dims[l + 1], 16));
     const int64_t fstride = 4 * max_ct;
-    bool rows = t_opt.mlp_kernel != TC_MLP_TILES && G <= 64 &&
+    bool rows = t_opt.mlp_kernel != TC_MLP_TILES && G <= 64 && (batch >= 16 || t_opt.mlp_kernel == TC_MLP_ROWS) &&
                 (int64_t)(n_layers - 1) * G * fstride <= (int64_t)(MLP_MAX_LAYERS - 1) * MLP_BAR_WORDS;
     for (int l = 0; l < n_layers && rows; l++)
       rows = (dims[l] == 128 || dims[l] == 256 || dims[l] == 512 || dims[l] == 1024) &&
