@@ -117,10 +117,11 @@ __device__ __forceinline__ void gi8_absmax4(const f4& v, int& smax, unsigned& um
 }
 __device__ __forceinline__ int gi8_magnitude(int smax, unsigned umax) { return max(max(smax, 0), (int)(umax & 0x7fffffffu)); }
 
-// X sliced once: one workgroup per (block of 128 k, block of 128 rows), thread t = (row t / 4, chunk t % 4).
+// X sliced once: a wavefront per (block of 128 k, block of 128 rows, 16 of the rows), lane l = (row l / 4, chunk l % 4).  (As many
+// workgroups as the chip has units at 128 x 4096: 6.9 us with one of 512 threads per block, of which there are 32.)
 template <int MIND>
-__global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_slice_x_kernel(const float* X, int K, i4* Xd, double* Xinv) {
-  const int tid = threadIdx.x, blk = blockIdx.x, nb = (K + GI8_KB - 1) / GI8_KB;
+__global__ __launch_bounds__(WAVE, 1) void gemm_i8_slice_x_kernel(const float* X, int K, i4* Xd, double* Xinv) {
+  const int tid = threadIdx.x + WAVE * blockIdx.z, blk = blockIdx.x, nb = (K + GI8_KB - 1) / GI8_KB;
   const int64_t rb = blockIdx.y;
   const int xrow = tid >> 2, cx = tid & 3;
   const float* xs = X + (rb * GI8_TN + xrow) * (int64_t)K + (int64_t)blk * GI8_KB + 4 * cx;
