@@ -8,7 +8,7 @@
 // A workgroup owns a strip of rows of X_b and a strip of rows of Y_b -- all of both where they are small, several batch elements
 // where they are smaller still -- and its wavefronts share the strips' 16 x 16 tiles out.  The strips are contiguous runs of
 // memory.  They travel straight to LDS (no registers, no LDS writes), every wavefront requests its part, and one barrier later
-// every wavefront reads what it needs.  Nothing is pipelined inside a workgroup: 34-110 registers and the LDS of one strip pair
+// every wavefront reads what it needs.  Nothing is pipelined inside a workgroup: 24-122 registers and the LDS of one strip pair
 // leave room for several workgroups per compute unit, whose loads, MFMAs and stores cover each other.
 //   * 16-byte pieces from the strip's first element on (4-byte alignment is enough), its last 1 .. 3 elements one by one: nothing
 //     beyond a strip is read.
