@@ -1241,7 +1241,7 @@ bool try_sconv_i8(const SconvI8Args& a, int64_t N, bool fp64_next, hipStream_t s
   }
   // Filters of 9 taps over a multiple of 32 channels: the input sliced once instead of once per tap, where the estimate of that is
   // 5 % lower (large layers; a small one has too little to do between its filters).  Of 220 random layers 25 go over, 1.27 times as
-  // fast, none of them slower; (N,C,F,H,W) at stride s: (32,64,128,56,56) at 2 46.9 -> 36 us, (32,64,64,56,56) at 1 112 -> 69,
+  // fast, none of them slower; (N,C,F,H,W) at stride s: (32,64,128,56,56) at 2 46.9 -> 34.9 us, (32,64,64,56,56) at 1 112 -> 69,
   // (15,128,192,13,72) at 1 82 -> 55, but (10,64,128,28,28) at 2 14.9 / 17.4.
   SconvPatchPlan patch{};
   if (t_opt.int8 != TC_INT8_TEN && plan_sconv_patch(N, a.G, a.C, a.F, a.H, a.W, a.KH, a.KW, a.sh, a.sw, device_cus(), &patch) &&

@@ -177,3 +177,25 @@ def test_nan_and_inf_stay_in_the_outputs_that_read_them(oracle_threads):
     hit[:, [5, 77]] = True
     assert np.isnan(got[hit]).all() and not np.isnan(got[~hit]).any()
     assert parity_error(np.where(hit, ref, got), ref) <= TIGHT_I8
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer,channel,at", [
+    ((32, 64, 128, 56, 56, 3, 3, 2, 2), 19, (7, 9)),   # the second 16 channels of a stage start 16 bytes later at even strides
+    ((32, 64, 128, 56, 56, 3, 3, 2, 2), 48, (55, 1)),  # under no window (rows 0 .. 54)
+    ((9, 64, 64, 58, 57, 3, 3, 1, 1), 31, (57, 56)),
+    ((9, 64, 64, 58, 57, 3, 3, 1, 1), 60, (20, 0)),
+])
+def test_inf_in_the_second_half_of_a_stage(layer, channel, at, oracle_threads):
+    N, C, F, H, W, KH, KW, sh, sw = layer
+    I, Wt, bias = inputs.make_sconv2d(N, C, F, H, W, KH, KW, seed=83)
+    ref = oracle.sconv2d(I, Wt, bias, sh, sw)
+    I[2, channel, at[0], at[1]] = np.inf
+    got = run(I, Wt, bias, sh, sw, ref.shape)
+    hit = np.zeros(ref.shape, dtype=bool)
+    for oh in range(ref.shape[2]):
+        for ow in range(ref.shape[3]):
+            if oh * sh <= at[0] < oh * sh + KH and ow * sw <= at[1] < ow * sw + KW:
+                hit[2, :, oh, ow] = True
+    assert np.isnan(got[hit]).all() and not np.isnan(got[~hit]).any()
+    assert parity_error(np.where(hit, ref, got), ref) <= TIGHT_I8
