@@ -25,7 +25,8 @@
 // order or interleaving), so the kernel is bound by that sum; blocks of 128 instead of 64 halve the per-block scaling work.
 // Per block a thread owns 32 elements of one X row (four lanes per row) and 16
 // of one Y row (eight lanes per row): row maximum across those lanes
-// (data-parallel primitives), scale (a power of two; S / max with 10 products, gi8_scales), digits, and 16-byte (8-byte) LDS writes per digit plane.  The position
+// (data-parallel primitives), scale = S / max by a reciprocal and two Newton
+// steps, digits, and 16-byte (8-byte) LDS writes per digit plane.  The position
 // of a k inside the 64 slots of an MFMA step is free as long as X and Y agree;
 // lanes fetch 16-byte pieces so that four (eight) neighbours read one
 // contiguous 256-byte row piece and still own 16 (8) consecutive slots.  The
@@ -69,29 +70,15 @@ constexpr int GI8_RS = GI8_KB + 32;
 constexpr int GI8_PLANE = GI8_ROWS * GI8_RS;
 constexpr int GI8_LDS_BYTES = 4 * GI8_PLANE + GI8_ROWS * 8;  // four digit planes and the rows' inverse scales (fp64): 124,416 bytes
 static_assert(GI8_LDS_BYTES % 16 == 0 && (4 * GI8_PLANE) % 16 == 0, "16-byte LDS accesses");
-// Scale and inverse scale of a block with largest magnitude bits mbits.
-// MIND = 2 (13 digit products): the power of two that takes the maximum just below the largest number of four signed digits,
-// 0x7F7F7F7F.  Elements above 2^-7 of the maximum then become integers without rounding, and only the others lose anything.
-// MIND = 3 (10 products): S / max, which fills the digits to the last bit, since what the dropped products lose is relative to them
-// (1.1e-6 against 1.1e-5 on the metric); the reciprocal by two Newton steps on the hardware estimate (relative error far below the
-// 2^-31 that keeps rint(max * scale) inside four digits).
-// (13 products with S / max as well: strided convolutions had errors of 1.9e-7 .. 3.5e-7 on the metric, 1.1e-7 .. 2.0e-7 now;
-// (N,M,K) = (128,16384,4096) with a workspace 120.5 -> 117.0 us, strided convolutions 2-4 % faster.)
-template <int MIND>
+// S / max and max / S for a block with largest magnitude bits mbits: the reciprocal by two Newton steps on the
+// hardware estimate (relative error far below the 2^-31 that keeps rint(max * scale) inside four digits).
 __device__ __forceinline__ void gi8_scales(unsigned mbits, double& scale, double& inverse) {
-  if constexpr (MIND == 2) {
-    const int e = (int)max((mbits + 0x10101u) >> 23, 1u);  // (significands above 0xFEFEFE count as the next binade's)
-    scale = __hiloint2double((1023 + 157 - e) << 20, 0);
-    inverse = __hiloint2double((1023 - 157 + e) << 20, 0);
-  } else {
-    const double inv = (double)__uint_as_float(mbits) * I8_INV_FULL;
-    double r = __builtin_amdgcn_rcp(inv);
-    r = __builtin_fma(__builtin_fma(-inv, r, 1.0), r, r);
-    r = __builtin_fma(__builtin_fma(-inv, r, 1.0), r, r);
-    scale = mbits ? r : 1.0;
-    inverse = inv;
-  }
-  if (i8_nonfinite(mbits)) inverse = __longlong_as_double(0x7ff8000000000000ll);
+  const double inv = (double)__uint_as_float(mbits) * I8_INV_FULL;
+  double r = __builtin_amdgcn_rcp(inv);
+  r = __builtin_fma(__builtin_fma(-inv, r, 1.0), r, r);
+  r = __builtin_fma(__builtin_fma(-inv, r, 1.0), r, r);
+  scale = mbits ? r : 1.0;
+  inverse = i8_nonfinite(mbits) ? __longlong_as_double(0x7ff8000000000000ll) : inv;
 }
 
 // MIND: the lowest digit diagonal k + l that is kept: 2 (13 products: what the library uses unless told that 10
@@ -119,7 +106,6 @@ __device__ __forceinline__ int gi8_magnitude(int smax, unsigned umax) { return m
 
 // X sliced once: a wavefront per (block of 128 k, block of 128 rows, 16 of the rows), lane l = (row l / 4, chunk l % 4).  (As many
 // workgroups as the chip has units at 128 x 4096: 6.9 us with one of 512 threads per block, of which there are 32.)
-template <int MIND>
 __global__ __launch_bounds__(WAVE, 1) void gemm_i8_slice_x_kernel(const float* X, int K, i4* Xd, double* Xinv) {
   const int tid = threadIdx.x + WAVE * blockIdx.z, blk = blockIdx.x, nb = (K + GI8_KB - 1) / GI8_KB;
   const int64_t rb = blockIdx.y;
@@ -143,7 +129,7 @@ __global__ __launch_bounds__(WAVE, 1) void gemm_i8_slice_x_kernel(const float* X
   v = max(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
   v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
   double scale, inverse;
-  gi8_scales<MIND>((unsigned)v, scale, inverse);
+  gi8_scales((unsigned)v, scale, inverse);
   i4* dst = Xd + (rb * nb + blk) * (int64_t)(GI8_STEPS * 4 * GI8_THREADS) + (xrow >> 4) * (4 * WAVE) + cx * 16 + (xrow & 15);
 #pragma unroll
   for (int s = 0; s < GI8_STEPS; s++) {
@@ -232,7 +218,7 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_kernel(GemmI8Args p) {
       v = max(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
       v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
       double scale, inverse;
-      gi8_scales<MIND>((unsigned)v, scale, inverse);
+      gi8_scales((unsigned)v, scale, inverse);
 #pragma unroll
       for (int s = 0; s < GI8_STEPS; s++) {
         int y[4][4];
@@ -261,7 +247,7 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_kernel(GemmI8Args p) {
       v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
       v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false));  // row_half_mirror: the other quad
       double scale, inverse;
-      gi8_scales<MIND>((unsigned)v, scale, inverse);
+      gi8_scales((unsigned)v, scale, inverse);
 #pragma unroll
       for (int s = 0; s < GI8_STEPS; s++) {
         int y[2][4];
@@ -427,7 +413,7 @@ __global__ __launch_bounds__(GI8_THREADS, 1) void gemm_i8_presliced_kernel(GemmI
     v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
     v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false));  // row_half_mirror: the other quad
     double scale, inverse;
-    gi8_scales<MIND>((unsigned)v, scale, inverse);
+    gi8_scales((unsigned)v, scale, inverse);
     char* base = gi8p_lds + buf * GP_BUF;
 #pragma unroll
     for (int s = 0; s < GI8_STEPS; s++) {

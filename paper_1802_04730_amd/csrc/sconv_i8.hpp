@@ -6,7 +6,7 @@
 // As a contraction this is the transposed matmul of gemm_i8.hpp: the rows of "X" are the filters (their
 // C * KH * KW taps are contiguous in W), the rows of "Y" are the N * OH * OW output pixels of the whole batch, whose
 // taps are gathered from I, and the reduction runs over the taps in W's order.  The arithmetic is that kernel's: in
-// every block of 128 taps each filter and each pixel is scaled so that its largest magnitude fills 31 bits (gi8_scales),
+// every block of 128 taps each filter and each pixel is scaled so that its largest magnitude maps to 0x7F7F7F7E,
 // rounded to a 32-bit integer and cut into four signed 8-bit digits; the digit products with k + l >= MIND are
 // summed exactly in int32 (v_mfma_i32_16x16x64_i8), scaled back and added over the blocks in fp64; one rounding to
 // fp32.  The last block of a reduction that is not a multiple of 128 is filled with zeros.
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(SI8_THREADS, 1) void sconv_i8_kernel(SconvI8Args p)
     v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
     if constexpr (TPR == 8) v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false));  // row_half_mirror: the other quad
     double inverse;
-    gi8_scales<MIND>((unsigned)v, xscale, inverse);
+    gi8_scales((unsigned)v, xscale, inverse);
     invs[xrow] = inverse;  // the lanes of the row write the same value
   };
   auto slice_x = [&](int u) {  // 16 elements of this thread's u-th step
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(SI8_THREADS, 1) void sconv_i8_kernel(SconvI8Args p)
     for (int i = 0; i < NT; i++) {  // pixels: 4 elements, row shared by 32 threads
       const int row = 16 * i + pl;
       double scale, inverse;
-      gi8_scales<MIND>(rmax[buf * TP + row], scale, inverse);
+      gi8_scales(rmax[buf * TP + row], scale, inverse);
       int y[4];
       gi8_digits4(ry[i], scale, y);
       char* dst = si8_lds + (TF + row) * SI8_RS + ycol;

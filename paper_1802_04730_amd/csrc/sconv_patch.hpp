@@ -60,6 +60,14 @@ constexpr int SP_MARKS = SP_MAXIMA + 16;       // [position] holds Inf or NaN in
 constexpr int SP_LDS_BYTES = SP_MARKS + SP_POSITIONS;
 static_assert(SP_LDS_BYTES <= 160 * 1024, "one workgroup per compute unit");
 
+// The power of two that takes the largest magnitude (its bits) just below the largest number of four signed digits, 0x7F7F7F7F,
+// and its inverse: elements above 2^-7 of the maximum become integers without rounding.
+__device__ __forceinline__ void sp_scales(unsigned mbits, double& scale, double& inverse) {
+  const int e = (int)max((mbits + 0x10101u) >> 23, 1u);  // (significands above 0xFEFEFE count as the next binade's)
+  scale = __hiloint2double((1023 + 157 - e) << 20, 0);
+  inverse = i8_nonfinite(mbits) ? __longlong_as_double(0x7ff8000000000000ll) : __hiloint2double((1023 - 157 + e) << 20, 0);
+}
+
 // n / d for n and d below 2^12 and magic = sp_magic(d)
 __device__ __forceinline__ int sp_div(int n, unsigned magic) { return (int)(((unsigned)n * magic) >> SP_MAGIC_SHIFT); }
 
@@ -216,7 +224,7 @@ __global__ __launch_bounds__(SP_THREADS, 1) void sconv_patch_kernel(SconvPatchAr
     }
     if (tid == 0) maxima[t ^ 1] = 0;  // read a stage ago, written behind the next barrier
     double pscale, pinverse;
-    gi8_scales<2>(m, pscale, pinverse);
+    sp_scales(m, pscale, pinverse);
 #pragma unroll
     for (int j = 0; j < SP_UNITS; j++)
       if (j < rounds) {
@@ -251,7 +259,7 @@ __global__ __launch_bounds__(SP_THREADS, 1) void sconv_patch_kernel(SconvPatchAr
       v = max(v, __shfl_xor(v, 16));
       v = max(v, __shfl_xor(v, 32));
       double scale, inverse;
-      gi8_scales<2>((unsigned)v, scale, inverse);
+      sp_scales((unsigned)v, scale, inverse);
       factor = inverse * pinverse * 16777216.0;  // 2^24: the weight of the lowest kept diagonal
 #pragma unroll
       for (int s = 0; s < STEPS; s++)

@@ -823,8 +823,7 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
       i4* xd = static_cast<i4*>(workspace);
       double* xinv = reinterpret_cast<double*>(static_cast<char*>(workspace) + rblocks * nb * GI8_XD_BYTES);
       const dim3 slices((unsigned)nb, (unsigned)rblocks, GI8_TN / 16);
-      if (ten) gemm_i8_slice_x_kernel<3><<<slices, dim3(WAVE), 0, s>>>(X, (int)K, xd, xinv);
-      else gemm_i8_slice_x_kernel<2><<<slices, dim3(WAVE), 0, s>>>(X, (int)K, xd, xinv);
+      gemm_i8_slice_x_kernel<<<slices, dim3(WAVE), 0, s>>>(X, (int)K, xd, xinv);
       const tc_status st = launch_status();
       if (st != TC_OK) return st;
       g.Xd = xd; g.Xinv = xinv;
