@@ -74,22 +74,20 @@ struct SconvI8Geom {
   static_assert(INVS % 16 == 0 && RMAX % 16 == 0 && TABLE % 16 == 0, "16-byte LDS accesses");
 };
 
+// The whole of a workgroup: TF filters from f0 on of group grp against the pixels p0 .. pend - 1 of the batch, 16 * NT at most.
 template <int TF, int NT, int MIND>
-__global__ __launch_bounds__(SI8_THREADS, 1) void sconv_i8_kernel(SconvI8Args p) {
+__device__ __forceinline__ void sconv_i8_block(const SconvI8Args& p, char* si8_lds, int p0, int pend, int f0, int grp) {
   static_assert(MIND == 2 || MIND == 3, "13 or 10 digit products");
   using Gm = SconvI8Geom<TF, NT>;
   constexpr int TP = Gm::TP, PLANE = Gm::PLANE, FT = Gm::FT, PG = Gm::PG, NTW = Gm::NTW, TPR = Gm::TPR, XS = Gm::XS;
   constexpr bool XALL = Gm::XTHREADS == SI8_THREADS;
-  extern __shared__ __attribute__((aligned(16))) char si8_lds[];
   const int tid = threadIdx.x;
   const int lane = tid & (WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
   const int r16 = lane & 15, q = lane >> 4;
   const int K = p.K, nb = (K + SI8_KB - 1) / SI8_KB;
-  const int f0 = blockIdx.y * TF;
-  const int p0 = blockIdx.x * TP;
   const int OHW = p.OH * p.OW;
-  const int G = p.G, grp = blockIdx.z;
+  const int G = p.G;
   double* invs = reinterpret_cast<double*>(si8_lds + Gm::INVS);
   unsigned* rmax = reinterpret_cast<unsigned*>(si8_lds + Gm::RMAX);
   unsigned* table = reinterpret_cast<unsigned*>(si8_lds + Gm::TABLE);
@@ -118,7 +116,7 @@ __global__ __launch_bounds__(SI8_THREADS, 1) void sconv_i8_kernel(SconvI8Args p)
   unsigned ybase[NT];  // byte offset of the pixel's first input element
 #pragma unroll
   for (int i = 0; i < NT; i++) {
-    const int pi = min(p0 + 16 * i + pl, p.P - 1);  // pixels past the end repeat the last one (never stored)
+    const int pi = min(p0 + 16 * i + pl, pend - 1);  // pixels past the end repeat the last one (never stored)
     const int img = pi / OHW, rem = pi - img * OHW, oh = rem / p.OW, ow = rem - oh * p.OW;
     ybase[i] = 4u * (unsigned)(((img * G + grp) * p.C * p.H + oh * p.sh) * p.W + ow * p.sw);
   }
@@ -307,7 +305,7 @@ __global__ __launch_bounds__(SI8_THREADS, 1) void sconv_i8_kernel(SconvI8Args p)
       for (int v = 0; v < 4; v++) ostage[(16 * ft + r16) * OS + 16 * (pg + PG * i) + 4 * q + v] = (float)(acc[i][v] + bz);
     if (tid < TP) {
       const int pi = p0 + tid, img = pi / OHW, rem = pi - img * OHW;
-      pxoff[tid] = pi < p.P ? (img * G + grp) * p.F * OHW + rem : -1;
+      pxoff[tid] = pi < pend ? (img * G + grp) * p.F * OHW + rem : -1;
     }
   }
   __syncthreads();
@@ -315,6 +313,12 @@ __global__ __launch_bounds__(SI8_THREADS, 1) void sconv_i8_kernel(SconvI8Args p)
     const int fl = idx / TP, px = idx - fl * TP, po = pxoff[px];
     if (po >= 0) store_stream(p.O + (int64_t)po + (int64_t)(f0 + fl) * OHW, ostage[fl * OS + px]);
   }
+}
+
+template <int TF, int NT, int MIND>
+__global__ __launch_bounds__(SI8_THREADS, 1) void sconv_i8_kernel(SconvI8Args p) {
+  extern __shared__ __attribute__((aligned(16))) char si8_lds[];
+  sconv_i8_block<TF, NT, MIND>(p, si8_lds, blockIdx.x * (16 * NT), p.P, blockIdx.y * TF, blockIdx.z);
 }
 
 }  // namespace tc355

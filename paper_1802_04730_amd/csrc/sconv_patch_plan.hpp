@@ -18,6 +18,12 @@ constexpr int SP_MAGIC_SHIFT = 21;
 inline unsigned sp_magic(int d) { return ((1u << SP_MAGIC_SHIFT) + (unsigned)d - 1) / (unsigned)d; }
 
 constexpr int SI8_BLOCK = 128, SI8_ROW = SI8_BLOCK + 32;  // taps per block of sconv_i8.hpp, bytes of their digits in LDS
+// LDS that tf filters, so many tiles of 16 pixels and the table of so many blocks of taps take there
+inline int64_t sconv_i8_lds(int64_t tf, int64_t tiles, int64_t blocks) {
+  return (tf + 16 * tiles) * (4 * SI8_ROW + 8) + 2 * 16 * tiles * 4 + blocks * SI8_BLOCK * 4;
+}
+// tiles at a time of a workgroup of sconv_patch.hpp that does its run by taps
+constexpr int sp_redo_tiles(int tf) { return tf == 128 ? 3 : tf == 64 ? 4 : 8; }
 
 struct SconvI8Deal {
   int tf, nt;  // filters, tiles of 16 pixels per workgroup
@@ -35,9 +41,8 @@ inline bool deal_sconv_i8(int64_t P, int64_t F, int64_t K, int64_t G, int cus, S
   const int64_t rounds = ceil_div(units, most * per_round);
   int nt = (int)ceil_div(ceil_div(units, rounds * per_round), step) * step;
   nt = std::min(most, std::max(step, nt));
-  auto lds = [&](int tiles) { return (tf + 16 * tiles) * (4 * SI8_ROW + 8) + 2 * 16 * tiles * 4 + blocks * SI8_BLOCK * 4; };
-  while (nt > step && lds(nt) > 160 * 1024) nt -= step;
-  if (lds(nt) > 160 * 1024) return false;
+  while (nt > step && sconv_i8_lds(tf, nt, blocks) > 160 * 1024) nt -= step;
+  if (sconv_i8_lds(tf, nt, blocks) > 160 * 1024) return false;
   d->tf = tf; d->nt = nt;
   d->gx = ceil_div(units, nt);
   if (d->gx > 2147483647 || fblocks > 65535) return false;
@@ -60,6 +65,8 @@ inline bool plan_sconv_patch(int64_t N, int64_t G, int64_t C, int64_t F, int64_t
   if (KH * KW != SP_TAPS || C % 32 != 0 || F % 32 != 0 || KH * W > SP_POSITIONS || H * W >= (1 << 24) || cus <= 0) return false;
   const int64_t OH = (H - KH) / sh + 1, OW = (W - KW) / sw + 1, OHW = OH * OW, tf = F % 128 == 0 ? 128 : F % 64 == 0 ? 64 : 32, pg = 128 / tf;
   if (F / tf > 65535 || G > 65535) return false;
+  const int64_t taps_lds = sconv_i8_lds(tf, sp_redo_tiles((int)tf), ceil_div(SP_TAPS * C, SI8_BLOCK));
+  if (taps_lds > 160 * 1024) return false;  // (from 1376 channels on at 128 filters, 2240 at 64, 1664 at 32)
   bool any = false;
   for (int64_t tiles = 2; tiles <= SP_MAX_TILES; tiles++) {  // (with one tile the estimate never wins)
     const int64_t most = 16 * tiles * pg;

@@ -1181,11 +1181,13 @@ template <int TF, int NTW>
 tc_status launch_sconv_patch(const SconvPatchArgs& a, dim3 grid, hipStream_t s) {
   static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
   if (!lds_ok.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(sconv_patch_kernel<TF, NTW>), hipFuncAttributeMaxDynamicSharedMemorySize, SP_LDS_BYTES) != hipSuccess)
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(sconv_patch_kernel<TF, NTW>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
       return TC_ERR_LAUNCH;
     lds_ok.store(1, std::memory_order_release);
   }
-  sconv_patch_kernel<TF, NTW><<<grid, dim3(SP_THREADS), SP_LDS_BYTES, s>>>(a);
+  const size_t lds = std::max<size_t>(SP_LDS_BYTES, SconvI8Geom<TF, sp_redo_tiles(TF)>::lds_bytes(ceil_div(a.e.K, SI8_KB)));
+  if (lds > 160 * 1024) return TC_ERR_LAUNCH;  // (the plan has checked)
+  sconv_patch_kernel<TF, NTW><<<grid, dim3(SP_THREADS), lds, s>>>(a);
   return launch_status();
 }
 
@@ -1202,8 +1204,7 @@ tc_status launch_sconv_patch_tiles(int tiles, const SconvPatchArgs& a, dim3 grid
 
 tc_status run_sconv_patch(const SconvI8Args& e, int64_t N, const SconvPatchPlan& pl, hipStream_t s) {
   SconvPatchArgs a{};
-  a.I = e.I; a.Wt = e.Wt; a.bias = e.bias; a.O = e.O;
-  a.C = e.C; a.F = e.F; a.H = e.H; a.W = e.W; a.KH = e.KH; a.KW = e.KW; a.sh = e.sh; a.sw = e.sw; a.OH = e.OH; a.OW = e.OW; a.G = e.G;
+  a.e = e;
   a.px = pl.px; a.blocks = pl.blocks;
   a.ow_magic = sp_magic(e.OW); a.kw_magic = sp_magic(e.KW);
   const dim3 grid((unsigned)(N * pl.blocks), (unsigned)(e.F / pl.tf), (unsigned)e.G);

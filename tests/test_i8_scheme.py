@@ -223,7 +223,7 @@ def test_digit_decomposition_round_trips():
     assert FULL + 1 <= 0x7F7F7F7F
 
 
-def emulate_tmm(X, Y, block=128, min_diagonal=3):
+def emulate_tmm(X, Y, block=128, min_diagonal=3, rounded=True):
     """The transposed matmul's variant of the scheme: every row of X and of Y is scaled on its own in every block of
     128 reduction indices; the blocks' exact integer sums are scaled back and added in float64."""
     N, K = X.shape
@@ -242,7 +242,7 @@ def emulate_tmm(X, Y, block=128, min_diagonal=3):
                     assert np.abs(part).max() < 2 ** 21        # 128 terms of 127^2
                     total = total + part.astype(object) * (256 ** (k + l))
         out += total.astype(np.float64) / (sx[:, None] * sy[None, :])
-    return out.astype(np.float32).astype(np.float64)
+    return out.astype(np.float32).astype(np.float64) if rounded else out
 
 
 def test_transposed_matmul_in_blocks_of_128_with_ten_products():
@@ -298,3 +298,84 @@ def test_strided_convolution_as_a_transposed_matmul_over_gathered_taps():
     got = (got + bias[:, None].astype(np.float64)).reshape(F, N, OH, OW).transpose(1, 0, 2, 3)
     err = parity_error(got, ref)
     assert err <= 1e-6, err
+
+
+def power_scale(m):
+    """The scale of the convolution by patches: the power of two that takes the largest magnitude m (> 0) to at most 0x7F7F7F00,
+    from the bits of m; and the binade it is made for."""
+    bits = np.asarray(m, dtype=np.float32).view(np.uint32).astype(np.int64)
+    e = np.maximum((bits + 0x10101) >> 23, 1)
+    return np.ldexp(1.0, (157 - e).astype(int)), e
+
+
+SPREAD = 3  # (restated: the test does not read the kernel's header)
+
+
+def emulate_patch(I, Wt, sh, sw, px):
+    """The convolution by patches (3 x 3 filters): runs of px pixels of an image, the input rows under a run with one scale per 32 channels,
+    filters with one per 288 taps, 13 products -- or, where such a scale is taken for more than 2^3 times the binade of the largest element of
+    some pixel's window or some filter, in either half of the channels, the run with the scales of blocks of 128 taps.  Returns
+    float64 sums [F, OH, OW], not rounded, and the number of runs of either kind."""
+    C, H, W = I.shape
+    F, OH, OW = Wt.shape[0], (H - 3) // sh + 1, (W - 3) // sw + 1
+    out, runs = np.zeros((F, OH * OW)), [0, 0]
+    for p0 in range(0, OH * OW, px):
+        pixels = np.arange(p0, min(p0 + px, OH * OW))
+        oh, ow = pixels // OW, pixels % OW
+        taps = np.stack([I[:, sh * h:sh * h + 3, sw * w:sw * w + 3] for h, w in zip(oh, ow)])  # [pixels, C, 3, 3]
+        total, failed = np.zeros((F, len(pixels))), False
+        for c0 in range(0, C, 32):
+            patch, t, w = I[c0:c0 + 32, sh * oh[0]:sh * oh[-1] + 3], taps[:, c0:c0 + 32], Wt[:, c0:c0 + 32]
+            scale, e = power_scale(np.abs(patch).max())
+            wm = np.abs(w).max(axis=(1, 2, 3))
+            wscale, we = power_scale(np.where(wm > 0, wm, 1.0))
+            for h in (slice(0, 16), slice(16, 32)):
+                own, wown = np.abs(t[:, h]).max(axis=(1, 2, 3)), np.abs(w[:, h]).max(axis=(1, 2, 3))
+                failed |= bool((e > power_scale(own)[1] + SPREAD)[own > 0].any() or (we > power_scale(wown)[1] + SPREAD)[wown > 0].any())
+            if failed:
+                break
+            dx = digits(np.rint(w.astype(np.float64) * wscale[:, None, None, None]).astype(np.int64).reshape(F, -1))
+            dy = digits(np.rint(t.astype(np.float64) * scale).astype(np.int64).reshape(len(pixels), -1))
+            stage = sum((dx[k].astype(np.float64) @ dy[l].astype(np.float64).T) * 256.0 ** (k + l) for k in range(4) for l in range(4) if k + l >= 2)
+            total += stage / (wscale[:, None] * scale)
+        runs[failed] += 1
+        out[:, pixels] = emulate_tmm(Wt.reshape(F, -1), taps.reshape(len(pixels), -1), min_diagonal=2, rounded=False) if failed else total
+    return out.reshape(F, OH, OW), runs
+
+
+@pytest.mark.parametrize("kind,by_taps", [
+    ("gauss", "none"), ("relu", "none"), ("an unread element", "some"), ("a dim region", "all"), ("dim by five", "none"), ("a channel", "some"),
+    ("a filter", "all"), ("zeros", "none")])
+def test_convolution_by_patches_holds_every_output_to_its_own_taps(kind, by_taps):
+    """Whatever else a patch holds: an output is off by no more than what one scale per half of its own window, 2^3 times too coarse,
+    and one per half of its filter would do to it (16 channels; K * 2^-27.9 * the two maxima), or by what blocks of 128 taps would
+    (K * 2^-30.5).  Ordinary data is done by patches throughout."""
+    I, Wt, _ = inputs.make_sconv2d(1, 64, 24, 17, 20, 3, 3, seed=31)
+    I = I[0]
+    if kind == "relu":
+        I = np.maximum(I, 0)
+    elif kind == "an unread element":
+        I[5, 9, 19] = 1e6  # stride 2: columns 0 .. 18 are read
+    elif kind == "a dim region":
+        I[:, :, 9:] *= np.float32(1e-5)
+    elif kind == "dim by five":
+        I[:, :, 9:] *= np.float32(0.2)
+    elif kind == "a channel":
+        I[40, 3, 3], Wt[:, 40] = 1e8, 0.0
+    elif kind == "a filter":
+        Wt[3, 16:32] *= np.float32(1e-4)
+    elif kind == "zeros":
+        I[:16, :, :8], Wt[5, 32:48] = 0.0, 0.0
+    got, runs = emulate_patch(I, Wt, 2, 2, 24)
+    assert {"none": runs[1] == 0, "all": runs[0] == 0, "some": min(runs) > 0}[by_taps], runs
+    ref = oracle.sconv2d(I[None], Wt, None, 2, 2)[0]
+    taps = np.stack([np.abs(I[:, 2 * h:2 * h + 3, 2 * w:2 * w + 3]).reshape(-1) for h in range(8) for w in range(9)]).astype(np.float64)
+    filters, bounds = np.abs(Wt).reshape(24, -1).astype(np.float64), []
+    for block, unit in ((144, 2.0 ** -27.9), (128, 2.0 ** -30.5)):
+        at = range(0, 576, block)
+        tm, fm = (np.stack([a[:, k:k + block].max(axis=1) for k in at], axis=1) for a in (taps, filters))
+        bounds.append(unit * (fm * [min(block, 576 - k) for k in at]) @ tm.T)
+    assert (np.abs(got - ref) <= np.maximum(*bounds).reshape(got.shape)).all()
+    others = (taps.max(axis=1) < 1e5).reshape(got.shape[1:])  # pixels that do not read the element of another size themselves
+    got, ref = got[:, others], ref[:, others]
+    assert np.linalg.norm(np.float32(got) - ref) <= 1.05 * np.linalg.norm(np.float32(ref) - ref)  # what is left is the one rounding

@@ -199,3 +199,77 @@ def test_inf_in_the_second_half_of_a_stage(layer, channel, at, oracle_threads):
                 hit[2, :, oh, ow] = True
     assert np.isnan(got[hit]).all() and not np.isnan(got[~hit]).any()
     assert parity_error(np.where(hit, ref, got), ref) <= TIGHT_I8
+
+
+def own_bound(I, Wt, sh, sw):
+    """What one scale per 128 taps of the output's OWN pixel and filter could do to it: K * 2^-30.5 * the two largest magnitudes, block by
+    block.  (By patches the worst case is K * 2^-27.9 with blocks of 16 channels, where every rounding has the same sign and a window just
+    passes; sums of rounding errors of either sign are far from it.)"""
+    N, F, K = I.shape[0], Wt.shape[0], Wt[0].size
+    taps = torch.nn.functional.unfold(torch.from_numpy(I).double().abs(), Wt.shape[2:], stride=(sh, sw)).transpose(1, 2)  # [N, pixels, K]
+    filters = torch.from_numpy(Wt).double().abs().reshape(F, K)
+    at = range(0, K, 128)
+    tm = torch.stack([taps[:, :, a:a + 128].amax(2) for a in at], 2)
+    fm = torch.stack([filters[:, a:a + 128].amax(1) * min(128, K - a) for a in at], 1)
+    return (2.0 ** -30.5 * tm @ fm.T).transpose(1, 2).reshape(N, F, (I.shape[2] - Wt.shape[2]) // sh + 1, -1).numpy()
+
+
+def unlike(layer, what, size, seed):
+    """Operands of a layer that takes the kernel, Gaussian but for something of another size in image 1."""
+    N, C, F, H, W, KH, KW, sh, sw = layer
+    I, Wt, _ = inputs.make_sconv2d(N, C, F, H, W, KH, KW, seed=seed)
+    if what == "a column that no window reads":
+        assert (W - KW) % sw != 0
+        I[1, 5, 10, W - 1] = size
+    elif what == "a corner":
+        I[1, C // 2 + 8, 0, 0] = size
+    elif what == "a channel of zero weights":
+        Wt[:, 33] = 0.0
+        I[1, 33, 12, 20] = size
+    elif what == "a dim region":
+        I[1, :, :, W // 2:] *= size
+    elif what == "dim channels":
+        I[1, 16:32] *= size
+    elif what == "half of a filter":
+        Wt[7, :16] *= size
+    return I, Wt
+
+
+ODD_STRIDE, EVEN_STRIDE = (9, 64, 64, 58, 57, 3, 3, 1, 1), (32, 64, 128, 56, 56, 3, 3, 2, 2)
+FLT_MAX = float(np.finfo(np.float32).max)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer,what,size", [
+    (EVEN_STRIDE, "a column that no window reads", 1e3),
+    (EVEN_STRIDE, "a column that no window reads", 1e10),
+    (EVEN_STRIDE, "a corner", 1e6),
+    (EVEN_STRIDE, "a channel of zero weights", -FLT_MAX),
+    (EVEN_STRIDE, "a dim region", 1e-4),
+    (ODD_STRIDE, "a corner", 1e3),
+    (ODD_STRIDE, "a corner", -FLT_MAX),
+    (ODD_STRIDE, "a channel of zero weights", 1e3),
+    (ODD_STRIDE, "a channel of zero weights", 1e10),
+    (ODD_STRIDE, "a dim region", 1e-6),
+    (ODD_STRIDE, "a dim region", 0.2),
+    (ODD_STRIDE, "a dim region", 1e-30),
+    (ODD_STRIDE, "dim channels", 1e-5),
+    (ODD_STRIDE, "half of a filter", 1e-5),
+    (ODD_STRIDE, "half of a filter", 0.0),
+    ((13, 32, 32, 184, 9, 3, 3, 1, 1), "a corner", 1e8),  # 32 filters, an only stage
+    ((11, 32, 448, 68, 14, 9, 1, 2, 2), "a dim region", 1e-5),  # nine taps in a column
+    ((8, 64, 256, 40, 60, 1, 9, 1, 2), "a dim region", 1e-5),  # and in a row
+])
+def test_elements_of_other_sizes_stay_in_the_outputs_that_read_them(plan, layer, what, size, oracle_threads):
+    """Every output is held to its own taps' magnitudes, whatever lies beside them in the patch."""
+    assert plan(layer)[0] == 2
+    N, C, F, H, W, KH, KW, sh, sw = layer
+    I, Wt = unlike(layer, what, size, 91)
+    OH, OW = (H - KH) // sh + 1, (W - KW) // sw + 1
+    got = run(I, Wt, None, sh, sw, (N, F, OH, OW))
+    images = [1, N - 1]
+    ref = oracle.sconv2d(I[images], Wt, None, sh, sw)
+    allowed = own_bound(I[images], Wt, sh, sw) + np.abs(ref) * 2.0 ** -24 + 2.0 ** -150
+    over = np.abs(got[images] - ref) / allowed
+    print("sconv2d by patches %s, %s of %g: %.3g of what is allowed" % (layer, what, size, over.max()), flush=True)
+    assert over.max() <= 1.0
