@@ -1176,7 +1176,7 @@ tc_status launch_sconv_i8(const SconvI8Args& a, int64_t blocks, dim3 grid, bool 
   return launch_status();
 }
 
-// The same for 3 x 3 taps over a multiple of 32 channels, the input sliced where it lies (sconv_patch.hpp).
+// The same for nine taps over a multiple of 32 channels, the input sliced where it lies (sconv_patch.hpp).
 template <int TF, int NTW>
 tc_status launch_sconv_patch(const SconvPatchArgs& a, dim3 grid, hipStream_t s) {
   static std::atomic<int> lds_ok{0};  // more than the default 64 KiB of dynamic LDS
@@ -1239,13 +1239,8 @@ bool try_sconv_i8(const SconvI8Args& a, int64_t N, bool fp64_next, hipStream_t s
     const SconvFp64Clocks c = sconv_fp64_clocks(N, a.C, a.H, a.W, a.F, a.K, a.P, a.sw > a.KW);
     if (std::min({c.tile, c.split1, c.split2}) / 2400 < 0.9 * deal.us) return false;
   }
-  // Filters of 9 taps over a multiple of 32 channels: the input sliced once instead of once per tap, where the estimate of that is
-  // 5 % lower (large layers; a small one has too little to do between its filters).  Of 220 random layers 25 go over, 1.27 times as
-  // fast, none of them slower; (N,C,F,H,W) at stride s: (32,64,128,56,56) at 2 46.9 -> 34.9 us, (32,64,64,56,56) at 1 112 -> 69,
-  // (15,128,192,13,72) at 1 82 -> 55, but (10,64,128,28,28) at 2 14.9 / 17.4.
   SconvPatchPlan patch{};
-  if (t_opt.int8 != TC_INT8_TEN && plan_sconv_patch(N, a.G, a.C, a.F, a.H, a.W, a.KH, a.KW, a.sh, a.sw, device_cus(), &patch) &&
-      patch.us < 0.95 * deal.us) {
+  if (t_opt.int8 != TC_INT8_TEN && sconv_by_patches(deal, N, a.G, a.C, a.F, a.H, a.W, a.KH, a.KW, a.sh, a.sw, device_cus(), &patch)) {
     *st = run_sconv_patch(a, N, patch, s);
     return true;
   }
