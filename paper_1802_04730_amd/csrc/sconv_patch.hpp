@@ -31,7 +31,7 @@
 // and each filter's for at most that of its own half (halves of zeros alone are exact and do not count).  A run that fails is
 // done by the workgroup from its first channel on as sconv_i8.hpp does it, with a scale per pixel and 128 taps.  The check (every
 // position's largest magnitude, which the patch's is made of as well, the maximum of nine of them per pixel, the minimum over the
-// pixels) takes 0.1 .. 2 us of a launch.  Where runs fail, the launch takes (us, all Gaussian / one element of 1e4 / log-normal, sigma 1.5 /
+// pixels) takes 0 .. 6 % of a launch, 2 % on average.  Where runs fail, the launch takes (us, all Gaussian / one element of 1e4 / log-normal, sigma 1.5 /
 // sconv_i8.hpp): (N,C,F,H,W) = (32,64,128,56,56) at stride 2 35.2 / 52 / 63 / 46.4, (32,64,64,56,56) at 1 68 / 88 / 112 / 109,
 // (12,96,96,45,46) at 1 42.5 / 84 / 85 / 95.  SP_SPREAD = 3: of patches of 11 rows of 56, emulated, fail at 1, 2, 3, 4: Gaussian 22 %,
 // none, none, none; rectified channels of different mean and size 83 %, 16 %, none, none; Student-t(3) all, 99 %, 67 %, 14 %; log-normal, sigma
@@ -82,7 +82,8 @@ __device__ __forceinline__ void sp_scales(unsigned mbits, double& scale, double&
   inverse = i8_nonfinite(mbits) ? __longlong_as_double(0x7ff8000000000000ll) : __hiloint2double((1023 - 157 + e) << 20, 0);
 }
 
-// n / d for n and d below 2^12 and magic = sp_magic(d)
+// n / d for n and d below 2^11 and magic = sp_magic(d)
+static_assert(SP_MAX_TILES * 16 * SP_WAVES / 2 + SP_POSITIONS <= 1 << 11, "a run of pixels from the last column on (KH * W, so OW too, is at most SP_POSITIONS)");
 __device__ __forceinline__ int sp_div(int n, unsigned magic) { return (int)(((unsigned)n * magic) >> SP_MAGIC_SHIFT); }
 
 // Largest magnitude of four elements, as bits; NaN is the largest.

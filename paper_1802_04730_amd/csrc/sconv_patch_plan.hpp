@@ -59,7 +59,7 @@ struct SconvPatchPlan {
 // The best run of pixels, and an estimate in us; false where the kernel does not take the layer.
 //   t = 3.55 + turns * (1.88 + stages * (4.69 + 1.38 * tiles + 0.49 * units * full)), with stages of 32 channels, `units` pieces of
 // 4 positions x 4 channels that a thread slices per stage, and `full` the share of the chip that a turn occupies: fitted to 220
-// layers at every run (4.4 % rms, 16 % at worst).
+// layers at every run (4.4 % rms, 16 % at worst; without the check of the scales, 2 % of a launch).
 inline bool plan_sconv_patch(int64_t N, int64_t G, int64_t C, int64_t F, int64_t H, int64_t W, int64_t KH, int64_t KW, int64_t sh, int64_t sw, int cus,
                              SconvPatchPlan* best) {
   if (KH * KW != SP_TAPS || C % 32 != 0 || F % 32 != 0 || KH * W > SP_POSITIONS || H * W >= (1 << 24) || cus <= 0) return false;
@@ -90,7 +90,8 @@ inline bool plan_sconv_patch(int64_t N, int64_t G, int64_t C, int64_t F, int64_t
 
 // Whether a layer that `deal` describes goes to sconv_patch.hpp, and how: filters of nine taps over a multiple of 32 channels, the
 // input sliced once instead of once per tap, where the estimate of that is 5 % lower (large layers; a small one has too little to do
-// between its filters).  Of 220 random layers 25 go over, 1.27 times as fast, none of them slower; (N,C,F,H,W) at stride s:
+// between its filters).  Of 220 random layers 25 went over, 1.27 times as fast, none of them slower.  The check of the scales came
+// later and takes 2 % on average: of 45 layers just beyond the line 44 are faster than by taps, one is 1 % slower.  (N,C,F,H,W) at stride s:
 // (32,64,128,56,56) at 2 46.4 -> 35.5 us, (32,64,64,56,56) at 1 109 -> 68, (15,128,192,13,72) at 1 79 -> 54.5, but (10,64,128,28,28) at 2
 // 14.9 / 17.4.
 inline bool sconv_by_patches(const SconvI8Deal& deal, int64_t N, int64_t G, int64_t C, int64_t F, int64_t H, int64_t W, int64_t KH, int64_t KW, int64_t sh,
