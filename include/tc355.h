@@ -22,10 +22,11 @@
  *  - Arithmetic: inputs are widened exactly to fp64, products and sums are
  *    taken in fp64 (fp64 matrix-core instructions), and each declared output
  *    is rounded once to fp32.  Values handed from one stage of a chain to the
- *    next stay in fp64.  The exceptions, see tc_group_conv and tc_tbmm: some
- *    16- and 32-channel 3 x 3 grouped convolutions and the transposed matmul
- *    with 128 rows sum exactly in integers over operands quantised to 2^-32
- *    of their block maximum.
+ *    next stay in fp64.  The exceptions, see tc_group_conv, tc_tbmm and tc_sconv2d: some
+ *    16- and 32-channel 3 x 3 grouped convolutions, convolutions with a
+ *    multiple of 32 filters and the transposed matmul with a multiple of 128
+ *    rows sum exactly in integers over operands quantised to 2^-32 of their
+ *    block maximum (2^-28 of an output's own in the worst case of tc_sconv2d).
  *  - Validation precedes any launch: on a non-zero status nothing was written.
  *    A batch extent of 0 returns TC_OK without launching.
  *  - Thread safety: the only mutable global state is a per-process cache of
@@ -130,7 +131,7 @@ const char *tc355_last_path(void);
  * Error bound: K * 2^-30.5 * max|X row block| * max|Y row block| absolute,
  * worst case (the rounding of the two operands; the dropped digit products
  * are 2^-7 of that); on max|gpu - ref| / (|ref| + 1e-3 max|ref|) below 2e-6
- * for uniform, Gaussian and log-normal (sigma 2 on both operands) data.
+ * for uniform, Gaussian and log-normal data (sigma 2 on both operands, K = 1024).
  * With option TC_OPT_INT8 = TC_INT8_TEN the diagonal k + l = 2 is dropped
  * (10 products, K * 2^-29.5: 3e-7 .. 9e-7 for uniform and Gaussian operands,
  * up to 1.2e-5 for log-normal magnitudes of sigma 2), with TC_INT8_OFF these
@@ -277,10 +278,10 @@ tc_status tc_mlp_fcrelu_static(const float *I, int64_t batch, int32_t n_layers,
  * gives NaN in all outputs that read the band.
  * Groups with F a multiple of 32 and C*KH*KW a multiple of 4 and at least 256
  * (G = 1 with such extents is the plain convolution of Section 3) run on the
- * int8 kernel of tc_sconv2d with stride 1, one group after the other in one
- * launch: its arithmetic (blocks of 128 taps, a scale per filter and per
- * output pixel in every block, 13 digit products; TC_INT8_TEN: 10), its
- * limits and its Inf/NaN behaviour are described there, and for G = 1 and F at
+ * int8 kernels of tc_sconv2d with stride 1, one group after the other in one
+ * launch: their arithmetic (blocks of 128 taps, a scale per filter and per
+ * output pixel in every block, 13 digit products; TC_INT8_TEN: 10; or by
+ * patches), limits and Inf/NaN behaviour are described there, and for G = 1 and F at
  * least 64 the long reductions on few pixels that take fp64 instead.
  */
 tc_status tc_group_conv(const float *I, const float *W1, const float *bias,
@@ -341,9 +342,22 @@ tc_status tc_kron(const float *W1, const float *W2, const float *X, float *Y,
  * rounded to a 32-bit integer and cut into four signed 8-bit digits; the 13
  * digit products of weight 256^2 and above are summed exactly in int32, scaled
  * back and added over the blocks in fp64; bias added in fp64, one rounding to
- * fp32.  Error bound and measured errors as for tc_tbmm (C*KH*KW for K);
- * TC_OPT_INT8 = TC_INT8_TEN drops the lowest diagonal (10 products),
- * TC_INT8_OFF keeps the fp64 kernel.  On the int8 path a NaN or an Inf among
+ * fp32.  Error bound and measured errors as for tc_tbmm (C*KH*KW for K).
+ * Layers with nine taps (3 x 3, 1 x 9, 9 x 1) over a multiple of 32 channels go
+ * by patches where that is estimated to take 5 % less time (all extents, N
+ * among them, and the device): in every 32 channels each filter has one scale,
+ * and so have the input rows under a run of neighbouring output pixels; scales
+ * are powers of two that take the largest magnitude to 2^30 .. 2^31.  A run for
+ * which one of these scales is more than 2^3 times (by powers of two) what the
+ * largest magnitude of some pixel's own taps, or of some filter, in the first or
+ * the last 16 of the channels asks for, is computed in blocks of 128 taps as
+ * above.  So an output's error is bounded by its own taps either way: by patches,
+ * over blocks of 16 channels, K * 2^-27.8 * max|filter block| * max|pixel block|
+ * in the worst case (elements above 2^-7 of the largest under a scale are exact;
+ * where scales differ little, as on Gaussian data, measured errors are below
+ * those of blocks of 128: 1.1e-7 .. 1.8e-7 against 1.9e-7 .. 3.5e-7).
+ * TC_OPT_INT8 = TC_INT8_TEN drops the lowest diagonal (10 products, never by
+ * patches), TC_INT8_OFF keeps the fp64 kernel.  On the int8 path a NaN or an Inf among
  * an output's own taps, or anywhere in its filter, gives NaN (the exact sum
  * would give an Inf where every infinite product has the same sign).
  */

@@ -348,7 +348,7 @@ def emulate_patch(I, Wt, sh, sw, px):
     ("a filter", "all"), ("zeros", "none")])
 def test_convolution_by_patches_holds_every_output_to_its_own_taps(kind, by_taps):
     """Whatever else a patch holds: an output is off by no more than what one scale per half of its own window, 2^3 times too coarse,
-    and one per half of its filter would do to it (16 channels; K * 2^-27.9 * the two maxima), or by what blocks of 128 taps would
+    and one per half of its filter would do to it (16 channels; K * 2^-27.8 * the two maxima), or by what blocks of 128 taps would
     (K * 2^-30.5).  Ordinary data is done by patches throughout."""
     I, Wt, _ = inputs.make_sconv2d(1, 64, 24, 17, 20, 3, 3, seed=31)
     I = I[0]
@@ -371,7 +371,7 @@ def test_convolution_by_patches_holds_every_output_to_its_own_taps(kind, by_taps
     ref = oracle.sconv2d(I[None], Wt, None, 2, 2)[0]
     taps = np.stack([np.abs(I[:, 2 * h:2 * h + 3, 2 * w:2 * w + 3]).reshape(-1) for h in range(8) for w in range(9)]).astype(np.float64)
     filters, bounds = np.abs(Wt).reshape(24, -1).astype(np.float64), []
-    for block, unit in ((144, 2.0 ** -27.9), (128, 2.0 ** -30.5)):
+    for block, unit in ((144, 2.0 ** -27.8), (128, 2.0 ** -30.5)):
         at = range(0, 576, block)
         tm, fm = (np.stack([a[:, k:k + block].max(axis=1) for k in at], axis=1) for a in (taps, filters))
         bounds.append(unit * (fm * [min(block, 576 - k) for k in at]) @ tm.T)

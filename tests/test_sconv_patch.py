@@ -223,7 +223,7 @@ def test_inf_in_the_second_half_of_a_stage(run, layer, channel, at, oracle_threa
 
 def own_bound(I, Wt, sh, sw):
     """What one scale per 128 taps of the output's OWN pixel and filter could do to it: K * 2^-30.5 * the two largest magnitudes, block by
-    block.  (By patches the worst case is K * 2^-27.9 with blocks of 16 channels, where every rounding has the same sign and a window just
+    block.  (By patches the worst case is K * 2^-27.8 with blocks of 16 channels, where every rounding has the same sign and a window just
     passes; sums of rounding errors of either sign are far from it.)"""
     N, F, K = I.shape[0], Wt.shape[0], Wt[0].size
     taps = torch.nn.functional.unfold(torch.from_numpy(I).double().abs(), Wt.shape[2:], stride=(sh, sw)).transpose(1, 2)  # [N, pixels, K]
