@@ -1,6 +1,6 @@
-"""Every variant of the batched matmul at any alignment: which one a shape takes (the library's own choice in csrc/tbmm_any_plan.hpp,
-compiled by the system's C++ compiler, for 256 compute units) and, on the GPU, its parity with the float64 oracle: one fp32
-rounding of the exact result (2.5e-7 on the metric, as for every fp64 kernel)."""
+"""Every tile and way out of the batched matmul at any alignment, with one to four batch elements per workgroup: which one a shape takes
+(the library's own choice in csrc/tbmm_any_plan.hpp, compiled by the system's C++ compiler, for 256 compute units) and, on the GPU, its
+parity with the float64 oracle: one fp32 rounding of the exact result (2.5e-7 on the metric, as for every fp64 kernel)."""
 import ctypes
 import os
 import subprocess
@@ -48,6 +48,14 @@ VARIANTS = {
     (270, 33, 70, 2): ((3, 3), (1, 2), 2, 1, (1, 1)),
     (305, 70, 69, 4): ((3, 3), (2, 2), 1, 1, (1, 1)),
     (387, 95, 41, 4): ((3, 3), (2, 1), 2, 0, (1, 1)),
+    # three and four batch elements per workgroup, the last one short of some
+    (2275, 8, 38, 13): ((1, 3), (1, 1), 3, 1, (1, 1)),
+    (2276, 8, 38, 13): ((1, 3), (1, 1), 3, 1, (1, 1)),
+    (11861, 3, 33, 35): ((1, 3), (1, 1), 4, 1, (1, 1)),
+    (3001, 7, 45, 60): ((1, 3), (1, 1), 4, 1, (1, 1)),
+    (4002, 9, 45, 60): ((1, 3), (1, 1), 4, 0, (1, 1)),
+    (3001, 20, 30, 33): ((2, 2), (1, 1), 4, 0, (1, 1)),
+    (3251, 41, 40, 51): ((3, 3), (1, 1), 4, 0, (1, 1)),
 }
 
 
