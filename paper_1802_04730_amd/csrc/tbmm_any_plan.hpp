@@ -18,7 +18,7 @@ struct TbmmAnyTile {
 constexpr TbmmAnyTile TA_TILES[] = {{1, 1, 8}, {1, 2, 8}, {1, 3, 8}, {1, 5, 5}, {2, 1, 8}, {2, 2, 8}, {2, 3, 5}, {3, 1, 8}, {3, 2, 5}, {3, 3, 4}};
 
 // The constants of the estimate below, in clocks (per 64 bytes and wavefront: TA_LOAD; bytes a clock and compute unit: TA_BW):
-// fitted to 500 shapes measured in every plan, with most weight on what the chosen plan loses (1.6 % on average, a quarter at
+// fitted to 500 shapes (K up to 103) measured in every plan, with most weight on what the chosen plan loses (1.6 % on average, a quarter at
 // worst) and on plans slower than what the wave-level strips that this kernel took over from needed.
 constexpr double TA_CVT = 1.63, TA_WAVE = 390, TA_OUT_DIRECT = 18.8, TA_OUT_LDS = 26.2, TA_LATENCY = 2680, TA_LOAD = 2.29, TA_LAYOUT = 462, TA_BW = 9.73,
                  TA_BW_DIRECT = 0.952, TA_MFMA_CHAIN = 13.4, TA_UNEVEN = 0.984, TA_LAST = 1.252;

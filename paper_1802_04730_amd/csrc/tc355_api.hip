@@ -619,7 +619,7 @@ tc_status launch_tbmm_any(const TbmmAnyPlan& pl, TbmmAnyArgs a, hipStream_t s) {
   return TC_OK;
 }
 
-// The plan of the thread's last shapes: choosing one takes 1-4 us of host time.
+// The plan of the thread's last shapes: choosing one takes 0.3-4 us of host time, 0.9 on average.
 const TbmmAnyPlan* tbmm_any_plan(int64_t B, int64_t N, int64_t M, int64_t K, int cus) {
   struct Entry {
     int64_t B, N, M, K;
@@ -636,7 +636,10 @@ const TbmmAnyPlan* tbmm_any_plan(int64_t B, int64_t N, int64_t M, int64_t K, int
   return e.any ? &e.plan : nullptr;
 }
 
-// Reductions up to 103: beyond, LDS holds too few workgroups.
+// Reductions up to 103.  That is what the registers of this kernel's earlier form held, and what the estimate was fitted with; it is
+// not a limit of this one: on 60 random shapes with K from 104 to 180 it would take half the time of the wave-level kernel, which has
+// them (us, that / this: (2648,42,68,130) 80 / 75, (412,79,95,111) 47 / 24.5, (42,78,62,105) 14.8 / 4.0; one is slower, (4287,35,12,104)
+// 26.2 / 27.7).
 bool try_tbmm_any(const float* X, const float* Y, float* Z, int64_t B, int64_t N, int64_t M, int64_t K, hipStream_t s, tc_status* st) {
   const int cus = device_cus();
   if (cus <= 0 || K > 103 || prod_reaches({B, N, K}, 1ll << 40) || prod_reaches({B, M, K}, 1ll << 40)) return false;
@@ -865,11 +868,13 @@ tc_status tbmm_run(const float* X, const float* Y, float* Z, int64_t B, int64_t 
     // four fifths ((1000,64,64,64) 19.3, 23.5 on the other one, but (700,96,96,96) 58 / 52), and from K = 88 on also where
     // three fifths of the chip's time would be spent on results ((984,53,56,88) 23.3 / 28.2, (124,108,99,92) 12.6 / 15.9, but
     // (311,64,48,88) 11.3 / 8.5).  The wave-level kernel keeps what is too short to stage ((30000,8,8,8) 14.7 / 15.4,
-    // (1175,77,4,1) 4.0 / 4.9), results that are one tile wide or more than 5 while the rows share LDS banks
+    // (1175,77,4,1) 4.0 / 4.9), results that are one tile wide or more than 5 where K is a multiple of 16
     // ((5709,51,5,96) 38 / 46, (6,51,120,80) 4.3 / 4.7) or the wide ones' odd reductions are short ((3129,12,92,5) 8.8 / 9.3).
     // Everything else is the other one's: (4000,27,61,35) 38.8 / 17.3, (23986,9,74,12) 87 / 39, (35,55,75,81) 13.7 / 4.5.  (The lines
-    // here and above were drawn against its earlier form, a wavefront per strip pair; it is 1.14 times as fast by now, and the wave-level
-    // kernel's share above would be 1.14 times as fast on it, the aligned kernel's 1.06 times: 15 and 76 shapes.)
+    // here and above were drawn against its earlier form, a wavefront per strip pair, in which rows at multiples of 16 shared LDS banks.
+    // The present one is 1.14 times as fast and has no such rows; it would have the wave-level kernel's share of multiples of 16
+    // too: (42,37,11,80) 4.2 / 3.4, (63,30,108,80) 4.4 / 3.7, (3520,100,10,96) 41.7 / 37.7.  Of 91 shapes beside the lines the wave-level
+    // kernel's 15 would be 1.14 times as fast on it, the aligned kernel's 76 1.06 times.)
     const int64_t cus = std::max(1, device_cus()), blocks = ceil_div(N, GT_BM) * ceil_div(M, GT_BN) * B, tiles = ceil_div(N, 16) * tiles_m * B;
     const double full = (double)N * M / (ceil_div(N, GT_BM) * GT_BM * ceil_div(M, GT_BN) * GT_BN);
     const bool block = K % 4 == 0 && N >= 48 && M >= 48 && blocks >= 128 &&
@@ -1001,11 +1006,11 @@ tc_status mlp_run(const float* I, int64_t batch, int32_t n_layers, const int64_t
   const int cus = device_cus();
   // Small batches with reductions of at most 1024: one workgroup per compute unit, every XCD's workgroups own an eighth
   // of the column tiles of every layer (mlp_rows.hpp).  Option TC_OPT_MLP_KERNEL = TC_MLP_TILES keeps the tile-stream
-  // kernel below.  Fewer than 16 rows do not fill a tile and go to one launch per layer (here / there, us: one row of 1024 -> 1024
-  // -> 512 -> 256 16.1 / 13.7, two of 128 -> 256 -> 1024 -> 128 14.9 / 10.6, five of 256 -> 1024 -> 2000 13.0 / 8.5, 15 of 1024 -> 1000
-  // 6.2 / 5.4), unless the caller asks for this kernel.  (The other lines were drawn against one launch per layer as it was before
-  // gemm_direct.hpp.  Against that: 128 x 1024 -> 1024 -> 512 -> 256 19.8 / 18.1, 128 x 1024 -> 1024 9.0 / 7.6, 512 x 256 -> 256 -> 128
-  // 11.9 / 6.6, 128 x 256 -> 1024 4.8 / 3.7; the tests hold chains of 16 rows and more to this kernel.)
+  // kernel below.  Fewer than 16 rows go to one launch per layer (here / there, us: one row of 1024 -> 1024 -> 512 -> 256 16.1 / 13.7,
+  // two of 128 -> 256 -> 1024 -> 128 14.9 / 10.6, five of 256 -> 1024 -> 2000 13.0 / 8.5, 15 of 1024 -> 1000 6.2 / 5.4), unless the
+  // caller asks for this kernel.  16 is not where the two cross: one launch per layer has become the faster one throughout
+  // (gemm_direct.hpp; 16 rows of 1024 -> 1024 -> 512 -> 256 15.9 / 14.3, 128 of them 19.8 / 18.1, 128 x 1024 -> 1024 9.0 / 7.6, 512 x 256
+  // -> 256 -> 128 11.9 / 6.6, 128 x 256 -> 1024 4.8 / 3.7), but from 16 rows on the tests name this kernel.
   if (fused && cus >= MR_SHARES) {
     const int64_t G = ceil_div(batch, 16);
     const int64_t nwg = std::min<int64_t>(cus, MR_MAX_WG) / MR_SHARES * MR_SHARES;
