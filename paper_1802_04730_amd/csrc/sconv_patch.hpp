@@ -32,14 +32,14 @@
 // done by the workgroup from its first channel on as sconv_i8.hpp does it, with a scale per pixel and 128 taps.  The check (every
 // position's largest magnitude, which the patch's is made of as well, the maximum of nine of them per pixel, the minimum over the
 // pixels) takes 0 .. 6 % of a launch, 2 % on average.  Where runs fail, the launch takes (us, all Gaussian / one element of 1e4 / log-normal, sigma 1.5 /
-// sconv_i8.hpp): (N,C,F,H,W) = (32,64,128,56,56) at stride 2 35.2 / 52 / 63 / 46.4, (32,64,64,56,56) at 1 68 / 88 / 112 / 109,
+// sconv_i8.hpp): (N,C,F,H,W) = (32,64,128,56,56) at stride 2 35.3 / 52 / 63 / 46.6, (32,64,64,56,56) at 1 68 / 88 / 112 / 109,
 // (12,96,96,45,46) at 1 42.5 / 84 / 85 / 95.  SP_SPREAD = 3: of patches of 11 rows of 56, emulated, fail at 1, 2, 3, 4: Gaussian 22 %,
 // none, none, none; rectified channels of different mean and size 83 %, 16 %, none, none; Student-t(3) all, 99 %, 67 %, 14 %; log-normal, sigma
-// 1.5, all, all, all, 90 %.  What it costs in rounding is a tenth of the one to fp32 where a window just passes.
-// Errors on the metric: 1.1e-7 .. 1.8e-7 on Gaussian data, 2e-7 .. 7e-7 on heavy-tailed.
+// 1.5, all, all, all, 90 %.  Where a window of Gaussian data just passes, the roundings are a quarter of the one to fp32, 3 % more error in all.
+// Errors on the metric: 1.1e-7 .. 1.8e-7 on Gaussian data, 2e-7 .. 4.5e-7 on heavy-tailed.
 // Inf and NaN reach what they reach there: a position that holds one is left out of the patch (and of its scale) and marked, and
 // pixels whose window touches a mark become NaN; a filter that holds one gives NaN everywhere.
-// (N,C,F,H,W) at stride s, sconv_i8.hpp -> this, us: (32,64,128,56,56) at 2 46.4 -> 35.2, (32,64,64,56,56) at 1 109 -> 68,
+// (N,C,F,H,W) at stride s, sconv_i8.hpp -> this, us: (32,64,128,56,56) at 2 46.6 -> 35.3, (32,64,64,56,56) at 1 109 -> 68,
 // (3,128,256,58,58) at 1 71 -> 51, (15,128,192,13,72) at 1 79 -> 54.5.  What bounds it: a stage of 6 tiles is 8 us, 5.2 of them MFMAs at
 // their rate; the 4 to 5 us in front of it are vector instructions (the filters' slicing above all) and LDS round trips that
 // nothing covers, so layers with few pixels per compute unit stay with sconv_i8.hpp.  Filters straight from memory in

@@ -92,7 +92,7 @@ inline bool plan_sconv_patch(int64_t N, int64_t G, int64_t C, int64_t F, int64_t
 // input sliced once instead of once per tap, where the estimate of that is 5 % lower (large layers; a small one has too little to do
 // between its filters).  Of 220 random layers 25 went over, 1.27 times as fast, none of them slower.  The check of the scales came
 // later and takes 2 % on average: of 45 layers just beyond the line 44 are faster than by taps, one is 1 % slower.  (N,C,F,H,W) at stride s:
-// (32,64,128,56,56) at 2 46.4 -> 35.5 us, (32,64,64,56,56) at 1 109 -> 68, (15,128,192,13,72) at 1 79 -> 54.5, but (10,64,128,28,28) at 2
+// (32,64,128,56,56) at 2 46.6 -> 35.3 us, (32,64,64,56,56) at 1 109 -> 68, (15,128,192,13,72) at 1 79 -> 54.5, but (10,64,128,28,28) at 2
 // 14.9 / 17.4.
 inline bool sconv_by_patches(const SconvI8Deal& deal, int64_t N, int64_t G, int64_t C, int64_t F, int64_t H, int64_t W, int64_t KH, int64_t KW, int64_t sh,
                              int64_t sw, int cus, SconvPatchPlan* best) {
