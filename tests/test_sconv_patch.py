@@ -189,6 +189,18 @@ def test_nan_and_inf_stay_in_the_outputs_that_read_them(run, oracle_threads):
     hit[7, :, 26, 26] = True
     assert np.isnan(got[hit]).all() and not np.isnan(got[~hit]).any()
     assert parity_error(np.where(hit, ref, got), ref) <= TIGHT_I8
+    # the same in runs that are done by taps: the NaN in the stage that finds it out, the other Inf in the one before
+    hit[7, :, 26, 26] = False
+    In[7, 40, 54, 54] = I[7, 40, 54, 54]
+    In[1, 9, 0, 55] = In[7, 63, 0, 0] = 1e6
+    In[7, 20, 10, 10] = np.inf
+    hit[7, :, 4:6, 4:6] = True
+    ref1 = ref.copy()
+    ref1[[1, 7]] = oracle.sconv2d(np.where(np.isfinite(In[[1, 7]]), In[[1, 7]], 0), Wt, bias, sh, sw)
+    got = run(In, Wt, bias, sh, sw, ref.shape)
+    assert np.isnan(got[hit]).all() and not np.isnan(got[~hit]).any()
+    hit[7, :, 0, 0] = True  # (reads 1e6 itself)
+    assert parity_error(np.where(hit, ref, got), np.where(hit, ref, ref1)) <= TIGHT_I8
     Wn = Wt.copy()
     Wn[77, 3, 1, 2] = np.nan
     Wn[5, 60, 2, 2] = np.inf
